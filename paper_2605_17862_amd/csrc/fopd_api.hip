@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -59,7 +60,7 @@ struct LmWorkspace {
     flags = 0;
     n_live = 128;                                        // the count of unmasked rows, on the device
     partial = 256;
-    ex = align_up(partial + static_cast<size_t>(kLmStripsMax) * t_pad * sizeof(float2), 256);
+    ex = align_up(partial + (static_cast<size_t>(kLmStrips) * t_pad + kLmPairsExtra) * sizeof(float2), 256);
     row_map = align_up(ex + (t + 1) * sizeof(int32_t), 256);
     total = align_up(row_map + t * sizeof(int32_t), 256);
   }
@@ -1090,19 +1091,25 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLmLdsBytes, allowed) != FOPD_OK) return FOPD_EHIP;
   const int n_token_tiles = static_cast<int>(lay.t_pad / kLmTile);
   const int n_vocab_tiles = static_cast<int>((V + kLmTile - 1) / kLmTile);
-  // strips: 8, 16 or 32, whichever leaves the smallest idle tail when the work items (token tile x strip,
-  // all of one length) are dealt to the 256 compute units round by round
-  int n_strips = 8;
+  // Strips: the work items (token tile x strip of the vocabulary) go to the 256 compute units round by round, a round
+  // takes as long as its longest strip has tiles (plus a little for the item itself: first loads, last merge), and the
+  // number of strips with the least total is taken.  Few token tiles give many short strips, so that one short rollout
+  // fills the chip too: 300 rows x 151,936 entries, d = 4096: 64 items of 19 tiles 1386 us, 256 items of 5 tiles 522 us.
+  // Whole groups only (tile_place): strips that leave part of a group empty share the weight's L2 copies worse (16,384
+  // rows: 4 strips in half-empty groups 17.0 ms, 8 strips 16.3 ms, although 4 of them end in one even round).
+  const int group_strips = 32 / tile_group_n(n_token_tiles);
+  const int64_t strips_max = kLmStrips + kLmPairsExtra / static_cast<int64_t>(lay.t_pad);
+  int n_strips = group_strips;
   double best = 0.0;
-  for (int cand = 8; cand <= kLmStripsMax; cand *= 2) {
-    const int64_t items = static_cast<int64_t>(n_token_tiles) * cand;
-    const double fill = static_cast<double>(items) / static_cast<double>((items + 255) / 256 * 256);
-    if (fill > best + 0.005) {
-      best = fill;
+  for (int cand = group_strips; cand <= strips_max && (cand == group_strips || cand <= n_vocab_tiles); cand += group_strips) {
+    const int64_t rounds = (static_cast<int64_t>(n_token_tiles) * cand + 255) / 256;
+    const double cost = static_cast<double>(rounds) * (static_cast<double>((n_vocab_tiles + cand - 1) / cand) + 0.15);
+    if (cand == group_strips || cost < best) {
+      best = cost;
       n_strips = cand;
     }
   }
-  const unsigned grid = static_cast<unsigned>((n_token_tiles + 31) / 32) * static_cast<unsigned>(n_strips / 8) * 256u;
+  const unsigned grid = static_cast<unsigned>((tile_groups(n_strips, n_token_tiles) + 7) / 8) * 256u;
   float2* partial = at<float2>(workspace, lay.partial);
   const __bf16* Wp = static_cast<const __bf16*>(weight);
   const __bf16* Hp = static_cast<const __bf16*>(hidden);
@@ -1149,7 +1156,7 @@ static fopd_status launch_gemm(bool accumulate, const __bf16* Am, int64_t lda, i
   if (allow_dynamic_lds(kern, kGemmLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTileN - 1) / kGemmTileN);
-  const int64_t rounds = static_cast<int64_t>((tiles_m + 7) / 8) * ((tiles_n + 31) / 32);
+  const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
@@ -1177,7 +1184,7 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Ak, int64_t lda
   if (allow_dynamic_lds(kern, kTnLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTileN - 1) / kGemmTileN);
-  const int64_t rounds = static_cast<int64_t>((tiles_m + 7) / 8) * ((tiles_n + 31) / 32);
+  const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);

@@ -96,25 +96,17 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
 
-  // Workgroups go to the eight XCDs in turn (id mod 8).  The 32 that an XCD runs together are 4 tiles along n
-  // x 8 tiles along m, so that each L2 serves 4 + 8 operand tiles to 32 users.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int m_blocks = (tiles_m + 7) >> 3;
-  const int round = slot >> 5;
-  int tile_m = ((round % m_blocks) << 3) + ((slot >> 2) & 7);
-  int tile_n = ((((round / m_blocks) << 3) + xcd) << 2) + (slot & 3);
+  // Only the first *n_live rows of Bn count when a count is given (it stays on the device, the launch covers all N):
+  // tiles past them are left out, and as the groups of tiles are dealt to the XCDs in turn, these stay evenly loaded
+  // whatever the count is.
   if (n_live != nullptr) {
-    // Only the first *n_live rows of Bn count (a device-side count: the launch covers all N): tiles past them are
-    // left out, and the groups of 4 x 8 tiles are dealt to the XCDs in turn, the groups along n fastest, so that
-    // the XCDs stay evenly loaded whatever the count is.
     const int live = *n_live;
     if (live <= 0) return;
     tiles_n = min(tiles_n, (live + TN - 1) / TN);
-    const int quads = (tiles_n + 3) >> 2;
-    const int unit = (round << 3) + xcd;
-    tile_m = ((unit / quads) << 3) + ((slot >> 2) & 7);
-    tile_n = ((unit % quads) << 2) + (slot & 3);
   }
+  const unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), slot = (blockIdx.x >> 3) & 31;
+  const TilePlace place = tile_place<true>(group, slot, tiles_m, tiles_n);
+  const int tile_m = place.m, tile_n = place.n;
   if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
   const int m0 = tile_m * kGemmTile, n0 = tile_n * TN;
   if constexpr (PROBE == 14) {
@@ -508,12 +500,11 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
 
-  // tile order: as fopd_gemm_nt (32 workgroups of an XCD = 4 tiles along n x 8 along m)
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int m_blocks = (tiles_m + 7) >> 3;
-  const int round = slot >> 5;
-  const int tile_m = ((round % m_blocks) << 3) + ((slot >> 2) & 7);
-  const int tile_n = ((((round / m_blocks) << 3) + xcd) << 2) + (slot & 3);
+  // the groups of one set of tiles along n follow each other on neighbouring XCDs: they read the same columns of Bk, by
+  // far the larger operand
+  const TilePlace place = tile_place<false>(((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), (blockIdx.x >> 3) & 31, tiles_m,
+                                            tiles_n);
+  const int tile_m = place.m, tile_n = place.n;
   if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
   const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTileN;
 

@@ -48,7 +48,8 @@ namespace fopd {
 constexpr int kLmTile = 256;                              // vocabulary rows and token rows of a workgroup tile
 constexpr int kLmK = 32;                                  // hidden elements per LDS stage
 constexpr int kLmStages = 4;                              // stages resident in the LDS
-constexpr int kLmStripsMax = 32;                          // vocabulary strips (8, 16 or 32) = partial pairs per token
+constexpr int kLmStrips = 32;                             // vocabulary strips = partial pairs per token: room for 32 of all
+constexpr int kLmPairsExtra = 57344;                      // tokens and this many pairs more (256 strips of one token tile)
 constexpr int kLmThreads = 512;                           // 8 wavefronts: 2 (vocabulary) x 4 (tokens)
 constexpr int kLmOperandBytes = kLmTile * kLmK * 2;       // one operand tile of one stage: 16 KB
 constexpr int kLmStageBytes = 2 * kLmOperandBytes;
@@ -78,6 +79,37 @@ __device__ __forceinline__ void lm_load_to_lds(const char* base, uint32_t voff, 
   __builtin_amdgcn_global_load_lds((gptr_t*)(base + voff), (lptr_t*)lds_base, 16, 0, 0);
 }
 
+// Which tile a workgroup owns.  A launch is a list of groups of 32 workgroups; workgroups go to the eight XCDs in turn
+// (id mod 8), so group g runs on XCD g mod 8 and its 32 tiles share that XCD's L2.  A group is up to 4 tiles along n
+// (the side with few tiles when the batch is small) x the 8 (16, 32) along m that fill it: with one or two tiles along n
+// the group takes 16 or 32 tiles along m instead of leaving workgroups without work.  That matters because an idle
+// workgroup is not free: it asks for the same 128 KB of LDS, so it queues for a compute unit like a working one.
+// Measured on 512 rows x 151,936 entries, d = 4096 (1188 tiles): 4 x 8 groups always, 19,200 workgroups, 928 us;
+// groups without idle workgroups, 1280 in all, 585 us.
+// Consecutive groups, and with them the XCDs, go along n first (N_FIRST) or along m first.
+struct TilePlace {
+  int m, n;
+};
+
+__host__ __device__ __forceinline__ int tile_group_n(int tiles_n) { return tiles_n >= 3 ? 4 : (tiles_n == 2 ? 2 : 1); }
+
+// Groups of a launch.  For fewer tiles along n never more groups than for more of them, so a launch sized for all rows
+// covers any smaller count that the device finds.
+__host__ __device__ __forceinline__ int64_t tile_groups(int tiles_m, int tiles_n) {
+  const int gn = tile_group_n(tiles_n), gm = 32 / gn;
+  return static_cast<int64_t>((tiles_n + gn - 1) / gn) * ((tiles_m + gm - 1) / gm);
+}
+
+template <bool N_FIRST>
+__device__ __forceinline__ TilePlace tile_place(unsigned group, unsigned slot, int tiles_m, int tiles_n) {
+  const int gn = tile_group_n(tiles_n), gm = 32 / gn;
+  const int groups_n = (tiles_n + gn - 1) / gn, groups_m = (tiles_m + gm - 1) / gm;
+  const int g = static_cast<int>(group), sl = static_cast<int>(slot);
+  const int at_n = N_FIRST ? g % groups_n : g / groups_m;
+  const int at_m = N_FIRST ? g / groups_n : g % groups_m;
+  return TilePlace{at_m * gm + sl / gn, at_n * gn + sl % gn};
+}
+
 }  // namespace
 
 __global__ void __launch_bounds__(kLmThreads)
@@ -90,29 +122,19 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;            // vocabulary half, token quarter of the tile
 
-  // Workgroups are handed to the eight XCDs in turn (id mod 8).  The 32 that run together on one XCD
-  // are 4 token tiles x 8 strips, so that each L2 serves 4 hidden tiles and 8 weight tiles to 32 users.
-  // With more than 8 strips (shorter work items, a shorter idle tail at the end of the launch) the groups
-  // of 8 strips of one set of token tiles follow each other.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int strip_groups = n_strips >> 3;
-  const int chunk_id = slot >> 5;
-  int strip = ((chunk_id % strip_groups) << 3) + ((slot >> 2) & 7);
-  int token_tile = ((((chunk_id / strip_groups) << 3) + xcd) << 2) + (slot & 3);
+  // Only the rows row_map[0 .. *n_live - 1] of H take part when a count is given (masked rows left out; the count stays
+  // on the device and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the
+  // loads.
   if (n_live != nullptr) {
-    // Only the rows row_map[0 .. *n_live - 1] of H take part (masked rows left out; the count stays on the device
-    // and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the loads, and
-    // the groups of 4 token tiles x 8 strips are dealt to the XCDs in turn so that they stay evenly loaded.
     T = *n_live;
     if (T <= 0) return;
     n_token_tiles = min(n_token_tiles, (T + kLmTile - 1) / kLmTile);
-    const int quads = (n_token_tiles + 3) >> 2;
-    const int unit = (chunk_id << 3) + xcd;
-    if (unit / quads >= strip_groups) return;
-    strip = ((unit / quads) << 3) + ((slot >> 2) & 7);
-    token_tile = ((unit % quads) << 2) + (slot & 3);
   }
-  if (token_tile >= n_token_tiles) return;             // whole workgroup, before any barrier
+  // m: vocabulary strips, n: token tiles; each L2 serves up to 4 hidden tiles and 8 strips of the weight to 32 users
+  const TilePlace place = tile_place<true>(((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), (blockIdx.x >> 3) & 31, n_strips,
+                                           n_token_tiles);
+  const int strip = place.m, token_tile = place.n;
+  if (strip >= n_strips || token_tile >= n_token_tiles) return;      // whole workgroup, before any barrier
   const int vt_begin = static_cast<int>(static_cast<int64_t>(strip) * n_vocab_tiles / n_strips);
   const int vt_end = static_cast<int>(static_cast<int64_t>(strip + 1) * n_vocab_tiles / n_strips);
   const int t0 = token_tile * kLmTile;
@@ -392,14 +414,19 @@ fopd_k7_finish(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restri
     for (int e = 0; e < 8; ++e) dot = fmaf(hx[e], wx[e], dot);
   }
   dot = wave_sum(dot);
+  // the strips' pairs: one per lane (up to 256 of them, at a distance of t_pad pairs), then across the wavefront
+  const int c = (ex != nullptr) ? ex[t] : t;             // the token's place among the rows that were projected
+  float m = kLmNone, s = 0.f;
+  for (int k = lane; k < n_strips; k += 64) {
+    const float2 e = partial[static_cast<int64_t>(k) * t_pad + c];
+    lm_merge(m, s, e.x, e.y);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const float m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(s, off, 64);
+    lm_merge(m, s, m2, s2);
+  }
   if (lane == 0) {
-    const int c = (ex != nullptr) ? ex[t] : t;           // the token's place among the rows that were projected
-    float2 e = partial[c];
-    float m = e.x, s = e.y;
-    for (int k = 1; k < n_strips; ++k) {
-      e = partial[static_cast<int64_t>(k) * t_pad + c];
-      lm_merge(m, s, e.x, e.y);
-    }
     const double l = static_cast<double>(m) + log(static_cast<double>(s));
     lse[t] = static_cast<float>(l);
     logp[t] = static_cast<float>(fmin(static_cast<double>(dot) - l, 0.0));

@@ -71,7 +71,7 @@ static int run(const char* name, const __bf16* A, int64_t lda, int M, const __bf
     return 0;
   }
   const int tiles_m = (M + kGemmTile - 1) / kGemmTile, tiles_n = (N + tn - 1) / tn;
-  const unsigned grid = static_cast<unsigned>(((tiles_m + 7) / 8) * ((tiles_n + 31) / 32) * 256);
+  const unsigned grid = static_cast<unsigned>((tile_groups(tiles_m, tiles_n) + 7) / 8 * 256);
   float total = 0.f;
   for (int rep = 0; rep < 4; ++rep) {          // first launch is a warm-up
     CHECK(hipEventRecord(e0, 0));
@@ -99,7 +99,7 @@ static int run_sustained(const __bf16* A, int64_t lda, int M, const __bf16* B, i
   constexpr int lds = gemm_lds_bytes(4, 2), tn = gemm_tile_n(4, 2);
   CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
   const int tiles_m = (M + kGemmTile - 1) / kGemmTile, tiles_n = (N + tn - 1) / tn;
-  const unsigned grid = static_cast<unsigned>(((tiles_m + 7) / 8) * ((tiles_n + 31) / 32) * 256);
+  const unsigned grid = static_cast<unsigned>((tile_groups(tiles_m, tiles_n) + 7) / 8 * 256);
   const double flops = 2.0 * M * static_cast<double>(N) * K;
   for (int group = 0; group < groups; ++group) {
     CHECK(hipEventRecord(e0, 0));
@@ -177,7 +177,7 @@ int main(int argc, char** argv) {
     // buffer B); three orders of the instructions inside a slice
     using namespace fopd;
     const int tm = 4096 / kGemmTile, tn = (151936 + kGemmTileN - 1) / kGemmTileN;
-    const unsigned grid = static_cast<unsigned>(((tm + 7) / 8) * ((tn + 31) / 32) * 256);
+    const unsigned grid = static_cast<unsigned>((tile_groups(tm, tn) + 7) / 8 * 256);
     const double flops = 2.0 * 4096 * 151936.0 * 4096;
     auto time_tn = [&](auto kern, const char* name) -> int {
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1,0 +1,39 @@
+"""The projection kernels at few rows, where a launch is made of short work items: token counts around the edges of
+the 256-row tiles and of the groups of tiles (1, 2, 3, 4, 5 tiles), with and without masked rows, against float64."""
+
+import numpy as np
+import pytest
+import torch
+
+from harness import workloads as wl
+from oracle import fopd_oracle as orc
+from paper_2605_17862_amd import binding as fb
+from parity_util import np64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _aligned(nbytes):
+    ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=DEV)
+    off = (-ws.data_ptr()) % 256
+    ws = ws[off:off + nbytes]
+    fb.fopd_workspace_init(ws)
+    return ws
+
+
+@pytest.mark.parametrize("T", [1, 255, 256, 257, 512, 513, 1024, 1029])
+@pytest.mark.parametrize("masked_every", [0, 3])
+def test_log_probs_at_the_edges_of_tiles_and_groups(T, masked_every):
+    # 79 vocabulary tiles, the last with 33 entries; 1e-4 as everywhere for log-probs of fp32 sums over bf16 products
+    w = wl.generate_lm_head(T, 64, 20001, DEV, seed=T, masked_every=masked_every)
+    ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
+    ref_lse, ref_lp = orc.lm_head_token_logprobs(np64(w["hidden"].float()), np64(w["weight"].float()),
+                                                 w["token_ids"].cpu().numpy(), w["mask"].cpu().numpy())
+    for mask in ([w["mask"]] if masked_every else [w["mask"], None]):
+        logp = torch.full((T,), 7.0, device=DEV)
+        lse = torch.full((T,), 7.0, device=DEV)
+        fb.fopd_lm_head_token_logprobs(w["hidden"], w["ldh"], w["weight"], w["ldw"], T, w["V"], w["d"],
+                                       w["token_ids"], mask, logp, lse, ws)
+        assert fb.fopd_workspace_status(ws) == (0, 0)
+        assert np.max(np.abs(np64(lse) - ref_lse)) <= 1e-4 and np.max(np.abs(np64(logp) - ref_lp)) <= 1e-4
