@@ -1141,13 +1141,36 @@ size_t fopd_lm_head_loss_workspace_bytes(int64_t T, int64_t V, int64_t d, int32_
   return LmLossWorkspace(T, V, d, B, rows_chunk).total;
 }
 
+// Into how many runs of the contraction index Out[N, M] = sum over K is cut, at most `most`.  A product with few result
+// tiles leaves most of the 256 compute units idle while the others walk a long contraction index; each run is a result of
+// its own that is summed afterwards.  Estimate in microseconds: the work items (tile x run) go to the compute units round
+// by round, an item takes 1.8 a pair of stages of 64 plus 12 for its first loads and its stores, and the partial results
+// are written and read at 4 TB/s.  512 rows x 4096, K = 151,936 (32 tiles): 1 run 2805 us, 8 runs 520 us.
+static int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
+  const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTileN - 1) / kGemmTileN), pairs = K / 64;
+  most = std::min<int64_t>(std::min<int64_t>(most, 32), pairs / 8);
+  int best = 1;
+  double least = 0.0;
+  for (int splits = 1; splits == 1 || splits <= most; ++splits) {
+    const double rounds = static_cast<double>((tiles * splits + 255) / 256);
+    double cost = rounds * (1.8 * static_cast<double>((pairs + splits - 1) / splits) + 12.0);
+    if (splits > 1) cost += static_cast<double>(splits) * static_cast<double>(M) * static_cast<double>(N) * 8.0 / 4.0e6;
+    if (splits == 1 || cost < least) {
+      least = cost;
+      best = splits;
+    }
+  }
+  return best;
+}
+
 // Out[n, m] (+)= sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  n_live != NULL: a device
-// int, the number of leading rows of Bn that count (the tiles past them are not computed).
+// int, the number of leading rows of Bn that count (the tiles past them are not computed).  splits > 1: that many
+// partial results, split_stride floats apart, each over a run of the contraction index (gemm_splits).
 static fopd_status launch_gemm(bool accumulate, const __bf16* Am, int64_t lda, int64_t M, const __bf16* Bn, int64_t ldb,
                                int64_t N, int64_t K, float* Out, int64_t ldo, int slot, hipStream_t s,
-                               const int* n_live = nullptr) {
+                               const int* n_live = nullptr, int splits = 1, int64_t split_stride = 0) {
   if (M <= 0 || N <= 0) return FOPD_OK;
-  if (K <= 0 || K % 64 != 0 || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL) return FOPD_ESHAPE;
+  if (K <= 0 || K % 64 != 0 || splits < 1 || splits > K / 64 || (accumulate && splits > 1) || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL) return FOPD_ESHAPE;
   // byte offsets inside one 256-row operand tile are 32-bit
   if (256 * lda * 2 >= 2147483648LL || 256 * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
   static bool allowed[2][kMaxDevices] = {};
@@ -1156,16 +1179,18 @@ static fopd_status launch_gemm(bool accumulate, const __bf16* Am, int64_t lda, i
   if (allow_dynamic_lds(kern, kGemmLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTileN - 1) / kGemmTileN);
-  const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
+  const int64_t rounds = (splits * tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
   if (accumulate)
     fopd_gemm_nt<true, 0><<<grid, block, kGemmLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bn, ldb, static_cast<int>(N),
-                                                          static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live);
+                                                          static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live, splits,
+                                                          split_stride);
   else
     fopd_gemm_nt<false, 0><<<grid, block, kGemmLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bn, ldb, static_cast<int>(N),
-                                                           static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live);
+                                                           static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live, splits,
+                                                          split_stride);
   return launched();
 }
 
@@ -1405,6 +1430,10 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if ((st = launched()) != FOPD_OK) return st;
   }
 
+  // dL/dhidden in how many runs over the vocabulary: by the rows of the call, not of a chunk, so that a row's sum has the
+  // same order whatever rows_chunk is (and with or without the masked rows).  The partial results of R rows, R d floats
+  // each, fit where the logits of R rows were.
+  const int dh_splits = grads ? gemm_splits(d, T, ldz, ldz / d) : 1;
   int64_t ci = 0;
   for (int sweep = two_sweeps ? 0 : 1; sweep < 2; ++sweep) {
   // (sweep 0, only when a sample does not fit into a chunk: logits and log-probs of every chunk, then the scores)
@@ -1470,7 +1499,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     auto scatter = [&]() -> fopd_status {
       if (!compact) return FOPD_OK;
       fopd_live_scatter<<<static_cast<unsigned>(R), 256, 0, s>>>(
-          row_map, n_live, map_off, row_base, lp_o, ls_o, tl_o, grad_ex, dH, static_cast<int>(d), logp, lse, tl,
+          row_map, n_live, map_off, row_base, lp_o, ls_o, tl_o, grad_ex, dH, dh_splits, R * d, static_cast<int>(d), logp, lse, tl,
           (grads && sweep == 1) ? dhidden : nullptr, lddh);
       return launched();
     };
@@ -1565,7 +1594,18 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
       if ((st = launched()) != FOPD_OK) return st;
     }
     // dL/dhidden of the chunk: rows x hidden, contraction over the vocabulary
-    if ((st = launch_gemm(false, Wt, ldz, d, G, ldz, R, ldz, dH, lddhc, 5, s, live)) != FOPD_OK) return st;
+    // (few rows: in several runs over the vocabulary whose results go where the chunk's logits were, read for the last
+    // time above, and are summed on their way to the caller's rows)
+    if (dh_splits > 1) {
+      dH = Z;
+      lddhc = d;
+    }
+    if ((st = launch_gemm(false, Wt, ldz, d, G, ldz, R, ldz, dH, lddhc, 5, s, live, dh_splits, R * d)) != FOPD_OK) return st;
+    if (dh_splits > 1 && !compact) {
+      fopd_sum_splits<<<static_cast<unsigned>(R), 256, 0, s>>>(Z, dh_splits, R * d, static_cast<int>(d), dhidden + a * lddh,
+                                                             lddh);
+      if ((st = launched()) != FOPD_OK) return st;
+    }
     // dL/dweight: vocabulary x hidden, contraction over the chunk's rows, both operands as they are stored
     const bool acc = (ci > 0) || (accumulate_dweight != 0);
     if (head_grad &&

@@ -43,8 +43,8 @@ constexpr int kGemmTileN = gemm_tile_n(kGemmWavesN, 8 / kGemmWavesN);
 constexpr int kGemmLdsBytes = gemm_lds_bytes(kGemmWavesN, 8 / kGemmWavesN);
 
 // ACCUMULATE = false: Out = product; true: Out += product (the caller's array holds the running sum).
-// K must be a positive multiple of 64; rows past the end of an operand are clamped (re-read) and their
-// results discarded.  Byte offsets inside one 256-row operand tile must fit 32 bits (checked on the host).
+// K must be a positive multiple of 64 (at least 64 for every split); rows past the end of an operand are clamped (re-read)
+// and their results discarded.  Byte offsets inside one 256-row operand tile must fit 32 bits (checked on the host).
 //
 // WM x WN wavefronts share the 256 x 256 tile, each holding (256 / WM) x (256 / WN) of it.  2 x 2 (four
 // wavefronts, one per SIMD, 128 x 128 each = 256 accumulator registers) reads a third less from the LDS per
@@ -82,7 +82,7 @@ template <bool ACCUMULATE, int PROBE = 0, int WM = kGemmWavesM, int WN = kGemmWa
 __global__ void __launch_bounds__(64 * WM * WN)
 fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __restrict__ Bn, int64_t ldb, int N,
              int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
-             const int* __restrict__ n_live) {
+             const int* __restrict__ n_live, int splits = 1, int64_t split_stride = 0) {
   extern __shared__ __align__(16) unsigned char gemm_smem[];
   constexpr int WAVES = WM * WN;
   constexpr int TI = 8 / WM;                   // 32-row blocks along m per wavefront
@@ -104,7 +104,21 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
     if (live <= 0) return;
     tiles_n = min(tiles_n, (live + TN - 1) / TN);
   }
-  const unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), slot = (blockIdx.x >> 3) & 31;
+  // With splits > 1 the contraction index is cut into that many runs of whole pairs of stages, each with a result of its
+  // own, split_stride floats apart, which the caller sums; the groups of a run follow each other.
+  unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7);
+  const unsigned slot = (blockIdx.x >> 3) & 31;
+  if (splits > 1) {
+    const unsigned per_split = static_cast<unsigned>(tile_groups(tiles_m, tiles_n));
+    const int split = static_cast<int>(group / per_split);
+    if (split >= splits) return;
+    group -= static_cast<unsigned>(split) * per_split;
+    const int pairs = K / 64, first = static_cast<int>(static_cast<int64_t>(pairs) * split / splits);
+    K = 64 * (static_cast<int>(static_cast<int64_t>(pairs) * (split + 1) / splits) - first);
+    Am += static_cast<int64_t>(first) * 64;
+    Bn += static_cast<int64_t>(first) * 64;
+    Out += split * split_stride;
+  }
   const TilePlace place = tile_place<true>(group, slot, tiles_m, tiles_n);
   const int tile_m = place.m, tile_n = place.n;
   if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
@@ -757,6 +771,8 @@ __global__ void __launch_bounds__(256) fopd_fill_zero_f32(float* out, int64_t ld
 
 constexpr int kLiveScanThreads = 1024;
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // keep[i] = 1 if sample i has a positive weight under the scores given (float64 ones if fresh64 != NULL, else the
 // float32 ones), else 0.
 __global__ void __launch_bounds__(256)
@@ -895,6 +911,23 @@ fopd_grad_tail_zero(const int* __restrict__ n_grad, uint16_t* __restrict__ G, in
   for (int v = threadIdx.x; v < d / 8; v += 256) h[v] = zero;
 }
 
+// dst[0 .. d) = sum over k < splits, in that order, of src[k split_stride ..], by 256 lanes.  src 16-byte aligned,
+// split_stride and d multiples of 4; dst 16-byte aligned where its pitch lddst is a multiple of 4.
+__device__ __forceinline__ void sum_splits_row(const float* __restrict__ src, int splits, int64_t split_stride, int d,
+                                               float* __restrict__ dst, int64_t lddst) {
+  const bool wide = (lddst & 3) == 0;
+  for (int v = threadIdx.x * 4; v < d; v += 1024) {
+    f32x4 sum = *reinterpret_cast<const f32x4*>(src + v);
+    for (int k = 1; k < splits; ++k) sum += *reinterpret_cast<const f32x4*>(src + k * split_stride + v);
+    if (wide) {
+      *reinterpret_cast<f32x4*>(dst + v) = sum;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dst[v + e] = sum[e];
+    }
+  }
+}
+
 // Dense row c = blockIdx.x of a chunk hands its outputs to the caller's row row_base + row_map[map_off + c] (nothing
 // if map_off + c >= n_live[0]): log-prob and log-sum-exp (logp, lse: NULL together), token loss, and as dL/dhidden row the dense gradient row
 // grad_ex[c] of dhidden_g if the row has one (grad_ex[c + 1] > grad_ex[c]), zeros if not.  token_loss / token_loss_c
@@ -903,8 +936,9 @@ __global__ void __launch_bounds__(256)
 fopd_live_scatter(const int* __restrict__ row_map, const int* __restrict__ n_live, int64_t map_off, int64_t row_base,
                   const float* __restrict__ logp_c, const float* __restrict__ lse_c,
                   const float* __restrict__ token_loss_c, const int* __restrict__ grad_ex,
-                  const float* __restrict__ dhidden_g, int d, float* __restrict__ logp, float* __restrict__ lse,
-                  float* __restrict__ token_loss, float* __restrict__ dhidden, int64_t lddh) {
+                  const float* __restrict__ dhidden_g, int splits, int64_t split_stride, int d,
+                  float* __restrict__ logp, float* __restrict__ lse, float* __restrict__ token_loss,
+                  float* __restrict__ dhidden, int64_t lddh) {
   const int64_t c = blockIdx.x;
   const int tid = threadIdx.x;
   if (map_off + c >= n_live[0]) return;
@@ -921,8 +955,20 @@ fopd_live_scatter(const int* __restrict__ row_map, const int* __restrict__ n_liv
     const bool has = grad_ex[c + 1] > g;
     const float* src = dhidden_g + static_cast<int64_t>(g) * d;
     float* dst = dhidden + t * lddh;
-    for (int v = tid; v < d; v += 256) dst[v] = has ? src[v] : 0.f;
+    if (has) {
+      sum_splits_row(src, splits, split_stride, d, dst, lddh);
+    } else {
+      for (int v = tid; v < d; v += 256) dst[v] = 0.f;
+    }
   }
+}
+
+// Row blockIdx.x of dhidden = the sum of the partial results of fopd_gemm_nt (R rows of d floats each).
+__global__ void __launch_bounds__(256)
+fopd_sum_splits(const float* __restrict__ partial, int splits, int64_t split_stride, int d, float* __restrict__ dhidden,
+                int64_t lddh) {
+  const int64_t r = blockIdx.x;
+  sum_splits_row(partial + r * d, splits, split_stride, d, dhidden + r * lddh, lddh);
 }
 
 // Zeros in the outputs of the rows 0 .. gridDim.x - 1 that take no part: masked ones (mask != NULL and mask[r] == 0)

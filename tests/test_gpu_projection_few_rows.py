@@ -9,6 +9,7 @@ from harness import workloads as wl
 from oracle import fopd_oracle as orc
 from paper_2605_17862_amd import binding as fb
 from parity_util import np64
+from test_gpu_projection_loss import _compare, _run, _scores_from_the_oracle
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -37,3 +38,15 @@ def test_log_probs_at_the_edges_of_tiles_and_groups(T, masked_every):
                                        w["token_ids"], mask, logp, lse, ws)
         assert fb.fopd_workspace_status(ws) == (0, 0)
         assert np.max(np.abs(np64(lse) - ref_lse)) <= 1e-4 and np.max(np.abs(np64(logp) - ref_lp)) <= 1e-4
+
+
+@pytest.mark.parametrize("seq,d,pad_h", [((1,), 64, 0), ((40, 25), 64, 2), ((100, 157), 320, 4), ((300, 214), 512, 3)])
+def test_gradients_with_the_vocabulary_cut_into_runs(seq, d, pad_h):
+    """One to sixteen result tiles of dL/dhidden: the contraction over 20,001 entries is cut into runs and the scatter
+    sums them, into rows whose pitch is and is not a multiple of four."""
+    T = sum(seq)
+    h = wl.generate_lm_head(T, d, 20001, DEV, seed=T, masked_every=4 if T > 1 else 0)
+    w = wl.attach_loss_inputs(h, seq, [1, 3][:len(seq)], seed=T)
+    scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
+    out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, (T + 63) // 64 * 64, scores, pad_h=pad_h)
+    _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)
