@@ -1227,11 +1227,12 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Ak, int64_t lda
 static fopd_status launch_transpose(const void* in, int64_t ld_in, int64_t rows, int64_t cols, void* out, int64_t ld_out,
                                     int64_t rows_pad, hipStream_t s) {
   if (rows_pad <= 0 || cols <= 0) return FOPD_OK;
-  const dim3 grid(static_cast<unsigned>((rows_pad + 63) / 64), static_cast<unsigned>((cols + 63) / 64));
+  const dim3 grid(static_cast<unsigned>((rows_pad + kTrTile - 1) / kTrTile),
+                  static_cast<unsigned>((cols + kTrTile - 1) / kTrTile));
   if (grid.y > 65535u) {      // the second grid dimension is short: walk it in slabs
-    for (int64_t c0 = 0; c0 < cols; c0 += 65535LL * 64) {
-      const int64_t cn = (cols - c0 < 65535LL * 64) ? cols - c0 : 65535LL * 64;
-      const dim3 g2(grid.x, static_cast<unsigned>((cn + 63) / 64));
+    for (int64_t c0 = 0; c0 < cols; c0 += 65535LL * kTrTile) {
+      const int64_t cn = (cols - c0 < 65535LL * kTrTile) ? cols - c0 : 65535LL * kTrTile;
+      const dim3 g2(grid.x, static_cast<unsigned>((cn + kTrTile - 1) / kTrTile));
       fopd_transpose_bf16<<<g2, 256, 0, s>>>(static_cast<const uint16_t*>(in) + c0, ld_in, static_cast<int>(rows),
                                              static_cast<int>(cn), static_cast<uint16_t*>(out) + c0 * ld_out, ld_out,
                                              static_cast<int>(rows_pad));
