@@ -1059,7 +1059,7 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
                                         int64_t T, int64_t V, int64_t d, const int32_t* token_ids,
                                         const uint8_t* mask, float* logp, float* lse, void* workspace,
                                         size_t workspace_bytes, void* stream) {
-  if (T < 0 || V <= 0 || d <= 0 || d % (2 * kLmK) != 0 || ldh < d || ldw < d) return FOPD_ESHAPE;
+  if (T < 0 || V <= 0 || d <= 0 || d % kLmK != 0 || ldh < d || ldw < d) return FOPD_ESHAPE;
   // every byte offset inside the projection matrix must fit 32 bits
   if (V * ldw >= 2147483648LL || ldh >= 2147483648LL) return FOPD_ESHAPE;
   if (hidden == nullptr || weight == nullptr || token_ids == nullptr || logp == nullptr || lse == nullptr)
@@ -1147,7 +1147,7 @@ size_t fopd_lm_head_loss_workspace_bytes(int64_t T, int64_t V, int64_t d, int32_
 // by round, an item takes 1.8 a pair of stages of 64 plus 12 for its first loads and its stores, and the partial results
 // are written and read at 4 TB/s.  512 rows x 4096, K = 151,936 (32 tiles): 1 run 2805 us, 8 runs 520 us.
 static int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
-  const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTileN - 1) / kGemmTileN), pairs = K / 64;
+  const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile), pairs = K / 64;
   most = std::min<int64_t>(std::min<int64_t>(most, 32), pairs / 8);
   int best = 1;
   double least = 0.0;
@@ -1163,34 +1163,29 @@ static int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
   return best;
 }
 
-// Out[n, m] (+)= sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  n_live != NULL: a device
-// int, the number of leading rows of Bn that count (the tiles past them are not computed).  splits > 1: that many
-// partial results, split_stride floats apart, each over a run of the contraction index (gemm_splits).
-static fopd_status launch_gemm(bool accumulate, const __bf16* Am, int64_t lda, int64_t M, const __bf16* Bn, int64_t ldb,
-                               int64_t N, int64_t K, float* Out, int64_t ldo, int slot, hipStream_t s,
-                               const int* n_live = nullptr, int splits = 1, int64_t split_stride = 0) {
+// Out[n, m] = sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  n_live != NULL: a device int, the
+// number of leading rows of Bn that count (the tiles past them are not computed).  splits > 1: that many partial results,
+// split_stride floats apart, each over a run of the contraction index (gemm_splits).
+static fopd_status launch_gemm(const __bf16* Am, int64_t lda, int64_t M, const __bf16* Bn, int64_t ldb, int64_t N,
+                               int64_t K, float* Out, int64_t ldo, int slot, hipStream_t s, const int* n_live = nullptr,
+                               int splits = 1, int64_t split_stride = 0) {
   if (M <= 0 || N <= 0) return FOPD_OK;
-  if (K <= 0 || K % 64 != 0 || splits < 1 || splits > K / 64 || (accumulate && splits > 1) || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL) return FOPD_ESHAPE;
+  if (K <= 0 || K % kLmK != 0 || splits < 1 || splits > K / kLmK || M > 2147483647LL || N > 2147483647LL ||
+      K > 2147483647LL)
+    return FOPD_ESHAPE;
   // byte offsets inside one 256-row operand tile are 32-bit
   if (256 * lda * 2 >= 2147483648LL || 256 * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
-  static bool allowed[2][kMaxDevices] = {};
-  const void* kern = accumulate ? reinterpret_cast<const void*>(fopd_gemm_nt<true, 0>)
-                                : reinterpret_cast<const void*>(fopd_gemm_nt<false, 0>);
-  if (allow_dynamic_lds(kern, kGemmLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
+  static bool allowed[kMaxDevices] = {};
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(fopd_gemm_nt), kLoopLdsBytes, allowed) != FOPD_OK) return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
-  const int tiles_n = static_cast<int>((N + kGemmTileN - 1) / kGemmTileN);
+  const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (splits * tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
-  if (accumulate)
-    fopd_gemm_nt<true, 0><<<grid, block, kGemmLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bn, ldb, static_cast<int>(N),
-                                                          static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live, splits,
-                                                          split_stride);
-  else
-    fopd_gemm_nt<false, 0><<<grid, block, kGemmLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bn, ldb, static_cast<int>(N),
-                                                           static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live, splits,
-                                                          split_stride);
+  fopd_gemm_nt<<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bn, ldb, static_cast<int>(N),
+                                                  static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live, splits,
+                                                  split_stride);
   return launched();
 }
 
@@ -1200,25 +1195,25 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Ak, int64_t lda
                                   const __bf16* Bk, int64_t ldb, int64_t N, int64_t K, float* Out, int64_t ldo, int slot,
                                   hipStream_t s, const int* k_live = nullptr) {
   if (M <= 0 || N <= 0) return FOPD_OK;
-  if (K <= 0 || K % 64 != 0 || rows_a < 1 || rows_a > K || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL ||
-      M % 8 != 0 || lda % 8 != 0 || ldb % 8 != 0 || lda < M || ldb < (N + 7) / 8 * 8)
+  if (K <= 0 || K % 64 != 0 || rows_a <= K - kLmK || rows_a > K || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL ||
+      M % 8 != 0 || lda % 8 != 0 || ldb % 8 != 0 || lda < M || ldb < (N + 7) / 8 * 8 || kLmK * lda * 2 >= 2147483648LL || kLmK * ldb * 2 >= 2147483648LL)
     return FOPD_ESHAPE;
   static bool allowed[2][kMaxDevices] = {};
   const void* kern = accumulate ? reinterpret_cast<const void*>(fopd_gemm_tn<true>)
                                 : reinterpret_cast<const void*>(fopd_gemm_tn<false>);
-  if (allow_dynamic_lds(kern, kTnLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
+  if (allow_dynamic_lds(kern, kLoopLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
-  const int tiles_n = static_cast<int>((N + kGemmTileN - 1) / kGemmTileN);
+  const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
   if (accumulate)
-    fopd_gemm_tn<true><<<grid, block, kTnLdsBytes, s>>>(Ak, lda, static_cast<int>(M), static_cast<int>(rows_a), Bk, ldb,
+    fopd_gemm_tn<true><<<grid, block, kLoopLdsBytes, s>>>(Ak, lda, static_cast<int>(M), static_cast<int>(rows_a), Bk, ldb,
                                                        static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m,
                                                        tiles_n, k_live);
   else
-    fopd_gemm_tn<false><<<grid, block, kTnLdsBytes, s>>>(Ak, lda, static_cast<int>(M), static_cast<int>(rows_a), Bk, ldb,
+    fopd_gemm_tn<false><<<grid, block, kLoopLdsBytes, s>>>(Ak, lda, static_cast<int>(M), static_cast<int>(rows_a), Bk, ldb,
                                                         static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m,
                                                         tiles_n, k_live);
   return launched();
@@ -1505,7 +1500,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
       return launched();
     };
     // logits of the chunk, fp32, never rounded to the storage type of stored logits
-    if ((st = launch_gemm(false, Wm, ldw, V, Hc, ldhc, R, d, Z, ldz, 4, s, live)) != FOPD_OK) return st;
+    if ((st = launch_gemm(Wm, ldw, V, Hc, ldhc, R, d, Z, ldz, 4, s, live)) != FOPD_OK) return st;
     if ((st = launch_k1(Z, FOPD_F32, R, V, ldz, tok, msk, lp_o, ls_o, nullptr, nullptr, flags, s)) != FOPD_OK) return st;
     if (listed != nullptr) {
       // the listed logits of each row are in the chunk's scratch: token loss, G_rest - l_t and the per-slot terms
@@ -1601,7 +1596,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
       dH = Z;
       lddhc = d;
     }
-    if ((st = launch_gemm(false, Wt, ldz, d, G, ldz, R, ldz, dH, lddhc, 5, s, live, dh_splits, R * d)) != FOPD_OK) return st;
+    if ((st = launch_gemm(Wt, ldz, d, G, ldz, R, ldz, dH, lddhc, 5, s, live, dh_splits, R * d)) != FOPD_OK) return st;
     if (dh_splits > 1 && !compact) {
       fopd_sum_splits<<<static_cast<unsigned>(R), 256, 0, s>>>(Z, dh_splits, R * d, static_cast<int>(d), dhidden + a * lddh,
                                                              lddh);

@@ -12,13 +12,9 @@
 //                                                         (W^T is formed once per call)
 //   dL/dweight  dW[V, d] += dZ[R, V]^T . H[R, d]          tn: n = vocabulary entry, m = hidden element, k = row
 //
-// Tiling and memory pipeline are those of the projection kernel fused with the log-sum-exp
-// (fopd_lm_head.hip): a workgroup of eight wavefronts (2 along m x 4 along n) owns a 256 x 256 tile of the
-// result; each wavefront holds 128 (m) x 64 (n) of it as 4 x 2 accumulators of v_mfma_f32_32x32x16_bf16;
-// stages of 32 k-elements of both operand tiles reach the LDS through vector registers, a quarter of a pair of
-// stages per 16-k slice, and are read back as 16-byte fragments through an XOR-swizzled map without bank
-// conflicts.  The n-side fragment is the instruction's first operand: the 32 lanes of a half-wave then hold
-// consecutive m of one output row, the contiguous side of the output.
+// Tiling and loop are those of the projection kernel fused with the log-sum-exp (fopd_lm_head.hip, matrix_step): a
+// workgroup of eight wavefronts owns a 256 x 256 tile of the result.  The n-side fragment is the instruction's first
+// operand: the 32 lanes of a half-wave then hold consecutive m of one output row, the contiguous side of the output.
 
 #ifndef FOPD_GEMM_HIP_
 #define FOPD_GEMM_HIP_
@@ -32,79 +28,54 @@
 namespace fopd {
 
 constexpr int kGemmTile = kLmTile;          // 256 x 256 result tile
-constexpr int kGemmWavesM = 2, kGemmWavesN = 4;   // eight wavefronts of 128 x 64: the faster of the measured shapes
-constexpr int kGemmStaging = 4;                   // operand stages go through registers, a quarter of a pair per slice
-constexpr int kGemmThreads = 64 * kGemmWavesM * kGemmWavesN;
-// Extent of the result tile along n and bytes of LDS (four stages of both operand tiles) for WN wavefronts along n
-// holding TJ 32-row blocks each.
-constexpr int gemm_tile_n(int wn, int tj) { return 32 * tj * wn; }
-constexpr int gemm_lds_bytes(int wn, int tj) { return kLmStages * (kLmOperandBytes + gemm_tile_n(wn, tj) * 64); }
-constexpr int kGemmTileN = gemm_tile_n(kGemmWavesN, 8 / kGemmWavesN);
-constexpr int kGemmLdsBytes = gemm_lds_bytes(kGemmWavesN, 8 / kGemmWavesN);
+constexpr int kGemmThreads = kLmThreads;
 
-// ACCUMULATE = false: Out = product; true: Out += product (the caller's array holds the running sum).
+// The wavefront's part of a finished tile, rows n0 .. , columns m0 .. of Out.  The n-side fragment is the matrix
+// instruction's first operand, so register r of acc[a][i][b] is output row n = 128 b + 32 wn + 8 (r / 4) + 4 (lane / 32) +
+// r % 4 of the tile, and the 32 lanes of a half-wave hold consecutive m = 128 a + 64 wm + 32 i + lane % 32: a store
+// instruction writes two whole 128-byte lines.  (With the m side first, a lane holds four consecutive m and an instruction
+// writes 32 bytes to each of 32 rows: 2 - 3 % slower.)
+template <bool ACCUMULATE>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][2][2], const MatrixPlace& place, int m0, int n0, int M,
+                                           int N, float* __restrict__ Out, int64_t ldo) {
+  const int lane = threadIdx.x & 63;
+  const int m = m0 + place.wm * 64 + (lane & 31);
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int n = n0 + b * 128 + place.wn * 32 + ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
+      if (n >= N) continue;
+      float* orow = Out + static_cast<int64_t>(n) * ldo;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int mi = m + (i >> 1) * 128 + (i & 1) * 32;
+        if (mi < M) {
+          // (every entry of Out belongs to one lane of one workgroup, so the hardware add, which does not wait for the
+          // old value to come back, gives the same sums as load - add - store, in the same order)
+          if (ACCUMULATE) unsafeAtomicAdd(orow + mi, acc[i >> 1][i & 1][b][r]);
+          else orow[mi] = acc[i >> 1][i & 1][b][r];
+        }
+      }
+    }
+}
+
 // K must be a positive multiple of 64 (at least 64 for every split); rows past the end of an operand are clamped (re-read)
 // and their results discarded.  Byte offsets inside one 256-row operand tile must fit 32 bits (checked on the host).
-//
-// WM x WN wavefronts share the 256 x 256 tile, each holding (256 / WM) x (256 / WN) of it.  2 x 2 (four
-// wavefronts, one per SIMD, 128 x 128 each = 256 accumulator registers) reads a third less from the LDS per
-// flop than 2 x 4 (eight wavefronts of 128 x 64): with 2 x 4 the LDS carries 192 KB of fragment reads + 64 KB of
-// stage writes per 64 k-elements, as many cycles at 128 bytes per clock as the matrix cores need at full rate.
-// Measured, 2 x 4 is the faster shape; the timing variants below show what the loop loses where.
-//
-// PROBE != 0 are timing variants for the bound analysis (built only into the gemm_probe program; their results
-// are wrong on purpose, every access stays inside the same buffers):
-//   1  every stage re-reads k = 0..63 of the operand tiles: with direct loads every request is an L2 hit on a hot
-//      line (direct loads do not allocate in the L1); with loads through registers every request hits the L1
-//   2  no global loads after the prologue: LDS reads + matrix cores only
-//   3  global loads as usual, fragments read once: no LDS reads in the loop
-//   4  neither: matrix-core issue only
-//   5  the first direct-load instruction of the n-side tile left out: 25 % (eight wavefronts) or 12.5 % (four) fewer
-//      bytes through the L1, as a wider tile would need per flop
-//   6  (register staging only) each line of pair p + 3 is requested once per XCD a pair before its loads, by one of
-//      the workgroups that share the tile: lower miss latency, no gain in time
-//   7  the wavefront raises its priority while it issues matrix instructions: no gain
-//   8  no result stores
-//   9  (results correct) non-temporal result stores
-//  14  (results correct) the first round of workgroups starts skewed in time (steps of 512 cycles inside an XCD), to
-//      spread the bursts of result stores: no gain (steps of 128 and 2048 cycles neither)
-//  10  (results correct) no scheduling group barriers: the order inside a slice is the scheduler's (memory instructions
-//      first); 11, 13: two other orders (fragment reads first; one memory instruction per gap)
-//
-// VIA_REGS != 0: the operand stages travel global -> vector registers -> LDS (ordinary loads, then ds_write_b128 to
-// the same swizzled slots) instead of global -> LDS directly.  1: the loads of pair p + 2 are issued at the start
-// of pair p and written to the LDS at the start of pair p + 1; 2, 3: the same with the loads issued in two / four
-// portions over the pair; 4 (shipped): each of the four 16-k slices of a pair writes one quarter of pair p + 1 to
-// the LDS and requests the same quarter of pair p + 2, so that every load has a whole pair to land and the L1 sees
-// an even stream of requests instead of a burst behind each barrier (measured: 0.45 -> 0.50 of peak).
-template <bool ACCUMULATE, int PROBE = 0, int WM = kGemmWavesM, int WN = kGemmWavesN, int TJ = 8 / WN,
-          int VIA_REGS = kGemmStaging>
-__global__ void __launch_bounds__(64 * WM * WN)
+__global__ void __launch_bounds__(kGemmThreads)
 fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __restrict__ Bn, int64_t ldb, int N,
              int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
-             const int* __restrict__ n_live, int splits = 1, int64_t split_stride = 0) {
+             const int* __restrict__ n_live, int splits, int64_t split_stride) {
   extern __shared__ __align__(16) unsigned char gemm_smem[];
-  constexpr int WAVES = WM * WN;
-  constexpr int TI = 8 / WM;                   // 32-row blocks along m per wavefront
-  constexpr int TN = 32 * TJ * WN;             // tile extent along n (TJ 32-row blocks per wavefront): 256, 320 or 384
-  constexpr int CPA = 16 / WAVES;              // direct-load instructions per stage and wavefront: m-side tile,
-  constexpr int CPB = (TN / 16) / WAVES;       // n-side tile
-  constexpr int kABytes = kLmOperandBytes;     // one stage of the m-side tile: 256 rows x 64 bytes
-  constexpr int kStage = kABytes + TN * 64;    // one stage of both tiles
-  static_assert(WAVES == 4 || WAVES == 8, "four or eight wavefronts");
-  static_assert((TN / 16) % WAVES == 0, "the n-side tile must split evenly over the wavefronts");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-
   // Only the first *n_live rows of Bn count when a count is given (it stays on the device, the launch covers all N):
   // tiles past them are left out, and as the groups of tiles are dealt to the XCDs in turn, these stay evenly loaded
   // whatever the count is.
   if (n_live != nullptr) {
     const int live = *n_live;
     if (live <= 0) return;
-    tiles_n = min(tiles_n, (live + TN - 1) / TN);
+    tiles_n = min(tiles_n, (live + kGemmTile - 1) / kGemmTile);
   }
-  // With splits > 1 the contraction index is cut into that many runs of whole pairs of stages, each with a result of its
+  // With splits > 1 the contraction index is cut into that many runs of whole steps, each with a result of its
   // own, split_stride floats apart, which the caller sums; the groups of a run follow each other.
   unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7);
   const unsigned slot = (blockIdx.x >> 3) & 31;
@@ -113,353 +84,54 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
     const int split = static_cast<int>(group / per_split);
     if (split >= splits) return;
     group -= static_cast<unsigned>(split) * per_split;
-    const int pairs = K / 64, first = static_cast<int>(static_cast<int64_t>(pairs) * split / splits);
-    K = 64 * (static_cast<int>(static_cast<int64_t>(pairs) * (split + 1) / splits) - first);
-    Am += static_cast<int64_t>(first) * 64;
-    Bn += static_cast<int64_t>(first) * 64;
+    const int steps = K / kLmK, first = static_cast<int>(static_cast<int64_t>(steps) * split / splits);
+    K = kLmK * (static_cast<int>(static_cast<int64_t>(steps) * (split + 1) / splits) - first);
+    Am += static_cast<int64_t>(first) * kLmK;
+    Bn += static_cast<int64_t>(first) * kLmK;
     Out += split * split_stride;
   }
   const TilePlace place = tile_place<true>(group, slot, tiles_m, tiles_n);
   const int tile_m = place.m, tile_n = place.n;
   if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
-  const int m0 = tile_m * kGemmTile, n0 = tile_n * TN;
-  if constexpr (PROBE == 14) {
-    // the workgroups of the first round start a little apart (those of one XCD 0 .. 31 steps of 512 cycles), so that
-    // the result stores of the compute units do not all fall into the same few microseconds
-    if (blockIdx.x < 256) {
-      const int steps = (blockIdx.x >> 3) & 31;
-      for (int i = 0; i < steps; ++i) __builtin_amdgcn_s_sleep(8);
-    }
-  }
+  const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
 
-  // global -> LDS copy: see the projection kernel.  An operand tile of a stage is 16 wave instructions of 1 KB;
-  // wavefront w issues instructions CPQ w .. CPQ w + CPQ - 1; instruction q fills rows 16 q .. 16 q + 15; lane i
-  // writes (row 16 q + i / 4, slot i % 4) and fetches logical 16-byte chunk (i % 4) ^ ((i / 16) % 4) of that row.
-  const int cp_chunk = (lane & 3) ^ ((lane >> 4) & 3);
+  const MatrixPlace mine = matrix_place(gemm_smem);
+  const RowMajorHalf at(mine);
   const char* Ab = reinterpret_cast<const char*>(Am) + static_cast<int64_t>(m0) * lda * 2;
   const char* Bb = reinterpret_cast<const char*>(Bn) + static_cast<int64_t>(n0) * ldb * 2;
-  uint32_t a_src[CPA], b_src[CPB];
+  uint32_t off[4][2];                                      // half tile, load
 #pragma unroll
-  for (int q = 0; q < CPA; ++q)
-    a_src[q] = static_cast<uint32_t>(min((wave * CPA + q) * 16 + (lane >> 2), M - 1 - m0)) * static_cast<uint32_t>(lda) * 2u +
-               cp_chunk * 16;
+  for (int h = 0; h < 4; ++h)
 #pragma unroll
-  for (int q = 0; q < CPB; ++q)
-    b_src[q] = static_cast<uint32_t>(min((wave * CPB + q) * 16 + (lane >> 2), N - 1 - n0)) * static_cast<uint32_t>(ldb) * 2u +
-               cp_chunk * 16;
-  auto load_pair = [&](int ko, int pb) {
-    const int64_t kb = static_cast<int64_t>(ko) * 2;
-    unsigned char* dst = gemm_smem + 2 * pb * kStage;
-#pragma unroll
-    for (int q = 0; q < CPA; ++q) {
-      lm_load_to_lds(Ab + kb, a_src[q], dst + (wave * CPA + q) * 1024);
-      lm_load_to_lds(Ab + kb + 64, a_src[q], dst + kStage + (wave * CPA + q) * 1024);
+    for (int e = 0; e < 2; ++e) {
+      const int row = (h & 1) * 128 + at.row + 8 * e;
+      off[h][e] = (h < 2 ? static_cast<uint32_t>(min(row, M - 1 - m0)) * static_cast<uint32_t>(lda)
+                         : static_cast<uint32_t>(min(row, N - 1 - n0)) * static_cast<uint32_t>(ldb)) * 2u + at.chunk[e];
     }
+  const int n_steps = K / kLmK;
+  auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
+    const char* src = (half < 2 ? Ab : Bb) + static_cast<int64_t>(min(step, n_steps - 1)) * (2 * kLmK);
+    const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
 #pragma unroll
-    for (int q = 0; q < CPB; ++q) {
-      if (PROBE == 5 && q == 0) continue;     // a quarter (8 wavefronts) or an eighth (4) of the fill left out
-      lm_load_to_lds(Bb + kb, b_src[q], dst + kABytes + (wave * CPB + q) * 1024);
-      lm_load_to_lds(Bb + kb + 64, b_src[q], dst + kStage + kABytes + (wave * CPB + q) * 1024);
-    }
+    for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
   };
 
-  // the same stages through vector registers: lane i of instruction q holds what the direct load would have put
-  // at LDS offset 1024 q + 16 i
-  u32x4 staged[VIA_REGS ? 2 * (CPA + CPB) : 1];
-  auto load_regs_a = [&](int ko) {
-    const int64_t kb = static_cast<int64_t>(ko) * 2;
+  f32x16 acc[2][2][2];
 #pragma unroll
-    for (int q = 0; q < CPA; ++q) {
-      staged[2 * q] = *reinterpret_cast<const u32x4*>(Ab + kb + a_src[q]);
-      staged[2 * q + 1] = *reinterpret_cast<const u32x4*>(Ab + kb + 64 + a_src[q]);
-    }
-  };
-  auto load_regs_b = [&](int ko) {
-    const int64_t kb = static_cast<int64_t>(ko) * 2;
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int q = 0; q < CPB; ++q) {
-      staged[2 * CPA + 2 * q] = *reinterpret_cast<const u32x4*>(Bb + kb + b_src[q]);
-      staged[2 * CPA + 2 * q + 1] = *reinterpret_cast<const u32x4*>(Bb + kb + 64 + b_src[q]);
-    }
-  };
-  auto load_regs = [&](int ko) {
-    load_regs_a(ko);
-    load_regs_b(ko);
-  };
-  // one quarter of a pair's loads: group g = 0, 1 the first / second half of the m-side instructions, 2, 3 of the n-side
-  auto load_regs_quarter = [&](int ko, int g) {
-    const int64_t kb = static_cast<int64_t>(ko) * 2;
-    if (g < 2) {
-#pragma unroll
-      for (int q = 0; q < CPA; ++q) {
-        if ((q * 2) / CPA != g) continue;
-        staged[2 * q] = *reinterpret_cast<const u32x4*>(Ab + kb + a_src[q]);
-        staged[2 * q + 1] = *reinterpret_cast<const u32x4*>(Ab + kb + 64 + a_src[q]);
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < CPB; ++q) {
-        if ((q * 2) / CPB != g - 2) continue;
-        staged[2 * CPA + 2 * q] = *reinterpret_cast<const u32x4*>(Bb + kb + b_src[q]);
-        staged[2 * CPA + 2 * q + 1] = *reinterpret_cast<const u32x4*>(Bb + kb + 64 + b_src[q]);
-      }
-    }
-  };
-  auto write_lds = [&](int pb) {
-    unsigned char* dst = gemm_smem + 2 * pb * kStage + lane * 16;
-#pragma unroll
-    for (int q = 0; q < CPA; ++q) {
-      *reinterpret_cast<u32x4*>(dst + (wave * CPA + q) * 1024) = staged[2 * q];
-      *reinterpret_cast<u32x4*>(dst + kStage + (wave * CPA + q) * 1024) = staged[2 * q + 1];
-    }
-#pragma unroll
-    for (int q = 0; q < CPB; ++q) {
-      *reinterpret_cast<u32x4*>(dst + kABytes + (wave * CPB + q) * 1024) = staged[2 * CPA + 2 * q];
-      *reinterpret_cast<u32x4*>(dst + kStage + kABytes + (wave * CPB + q) * 1024) = staged[2 * CPA + 2 * q + 1];
-    }
-  };
-
-  auto write_lds_quarter = [&](int pb, int g) {
-    unsigned char* dst = gemm_smem + 2 * pb * kStage + lane * 16;
-    if (g < 2) {
-#pragma unroll
-      for (int q = 0; q < CPA; ++q) {
-        if ((q * 2) / CPA != g) continue;
-        *reinterpret_cast<u32x4*>(dst + (wave * CPA + q) * 1024) = staged[2 * q];
-        *reinterpret_cast<u32x4*>(dst + kStage + (wave * CPA + q) * 1024) = staged[2 * q + 1];
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < CPB; ++q) {
-        if ((q * 2) / CPB != g - 2) continue;
-        *reinterpret_cast<u32x4*>(dst + kABytes + (wave * CPB + q) * 1024) = staged[2 * CPA + 2 * q];
-        *reinterpret_cast<u32x4*>(dst + kStage + kABytes + (wave * CPB + q) * 1024) = staged[2 * CPA + 2 * q + 1];
-      }
-    }
-  };
-
-  const int frag_row = (lane & 31) * 64;
-  const int a_off = wm * TI * 32 * 64 + frag_row;
-  const int b_off = kABytes + wn * TJ * 32 * 64 + frag_row;
-  int xk[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) xk[ks] = ((2 * ks + (lane >> 5)) ^ ((lane >> 2) & 3)) << 4;
-
-  f32x16 acc[TI][TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int n_pairs = K / 64;
-  int p_ld = 0;
-  auto request_next = [&](int pb) {           // the last pair is requested again at the tail (never read)
-    if (PROBE == 2 || PROBE == 4) return;
-    load_pair(PROBE == 1 ? 0 : p_ld * 64, pb);
-    if (p_ld + 1 < n_pairs) ++p_ld;
-  };
-
-  bf16x8 fa[2][TI], fb[2][TJ];
-  bool in_loop = false;
-  auto read_frags = [&](int buf, const unsigned char* stage, int ks) {
-    if ((PROBE == 3 || PROBE == 4) && in_loop) return;
-#pragma unroll
-    for (int i = 0; i < TI; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(stage + a_off + i * 2048 + xk[ks]);
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) fb[buf][j] = *reinterpret_cast<const bf16x8*>(stage + b_off + j * 2048 + xk[ks]);
-  };
-  auto multiply = [&](int buf) {
-    if (PROBE == 7) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[buf][j], fa[buf][i], acc[i][j], 0, 0, 0);
-    if (PROBE == 7) __builtin_amdgcn_s_setprio(0);
-  };
-
-  // PROBE 10: within a slice, the two LDS writes, the two global loads and the six fragment reads are spread
-  // between the eight matrix instructions instead of being left to the scheduler
-#define FOPD_SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
-  // Order of the instructions inside a 16-k slice, fixed by scheduling group barriers (masks: 0x008 matrix
-  // instruction, 0x020 global load, 0x100 LDS read, 0x200 LDS write).  Left to itself the scheduler puts a slice's ten
-  // memory instructions ahead of its eight matrix instructions; with one or two of them between consecutive matrix
-  // instructions the matrix pipe keeps issuing while they go out: 4 - 5 % on the whole loop (gemm_probe).  Slices
-  // 0 - 2: the two LDS writes, the two global loads, then the six fragment reads in pairs.  Slice 3 sits behind the
-  // barrier: fragment reads in pairs, then the two global loads, each followed by a matrix instruction.
-  // (the counts are those of the shipped shape: eight wavefronts, a quarter of a pair per slice)
-  constexpr bool kShippedShape = (VIA_REGS == 4 && WAVES == 8 && TJ == 2);
-  constexpr int kSched = (!kShippedShape || PROBE == 10) ? 0 : (PROBE == 11) ? 11 : (PROBE == 13) ? 13 : 12;
-  auto interleave_tail = [&]() {
-    if constexpr (kSched != 0) {
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 4);
-    }
-  };
-  auto interleave = [&]() {
-    if constexpr (kSched == 11) {           // fragment reads first, then the LDS writes, the loads last
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 2);
-    }
-    if constexpr (kSched == 12) {           // shipped
-      FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 2);
-    }
-    if constexpr (kSched == 13) {           // one memory instruction per gap where there is room
-      FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1);
-    }
-  };
-  [[maybe_unused]] uint32_t pf_word = 0;
-  [[maybe_unused]] const char* pf_base = Ab;
-  if constexpr (PROBE == 6) {
-    static_assert(PROBE != 6 || (WAVES == 8 && TN == 256 && VIA_REGS == 4), "written for the shipped shape");
-    const int u = wave * 12 + min(lane, 11);                 // line 0 .. 95 of this workgroup's share
-    if (u < 64) pf_base = Ab + static_cast<int64_t>(min(64 * (slot & 3) + u, M - 1 - m0)) * lda * 2;
-    else pf_base = Bb + static_cast<int64_t>(min(32 * ((slot >> 2) & 7) + (u - 64), N - 1 - n0)) * ldb * 2;
+    for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+  matrix_begin(mine, true, [&](int half, int ahead) { request(half, ahead, ahead); });
+  for (int step = 0; step < n_steps; ++step) {
+    const int cur = step & 1;
+    const unsigned char* here = gemm_smem + cur * kStepBytes;
+    matrix_step<true>(
+        acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
+        [&](int half, int ks) { return at.b(here, half, ks); },
+        [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
-  if constexpr (VIA_REGS) {
-    // pair 0 into the LDS, pair 1 into registers; then, per pair p: registers (pair p + 1) -> the buffers pair
-    // p - 1 has left, loads of pair p + 2 -> registers, multiply pair p, barrier.
-    load_regs(0);
-    write_lds(0);
-    load_regs(n_pairs > 1 ? 64 : 0);
-    __syncthreads();
-    read_frags(0, gemm_smem, 0);
-    for (int p = 0; p < n_pairs; ++p) {
-      const int pb = p & 1;
-      const unsigned char* lo = gemm_smem + 2 * pb * kStage;
-      const unsigned char* hi = lo + kStage;
-      const unsigned char* next = gemm_smem + 2 * (pb ^ 1) * kStage;
-      // pair p + 2; the last pair again at the tail
-      const int k_next = (PROBE == 1) ? 0 : min(p + 2, n_pairs - 1) * 64;
-      if (VIA_REGS == 4) {
-        // every quarter of pair p + 1 goes to the LDS a whole pair after it was requested, and the request for
-        // the same quarter of pair p + 2 follows at once: loads and LDS writes are spread evenly over the pair
-        write_lds_quarter(pb ^ 1, 0);
-        load_regs_quarter(k_next, 0);
-      } else {
-        write_lds(pb ^ 1);                                   // pair p + 1 (the compiler waits for its loads)
-        if (VIA_REGS == 2) load_regs_a(k_next);
-        else if (VIA_REGS == 3) load_regs_quarter(k_next, 0);
-        else load_regs(k_next);
-      }
-      read_frags(1, lo, 1);
-      multiply(0);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      if (VIA_REGS == 4) write_lds_quarter(pb ^ 1, 1);
-      if (VIA_REGS >= 3) load_regs_quarter(k_next, 1);
-      read_frags(0, hi, 0);
-      multiply(1);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      if (VIA_REGS == 2) load_regs_b(k_next);
-      if (VIA_REGS == 4) write_lds_quarter(pb ^ 1, 2);
-      if (VIA_REGS >= 3) load_regs_quarter(k_next, 2);
-      read_frags(1, hi, 1);
-      multiply(0);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      if (VIA_REGS == 4) write_lds_quarter(pb ^ 1, 3);
-      __syncthreads();
-      if (VIA_REGS >= 3) load_regs_quarter(k_next, 3);
-      if constexpr (PROBE == 6) {
-        // pair p + 3 into the L2, a pair before its loads are issued: each of its lines is requested by one of
-        // the workgroups that share the operand tile (m-side: 4 workgroups, 64 rows each; n-side: 8, 32 rows each)
-        asm volatile("" ::"v"(pf_word));                     // the previous request has returned
-        if (lane < 12) pf_word = *reinterpret_cast<const uint32_t*>(pf_base + static_cast<int64_t>(min(p + 3, n_pairs - 1)) * 128);
-      }
-      read_frags(0, next, 0);
-      if constexpr (kSched == 0) __builtin_amdgcn_sched_barrier(0);
-      multiply(1);
-      interleave_tail();
-      if constexpr (kSched != 0) __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    // Same schedule as the projection kernel: two pairs of stages in the LDS; while pair p multiplies, pair p + 1
-    // lands; one barrier per pair.  Loads complete in order: after the prologue's two requests (4 CPQ instructions
-    // per wavefront each), "at most 4 CPQ outstanding" means pair 0 has landed.
-    if (PROBE == 2 || PROBE == 4) {             // the probes without loads still start from loaded stages
-      load_pair(0, 0);
-      load_pair(0, 1);
-    }
-    request_next(0);
-    request_next(1);
-    // "at most one pair's worth of own loads outstanding": 2 (CPA + CPB) instructions per wavefront and pair
-    if (PROBE == 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (2 * (CPA + CPB) == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    else if (2 * (CPA + CPB) == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    else if (2 * (CPA + CPB) == 18) asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
-    static_assert(2 * (CPA + CPB) == 8 || 2 * (CPA + CPB) == 16 || 2 * (CPA + CPB) == 18 || 2 * (CPA + CPB) == 20,
-                  "wait count of the prologue");
-    __syncthreads();
-    read_frags(0, gemm_smem, 0);
-    if (PROBE == 3 || PROBE == 4) read_frags(1, gemm_smem, 1);
-    in_loop = true;
-    for (int p = 0; p < n_pairs; ++p) {
-      const int pb = p & 1;
-      const unsigned char* lo = gemm_smem + 2 * pb * kStage;
-      const unsigned char* hi = lo + kStage;
-      const unsigned char* next = gemm_smem + 2 * (pb ^ 1) * kStage;
-      read_frags(1, lo, 1);
-      multiply(0);
-      __builtin_amdgcn_sched_barrier(0);
-      read_frags(0, hi, 0);
-      multiply(1);
-      __builtin_amdgcn_sched_barrier(0);
-      read_frags(1, hi, 1);
-      multiply(0);
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      request_next(pb);
-      read_frags(0, next, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(1);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the tail's unused requests still target the LDS
-
-  }
-
-  if constexpr (PROBE == 8) {                      // no result stores (one conditional store keeps the loop alive)
-    float sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += acc[i][j][r];
-    if (sum == 1.2345e-30f) Out[0] = sum;
-    return;
-  }
-  // The n-side fragment is the matrix instruction's first operand, so register r of block (i, j) is output row
-  // n = 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4 of the wavefront's 32 TJ, and the 32 lanes of a half-wave hold
-  // consecutive m = 32 i + lane % 32: a store instruction writes two whole 128-byte lines.  (With the m side
-  // first, a lane holds four consecutive m and an instruction writes 32 bytes to each of 32 rows: 2 - 3 % slower.)
-  const int m = m0 + wm * TI * 32 + (lane & 31);
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int n = n0 + wn * TJ * 32 + 32 * j + ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
-      if (n >= N) continue;
-      float* orow = Out + static_cast<int64_t>(n) * ldo;
-#pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        if (m + 32 * i < M) {
-          if (ACCUMULATE) orow[m + 32 * i] += acc[i][j][r];
-          else if (PROBE == 9) __builtin_nontemporal_store(acc[i][j][r], orow + m + 32 * i);
-          else orow[m + 32 * i] = acc[i][j][r];
-        }
-      }
-    }
+  matrix_end(mine);
+  store_tile<false>(acc, mine, m0, n0, M, N, Out, ldo);
 }
 
 // The same contraction with both operands k-major (the contraction index is the row index of both matrices):
@@ -467,43 +139,37 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
 //   fopd_gemm_tn            Out[n, m] (+)= sum_{k < K} Bk[k, n] * Ak[k, m]
 //
 // which is the weight gradient as its operands are stored, dW[v, j] += sum_t dZ[t, v] H[t, j], without a transposed
-// copy of either.  Tiling, register staging in quarters, barrier placement and the result stores are those of
-// fopd_gemm_nt; what differs is the LDS layout and how fragments leave it.  A stage holds 32 k-rows of both
-// operand tiles as they are in memory (256 consecutive m or n per row, 512 bytes), row pitch 576 bytes so that
-// consecutive rows start 16 banks apart.  A fragment of the matrix instruction (lane = one m, eight consecutive k)
-// is two LDS transpose reads (ds_read_b64_tr_b16): within a group of 16 lanes, lane 4 e + q supplies the address of
-// four consecutive 16-bit entries and lane i receives entry i % 4 of the lanes 4 e + i / 4, e = 0..3 (measured
-// with an in-bounds probe); with lane 4 e + q pointing at row k + e, entries m + 4 q .. 4 q + 3, lane i gets rows
-// k .. k + 3 of entry m + i.  The 32 lanes of a pass read 4 rows x 64 bytes: all 64 banks once.
+// copy of either.  Loop and result stores are those of fopd_gemm_nt; what differs is the LDS layout and how fragments
+// leave it.  A half tile of a step holds 64 k-rows of 128 consecutive m or n as they are in memory, 256 bytes per row, the
+// four 64-byte blocks of a row permuted by bits 0 and 1 of the row.  A fragment of the matrix instruction (lane = one m,
+// eight consecutive k) is two LDS transpose reads (ds_read_b64_tr_b16): within a group of 16 lanes, lane 4 e + q supplies
+// the address of four consecutive 16-bit entries and lane i receives entry i % 4 of the lanes 4 e + i / 4, e = 0..3
+// (measured with an in-bounds probe); with lane 4 e + q pointing at row k + e, entries m + 4 q .. 4 q + 3, lane i gets rows
+// k .. k + 3 of entry m + i.  The 32 lanes of a pass read 4 rows x 64 bytes, by the permutation in four different
+// blocks: all 64 banks once.
 //
-// K must be a positive multiple of 64.  Ak has rows_a (1 <= rows_a <= K) readable rows; rows rows_a .. K - 1 are
+// K must be a positive multiple of 64.  Ak has rows_a (K - 64 < rows_a <= K) readable rows; rows rows_a .. K - 1 are
 // taken from row rows_a - 1, so the caller's Bk must hold zeros in every row that is not to count (Bk has K
 // readable rows).  M and N need not be multiples of the tile: 16-byte pieces past entry M - 1 / N - 1 of a row are
 // clamped (re-read) and their results discarded; M % 8 == 0, lda % 8 == 0, ldb % 8 == 0, and every row of Bk is
-// readable up to N rounded up to 8 (ldb is at least that).
-constexpr int kTnPitch = 576;                               // bytes per k-row of an operand tile in the LDS
-constexpr int kTnOperandBytes = 32 * kTnPitch;              // one operand tile of one stage
-constexpr int kTnStageBytes = 2 * kTnOperandBytes;
-constexpr int kTnLdsBytes = kLmStages * kTnStageBytes;      // 147,456 of the 163,840 bytes
-
+// readable up to N rounded up to 8 (ldb is at least that).  Byte offsets inside 64 rows must fit 32 bits.
 typedef short tn_i16x4 __attribute__((ext_vector_type(4)));
 typedef short tn_i16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ bf16x8 tn_read_fragment(const unsigned char* p) {
   typedef __attribute__((address_space(3))) tn_i16x4* lds_ptr;
   const tn_i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-  const tn_i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * kTnPitch));
+  const tn_i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 256));
   const tn_i16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, both);
 }
 
-template <bool ACCUMULATE, int SCHED = 2>
+template <bool ACCUMULATE>
 __global__ void __launch_bounds__(kGemmThreads)
 fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, const __bf16* __restrict__ Bk, int64_t ldb,
              int N, int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
              const int* __restrict__ k_live) {
   extern __shared__ __align__(16) unsigned char gemm_smem[];
-  constexpr int WM = kGemmWavesM, WN = kGemmWavesN, TI = 8 / WM, TJ = 8 / WN;
   if (k_live != nullptr) {
     // only the first *k_live rows of the operands count (a device-side count; the rows after them, up to the next
     // multiple of 64, hold zeros in Bk and finite values in Ak)
@@ -511,169 +177,62 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
     if (ACCUMULATE && live <= 0) return;
     K = min(K, max(64, (live + 63) & ~63));
   }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-
   // the groups of one set of tiles along n follow each other on neighbouring XCDs: they read the same columns of Bk, by
   // far the larger operand
   const TilePlace place = tile_place<false>(((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), (blockIdx.x >> 3) & 31, tiles_m,
                                             tiles_n);
   const int tile_m = place.m, tile_n = place.n;
   if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
-  const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTileN;
+  const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
 
-  // global -> registers -> LDS.  A pair of stages is 64 k-rows of 512 bytes per operand = 2048 pieces of 16 bytes,
-  // four per lane: piece u of stage h is row 32 h + 16 u + tid / 32 of the pair, entries 8 (tid % 32) .. + 7 of
-  // the tile; a wave instruction covers two whole rows of the tile.
-  const int krow = tid >> 5;
-  const int a_piece = min((m0 >> 3) + (tid & 31), (M >> 3) - 1);
-  const int b_piece = min((n0 >> 3) + (tid & 31), ((N + 7) >> 3) - 1);
-  const char* Ab = reinterpret_cast<const char*>(Ak) + static_cast<int64_t>(a_piece) * 16;
-  const char* Bb = reinterpret_cast<const char*>(Bk) + static_cast<int64_t>(b_piece) * 16;
-  const int64_t lda2 = lda * 2, ldb2 = ldb * 2;
-  const int lds_piece = krow * kTnPitch + (tid & 31) * 16;
-  u32x4 staged[8];
-  // quarter g of the pair that starts at row k0: g = 0, 1 the m-side operand's stage 0 / 1, g = 2, 3 the n-side's
-  auto load_quarter = [&](int k0, int g) {
-    const int h = g & 1;
+  // Wavefront w fills k-rows 8 w .. + 7 of a half tile in two loads of four rows: lane i writes 16-byte piece i % 16 of row
+  // i / 16 and so fetches piece (i % 16) ^ 4 (row % 4) of the 128 entries
+  const int lane = threadIdx.x & 63;
+  const MatrixPlace mine = matrix_place(gemm_smem);
+  const int krow = 8 * (mine.wm * 4 + mine.wn) + (lane >> 4);
+  const int piece = (lane & 15) ^ ((lane >> 4) << 2);
+  uint32_t col[4];                                         // byte offset in a row, by half tile
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int k = k0 + 32 * h + 16 * u + krow;
-      if (g < 2) staged[2 * g + u] = *reinterpret_cast<const u32x4*>(Ab + static_cast<int64_t>(min(k, rows_a - 1)) * lda2);
-      else staged[2 * g + u] = *reinterpret_cast<const u32x4*>(Bb + static_cast<int64_t>(k) * ldb2);
+  for (int h = 0; h < 4; ++h)
+    col[h] = 16u * static_cast<uint32_t>(h < 2 ? min((m0 >> 3) + 16 * h + piece, (M >> 3) - 1)
+                                               : min((n0 >> 3) + 16 * (h - 2) + piece, ((N + 7) >> 3) - 1));
+  const uint32_t lda2 = static_cast<uint32_t>(lda) * 2u, ldb2 = static_cast<uint32_t>(ldb) * 2u;
+  const int n_steps = K / kLmK;
+  auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
+    const int k0 = min(step, n_steps - 1) * kLmK;
+    const char* src = half < 2 ? reinterpret_cast<const char*>(Ak) + static_cast<int64_t>(k0) * lda * 2
+                               : reinterpret_cast<const char*>(Bk) + static_cast<int64_t>(k0) * ldb * 2;
+    const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int k = krow + 4 * e;
+      load_to_lds(src, col[half] + (half < 2 ? static_cast<uint32_t>(min(k, rows_a - 1 - k0)) * lda2
+                                             : static_cast<uint32_t>(k) * ldb2), dst + e * 1024);
     }
   };
-  auto write_quarter = [&](int pb, int g) {
-    unsigned char* dst = gemm_smem + (2 * pb + (g & 1)) * kTnStageBytes + (g < 2 ? 0 : kTnOperandBytes) + lds_piece;
-    *reinterpret_cast<u32x4*>(dst) = staged[2 * g];
-    *reinterpret_cast<u32x4*>(dst + 16 * kTnPitch) = staged[2 * g + 1];
-  };
+  // LDS -> fragment: lane 16 g + 4 e + q points at row 8 (g / 2) + e (+ 4 for the second read) of the 16 of a slice,
+  // entries 16 (g % 2) + 4 q .. + 3 of a 32-entry block
+  const int in_rows = (((lane >> 5) << 3) + ((lane >> 2) & 3)) * 256 + (((lane >> 4) & 1) << 5) + ((lane & 3) << 3);
+  const int a_off[2] = {in_rows + (((2 * mine.wm) ^ ((lane >> 2) & 3)) << 6),
+                        in_rows + (((2 * mine.wm + 1) ^ ((lane >> 2) & 3)) << 6)};
+  const int b_off = 2 * kHalfBytes + in_rows + ((mine.wn ^ ((lane >> 2) & 3)) << 6);
 
-  // LDS -> fragment: lane 16 g + 4 e + q points at row 8 (g / 2) + e (+ 4 for the second read), entries
-  // 16 (g % 2) + 4 q .. + 3 of a 32-entry block
-  const int frag_off = (((lane >> 5) << 3) + ((lane >> 2) & 3)) * kTnPitch + (((lane >> 4) & 1) << 5) + ((lane & 3) << 3);
-  const int a_off = frag_off + wm * TI * 64;
-  const int b_off = kTnOperandBytes + frag_off + wn * TJ * 64;
-
-  f32x16 acc[TI][TJ];
+  f32x16 acc[2][2][2];
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  bf16x8 fa[2][TI], fb[2][TJ];
-  auto read_frags = [&](int buf, const unsigned char* stage, int ks) {
-    const unsigned char* base = stage + ks * 16 * kTnPitch;
-#pragma unroll
-    for (int i = 0; i < TI; ++i) fa[buf][i] = tn_read_fragment(base + a_off + i * 64);
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) fb[buf][j] = tn_read_fragment(base + b_off + j * 64);
-  };
-  auto multiply = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[buf][j], fa[buf][i], acc[i][j], 0, 0, 0);
-  };
-
-  // the order inside a slice, as in fopd_gemm_nt: the two LDS writes, the two global loads and the twelve transpose
-  // reads (four per gap) go between the eight matrix instructions
-  // SCHED (timing variants of gemm_probe): 0 the scheduler's own order, 1 reads four per gap behind the writes and
-  // loads, 2 two memory instructions in every gap
-  auto tn_interleave = [&]() {
-    if constexpr (SCHED == 1) {
-      FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x200, 1); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 4); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 4); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 4); FOPD_SGB(0x008, 2);
-    }
-    if constexpr (SCHED == 2) {
-      FOPD_SGB(0x200, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-    }
-  };
-
-  // pair 0 into the LDS, pair 1 into registers (requested in the order the loop keeps); then per pair p and 16-k
-  // slice s: quarter s of pair p + 1 -> LDS, request quarter s of pair p + 2, multiply slice s of pair p
-  const int n_pairs = K / 64;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) load_quarter(0, g);
-#pragma unroll
-  for (int g = 0; g < 4; ++g) write_quarter(0, g);
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    __builtin_amdgcn_sched_barrier(0);
-    load_quarter(n_pairs > 1 ? 64 : 0, g);
+    for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+  matrix_begin(mine, true, [&](int half, int ahead) { request(half, ahead, ahead); });
+  for (int step = 0; step < n_steps; ++step) {
+    const int cur = step & 1;
+    const unsigned char* here = gemm_smem + cur * kStepBytes;
+    matrix_step<true>(
+        acc, [&](int half, int i, int ks) { return tn_read_fragment(here + half * kHalfBytes + a_off[i] + ks * 4096); },
+        [&](int half, int ks) { return tn_read_fragment(here + half * kHalfBytes + b_off + ks * 4096); },
+        [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
-  __builtin_amdgcn_sched_barrier(0);
-  __syncthreads();
-  read_frags(0, gemm_smem, 0);
-  for (int p = 0; p < n_pairs; ++p) {
-    const int pb = p & 1;
-    const unsigned char* lo = gemm_smem + 2 * pb * kTnStageBytes;
-    const unsigned char* hi = lo + kTnStageBytes;
-    const unsigned char* next = gemm_smem + 2 * (pb ^ 1) * kTnStageBytes;
-    const int k_next = min(p + 2, n_pairs - 1) * 64;       // pair p + 2; the last pair again at the tail
-    write_quarter(pb ^ 1, 0);
-    load_quarter(k_next, 0);
-    read_frags(1, lo, 1);
-    multiply(0);
-    tn_interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    write_quarter(pb ^ 1, 1);
-    load_quarter(k_next, 1);
-    read_frags(0, hi, 0);
-    multiply(1);
-    tn_interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    write_quarter(pb ^ 1, 2);
-    load_quarter(k_next, 2);
-    read_frags(1, hi, 1);
-    multiply(0);
-    tn_interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    write_quarter(pb ^ 1, 3);
-    __syncthreads();
-    load_quarter(k_next, 3);
-    read_frags(0, next, 0);
-    if constexpr (SCHED == 0) __builtin_amdgcn_sched_barrier(0);
-    multiply(1);
-    // behind the barrier: the transpose reads, then the two global loads, between the matrix instructions
-    if constexpr (SCHED == 1) {
-      FOPD_SGB(0x100, 4); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 4); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 4); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 1); FOPD_SGB(0x020, 1); FOPD_SGB(0x008, 4);
-    }
-    if constexpr (SCHED == 2) {
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1); FOPD_SGB(0x100, 2); FOPD_SGB(0x008, 1);
-      FOPD_SGB(0x020, 2); FOPD_SGB(0x008, 2);
-    }
-    if constexpr (SCHED != 0) __builtin_amdgcn_sched_barrier(0);
-  }
-
-  // result stores: as fopd_gemm_nt (register r of block (i, j): n = 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4,
-  // m = 32 i + lane % 32)
-  const int m = m0 + wm * TI * 32 + (lane & 31);
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int n = n0 + wn * TJ * 32 + 32 * j + ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
-      if (n >= N) continue;
-      float* orow = Out + static_cast<int64_t>(n) * ldo;
-#pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        if (m + 32 * i < M) {
-          // (every entry of Out belongs to one lane of one workgroup, so the hardware add below, which does not
-          // wait for the old value to come back, gives the same sums as load - add - store, in the same order)
-          if (ACCUMULATE) unsafeAtomicAdd(orow + m + 32 * i, acc[i][j][r]);
-          else orow[m + 32 * i] = acc[i][j][r];
-        }
-      }
-    }
+  matrix_end(mine);
+  store_tile<ACCUMULATE>(acc, mine, m0, n0, M, N, Out, ldo);
 }
 
 // out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  128 x 128 tiles through the LDS;

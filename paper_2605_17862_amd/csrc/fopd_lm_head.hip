@@ -17,21 +17,9 @@
 // cross-lane step (the two half-waves).  Both operands are k-contiguous in memory (hidden [T, d],
 // weight [V, d]), so a lane's 8-element fragment is one 16-byte LDS read.
 //
-// Memory pipeline.  A stage is 32 hidden elements of both tiles (2 x 16 KB); the LDS holds two pairs of
-// stages (128 KB of the CU's 160 KB), a pair being 64 hidden elements, i.e. whole 128-byte lines of
-// both matrices.  A pair travels global -> vector registers -> LDS in four quarters, one per 16-element slice
-// of the pair being multiplied: each slice writes one quarter of the next pair to the LDS and requests the same
-// quarter of the pair after it, so every load has a whole pair of matrix work to land and the L1 sees an even
-// stream of requests.  (Direct global -> LDS loads, 16 bytes per lane with lane i writing LDS bytes
-// [base + 16 i, + 16), were used first: they can only be issued in a burst behind the barrier that frees the
-// buffers, which costs 9 % on this loop.)  The slots are those a direct load would fill, so the map below holds.
-// Measured on MI355X: this loop is bound by the L1 miss path from the L2, about 17 - 19 bytes per clock and
-// compute unit where full MFMA rate on a 256 x 256 tile needs 32 (timing variants and counters: gemm_probe).
-// LDS rows are 64 bytes; the LDS serves 16 lanes x 16 bytes per clock (64 banks), so the 16 rows that a
-// quarter-wave reads at one logical 16-byte chunk must land on 16 different chunk slots modulo 16:
-// the chunk index is XOR-ed with bits 2..3 of the row (rows r .. r + 3 already differ by 4 slots).
-// The LDS side of a slot is fixed by the lane number (as a direct load fixes it), so the permutation is applied
-// on the global side: lane i fetches the chunk that belongs in slot i.
+// The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Measured on MI355X it is
+// bound by the L1 miss path from the L2: about 20 bytes per clock and compute unit where full MFMA rate on a 256 x 256
+// tile needs 32.
 
 #ifndef FOPD_LM_HEAD_HIP_
 #define FOPD_LM_HEAD_HIP_
@@ -46,14 +34,14 @@
 namespace fopd {
 
 constexpr int kLmTile = 256;                              // vocabulary rows and token rows of a workgroup tile
-constexpr int kLmK = 32;                                  // hidden elements per LDS stage
-constexpr int kLmStages = 4;                              // stages resident in the LDS
+constexpr int kLmK = 64;                                  // hidden elements of a step
 constexpr int kLmStrips = 32;                             // vocabulary strips = partial pairs per token: room for 32 of all
 constexpr int kLmPairsExtra = 57344;                      // tokens and this many pairs more (256 strips of one token tile)
 constexpr int kLmThreads = 512;                           // 8 wavefronts: 2 (vocabulary) x 4 (tokens)
-constexpr int kLmOperandBytes = kLmTile * kLmK * 2;       // one operand tile of one stage: 16 KB
-constexpr int kLmStageBytes = 2 * kLmOperandBytes;
-constexpr int kLmLdsBytes = kLmStages * kLmStageBytes + 2 * kLmTile * 8;   // + the cross-wave exchange
+constexpr int kHalfBytes = 128 * kLmK * 2;                // half an operand tile of a step: 16 KB
+constexpr int kStepBytes = 4 * kHalfBytes;                // both operand tiles of a step
+constexpr int kLoopLdsBytes = 2 * kStepBytes;             // two steps: 128 KB of the compute unit's 160
+constexpr int kLmLdsBytes = kLoopLdsBytes + 2 * kLmTile * 8;                // + the cross-wave exchange
 constexpr float kLmNone = -__builtin_inff();              // "no value yet": the reference of an empty pair
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -69,14 +57,6 @@ __device__ __forceinline__ void lm_merge(float& m, float& s, float m2, float s2)
   const float b = (m2 == mx) ? 1.f : fast_exp2((m2 - mx) * kLog2e);
   s = s * a + s2 * b;
   m = mx;
-}
-
-// 16 bytes per lane from (uniform base) + (per-lane byte offset) straight into the LDS: lane i of the
-// wavefront writes lds_base + 16 i (lds_base is the same for all lanes).
-__device__ __forceinline__ void lm_load_to_lds(const char* base, uint32_t voff, unsigned char* lds_base) {
-  typedef __attribute__((address_space(1))) const void gptr_t;
-  typedef __attribute__((address_space(3))) void lptr_t;
-  __builtin_amdgcn_global_load_lds((gptr_t*)(base + voff), (lptr_t*)lds_base, 16, 0, 0);
 }
 
 // Which tile a workgroup owns.  A launch is a list of groups of 32 workgroups; workgroups go to the eight XCDs in turn
@@ -110,6 +90,167 @@ __device__ __forceinline__ TilePlace tile_place(unsigned group, unsigned slot, i
   return TilePlace{at_m * gm + sl / gn, at_n * gn + sl % gn};
 }
 
+// ---- the loop of the matrix kernels -------------------------------------------------------------------------------
+// A workgroup of eight wavefronts multiplies a 256-row tile A by a 256-row tile B, 64 elements of the contraction index a
+// step.  Each tile is two halves of 128 rows (A0, A1, B0, B1: 16 KB each); the LDS holds two steps.  Wavefront (wm, wn),
+// wm = wave / 4, wn = wave % 4, owns rows 64 wm .. + 63 of both A halves and 32 wn .. + 31 of both B halves: four
+// products of 64 x 32, acc[A half][32-row block][B half], one a phase.
+//
+// A phase is two slots between barriers: LDS reads and requests of one half tile, then the eight matrix instructions of
+// a product.  The wavefronts of wm = 1 pass one barrier more at the start, so they are always one slot behind: on each
+// SIMD, which holds one wavefront of either kind, one multiplies while the other reads.  A half tile goes from memory
+// straight to the LDS (16 bytes a lane) as soon as both kinds have read what it replaces, five to seven phases before it
+// is read, and nothing ever waits for all requests:
+//
+//   phase   reads      multiplies   requests              waits for (besides its own LDS reads)
+//     1     B0, A0     A0 x B0      A1 of the next step
+//     2     B1         A0 x B1      B0 of the next but one   A1 of this step       (5 half tiles stay in flight)
+//     3     A1         A1 x B1      A0 of the next but one
+//     4                A1 x B0      B1 of the next but one   B0, A0, B1 of the next step   (4 stay in flight)
+//
+// What replaces what: a half tile is requested in the slot after the one in which the later kind's reads of its
+// predecessor have returned (each reading slot ends with a wait for the LDS, then the barrier).  A wavefront's two loads a
+// phase are followed by its wait count one barrier before the earlier kind reads.
+//
+// Measured on the log-probs of 16,384 rows x 151,936 entries, d = 4096, against the loop before (tiles through vector
+// registers, a quarter of 64 elements per 16, one barrier per 64): 16.40 - 16.73 -> 15.91 - 15.95 ms on one box.
+// Without the loads it takes 12.8 ms, with every load a hit in the L2 14.3.  Slower: the loads of a slot before its LDS
+// reads (+ 14 %), inside the run of matrix instructions (+ 10 - 16 %): requests wait at the L1, and hold up what follows
+// them; non-temporal loads (+ 14 %); B0 read a phase earlier to even out the reads (+ 1 %).
+
+struct MatrixPlace {
+  int wm, wn;
+  uint32_t lds;        // LDS address of the wavefront's share of half tile A0 of step buffer 0
+};
+
+__device__ __forceinline__ MatrixPlace matrix_place(const unsigned char* smem) {
+  typedef __attribute__((address_space(3))) const unsigned char lds_byte;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  return MatrixPlace{wave >> 2, wave & 3, static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte*)smem)) + wave * 2048u};
+}
+
+// 16 bytes a lane from (uniform base) + (32-bit offset of the lane) to LDS bytes lds + 16 lane.  Has no result register;
+// whoever reads the LDS bytes waits for the wavefront's count of loads first.
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base)
+               : "memory");
+}
+
+// Barrier of the workgroup that no instruction passes in either direction (nothing else is waited for).
+__device__ __forceinline__ void slot_end() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+enum { kHalfA0 = 0, kHalfA1 = 1, kHalfB0 = 2, kHalfB1 = 3 };
+
+// B_FIRST: the B fragment is the matrix instruction's first operand (its 32 rows are then spread over the registers and the
+// A rows over the lanes), else the A fragment is.
+template <bool B_FIRST>
+__device__ __forceinline__ void multiply_phase(f32x16 (&acc)[2][2][2], int a, int b, const bf16x8 (&fa)[2][4],
+                                               const bf16x8 (&fb)[4]) {
+  __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      acc[a][i][b] = B_FIRST ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks], fa[i][ks], acc[a][i][b], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[ks], acc[a][i][b], 0, 0, 0);
+  __builtin_amdgcn_s_setprio(0);
+}
+
+// One step.  read_a(half, i, ks) / read_b(half, ks): the fragment of 32-row block i, elements 16 ks .. + 15, from this
+// step's buffer.  request(half, ahead): the wavefront's two loads of that half tile of the step `ahead` steps later (any
+// readable step past the last one: never read).
+template <bool B_FIRST, typename ReadA, typename ReadB, typename Request>
+__device__ __forceinline__ void matrix_step(f32x16 (&acc)[2][2][2], ReadA read_a, ReadB read_b, Request request) {
+  bf16x8 fa[2][4], fb0[4], fb1[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) fb0[ks] = read_b(0, ks);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) fa[i][ks] = read_a(0, i, ks);
+  request(kHalfA1, 1);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  slot_end();
+  multiply_phase<B_FIRST>(acc, 0, 0, fa, fb0);
+  slot_end();
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) fb1[ks] = read_b(1, ks);
+  request(kHalfB0, 2);
+  asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
+  slot_end();
+  multiply_phase<B_FIRST>(acc, 0, 1, fa, fb1);
+  slot_end();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) fa[i][ks] = read_a(1, i, ks);
+  request(kHalfA0, 2);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  slot_end();
+  multiply_phase<B_FIRST>(acc, 1, 1, fa, fb1);
+  slot_end();
+  request(kHalfB1, 2);
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  slot_end();
+  multiply_phase<B_FIRST>(acc, 1, 0, fa, fb0);
+  slot_end();
+}
+
+// Before the first step: the seven half tiles that precede its own requests, in the order of the steps, and the extra
+// barrier of wm = 1.  request(half, ahead) counts from step 0 here.
+template <typename Request>
+__device__ __forceinline__ void matrix_begin(const MatrixPlace& place, bool any_step, Request request) {
+  if (any_step) {
+    request(kHalfB0, 0);
+    request(kHalfA0, 0);
+    request(kHalfB1, 0);
+    request(kHalfA1, 0);
+    request(kHalfB0, 1);
+    request(kHalfA0, 1);
+    request(kHalfB1, 1);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  }
+  slot_end();
+  if (place.wm == 1) slot_end();
+}
+
+// After the last step: every wavefront has passed the same number of barriers, and no request is left in flight (they
+// write to the LDS).
+__device__ __forceinline__ void matrix_end(const MatrixPlace& place) {
+  if (place.wm == 0) slot_end();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
+// Operands with the contraction index contiguous.  A row of a half tile is 128 bytes in the LDS; its eight 16-byte chunks
+// are permuted by bits 1 .. 3 of the row, so that the sixteen rows that a quarter of a wavefront reads at one chunk lie in
+// all 64 banks.  Wavefront w fills rows 16 w .. + 15 in two loads of eight rows: lane i writes chunk i % 8 of row i / 8
+// and so fetches chunk (i % 8) ^ (row / 2 % 8).
+struct RowMajorHalf {
+  int row, chunk[2];           // row of the wavefront's first load (the second: + 8), bytes of the chunk in the row
+  uint32_t a_off, b_off, xk[4];
+  __device__ __forceinline__ explicit RowMajorHalf(const MatrixPlace& p) {
+    const int lane = threadIdx.x & 63;
+    row = 16 * (p.wm * 4 + p.wn) + (lane >> 3);
+    chunk[0] = ((lane & 7) ^ (lane >> 4)) * 16;
+    chunk[1] = chunk[0] ^ 64;
+    a_off = (p.wm * 64 + (lane & 31)) * 128;
+    b_off = 2 * kHalfBytes + (p.wn * 32 + (lane & 31)) * 128;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) xk[ks] = ((2 * ks + (lane >> 5)) ^ ((lane >> 1) & 7)) << 4;
+  }
+  __device__ __forceinline__ bf16x8 a(const unsigned char* step, int half, int i, int ks) const {
+    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + a_off + i * 4096 + xk[ks]);
+  }
+  __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int ks) const {
+    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + b_off + xk[ks]);
+  }
+};
+
 }  // namespace
 
 __global__ void __launch_bounds__(kLmThreads)
@@ -117,10 +258,7 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
                     int T, int V, int d, float2* __restrict__ partial, int n_token_tiles, int n_vocab_tiles,
                     int n_strips, int64_t t_pad, const int* __restrict__ row_map, const int* __restrict__ n_live) {
   extern __shared__ __align__(16) unsigned char lm_smem[];
-  constexpr int WN = 4;                                // wavefronts along the tokens
-  constexpr int NJ = 8 / WN;                           // 32-token blocks per wavefront
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;            // vocabulary half, token quarter of the tile
+  const int tid = threadIdx.x, lane = tid & 63;
 
   // Only the rows row_map[0 .. *n_live - 1] of H take part when a count is given (masked rows left out; the count stays
   // on the device and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the
@@ -138,111 +276,70 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
   const int vt_begin = static_cast<int>(static_cast<int64_t>(strip) * n_vocab_tiles / n_strips);
   const int vt_end = static_cast<int>(static_cast<int64_t>(strip + 1) * n_vocab_tiles / n_strips);
   const int t0 = token_tile * kLmTile;
-  const int nk = d / kLmK;
-  const int n_iter = (vt_end - vt_begin) * nk;
+  const int nkp = d / kLmK, n_steps = (vt_end - vt_begin) * nkp;
+  const MatrixPlace mine = matrix_place(lm_smem);
+  const RowMajorHalf at(mine);
 
-  // global -> LDS copy.  An operand tile of a stage is 1024 chunks of 16 bytes = 16 wave instructions;
-  // wavefront w issues instructions 2 w and 2 w + 1 of each operand.  Instruction q fills rows
-  // 16 q .. 16 q + 15: lane i writes slot (row 16 q + i / 4, physical chunk i % 4) and therefore fetches
-  // logical chunk (i % 4) ^ ((i / 16) % 4) of that row.  Rows past the end of a matrix re-read its last
-  // row (they are discarded later): the row is clamped, which changes nothing inside the matrix, so
-  // the loop has no branch.  All offsets fit 32 bits (checked on the host).
-  const int cp_row = wave * 32 + (lane >> 2);          // row of instruction 2 w; instruction 2 w + 1: + 16
-  const int cp_chunk = (lane & 3) ^ ((lane >> 4) & 3);
-  const int cp_lds = wave * 2048;                      // LDS offset of instruction 2 w inside the operand
+  // Rows past the end of a matrix re-read its last row (they are discarded later): the row is clamped, which changes
+  // nothing inside the matrix, so the loop has no branch.  All offsets fit 32 bits (checked on the host).
   const char* Wb = reinterpret_cast<const char*>(W);
   const char* Hb = reinterpret_cast<const char*>(H) + (row_map != nullptr ? 0 : static_cast<int64_t>(t0) * ldh * 2);
   const uint32_t ldw2 = static_cast<uint32_t>(ldw) * 2u;
-  uint32_t h_off[2];
+  uint32_t h_off[2][2];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int r = min(cp_row + 16 * q, T - 1 - t0);
-    const uint32_t row = (row_map != nullptr) ? static_cast<uint32_t>(row_map[t0 + r]) : static_cast<uint32_t>(r);
-    h_off[q] = row * static_cast<uint32_t>(ldh) * 2u + cp_chunk * 16;
-  }
-
-  // The two stages that hold vocabulary tile `vtile`, hidden elements ko .. ko + 63, travel through vector
-  // registers in four quarters (ordinary 16-byte loads, then ds_write_b128 to LDS offset 1024 q + 16 lane of
-  // instruction q): one quarter = one instruction of one operand, both halves of its 128-byte lines, requested
-  // back to back.  Group g = 0, 1: weight rows, instruction 0 / 1; 2, 3: hidden rows.
-  u32x4 staged[8];
-  auto load_quarter = [&](int vtile, int ko, int g) {
-    const int64_t kb = static_cast<int64_t>(ko) * 2;
-    const int q = g & 1;
-    if (g < 2) {
-      const int last = V - 1 - vtile * kLmTile;
-      const char* wsrc = Wb + static_cast<int64_t>(vtile) * kLmTile * ldw * 2 + kb;
-      const uint32_t w_off = static_cast<uint32_t>(min(cp_row + 16 * q, last)) * ldw2 + cp_chunk * 16;
-      staged[2 * g] = *reinterpret_cast<const u32x4*>(wsrc + w_off);
-      staged[2 * g + 1] = *reinterpret_cast<const u32x4*>(wsrc + 64 + w_off);
-    } else {
-      staged[2 * g] = *reinterpret_cast<const u32x4*>(Hb + kb + h_off[q]);
-      staged[2 * g + 1] = *reinterpret_cast<const u32x4*>(Hb + kb + 64 + h_off[q]);
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int r = min(h * 128 + at.row + 8 * e, T - 1 - t0);
+      const uint32_t row = (row_map != nullptr) ? static_cast<uint32_t>(row_map[t0 + r]) : static_cast<uint32_t>(r);
+      h_off[h][e] = row * static_cast<uint32_t>(ldh) * 2u + at.chunk[e];
+    }
+  // vocabulary tile and 64 hidden elements of the next step [0] and the one after it [1]; they stop at the last
+  int vt_at[2] = {vt_begin, vt_begin}, k_at[2] = {0, 0}, left = n_steps - 1;
+  auto advance = [&]() {
+    vt_at[0] = vt_at[1];
+    k_at[0] = k_at[1];
+    if (left > 0) {
+      --left;
+      if (++k_at[1] == nkp) {
+        k_at[1] = 0;
+        ++vt_at[1];
+      }
     }
   };
-  auto write_quarter = [&](int pb, int g) {
-    unsigned char* dst = lm_smem + 2 * pb * kLmStageBytes + cp_lds + (g & 1) * 1024 + lane * 16 +
-                         (g < 2 ? 0 : kLmOperandBytes);
-    *reinterpret_cast<u32x4*>(dst) = staged[2 * g];
-    *reinterpret_cast<u32x4*>(dst + kLmStageBytes) = staged[2 * g + 1];
+  auto request = [&](int half, int vtile, int k, int buf) {
+    const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
+    const int64_t kb = static_cast<int64_t>(k) * (2 * kLmK);
+    if (half < 2) {
+      const int last = V - 1 - vtile * kLmTile;
+      const char* src = Wb + static_cast<int64_t>(vtile) * kLmTile * ldw * 2 + kb;
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        load_to_lds(src, static_cast<uint32_t>(min(half * 128 + at.row + 8 * e, last)) * ldw2 + at.chunk[e], dst + e * 1024);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) load_to_lds(Hb + kb, h_off[half - 2][e], dst + e * 1024);
+    }
   };
 
-  // LDS -> fragment: lane reads row (lane % 32) of a 32-row block, hidden elements
-  // 16 ks + 8 (lane / 32) .. + 7 of the stage, i.e. logical chunk 2 ks + lane / 32
-  const int frag_row = (lane & 31) * 64;
-  const int a_off = wm * 128 * 64 + frag_row;
-  const int b_off = kLmOperandBytes + wn * NJ * 32 * 64 + frag_row;
-  int xk[2];
+  f32x16 acc[2][2][2];
+  float run_ref[2], run_sum[2];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) xk[ks] = ((2 * ks + (lane >> 5)) ^ ((lane >> 2) & 3)) << 4;
-
-  f32x16 acc[4][NJ];
-  float run_ref[NJ], run_sum[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
+  for (int j = 0; j < 2; ++j) {
     run_ref[j] = kLmNone;
     run_sum[j] = 0.f;
   }
 
-  // (vt_ld, kt_ld) is the next pair to request; it stops at the last pair, which the tail requests
-  // again (never read) instead of branching.
-  int vt_ld = vt_begin, kt_ld = 0, s_ld = 0;
-  const int n_pairs = n_iter / 2, nkp = nk / 2;
-  auto advance_next = [&]() {
-    if (s_ld + 1 < n_pairs) {
-      ++s_ld;
-      if (++kt_ld == nkp) {
-        kt_ld = 0;
-        ++vt_ld;
-      }
-    }
-  };
-
-  bf16x8 fa[2][4], fb[2][NJ];
-  auto read_frags = [&](int buf, const unsigned char* stage, int ks) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(stage + a_off + i * 2048 + xk[ks]);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) fb[buf][j] = *reinterpret_cast<const bf16x8*>(stage + b_off + j * 2048 + xk[ks]);
-  };
-  auto multiply = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
-  };
-
-  // One finished tile.  Result register r of block (i, j) is vocabulary row
-  // 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4 of the wavefront's 128, token 32 j + lane % 32.
-  // RAGGED (the last vocabulary tile only): rows at or past V count as "no value".
+  // One finished tile.  Result register r of block i = 2 (half of the tile) + 32-row block, token half j, is vocabulary
+  // row 128 (i / 2) + 32 (i % 2) + 8 (r / 4) + 4 (lane / 32) + r % 4 from the wavefront's first, token
+  // 128 j + 32 wn + lane % 32.  RAGGED (the last vocabulary tile only): rows at or past V count as "no value".
   auto epilogue = [&](auto ragged_tag, int vlane) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
+    for (int j = 0; j < 2; ++j) {
       auto value = [&](int i, int r) -> float {
-        if (RAGGED && vlane + i * 32 + ((r >> 2) << 3) + (r & 3) >= V) return kLmNone;
-        return acc[i][j][r];
+        if (RAGGED && vlane + (i >> 1) * 128 + (i & 1) * 32 + ((r >> 2) << 3) + (r & 3) >= V) return kLmNone;
+        return acc[i >> 1][i & 1][j][r];
       };
       float mx = run_ref[j];
 #pragma unroll
@@ -267,104 +364,41 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
     }
   };
 
-  // Schedule of pair p (buffers 2 (p % 2) and 2 (p % 2) + 1), four 16-element slices.  The registers `staged` hold
-  // pair p + 1, requested a whole pair earlier; slice s of pair p
-  //   writes quarter s of pair p + 1 to the other pair of buffers (free since the barrier that ended pair p - 1),
-  //   requests quarter s of pair p + 2 into the same registers,
-  //   reads the fragments of the next slice and multiplies the current one;
-  // the one barrier per pair sits in slice 3, after the last write: behind it pair p + 1 is complete and pair p
-  // fully read.  Loads and LDS writes are thus spread evenly over the pair (a burst of requests behind each
-  // barrier, as direct global -> LDS loads give, costs 9 % on this loop).
-  // The order inside a slice is fixed by scheduling group barriers (masks: 0x008 matrix instruction, 0x020 global
-  // load, 0x100 LDS read, 0x200 LDS write).  Left to itself the scheduler puts a slice's ten memory instructions ahead
-  // of its eight matrix instructions; with one or two of them between consecutive matrix instructions the matrix
-  // pipe keeps issuing while they go out.  Measured in one process on the bench shape: 172.6 -> 165.5 ms; one
-  // memory instruction per gap 168.4, pairs of writes and of loads per gap 172.6 (no gain).
-#define LM_SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
-  auto interleave = [&]() {
-    LM_SGB(0x200, 1); LM_SGB(0x008, 1); LM_SGB(0x200, 1); LM_SGB(0x008, 1);
-    LM_SGB(0x020, 1); LM_SGB(0x008, 1); LM_SGB(0x020, 1); LM_SGB(0x008, 1);
-    LM_SGB(0x100, 2); LM_SGB(0x008, 1); LM_SGB(0x100, 2); LM_SGB(0x008, 1); LM_SGB(0x100, 2); LM_SGB(0x008, 2);
-  };
-  if (n_iter > 0) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) load_quarter(vt_ld, kt_ld * 64, g);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) write_quarter(0, g);
-    advance_next();
-    // in the order the loop keeps (the wait counts at the loop's head assume the less favourable of the two
-    // orders that reach it, so a prologue that requests the quarters in another order shortens every wait)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      __builtin_amdgcn_sched_barrier(0);
-      load_quarter(vt_ld, kt_ld * 64, g);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    advance_next();
-  }
-  __syncthreads();
-  if (n_iter > 0) read_frags(0, lm_smem, 0);
-
-  int pit = 0;
+  matrix_begin(mine, n_steps > 0, [&](int half, int ahead) {
+    if (half == kHalfB0 && ahead == 1) advance();
+    request(half, vt_at[1], k_at[1], ahead);
+  });
+  if (n_steps > 0) advance();
+  int step = 0;
   for (int vt = vt_begin; vt < vt_end; ++vt) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    for (int kt = 0; kt < nkp; ++kt, ++pit) {
-      const int pb = pit & 1;
-      const unsigned char* lo = lm_smem + 2 * pb * kLmStageBytes;
-      const unsigned char* hi = lo + kLmStageBytes;
-      const unsigned char* next = lm_smem + 2 * (pb ^ 1) * kLmStageBytes;
-      const int vt_nx = vt_ld, ko_nx = kt_ld * 64;          // pair p + 2
-      write_quarter(pb ^ 1, 0);
-      load_quarter(vt_nx, ko_nx, 0);
-      read_frags(1, lo, 1);
-      multiply(0);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      write_quarter(pb ^ 1, 1);
-      load_quarter(vt_nx, ko_nx, 1);
-      read_frags(0, hi, 0);
-      multiply(1);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      write_quarter(pb ^ 1, 2);
-      load_quarter(vt_nx, ko_nx, 2);
-      read_frags(1, hi, 1);
-      multiply(0);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      write_quarter(pb ^ 1, 3);
-      __syncthreads();
-      load_quarter(vt_nx, ko_nx, 3);
-      advance_next();
-      read_frags(0, next, 0);
-      multiply(1);
-      // behind the barrier: fragment reads in pairs, then the two global loads, between the matrix instructions
-      LM_SGB(0x100, 2); LM_SGB(0x008, 1); LM_SGB(0x100, 2); LM_SGB(0x008, 1); LM_SGB(0x100, 2); LM_SGB(0x008, 1);
-      LM_SGB(0x020, 1); LM_SGB(0x008, 1); LM_SGB(0x020, 1); LM_SGB(0x008, 4);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+    for (int kt = 0; kt < nkp; ++kt, ++step) {
+      const int cur = step & 1;
+      const unsigned char* here = lm_smem + cur * kStepBytes;
+      matrix_step<false>(
+          acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
+          [&](int half, int ks) { return at.b(here, half, ks); },
+          [&](int half, int ahead) { request(half, vt_at[ahead - 1], k_at[ahead - 1], ahead == 1 ? cur ^ 1 : cur); });
+      advance();
     }
-
-    const int vlane = vt * kLmTile + wm * 128 + ((lane >> 5) << 2);
+    const int vlane = vt * kLmTile + mine.wm * 64 + ((lane >> 5) << 2);
     if (vt * kLmTile + kLmTile > V) epilogue(std::true_type(), vlane);
     else epilogue(std::false_type(), vlane);
   }
+  matrix_end(mine);
 
   // half-waves, then the two wavefronts that share these tokens, then one pair per token and strip
-  __syncthreads();
-  float2* ex = reinterpret_cast<float2*>(lm_smem + kLmStages * kLmStageBytes);
+  float2* ex = reinterpret_cast<float2*>(lm_smem + kLoopLdsBytes);
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
+  for (int j = 0; j < 2; ++j) {
     float m = run_ref[j], s = run_sum[j];
     const float m2 = __shfl_xor(m, 32), s2 = __shfl_xor(s, 32);
     if (lane < 32) {
       lm_merge(m, s, m2, s2);
-      ex[wm * kLmTile + wn * NJ * 32 + j * 32 + lane] = make_float2(m, s);
+      ex[mine.wm * kLmTile + j * 128 + mine.wn * 32 + lane] = make_float2(m, s);
     }
   }
   __syncthreads();
