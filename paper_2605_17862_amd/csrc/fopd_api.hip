@@ -84,7 +84,7 @@ namespace {
 void* g_scratch_ptr[64] = {};
 
 // Workspace of the loss pass through the projection: flags, offsets and counts, the per-chunk O(R) arrays, then
-// the chunk's fp32 logits, its bf16 gradient rows and the transposed projection matrix.  ldz = V rounded up to 64
+// the chunk's fp32 logits, its bf16 gradient rows and (for many rows) the transposed projection matrix.  ldz = V rounded up to 64
 // (the k-extent of the dL/dhidden contraction).
 struct LmLossWorkspace {
   size_t flags = 0, cu = 0, n_train = 0, n_roll = 0, fresh64 = 0, coef = 0, partials = 0, chunk_loss = 0, z = 0, g = 0,
@@ -97,6 +97,12 @@ struct LmLossWorkspace {
   size_t ex = 0, row_map = 0, n_live = 0, cu_c = 0, tok_c = 0, mask_c = 0, behav_c = 0, teach_c = 0, stale_c = 0,
          logp_c = 0, lse_c = 0, tl_c = 0, ids_c = 0, llp_c = 0, h_c = 0, dh_c = 0, grad_ex = 0, h_g = 0, keep = 0;
   int64_t ldz = 0, r_pad = 0, n_chunks = 0;
+  // dL/dhidden of more rows than this reads a transposed copy of the projection matrix.  The copy takes 450 us (151,936 x
+  // 4096) whatever the rows; without it the contraction itself is slower by about 0.1 us a row (its A fragments leave the LDS
+  // in two transposing reads instead of one).  Whole call with / without the copy, us: 512 rows 2737 / 2262, 2048 rows
+  // 7619 / 7239, 4096 rows 14159 / 13969, 16,384 rows 54,649 / 55,947.
+  static constexpr int64_t kTransposeRows = 4096;
+  bool with_wt = false;
   LmLossWorkspace(int64_t T, int64_t V, int64_t d, int32_t B, int64_t rows_chunk, int32_t k = 0) {
     const size_t b = static_cast<size_t>(B < 0 ? 0 : B);
     const int64_t t = T < 0 ? 0 : T;
@@ -104,6 +110,7 @@ struct LmLossWorkspace {
     const size_t r = static_cast<size_t>(t < rc ? (t + 63) / 64 * 64 : rc);     // rows of the largest chunk, padded
     r_pad = static_cast<int64_t>(r);
     n_chunks = (t + rc - 1) / rc;
+    with_wt = t > kTransposeRows;
     ldz = (V + 63) / 64 * 64;
     const size_t dd = static_cast<size_t>(d < 0 ? 0 : d);
     size_t off = 0;
@@ -118,7 +125,7 @@ struct LmLossWorkspace {
     chunk_loss = Workspace::take(off, (static_cast<size_t>(n_chunks) + b + 1) * sizeof(float));
     z = Workspace::take(off, r * static_cast<size_t>(ldz) * sizeof(float));
     g = Workspace::take(off, r * static_cast<size_t>(ldz) * 2);
-    wt = Workspace::take(off, dd * static_cast<size_t>(ldz) * 2);
+    wt = Workspace::take(off, with_wt ? dd * static_cast<size_t>(ldz) * 2 : 0);
     if (k > 0) {
       const size_t kk = static_cast<size_t>(k);
       token_loss = Workspace::take(off, static_cast<size_t>(t) * sizeof(float));
@@ -1163,29 +1170,33 @@ static int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
   return best;
 }
 
-// Out[n, m] = sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  n_live != NULL: a device int, the
-// number of leading rows of Bn that count (the tiles past them are not computed).  splits > 1: that many partial results,
-// split_stride floats apart, each over a run of the contraction index (gemm_splits).
-static fopd_status launch_gemm(const __bf16* Am, int64_t lda, int64_t M, const __bf16* Bn, int64_t ldb, int64_t N,
-                               int64_t K, float* Out, int64_t ldo, int slot, hipStream_t s, const int* n_live = nullptr,
-                               int splits = 1, int64_t split_stride = 0) {
+// Out[n, m] = sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  a_k_major: Am is stored [k, m] and
+// has rows_a readable rows (Bn holds zeros in the columns past them); else it has M rows and rows_a is not used.  n_live !=
+// NULL: a device int, the number of leading rows of Bn that count (the tiles past them are not computed).  splits > 1: that
+// many partial results, split_stride floats apart, each over a run of the contraction index (gemm_splits).
+static fopd_status launch_gemm(bool a_k_major, const __bf16* Am, int64_t lda, int64_t M, int64_t rows_a, const __bf16* Bn,
+                               int64_t ldb, int64_t N, int64_t K, float* Out, int64_t ldo, int slot, hipStream_t s,
+                               const int* n_live = nullptr, int splits = 1, int64_t split_stride = 0) {
   if (M <= 0 || N <= 0) return FOPD_OK;
   if (K <= 0 || K % kLmK != 0 || splits < 1 || splits > K / kLmK || M > 2147483647LL || N > 2147483647LL ||
       K > 2147483647LL)
     return FOPD_ESHAPE;
+  if (a_k_major && (rows_a <= K - kLmK || rows_a > K || M % 8 != 0 || lda % 8 != 0 || lda < M)) return FOPD_ESHAPE;
   // byte offsets inside one 256-row operand tile are 32-bit
   if (256 * lda * 2 >= 2147483648LL || 256 * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
-  static bool allowed[kMaxDevices] = {};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(fopd_gemm_nt), kLoopLdsBytes, allowed) != FOPD_OK) return FOPD_EHIP;
+  static bool allowed[2][kMaxDevices] = {};
+  auto kern = a_k_major ? fopd_gemm_nt<true> : fopd_gemm_nt<false>;
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLoopLdsBytes, allowed[a_k_major ? 1 : 0]) != FOPD_OK)
+    return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (splits * tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
-  fopd_gemm_nt<<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bn, ldb, static_cast<int>(N),
-                                                  static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live, splits,
-                                                  split_stride);
+  kern<<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), static_cast<int>(rows_a), Bn, ldb,
+                                          static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live,
+                                          splits, split_stride);
   return launched();
 }
 
@@ -1387,8 +1398,9 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     }
     return FOPD_OK;
   }
-  // the projection matrix with the vocabulary contiguous (zero beyond V), once per call
-  if (grads && (st = launch_transpose(weight, ldw, V, d, Wt, ldz, ldz, s)) != FOPD_OK) return st;
+  // for many rows the projection matrix with the vocabulary contiguous (zero beyond V), once per call
+  const bool wt = grads && lay.with_wt;
+  if (wt && (st = launch_transpose(weight, ldw, V, d, Wt, ldz, ldz, s)) != FOPD_OK) return st;
 
   // Masked rows have no log-prob and no gradient row: each chunk's live rows are moved to the front (dense copies
   // of the per-row inputs and of the hidden rows), every kernel of the chunk runs on those, the contractions read
@@ -1500,7 +1512,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
       return launched();
     };
     // logits of the chunk, fp32, never rounded to the storage type of stored logits
-    if ((st = launch_gemm(Wm, ldw, V, Hc, ldhc, R, d, Z, ldz, 4, s, live)) != FOPD_OK) return st;
+    if ((st = launch_gemm(false, Wm, ldw, V, V, Hc, ldhc, R, d, Z, ldz, 4, s, live)) != FOPD_OK) return st;
     if ((st = launch_k1(Z, FOPD_F32, R, V, ldz, tok, msk, lp_o, ls_o, nullptr, nullptr, flags, s)) != FOPD_OK) return st;
     if (listed != nullptr) {
       // the listed logits of each row are in the chunk's scratch: token loss, G_rest - l_t and the per-slot terms
@@ -1596,7 +1608,9 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
       dH = Z;
       lddhc = d;
     }
-    if ((st = launch_gemm(Wt, ldz, d, G, ldz, R, ldz, dH, lddhc, 5, s, live, dh_splits, R * d)) != FOPD_OK) return st;
+    if ((st = launch_gemm(!wt, wt ? Wt : Wm, wt ? ldz : ldw, d, V, G, ldz, R, ldz, dH, lddhc, 5, s, live, dh_splits,
+                          R * d)) != FOPD_OK)
+      return st;
     if (dh_splits > 1 && !compact) {
       fopd_sum_splits<<<static_cast<unsigned>(R), 256, 0, s>>>(Z, dh_splits, R * d, static_cast<int>(d), dhidden + a * lddh,
                                                              lddh);

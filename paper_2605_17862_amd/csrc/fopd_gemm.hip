@@ -1,15 +1,16 @@
 // Dense bf16 contractions on the matrix cores of gfx950 (CDNA4), and the small kernels around them, for the
 // loss pass whose logits are the output projection of the hidden states and are made chunk by chunk:
 //
-//   fopd_gemm_nt            Out[n, m] (+)= sum_k Bn[n, k] * Am[m, k]     bf16 in, fp32 accumulate, fp32 out
+//   fopd_gemm_nt            Out[n, m] = sum_k Bn[n, k] * Am[m, k]         bf16 in, fp32 accumulate, fp32 out; Am as it
+//                                                                        is written or stored [k, m]
 //   fopd_gemm_tn            Out[n, m] (+)= sum_k Bk[k, n] * Ak[k, m]     the same with both operands k-major
 //   fopd_transpose_bf16     out[c, r] = in[r, c], zero-padded along r    (brings an operand into k-contiguous form)
 //   fopd_k4_grad_wide       gradient rows from fp32 logits to bf16        c_t (softmax(z_t) - onehot)
 //
 // The three contractions of one chunk of R rows (d hidden size, V vocabulary):
 //   logits      Z[R, V]   = H[R, d]  . W[V, d]^T          nt: n = row, m = vocabulary entry, k = hidden element
-//   dL/dhidden  dH[R, d]  = dZ[R, V] . (W^T)[d, V]^T      nt: n = row, m = hidden element, k = vocabulary entry
-//                                                         (W^T is formed once per call)
+//   dL/dhidden  dH[R, d]  = dZ[R, V] . W[V, d]            nt: n = row, m = hidden element, k = vocabulary entry; W as it
+//                                                         is (k-major), or for many rows W^T, formed once per call
 //   dL/dweight  dW[V, d] += dZ[R, V]^T . H[R, d]          tn: n = vocabulary entry, m = hidden element, k = row
 //
 // Tiling and loop are those of the projection kernel fused with the log-sum-exp (fopd_lm_head.hip, matrix_step): a
@@ -60,11 +61,59 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][2][2], const M
     }
 }
 
-// K must be a positive multiple of 64 (at least 64 for every split); rows past the end of an operand are clamped (re-read)
-// and their results discarded.  Byte offsets inside one 256-row operand tile must fit 32 bits (checked on the host).
+// Operands with the contraction index as their row index (k-major).  A half tile of a step holds 64 k-rows of 128
+// consecutive m or n as they are in memory, 256 bytes per row, the four 64-byte blocks of a row permuted by bits 0 and 1 of
+// the row.  A fragment of the matrix instruction (lane = one m, eight consecutive k) is two LDS transpose reads
+// (ds_read_b64_tr_b16): within a group of 16 lanes, lane 4 e + q supplies the address of four consecutive 16-bit entries and
+// lane i receives entry i % 4 of the lanes 4 e + i / 4, e = 0..3 (measured with an in-bounds probe); with lane 4 e + q
+// pointing at row k + e, entries m + 4 q .. 4 q + 3, lane i gets rows k .. k + 3 of entry m + i.  The 32 lanes of a pass read
+// 4 rows x 64 bytes, by the permutation in four different blocks: all 64 banks once.
+//
+// Wavefront w fills k-rows 8 w .. + 7 of a half tile in two loads of four rows: lane i writes 16-byte piece i % 16 of row
+// i / 16 and so fetches piece (i % 16) ^ 4 (row % 4) of the 128 entries.
+typedef short tn_i16x4 __attribute__((ext_vector_type(4)));
+typedef short tn_i16x8 __attribute__((ext_vector_type(8)));
+
+struct KMajorHalf {
+  int krow, piece;             // row of the wavefront's first load (the second: + 4), 16-byte piece of the row
+  int a_off[2], b_off;
+  __device__ __forceinline__ explicit KMajorHalf(const MatrixPlace& p) {
+    const int lane = threadIdx.x & 63;
+    krow = 8 * (p.wm * 4 + p.wn) + (lane >> 4);
+    piece = (lane & 15) ^ ((lane >> 4) << 2);
+    // LDS -> fragment: lane 16 g + 4 e + q points at row 8 (g / 2) + e (+ 4 for the second read) of the 16 of a slice,
+    // entries 16 (g % 2) + 4 q .. + 3 of a 32-entry block
+    const int in_rows = (((lane >> 5) << 3) + ((lane >> 2) & 3)) * 256 + (((lane >> 4) & 1) << 5) + ((lane & 3) << 3);
+    a_off[0] = in_rows + (((2 * p.wm) ^ ((lane >> 2) & 3)) << 6);
+    a_off[1] = in_rows + (((2 * p.wm + 1) ^ ((lane >> 2) & 3)) << 6);
+    b_off = 2 * kHalfBytes + in_rows + ((p.wn ^ ((lane >> 2) & 3)) << 6);
+  }
+  __device__ __forceinline__ bf16x8 fragment(const unsigned char* p) const {
+    typedef __attribute__((address_space(3))) tn_i16x4* lds_ptr;
+    const tn_i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+    const tn_i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 256));
+    const tn_i16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, both);
+  }
+  __device__ __forceinline__ bf16x8 a(const unsigned char* step, int half, int i, int ks) const {
+    return fragment(step + half * kHalfBytes + a_off[i] + ks * 4096);
+  }
+  __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int ks) const {
+    return fragment(step + half * kHalfBytes + b_off + ks * 4096);
+  }
+};
+
+// K must be a positive multiple of 64 (at least 64 for every split); rows of Bn, and with A_K_MAJOR = false of Am, past the
+// end of an operand are clamped (re-read) and their results discarded.  Byte offsets inside one 256-row operand tile must
+// fit 32 bits (checked on the host).
+//
+// A_K_MAJOR: Am is stored [k, m] and has rows_a (K - 64 < rows_a <= K) readable rows; rows rows_a .. K - 1 are taken from
+// row rows_a - 1, so Bn must hold zeros in those columns; pieces past entry M - 1 of a row are clamped.  M % 8 == 0, lda % 8
+// == 0.  This is dL/dhidden with the projection matrix as it is stored, for few rows.
+template <bool A_K_MAJOR>
 __global__ void __launch_bounds__(kGemmThreads)
-fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __restrict__ Bn, int64_t ldb, int N,
-             int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
+fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, const __bf16* __restrict__ Bn, int64_t ldb,
+             int N, int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
              const int* __restrict__ n_live, int splits, int64_t split_stride) {
   extern __shared__ __align__(16) unsigned char gemm_smem[];
   // Only the first *n_live rows of Bn count when a count is given (it stays on the device, the launch covers all N):
@@ -86,7 +135,8 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
     group -= static_cast<unsigned>(split) * per_split;
     const int steps = K / kLmK, first = static_cast<int>(static_cast<int64_t>(steps) * split / splits);
     K = kLmK * (static_cast<int>(static_cast<int64_t>(steps) * (split + 1) / splits) - first);
-    Am += static_cast<int64_t>(first) * kLmK;
+    Am += static_cast<int64_t>(first) * kLmK * (A_K_MAJOR ? lda : 1);
+    rows_a -= first * kLmK;
     Bn += static_cast<int64_t>(first) * kLmK;
     Out += split * split_stride;
   }
@@ -96,24 +146,35 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
 
   const MatrixPlace mine = matrix_place(gemm_smem);
+  typedef typename std::conditional<A_K_MAJOR, KMajorHalf, RowMajorHalf>::type HalfA;
+  const HalfA at_a(mine);
   const RowMajorHalf at(mine);
-  const char* Ab = reinterpret_cast<const char*>(Am) + static_cast<int64_t>(m0) * lda * 2;
+  const char* Ab = reinterpret_cast<const char*>(Am) + (A_K_MAJOR ? 0 : static_cast<int64_t>(m0) * lda * 2);
   const char* Bb = reinterpret_cast<const char*>(Bn) + static_cast<int64_t>(n0) * ldb * 2;
-  uint32_t off[4][2];                                      // half tile, load
+  const uint32_t lda2 = static_cast<uint32_t>(lda) * 2u, ldb2 = static_cast<uint32_t>(ldb) * 2u;
+  uint32_t a_at[2][2], b_at[2][2];                         // byte offsets by half tile, load (k-major: inside a row)
 #pragma unroll
-  for (int h = 0; h < 4; ++h)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const int row = (h & 1) * 128 + at.row + 8 * e;
-      off[h][e] = (h < 2 ? static_cast<uint32_t>(min(row, M - 1 - m0)) * static_cast<uint32_t>(lda)
-                         : static_cast<uint32_t>(min(row, N - 1 - n0)) * static_cast<uint32_t>(ldb)) * 2u + at.chunk[e];
+      const int row = h * 128 + at.row + 8 * e;
+      if constexpr (A_K_MAJOR) a_at[h][e] = 16u * static_cast<uint32_t>(min((m0 >> 3) + 16 * h + at_a.piece, (M >> 3) - 1));
+      else a_at[h][e] = static_cast<uint32_t>(min(row, M - 1 - m0)) * lda2 + at.chunk[e];
+      b_at[h][e] = static_cast<uint32_t>(min(row, N - 1 - n0)) * ldb2 + at.chunk[e];
     }
   const int n_steps = K / kLmK;
   auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
-    const char* src = (half < 2 ? Ab : Bb) + static_cast<int64_t>(min(step, n_steps - 1)) * (2 * kLmK);
+    const int k0 = min(step, n_steps - 1) * kLmK;
     const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
+    const char* src = half >= 2 ? Bb + 2 * static_cast<int64_t>(k0) : Ab + 2 * k0 * (A_K_MAJOR ? lda : 1);
 #pragma unroll
-    for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
+    for (int e = 0; e < 2; ++e) {
+      uint32_t off = half >= 2 ? b_at[half & 1][e] : a_at[half & 1][e];
+      if constexpr (A_K_MAJOR) {
+        if (half < 2) off += static_cast<uint32_t>(min(at_a.krow + 4 * e, rows_a - 1 - k0)) * lda2;
+      }
+      load_to_lds(src, off, dst + e * 1024);
+    }
   };
 
   f32x16 acc[2][2][2];
@@ -126,7 +187,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
     const int cur = step & 1;
     const unsigned char* here = gemm_smem + cur * kStepBytes;
     matrix_step<true>(
-        acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
+        acc, [&](int half, int i, int ks) { return at_a.a(here, half, i, ks); },
         [&](int half, int ks) { return at.b(here, half, ks); },
         [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
@@ -139,31 +200,13 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
 //   fopd_gemm_tn            Out[n, m] (+)= sum_{k < K} Bk[k, n] * Ak[k, m]
 //
 // which is the weight gradient as its operands are stored, dW[v, j] += sum_t dZ[t, v] H[t, j], without a transposed
-// copy of either.  Loop and result stores are those of fopd_gemm_nt; what differs is the LDS layout and how fragments
-// leave it.  A half tile of a step holds 64 k-rows of 128 consecutive m or n as they are in memory, 256 bytes per row, the
-// four 64-byte blocks of a row permuted by bits 0 and 1 of the row.  A fragment of the matrix instruction (lane = one m,
-// eight consecutive k) is two LDS transpose reads (ds_read_b64_tr_b16): within a group of 16 lanes, lane 4 e + q supplies
-// the address of four consecutive 16-bit entries and lane i receives entry i % 4 of the lanes 4 e + i / 4, e = 0..3
-// (measured with an in-bounds probe); with lane 4 e + q pointing at row k + e, entries m + 4 q .. 4 q + 3, lane i gets rows
-// k .. k + 3 of entry m + i.  The 32 lanes of a pass read 4 rows x 64 bytes, by the permutation in four different
-// blocks: all 64 banks once.
+// copy of either.  Loop and result stores are those of fopd_gemm_nt; both operands leave the LDS as KMajorHalf says.
 //
 // K must be a positive multiple of 64.  Ak has rows_a (K - 64 < rows_a <= K) readable rows; rows rows_a .. K - 1 are
 // taken from row rows_a - 1, so the caller's Bk must hold zeros in every row that is not to count (Bk has K
 // readable rows).  M and N need not be multiples of the tile: 16-byte pieces past entry M - 1 / N - 1 of a row are
 // clamped (re-read) and their results discarded; M % 8 == 0, lda % 8 == 0, ldb % 8 == 0, and every row of Bk is
 // readable up to N rounded up to 8 (ldb is at least that).  Byte offsets inside 64 rows must fit 32 bits.
-typedef short tn_i16x4 __attribute__((ext_vector_type(4)));
-typedef short tn_i16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ bf16x8 tn_read_fragment(const unsigned char* p) {
-  typedef __attribute__((address_space(3))) tn_i16x4* lds_ptr;
-  const tn_i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-  const tn_i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 256));
-  const tn_i16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, both);
-}
-
 template <bool ACCUMULATE>
 __global__ void __launch_bounds__(kGemmThreads)
 fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, const __bf16* __restrict__ Bk, int64_t ldb,
@@ -185,17 +228,13 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
   if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
   const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
 
-  // Wavefront w fills k-rows 8 w .. + 7 of a half tile in two loads of four rows: lane i writes 16-byte piece i % 16 of row
-  // i / 16 and so fetches piece (i % 16) ^ 4 (row % 4) of the 128 entries
-  const int lane = threadIdx.x & 63;
   const MatrixPlace mine = matrix_place(gemm_smem);
-  const int krow = 8 * (mine.wm * 4 + mine.wn) + (lane >> 4);
-  const int piece = (lane & 15) ^ ((lane >> 4) << 2);
+  const KMajorHalf at(mine);
   uint32_t col[4];                                         // byte offset in a row, by half tile
 #pragma unroll
   for (int h = 0; h < 4; ++h)
-    col[h] = 16u * static_cast<uint32_t>(h < 2 ? min((m0 >> 3) + 16 * h + piece, (M >> 3) - 1)
-                                               : min((n0 >> 3) + 16 * (h - 2) + piece, ((N + 7) >> 3) - 1));
+    col[h] = 16u * static_cast<uint32_t>(h < 2 ? min((m0 >> 3) + 16 * h + at.piece, (M >> 3) - 1)
+                                               : min((n0 >> 3) + 16 * (h - 2) + at.piece, ((N + 7) >> 3) - 1));
   const uint32_t lda2 = static_cast<uint32_t>(lda) * 2u, ldb2 = static_cast<uint32_t>(ldb) * 2u;
   const int n_steps = K / kLmK;
   auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
@@ -205,18 +244,11 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
     const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const int k = krow + 4 * e;
+      const int k = at.krow + 4 * e;
       load_to_lds(src, col[half] + (half < 2 ? static_cast<uint32_t>(min(k, rows_a - 1 - k0)) * lda2
                                              : static_cast<uint32_t>(k) * ldb2), dst + e * 1024);
     }
   };
-  // LDS -> fragment: lane 16 g + 4 e + q points at row 8 (g / 2) + e (+ 4 for the second read) of the 16 of a slice,
-  // entries 16 (g % 2) + 4 q .. + 3 of a 32-entry block
-  const int in_rows = (((lane >> 5) << 3) + ((lane >> 2) & 3)) * 256 + (((lane >> 4) & 1) << 5) + ((lane & 3) << 3);
-  const int a_off[2] = {in_rows + (((2 * mine.wm) ^ ((lane >> 2) & 3)) << 6),
-                        in_rows + (((2 * mine.wm + 1) ^ ((lane >> 2) & 3)) << 6)};
-  const int b_off = 2 * kHalfBytes + in_rows + ((mine.wn ^ ((lane >> 2) & 3)) << 6);
-
   f32x16 acc[2][2][2];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
@@ -227,8 +259,8 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
     const int cur = step & 1;
     const unsigned char* here = gemm_smem + cur * kStepBytes;
     matrix_step<true>(
-        acc, [&](int half, int i, int ks) { return tn_read_fragment(here + half * kHalfBytes + a_off[i] + ks * 4096); },
-        [&](int half, int ks) { return tn_read_fragment(here + half * kHalfBytes + b_off + ks * 4096); },
+        acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
+        [&](int half, int ks) { return at.b(here, half, ks); },
         [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
   matrix_end(mine);

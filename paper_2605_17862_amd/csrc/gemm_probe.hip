@@ -103,10 +103,11 @@ int main(int argc, char** argv) {
   const int tiles_m = (M + kGemmTile - 1) / kGemmTile, tiles_n = (N + kGemmTile - 1) / kGemmTile;
   const unsigned grid = static_cast<unsigned>((tile_groups(tiles_m, tiles_n) + 7) / 8 * 256);
   const double flops = 2.0 * M * static_cast<double>(N) * K;
-  CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fopd_gemm_nt), hipFuncAttributeMaxDynamicSharedMemorySize,
+  CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fopd_gemm_nt<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             kLoopLdsBytes));
   auto nt = [&]() {
-    fopd_gemm_nt<<<grid, kGemmThreads, kLoopLdsBytes>>>(A, ld, M, B, ld, N, K, out, M, tiles_m, tiles_n, nullptr, 1, 0);
+    fopd_gemm_nt<false><<<grid, kGemmThreads, kLoopLdsBytes>>>(A, ld, M, M, B, ld, N, K, out, M, tiles_m, tiles_n, nullptr,
+                                                               1, 0);
   };
   if (time_groups("fopd_gemm_nt", 4, 1, flops, e0, e1, nt)) return 1;
   if (time_groups("fopd_gemm_nt", groups, 20, flops, e0, e1, nt)) return 1;

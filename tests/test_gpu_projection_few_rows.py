@@ -50,3 +50,15 @@ def test_gradients_with_the_vocabulary_cut_into_runs(seq, d, pad_h):
     scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
     out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, (T + 63) // 64 * 64, scores, pad_h=pad_h)
     _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)
+
+
+@pytest.mark.parametrize("T", [4096, 4097])
+@pytest.mark.parametrize("V,d", [(129, 64), (200, 192)])
+def test_gradients_at_the_line_between_the_two_layouts_of_the_projection_matrix(T, V, d):
+    """4096 rows take dL/dhidden from the matrix as it is, its last step with fewer rows than 64; 4097 from a transposed
+    copy.  A pitch wider than the rows of the matrix in both."""
+    h = wl.generate_lm_head(T, d, V, DEV, seed=T, masked_every=5, ldw=d + 8)
+    w = wl.attach_loss_inputs(h, (T - 1500, 1500), [1, 3], seed=T)
+    scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
+    out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, 4160, scores)
+    _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)
