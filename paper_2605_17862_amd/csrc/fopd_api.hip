@@ -315,10 +315,32 @@ fopd_status launch_k1(const void* logits, fopd_dtype dt, int64_t T, int64_t V, i
   return launched();
 }
 
+fopd_status launch_loss_final(const LossFinal& fin, hipStream_t s) {
+  fopd_loss_final<<<1, kSegThreads, 0, s>>>(fin);
+  return launched();
+}
+
+// The whole-batch calls on stored logits: the offsets are formed by the workgroups of fopd_segment_stats where one length a
+// lane is enough (kStatThreads samples), which saves a launch; the row coefficients as well where a workgroup has few rows a
+// lane.  512 rows x 4096: six launches 30.0 us, three 20.2 us.  Coefficients there / in their own launch, 4096 rows x 4096:
+// one sample 43.6 / 41.8 us, four samples 37.1 / 38.4 us, so the line lies at half of that.
+constexpr int64_t kFoldCoefRows = 2048;
+
+inline SegmentFold fold_offsets(const int32_t* seq_lens, int32_t B, int64_t* cu, int32_t* flags) {
+  SegmentFold fold;
+  if (B > kStatThreads) return fold;
+  fold.seq_lens = seq_lens;
+  fold.cu = cu;
+  fold.flags = flags;
+  fold.B = B;
+  return fold;
+}
+
+// Gradient rows from coefficients; the loss is finished on the way.
 fopd_status launch_k4(const void* logits, void* dlogits, fopd_dtype dt, int64_t T, int64_t V, int64_t ld,
                       const int32_t* token_ids, const float* lse, const float* logp, const float* coef,
-                      hipStream_t s, bool timed = true) {
-  if (T == 0) return FOPD_OK;
+                      const LossFinal& fin, hipStream_t s, bool timed = true) {
+  if (T == 0) return launch_loss_final(fin, s);
   const Options opt = current_options();
   ScopedTimer timer(1, s, timed);
   constexpr int kRegRowVectors = 19;
@@ -335,19 +357,19 @@ fopd_status launch_k4(const void* logits, void* dlogits, fopd_dtype dt, int64_t 
     const dim3 grid(static_cast<unsigned>(items < wgs ? items : wgs)), block(1024);
     if (dt == FOPD_BF16)
       fopd_k4_grad_regs<FOPD_BF16, kRegRowVectors><<<grid, block, 0, s>>>(
-          logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments, seg_vecs);
+          logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments, seg_vecs, fin);
     else
       fopd_k4_grad_regs<FOPD_F32, kRegRowVectors><<<grid, block, 0, s>>>(
-          logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments, seg_vecs);
+          logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments, seg_vecs, fin);
     return launched();
   }
-  const dim3 grid(static_cast<unsigned>(T)), block(kGradThreads);
+  const dim3 grid(static_cast<unsigned>(T + 1)), block(kGradThreads);
   if (dt == FOPD_BF16)
     fopd_k4_grad<FOPD_BF16, kGradUnroll><<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld,
-                                                            token_ids, lse, logp, coef);
+                                                            token_ids, lse, logp, coef, fin);
   else
     fopd_k4_grad<FOPD_F32, kGradUnroll><<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld,
-                                                           token_ids, lse, logp, coef);
+                                                           token_ids, lse, logp, coef, fin);
   return launched();
 }
 
@@ -450,8 +472,12 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
 
   // segment offsets; whole-sample calls must cover exactly T rows, chunks at least their range
   const bool whole = (n_train_in == nullptr);
-  fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, whole ? T : -1, row_begin + T, cu, flags);
-  if ((st = launched()) != FOPD_OK) return st;
+  SegmentFold fold;
+  if (whole && !(scored && !have_lse)) fold = fold_offsets(seq_lens, B, cu, flags);
+  if (fold.seq_lens == nullptr) {
+    fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, whole ? T : -1, row_begin + T, cu, flags);
+    if ((st = launched()) != FOPD_OK) return st;
+  }
 
   // Scores supplied, log-probs not: both passes over each row run in one kernel, and the second
   // read of the row comes out of the cache.
@@ -467,9 +493,8 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
     const RowPassArgs a{token_ids, mask, behav_logp, teacher_logp, cu, n_use, nr_use, lag, freshness_in, B,
                         row_begin, hp, grad_scale, logp, partials, flags};
     if ((st = launch_k14(logits, dlogits, dt, T, V, ld, a, s, timed)) != FOPD_OK) return st;
-    fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, T, n_use, nr_use, lag, nullptr, freshness_in, B, hp.xi, loss,
-                                              weights, freshness);
-    return launched();
+    return launch_loss_final({partials, T, n_use, nr_use, lag, nullptr, freshness_in, B, hp.xi, loss, weights,
+                              freshness}, s);
   }
 
   // token log-probabilities: computed here, or taken from an earlier fopd_token_logprobs
@@ -489,28 +514,32 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
   // per-sample counts and scores
   const int32_t* n_use = n_train_in;
   const int32_t* nr_use = n_roll_in;                    // NULL: the two counts coincide
+  bool have_coef = false;
   if (whole) {
-    fopd_segment_stats<<<B, kSegThreads, 0, s>>>(logp_use, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
+    have_coef = fold.seq_lens != nullptr && !scored && T <= kFoldCoefRows && B <= T;
+    if (have_coef) {
+      fold.coef = coef;
+      fold.partials = partials;
+      fold.grad_scale = grad_scale;
+    }
+    fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_use, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
                                                  mask, cu, lag, T, hp, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, f64, nws, nrws);
+                                                 nullptr, nullptr, nullptr, f64, nws, nrws, fold);
     if ((st = launched()) != FOPD_OK) return st;
     n_use = nws;
     nr_use = nrws;
   }
   const double* f64_use = scored ? nullptr : f64;
 
-  const int64_t nblk = (T + kStreamThreads - 1) / kStreamThreads;
-  if (T > 0) {
+  const int64_t nblk = have_coef ? B : (T + kStreamThreads - 1) / kStreamThreads;
+  if (T > 0 && !have_coef) {
     fopd_coef_loss<<<static_cast<unsigned>(nblk), kStreamThreads, 0, s>>>(
         logp_use, behav_logp, teacher_logp, mask, cu, n_use, nr_use, lag, f64_use, freshness_in, T, B, row_begin, hp,
         grad_scale, coef, partials, flags);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss,
-                                            weights, freshness);
-  if ((st = launched()) != FOPD_OK) return st;
-
-  return launch_k4(logits, dlogits, dt, T, V, ld, token_ids, lse_use, logp_use, coef, s, timed);
+  const LossFinal fin{partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights, freshness};
+  return launch_k4(logits, dlogits, dt, T, V, ld, token_ids, lse_use, logp_use, coef, fin, s, timed);
 }
 
 // Host-checkable conditions of fopd_loss_fwd_bwd other than the workspace.
@@ -624,11 +653,14 @@ fopd_status fopd_freshness_score(const float* logp, const float* behav_logp, con
   int32_t* nrws = at<int32_t>(workspace, w.n_roll);
   double* f64 = at<double>(workspace, w.fresh64);
 
-  fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, T, 0, cu, flags);
-  if ((st = launched()) != FOPD_OK) return st;
-  fopd_segment_stats<<<B, kSegThreads, 0, s>>>(logp, behav_logp, roll_kl, token_loss, teacher_logp, teacher_logp_stale,
+  const SegmentFold fold = fold_offsets(seq_lens, B, cu, flags);
+  if (fold.seq_lens == nullptr) {
+    fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, T, 0, cu, flags);
+    if ((st = launched()) != FOPD_OK) return st;
+  }
+  fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp, behav_logp, roll_kl, token_loss, teacher_logp, teacher_logp_stale,
                                                mask, cu, lag, T, hp, n_train, n_roll, D_roll, D_sup, ell, cover,
-                                               cover_roll, freshness, f64, nws, nrws);
+                                               cover_roll, freshness, f64, nws, nrws, fold);
   if ((st = launched()) != FOPD_OK) return st;
   if (agg != nullptr) {
     fopd_aggregate<<<1, kSegThreads, 0, s>>>(f64, nws, nrws, lag, cu, B, agg);
@@ -687,9 +719,9 @@ fopd_status fopd_loss_fwd_bwd_unit(const void* logits, fopd_dtype dt, int64_t T,
                       0, hp, grad_scale, logp_ws, partials, flags};
   if ((st = launch_k14(logits, unit_rows, dt, T, V, ld, a, s, true)) != FOPD_OK) return st;
   // scores, weights and the loss from the log-probs, exactly as the two-pass call forms them
-  fopd_segment_stats<<<B, kSegThreads, 0, s>>>(logp_ws, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
+  fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_ws, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
                                                mask, cu, lag, T, hp, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                               nullptr, nullptr, nullptr, f64, nws, nrws);
+                                               nullptr, nullptr, nullptr, f64, nws, nrws, SegmentFold());
   if ((st = launched()) != FOPD_OK) return st;
   const int64_t nblk = (T + kStreamThreads - 1) / kStreamThreads;
   if (T > 0) {
@@ -698,9 +730,7 @@ fopd_status fopd_loss_fwd_bwd_unit(const void* logits, fopd_dtype dt, int64_t T,
         partials, flags);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, nblk, nws, nrws, lag, f64, nullptr, B, hp.xi, loss, weights,
-                                            freshness);
-  return launched();
+  return launch_loss_final({partials, nblk, nws, nrws, lag, f64, nullptr, B, hp.xi, loss, weights, freshness}, s);
 }
 
 fopd_status fopd_loss_fwd_bwd_static(const void* logits, fopd_dtype dt, int64_t T, int64_t V, int64_t ld,
@@ -804,8 +834,11 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
   float* c2 = at<float>(workspace, w.coef2);
   double* partials = at<double>(workspace, w.partials);
 
-  fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, chunk ? -1 : T, row_begin + T, cu, flags);
-  if ((st = launched()) != FOPD_OK) return st;
+  const SegmentFold fold = chunk ? SegmentFold() : fold_offsets(seq_lens, B, cu, flags);
+  if (fold.seq_lens == nullptr) {
+    fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, chunk ? -1 : T, row_begin + T, cu, flags);
+    if ((st = launched()) != FOPD_OK) return st;
+  }
 
   const float* lse_use = lse_in;
   const float* logp_use = logp_in;
@@ -826,10 +859,10 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
     if (st != FOPD_OK) return st;
     if (teacher) lq_use = logq_ws;      // the teacher's log-prob of the sampled token, for D^sup
     // stale tensor: drift = the full KL, token loss = sampled form; teacher tensor: the other way round
-    fopd_segment_stats<<<B, kSegThreads, 0, s>>>(logp_ws, behav_logp, teacher ? nullptr : kl_ws,
+    fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_ws, behav_logp, teacher ? nullptr : kl_ws,
                                                  teacher ? kl_ws : nullptr, lq_use, teacher_logp_stale, mask, cu, lag,
                                                  T, hp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                 nullptr, f64, nws, nrws);
+                                                 nullptr, f64, nws, nrws, fold);
     if ((st = launched()) != FOPD_OK) return st;
     lse_use = lse_ws;
     logp_use = logp_ws;
@@ -855,20 +888,18 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
         grad_scale, !teacher, c1, c2, partials);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss,
-                                            weights, freshness);
-  if ((st = launched()) != FOPD_OK) return st;
-  if (T == 0) return FOPD_OK;
+  const LossFinal fin{partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights, freshness};
+  if (T == 0) return launch_loss_final(fin, s);
   ScopedTimer timer(1, s);
-  const dim3 grid(static_cast<unsigned>(T)), block(kStreamThreads);
+  const dim3 grid(static_cast<unsigned>(T + 1)), block(kStreamThreads);
   if (dt == FOPD_BF16)
     fopd_k6_grad_kl<FOPD_BF16, kUnroll><<<grid, block, 0, s>>>(logits, second, dlogits, T, static_cast<int>(V), ld,
                                                                ld_second, token_ids, lse_use, dlse_use, kl_use, logp_use,
-                                                               c1, c2);
+                                                               c1, c2, fin);
   else
     fopd_k6_grad_kl<FOPD_F32, kUnroll><<<grid, block, 0, s>>>(logits, second, dlogits, T, static_cast<int>(V), ld,
                                                               ld_second, token_ids, lse_use, dlse_use, kl_use, logp_use,
-                                                              c1, c2);
+                                                              c1, c2, fin);
   return launched();
 }
 
@@ -984,8 +1015,11 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
   float* p_list = at<float>(workspace, w.total);
   float* h_list = at<float>(workspace, w.total + list_bytes);
 
-  fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, chunk ? -1 : T, row_begin + T, cu, flags);
-  if ((st = launched()) != FOPD_OK) return st;
+  const SegmentFold fold = chunk ? SegmentFold() : fold_offsets(seq_lens, B, cu, flags);
+  if (fold.seq_lens == nullptr) {
+    fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, chunk ? -1 : T, row_begin + T, cu, flags);
+    if ((st = launched()) != FOPD_OK) return st;
+  }
   const float* lse_use = lse_in;
   const float* logp_use = logp_in;
   const int32_t* n_use = n_train_in;
@@ -1009,9 +1043,9 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
   if (!chunk) {
     // token loss = the distribution-level value per row; rollout drift = the sampled estimator; D^sup from the two
     // sampled-token arrays when both are there
-    fopd_segment_stats<<<B, kSegThreads, 0, s>>>(logp_use, behav_logp, nullptr, tl_ws, teacher_logp,
+    fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_use, behav_logp, nullptr, tl_ws, teacher_logp,
                                                  teacher_logp_stale, mask, cu, lag, T, hp, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, nullptr, nullptr, f64, nws, nrws);
+                                                 nullptr, nullptr, nullptr, nullptr, nullptr, f64, nws, nrws, fold);
     if ((st = launched()) != FOPD_OK) return st;
     n_use = nws;
     nr_use = nrws;
@@ -1024,13 +1058,12 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
         grad_scale, false, c1, c2, partials);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss,
-                                            weights, freshness);
-  if ((st = launched()) != FOPD_OK) return st;
-  if (T == 0) return FOPD_OK;
+  const LossFinal fin{partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights, freshness};
+  if (T == 0) return launch_loss_final(fin, s);
   fopd_topk_row_coef<<<static_cast<unsigned>(nblk), kStreamThreads, 0, s>>>(c1, c2, g_rest, T, row_coef);
   if ((st = launched()) != FOPD_OK) return st;
-  if ((st = launch_k4(logits, dlogits, dt, T, V, ld, token_ids, lse_use, logp_use, row_coef, s)) != FOPD_OK) return st;
+  if ((st = launch_k4(logits, dlogits, dt, T, V, ld, token_ids, lse_use, logp_use, row_coef, fin, s)) != FOPD_OK)
+    return st;
   const dim3 grid(static_cast<unsigned>((T + kListRows - 1) / kListRows)), block(kListThreads);
   if (dt == FOPD_BF16)
     fopd_topk_fixup<FOPD_BF16><<<grid, block, 0, s>>>(dlogits, T, static_cast<int>(V), ld, token_ids, list_ids, k,
@@ -1384,14 +1417,13 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
   if (T == 0) {      // an empty batch: loss 0, the weights of the scores, a zero projection gradient
     if (!scored) {
-      fopd_segment_stats<<<B, kSegThreads, 0, s>>>(logp, behav_logp, nullptr, nullptr, teacher_logp, nullptr, mask, cu,
+      fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp, behav_logp, nullptr, nullptr, teacher_logp, nullptr, mask, cu,
                                                    lag, T, hp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                   nullptr, nullptr, f64, nws, nrws);
+                                                   nullptr, nullptr, f64, nws, nrws, SegmentFold());
       if ((st = launched()) != FOPD_OK) return st;
     }
-    fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, 0, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss,
-                                              weights, freshness);
-    if ((st = launched()) != FOPD_OK) return st;
+    if ((st = launch_loss_final({partials, 0, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights,
+                                 freshness}, s)) != FOPD_OK) return st;
     if (head_grad && accumulate_dweight == 0) {
       fopd_fill_zero_f32<<<static_cast<unsigned>(V), 256, 0, s>>>(dweight, lddw, static_cast<int>(d));
       return launched();
@@ -1528,14 +1560,14 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if (!fixed) {
       // the chunk holds whole samples: their scores follow from the log-probs just made
       if (compact)
-        fopd_segment_stats<<<static_cast<unsigned>(c.i1 - c.i0), kSegThreads, 0, s>>>(
+        fopd_segment_stats<<<static_cast<unsigned>(c.i1 - c.i0), kStatThreads, 0, s>>>(
             lp_o, bl, nullptr, tl_o, tq, (stale != nullptr) ? at<float>(workspace, lay.stale_c) : nullptr, msk,
             cu_c + c.i0, lag + c.i0, R, hp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-            f64 + c.i0, nws + c.i0, nrws + c.i0);
+            f64 + c.i0, nws + c.i0, nrws + c.i0, SegmentFold());
       else
-        fopd_segment_stats<<<static_cast<unsigned>(c.i1 - c.i0), kSegThreads, 0, s>>>(
+        fopd_segment_stats<<<static_cast<unsigned>(c.i1 - c.i0), kStatThreads, 0, s>>>(
             logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu + c.i0, lag + c.i0, T, hp, nullptr, nullptr,
-            nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, f64 + c.i0, nws + c.i0, nrws + c.i0);
+            nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, f64 + c.i0, nws + c.i0, nrws + c.i0, SegmentFold());
       if ((st = launched()) != FOPD_OK) return st;
     }
     const int64_t nblk = (R + kStreamThreads - 1) / kStreamThreads;
@@ -1553,9 +1585,8 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     }
     if ((st = launched()) != FOPD_OK) return st;
     // (weights and scores of samples whose chunk is still to come are overwritten by the later calls)
-    fopd_loss_final<<<1, kSegThreads, 0, s>>>(partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi,
-                                              chunk_loss + ci, weights, freshness);
-    if ((st = launched()) != FOPD_OK) return st;
+    if ((st = launch_loss_final({partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi,
+                                 chunk_loss + ci, weights, freshness}, s)) != FOPD_OK) return st;
     if (!grads) {
       if ((st = scatter()) != FOPD_OK) return st;
       ++ci;
@@ -1626,9 +1657,9 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
   if (sweep == 0) {
     // every sample's log-probs (and token losses) are in the caller's arrays: the scores of all samples at once
-    fopd_segment_stats<<<static_cast<unsigned>(B), kSegThreads, 0, s>>>(
+    fopd_segment_stats<<<static_cast<unsigned>(B), kStatThreads, 0, s>>>(
         logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu, lag, T, hp, nullptr, nullptr, nullptr, nullptr,
-        nullptr, nullptr, nullptr, nullptr, f64, nws, nrws);
+        nullptr, nullptr, nullptr, nullptr, f64, nws, nrws, SegmentFold());
     if ((st = launched()) != FOPD_OK) return st;
     if (global_rows) {
       // the log-probs of every live row are in place: the second sweep leaves the samples of weight 0 out altogether

@@ -35,6 +35,7 @@ constexpr int kGradUnroll = 2;        // A/B-tested in one process; all within 1
 constexpr int kUnroll = 4;            // 16-byte loads in flight per lane and loop trip
 constexpr int kScanThreads = 1024;
 constexpr int kSegThreads = 512;
+constexpr int kStatThreads = 1024;
 enum : int32_t { kFlagToken = 1, kFlagSegments = 2, kFlagLag = 4, kFlagSets = 8 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -516,6 +517,47 @@ __device__ __forceinline__ int sample_of_row(const int64_t* cu, int32_t B, int64
   return lo;
 }
 
+// The end of the loss: its partials summed in a fixed order, the weights and the freshness copy.  It needs nothing of the
+// gradient kernel nor the gradient kernel of it, so the first workgroup of that one does it (a launch of its own, for one
+// workgroup, was 4 to 5 us of every call).
+struct LossFinal {
+  const double* partials;
+  int64_t nparts;
+  const int32_t* n_train;
+  const int32_t* n_roll;        // NULL: the counts of n_train
+  const int32_t* lag;
+  const double* fresh64;        // NULL: fresh32
+  const float* fresh32;
+  int32_t B;
+  float xi;
+  float *loss, *weights, *freshness;       // weights, freshness: may be NULL
+};
+
+template <int NT>
+__device__ __forceinline__ void loss_final(const LossFinal& fin, double* sh) {
+  // eight independent partial sums per lane keep eight loads in flight (nparts is T in the
+  // two-passes-per-row path); the order of additions is still fixed
+  double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  int64_t i = threadIdx.x;
+  for (; i + 7 * NT < fin.nparts; i += 8 * NT) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] += fin.partials[i + k * NT];
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (i + k * NT < fin.nparts) acc[k] += fin.partials[i + k * NT];
+  const double s = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  const double tot = block_sum<NT>(s, sh);
+  if (threadIdx.x == 0) fin.loss[0] = static_cast<float>(tot);
+  for (int32_t j = threadIdx.x; j < fin.B; j += NT) {
+    const double f = (fin.fresh64 != nullptr) ? fin.fresh64[j] : static_cast<double>(fin.fresh32[j]);
+    const int32_t n = fin.n_train[j];
+    if (fin.weights != nullptr)
+      fin.weights[j] = static_cast<float>(weight_of(f, n, (fin.n_roll != nullptr) ? fin.n_roll[j] : n, fin.lag[j], fin.xi));
+    if (fin.freshness != nullptr) fin.freshness[j] = static_cast<float>(f);
+  }
+}
+
 }  // namespace
 
 // =========================================================================================
@@ -569,8 +611,13 @@ fopd_k1_lse(const void* logits, int64_t T, int V, int64_t ld, const int32_t* tok
 template <int DT, int U>
 __global__ void __launch_bounds__(kGradThreads)
 fopd_k4_grad(const void* logits, void* dlogits, int64_t T, int V, int64_t ld,
-             const int32_t* token_ids, const float* lse, const float* logp, const float* coef) {
-  const int64_t t = blockIdx.x;
+             const int32_t* token_ids, const float* lse, const float* logp, const float* coef, LossFinal fin) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) - 1;  // (the first workgroup finishes the loss)
+  if (t < 0) {
+    __shared__ double sh[kGradThreads / 64];
+    loss_final<kGradThreads>(fin, sh);
+    return;
+  }
   const float c = coef[t];
   const int y = token_ids[t];
   char* orow = static_cast<char*>(dlogits) + t * ld * Elem<DT>::kBytes;
@@ -913,7 +960,11 @@ struct LaneStateKl {
 template <int DT, int NV>
 __global__ void __launch_bounds__(1024)
 fopd_k4_grad_regs(const void* logits, void* dlogits, int64_t T, int V, int64_t ld, const int32_t* token_ids,
-                  const float* lse, const float* logp, const float* coef, int segments, int seg_vecs) {
+                  const float* lse, const float* logp, const float* coef, int segments, int seg_vecs, LossFinal fin) {
+  if (blockIdx.x == 0) {                                   // then its rows as every other workgroup
+    __shared__ double sh[1024 / 64];
+    loss_final<1024>(fin, sh);
+  }
   // A row longer than 1024 NV vectors is cut into `segments` runs of seg_vecs vectors (<= 1024 NV; the last one may be
   // shorter and also takes the row's ragged end): with lse_t and c_t known, the runs of a row are independent.
   constexpr int E = Elem<DT>::kPerVec;
@@ -1274,11 +1325,16 @@ template <int DT, int U>
 __global__ void __launch_bounds__(kStreamThreads)
 fopd_k6_grad_kl(const void* logits, const void* logits_stale, void* dlogits, int64_t T, int V, int64_t ld,
                 int64_t ld_stale, const int32_t* token_ids, const float* lse, const float* dlse,
-                const float* roll_kl, const float* logp, const float* c1, const float* c2) {
+                const float* roll_kl, const float* logp, const float* c1, const float* c2, LossFinal fin) {
   constexpr int E = Elem<DT>::kPerVec;
   constexpr int NT = kStreamThreads;
-  const int64_t t = blockIdx.x;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) - 1;  // (the first workgroup finishes the loss)
   const int tid = threadIdx.x;
+  if (t < 0) {
+    __shared__ double sh[NT / 64];
+    loss_final<NT>(fin, sh);
+    return;
+  }
   const float a = c1[t], b = c2[t];
   char* orow = static_cast<char*>(dlogits) + t * ld * Elem<DT>::kBytes;
   if ((a == 0.f && b == 0.f) || token_ids[t] < 0 || token_ids[t] >= V) {   // out of range: flagged earlier
@@ -1427,23 +1483,69 @@ fopd_count_train(const uint8_t* mask, const int64_t* cu, int64_t T, int32_t* n_t
   }
 }
 
+// What fopd_segment_stats does besides, so that a call of few rows needs fewer launches (each about 3 us of a small call,
+// between 2 and 4 us of work for one workgroup).
+//   seq_lens != NULL   the offsets are formed here, not by fopd_scan_seqlens: a workgroup adds up the lengths before its
+//                      sample, checks its own and writes its entry of cu; at most kStatThreads samples, one length a lane
+//   coef != NULL       (needs seq_lens) the row coefficients and the sample's share of the loss, as fopd_coef_loss forms
+//                      them, follow at once; partials has one entry per sample
+struct SegmentFold {
+  const int32_t* seq_lens = nullptr;
+  int64_t* cu = nullptr;
+  int32_t* flags = nullptr;
+  int32_t B = 0;
+  float* coef = nullptr;
+  double* partials = nullptr;
+  float grad_scale = 0.f;
+};
+
 // One workgroup per sample: D^roll as the token mean over U^roll, D^sup and the token loss as token means
 // over U^sup (Eq. "kl-diagnostics", Eq. "sample-aggregated-loss"), then the freshness score; a sample
-// with either set empty is invalid and gets zeros (Algorithm 1).
-__global__ void __launch_bounds__(kSegThreads)
+// with either set empty is invalid and gets zeros (Algorithm 1).  Bound by latency: a chain of loads and fp64
+// exponentials per row of a lane, so it has as many lanes as a workgroup can: scoring loop of 16,384 rows in two samples
+// 525 us with 512 lanes and the offsets in a launch of their own, 516 us so.
+__global__ void __launch_bounds__(kStatThreads)
 fopd_segment_stats(const float* logp, const float* behav_logp, const float* roll_kl, const float* ell_term,
                    const float* teacher_logp, const float* teacher_logp_stale, const uint8_t* mask,
                    const int64_t* cu,
                    const int32_t* lag, int64_t T, fopd_hparams hp, int32_t* n_train, int32_t* n_roll, float* D_roll,
                    float* D_sup, float* ell, float* cover, float* cover_roll, float* freshness, double* fresh64,
-                   int32_t* n_train_ws, int32_t* n_roll_ws) {
-  __shared__ double sh[kSegThreads / 64];
+                   int32_t* n_train_ws, int32_t* n_roll_ws, SegmentFold fold) {
+  constexpr int kWaves = kStatThreads / 64;
+  __shared__ double sh[5][kWaves];
+  __shared__ double sh_w;
+  __shared__ int32_t sh_n[2];
   const int i = blockIdx.x;
-  const int64_t a = cu[i];
-  int64_t b = cu[i + 1];
-  if (b > T) b = T;                      // lengths that overrun T are flagged by the scan
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int64_t a, end;
+  if (fold.seq_lens != nullptr) {
+    // whole numbers below 2^42: exact in fp64
+    const double before = wave_sum(tid < i ? static_cast<double>(max(fold.seq_lens[tid], 0)) : 0.0);
+    if (lane == 0) sh[0][wave] = before;
+    __syncthreads();
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += sh[0][w];
+    __syncthreads();
+    const int32_t len = fold.seq_lens[i];
+    a = static_cast<int64_t>(sum);
+    end = a + max(len, 0);
+    if (tid == 0) {
+      fold.cu[i] = a;
+      if (len < 0) atomicOr(fold.flags, kFlagSegments);
+      if (lag[i] < 0) atomicOr(fold.flags, kFlagLag);
+      if (i == fold.B - 1) {
+        fold.cu[fold.B] = end;
+        if (end != T) atomicOr(fold.flags, kFlagSegments);
+      }
+    }
+  } else {
+    a = cu[i];
+    end = cu[i + 1];
+  }
+  const int64_t b = min(end, T);         // lengths that overrun T are flagged by the scan
   double sr = 0.0, ss = 0.0, sl = 0.0, cs = 0.0, cr = 0.0;
-  for (int64_t t = a + threadIdx.x; t < b; t += kSegThreads) {
+  for (int64_t t = a + tid; t < b; t += kStatThreads) {
     const bool sup = in_sup_set(mask, t), roll = in_roll_set(mask, t);
     if (!sup && !roll) continue;
     const double lp = logp[t];
@@ -1462,14 +1564,25 @@ fopd_segment_stats(const float* logp, const float* behav_logp, const float* roll
       cs += 1.0;
     }
   }
-  const double tr = block_sum<kSegThreads>(sr, sh);
-  const double ts = block_sum<kSegThreads>(ss, sh);
-  const double tl = block_sum<kSegThreads>(sl, sh);
-  const double tns = block_sum<kSegThreads>(cs, sh);
-  const double tnr = block_sum<kSegThreads>(cr, sh);
-  if (threadIdx.x == 0) {
+  // all five sums through the LDS at once, wavefront by wavefront in order
+  const double part[5] = {sr, ss, sl, cs, cr};
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const double v = wave_sum(part[k]);
+    if (lane == 0) sh[k][wave] = v;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double tot[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      tot[k] = 0.0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) tot[k] += sh[k][w];
+    }
+    const double tr = tot[0], ts = tot[1], tl = tot[2], tns = tot[3], tnr = tot[4];
     const int32_t ns = static_cast<int32_t>(tns), nr = static_cast<int32_t>(tnr);
-    const int64_t H = cu[i + 1] - a;
+    const int64_t H = end - a;
     double dr = 0.0, ds = 0.0, el = 0.0, cv = 0.0, cvr = 0.0, f = 0.0;
     if (ns > 0 && nr > 0 && lag[i] >= 0) {       // a negative lag is flagged by the scan; the sample is invalid
       dr = tr / tnr;
@@ -1493,7 +1606,29 @@ fopd_segment_stats(const float* logp, const float* behav_logp, const float* roll
     if (cover_roll != nullptr) cover_roll[i] = static_cast<float>(cvr);
     if (freshness != nullptr) freshness[i] = static_cast<float>(f);
     if (fresh64 != nullptr) fresh64[i] = f;
+    sh_w = weight_of(f, ns, nr, lag[i], hp.xi);
+    sh_n[0] = ns;
+    sh_n[1] = nr;
   }
+  if (fold.coef == nullptr) return;
+  __syncthreads();
+  const double w = sh_w;
+  const int32_t n = sh_n[0], nr = sh_n[1];
+  double share = 0.0;
+  for (int64_t t = a + tid; t < b; t += kStatThreads) {
+    const bool sup = in_sup_set(mask, t), roll = in_roll_set(mask, t);
+    float c = 0.f;
+    if ((sup || roll) && w > 0.0) {
+      double lt;
+      c = coef_and_loss(logp[t], behav_logp[t], teacher_logp[t], w, n, nr, sup, roll, fold.B, hp, fold.grad_scale, &lt);
+      share += lt;
+    }
+    fold.coef[t] = c;
+  }
+  if (i == fold.B - 1)                   // rows that belong to no sample (the lengths fall short, which is flagged)
+    for (int64_t t = b + tid; t < T; t += kStatThreads) fold.coef[t] = 0.f;
+  const double total = block_sum<kStatThreads>(share, sh[0]);
+  if (tid == 0) fold.partials[i] = total;
 }
 
 // mean_i f_i, mean_i |U_i^roll| / H_i and mean_i |U_i^sup| / H_i over all B samples (one workgroup);
@@ -1551,31 +1686,10 @@ fopd_coef_loss(const float* logp, const float* behav_logp, const float* teacher_
   if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-// Sums the loss partials in a fixed order; writes the weights and the freshness copy.
-__global__ void __launch_bounds__(kSegThreads)
-fopd_loss_final(const double* partials, int64_t nparts, const int32_t* n_train, const int32_t* n_roll,
-                const int32_t* lag, const double* fresh64, const float* fresh32, int32_t B, float xi, float* loss, float* weights,
-                float* freshness) {
+// (own launch, where no gradient kernel follows that could carry it)
+__global__ void __launch_bounds__(kSegThreads) fopd_loss_final(LossFinal fin) {
   __shared__ double sh[kSegThreads / 64];
-  // eight independent partial sums per lane keep eight loads in flight (nparts is T in the
-  // two-passes-per-row path); the order of additions is still fixed
-  double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  int64_t i = threadIdx.x;
-  for (; i + 7 * kSegThreads < nparts; i += 8 * kSegThreads) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] += partials[i + k * kSegThreads];
-  }
-  for (int k = 0; i < nparts; i += kSegThreads, ++k) acc[k & 7] += partials[i];
-  const double s = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-  const double tot = block_sum<kSegThreads>(s, sh);
-  if (threadIdx.x == 0) loss[0] = static_cast<float>(tot);
-  for (int i = threadIdx.x; i < B; i += kSegThreads) {
-    const double f = (fresh64 != nullptr) ? fresh64[i] : static_cast<double>(fresh32[i]);
-    if (weights != nullptr)
-      weights[i] =
-          static_cast<float>(weight_of(f, n_train[i], (n_roll != nullptr) ? n_roll[i] : n_train[i], lag[i], xi));
-    if (freshness != nullptr) freshness[i] = static_cast<float>(f);
-  }
+  loss_final<kSegThreads>(fin, sh);
 }
 
 // =========================================================================================
