@@ -147,14 +147,14 @@ def _ptr(x, dtype=None, name="argument"):
     if x is None:
         return None
     if isinstance(x, int):
-        return ctypes.c_void_p(x)
+        return x
     if not x.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
     if not x.is_cuda:
         raise ValueError("%s must live in device memory" % name)
-    if dtype is not None and x.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+    if dtype is not None and x.dtype is not dtype and not (isinstance(dtype, tuple) and x.dtype in dtype):
         raise ValueError("%s has dtype %s, expected %s" % (name, x.dtype, dtype))
-    return ctypes.c_void_p(x.data_ptr())
+    return x.data_ptr()
 
 
 def _stream(stream):
