@@ -296,14 +296,32 @@ inline fopd_status static_scratch(void** out) {
 
 // ---- launch helpers ---------------------------------------------------------------------
 
+// Calls that read their rows twice.  The rows from first_cached_row on are read by ordinary loads the first time and are then
+// still in the 256 MB Infinity Cache when the second pass, which starts at the end, comes to them; all others are read
+// non-temporally.  One tensor, step of 256 / 1024 / 2048 rows x 151,936: 67.4 / 177.8 / 339.6 -> 60.7 / 167.1 / 328.0 us; the
+// last 160 MB 61.2 / 172.1 / 346.7, the last 320 MB 60.3 / 169.5 / 336.1.  With much more than the cache holds the order costs
+// what the cache gives (4096 rows 665 / 664 us, listed teacher 682 / 691 us, 32,768 rows + 0.9 %), so kCachedTotal is the line.
+// Two tensors: 256 / 1024 / 4096 rows x 151,936 110.5 / 291.9 / 1105 -> 95.0 / 259.7 / 1043 us with the last 320 MB of both
+// (240 MB: 95.2 / 261.9 / 1074), more rows no slower.
+constexpr int64_t kCachedBytes = 240LL << 20, kCachedTotal = 640LL << 20;
+constexpr int64_t kCachedBytesTwo = 320LL << 20;
+inline int64_t first_cached_row(int64_t T, int64_t row_bytes, int64_t bytes) {
+  const int64_t rows = bytes / row_bytes;
+  return T > rows ? T - rows : 0;
+}
+inline bool worth_caching(int64_t T, int64_t V, fopd_dtype dt) { return T * V * (dt == FOPD_BF16 ? 2 : 4) <= kCachedTotal; }
+
 fopd_status launch_k1(const void* logits, fopd_dtype dt, int64_t T, int64_t V, int64_t ld,
                       const int32_t* token_ids, const uint8_t* mask, float* logp, float* lse,
-                      int64_t* gather_idx, float* entropy, int32_t* flags, hipStream_t s, bool timed = true) {
+                      int64_t* gather_idx, float* entropy, int32_t* flags, bool read_again, hipStream_t s,
+                      bool timed = true) {
   if (T == 0) return FOPD_OK;
   ScopedTimer timer(0, s, timed);
   const dim3 grid(static_cast<unsigned>(T)), block(kStreamThreads);
   const int v = static_cast<int>(V);
-#define FOPD_K1_ARGS logits, T, v, ld, token_ids, mask, logp, lse, gather_idx, entropy, flags
+  const int64_t cached_from = read_again && worth_caching(T, V, dt)
+                                  ? first_cached_row(T, V * (dt == FOPD_BF16 ? 2 : 4), kCachedBytes) : T;
+#define FOPD_K1_ARGS logits, T, v, ld, token_ids, mask, logp, lse, gather_idx, entropy, flags, cached_from
   if (dt == FOPD_BF16) {
     if (entropy != nullptr) fopd_k1_lse<FOPD_BF16, kUnroll, true><<<grid, block, 0, s>>>(FOPD_K1_ARGS);
     else fopd_k1_lse<FOPD_BF16, kUnroll, false><<<grid, block, 0, s>>>(FOPD_K1_ARGS);
@@ -341,6 +359,7 @@ fopd_status launch_k4(const void* logits, void* dlogits, fopd_dtype dt, int64_t 
                       const int32_t* token_ids, const float* lse, const float* logp, const float* coef,
                       const LossFinal& fin, hipStream_t s, bool timed = true) {
   if (T == 0) return launch_loss_final(fin, s);
+  const bool from_the_end = worth_caching(T, V, dt);
   const Options opt = current_options();
   ScopedTimer timer(1, s, timed);
   constexpr int kRegRowVectors = 19;
@@ -353,23 +372,23 @@ fopd_status launch_k4(const void* logits, void* dlogits, fopd_dtype dt, int64_t 
     const int seg_vecs = static_cast<int>((nvec + segments - 1) / segments);
     // (sixteen workgroups per compute unit, handed out as the units finish: 1 % faster than two where the placement
     // of the buffers makes some units slower than others, the same elsewhere)
-    const int64_t wgs = 16 * compute_units(), items = T * segments;
+    const int64_t wgs = 16 * compute_units(), items = (from_the_end ? (T + 7) / 8 * 8 : T) * segments;
     const dim3 grid(static_cast<unsigned>(items < wgs ? items : wgs)), block(1024);
-    if (dt == FOPD_BF16)
-      fopd_k4_grad_regs<FOPD_BF16, kRegRowVectors><<<grid, block, 0, s>>>(
-          logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments, seg_vecs, fin);
-    else
-      fopd_k4_grad_regs<FOPD_F32, kRegRowVectors><<<grid, block, 0, s>>>(
-          logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments, seg_vecs, fin);
+    auto kern = dt == FOPD_BF16 ? (from_the_end ? fopd_k4_grad_regs<FOPD_BF16, kRegRowVectors, true>
+                                                : fopd_k4_grad_regs<FOPD_BF16, kRegRowVectors, false>)
+                                : (from_the_end ? fopd_k4_grad_regs<FOPD_F32, kRegRowVectors, true>
+                                                : fopd_k4_grad_regs<FOPD_F32, kRegRowVectors, false>);
+    kern<<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld, token_ids, lse, logp, coef, segments,
+                                seg_vecs, fin);
     return launched();
   }
-  const dim3 grid(static_cast<unsigned>(T + 1)), block(kGradThreads);
+  const dim3 grid(static_cast<unsigned>((T + 7) / 8 * 8 + 8)), block(kGradThreads);
   if (dt == FOPD_BF16)
     fopd_k4_grad<FOPD_BF16, kGradUnroll><<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld,
-                                                            token_ids, lse, logp, coef, fin);
+                                                            token_ids, lse, logp, coef, fin, from_the_end);
   else
     fopd_k4_grad<FOPD_F32, kGradUnroll><<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld,
-                                                           token_ids, lse, logp, coef, fin);
+                                                           token_ids, lse, logp, coef, fin, from_the_end);
   return launched();
 }
 
@@ -501,7 +520,7 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
   const float* lse_use = lse_in;
   const float* logp_use = logp_in;
   if (!have_lse) {
-    st = launch_k1(logits, dt, T, V, ld, token_ids, mask, logp_ws, lse_ws, nullptr, nullptr, flags, s, timed);
+    st = launch_k1(logits, dt, T, V, ld, token_ids, mask, logp_ws, lse_ws, nullptr, nullptr, flags, true, s, timed);
     if (st != FOPD_OK) return st;
     lse_use = lse_ws;
     logp_use = logp_ws;
@@ -625,7 +644,7 @@ fopd_status fopd_token_logprobs(const void* logits, fopd_dtype dt, int64_t T, in
   if (st != FOPD_OK) return st;
   Workspace w(T, 0);
   return launch_k1(logits, dt, T, V, ld, token_ids, mask, logp, lse, gather_idx, entropy,
-                   at<int32_t>(workspace, w.flags), static_cast<hipStream_t>(stream));
+                   at<int32_t>(workspace, w.flags), false, static_cast<hipStream_t>(stream));
 }
 
 fopd_status fopd_freshness_score(const float* logp, const float* behav_logp, const float* roll_kl,
@@ -764,7 +783,7 @@ fopd_status fopd_loss_fwd_bwd_static(const void* logits, fopd_dtype dt, int64_t 
   return st;
 }
 
-fopd_status fopd_rollout_kl(const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T, int64_t V,
+static fopd_status rollout_kl(bool read_again, const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T, int64_t V,
                             int64_t ld, int64_t ld_stale, const int32_t* token_ids, const uint8_t* mask,
                             float* roll_kl, float* logp, float* lse, float* dlse, float* logq, void* workspace,
                             size_t workspace_bytes, void* stream) {
@@ -778,16 +797,26 @@ fopd_status fopd_rollout_kl(const void* logits, const void* logits_stale, fopd_d
   Workspace w(T, 0);
   hipStream_t s = static_cast<hipStream_t>(stream);
   ScopedTimer timer(0, s);
+  const int es = (dt == FOPD_BF16) ? 2 : 4;
+  const int64_t cached_from = read_again ? first_cached_row(T, 2 * V * es, kCachedBytesTwo) : T;
   const dim3 grid(static_cast<unsigned>(T)), block(kStreamThreads);
   if (dt == FOPD_BF16)
     fopd_k5_kl<FOPD_BF16, kUnroll><<<grid, block, 0, s>>>(logits, logits_stale, T, static_cast<int>(V), ld, ld_stale,
                                                           token_ids, mask, roll_kl, logp, lse, dlse, logq,
-                                                          at<int32_t>(workspace, w.flags));
+                                                          at<int32_t>(workspace, w.flags), cached_from);
   else
     fopd_k5_kl<FOPD_F32, kUnroll><<<grid, block, 0, s>>>(logits, logits_stale, T, static_cast<int>(V), ld, ld_stale,
                                                          token_ids, mask, roll_kl, logp, lse, dlse, logq,
-                                                         at<int32_t>(workspace, w.flags));
+                                                         at<int32_t>(workspace, w.flags), cached_from);
   return launched();
+}
+
+fopd_status fopd_rollout_kl(const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T, int64_t V,
+                            int64_t ld, int64_t ld_stale, const int32_t* token_ids, const uint8_t* mask,
+                            float* roll_kl, float* logp, float* lse, float* dlse, float* logq, void* workspace,
+                            size_t workspace_bytes, void* stream) {
+  return rollout_kl(false, logits, logits_stale, dt, T, V, ld, ld_stale, token_ids, mask, roll_kl, logp, lse, dlse, logq,
+                    workspace, workspace_bytes, stream);
 }
 
 // The two-tensor variants share everything but the meaning of the second tensor.
@@ -854,7 +883,7 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
     float* logq_ws = at<float>(workspace, w.logq);
     float* logp_ws = (logp != nullptr) ? logp : at<float>(workspace, w.logp);
     float* kl_ws = (token_kl != nullptr) ? token_kl : at<float>(workspace, w.kl);
-    st = fopd_rollout_kl(logits, second, dt, T, V, ld, ld_second, token_ids, mask, kl_ws, logp_ws, lse_ws, dlse_ws,
+    st = rollout_kl(true, logits, second, dt, T, V, ld, ld_second, token_ids, mask, kl_ws, logp_ws, lse_ws, dlse_ws,
                          teacher ? logq_ws : nullptr, workspace, workspace_bytes, stream);
     if (st != FOPD_OK) return st;
     if (teacher) lq_use = logq_ws;      // the teacher's log-prob of the sampled token, for D^sup
@@ -891,7 +920,7 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
   const LossFinal fin{partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights, freshness};
   if (T == 0) return launch_loss_final(fin, s);
   ScopedTimer timer(1, s);
-  const dim3 grid(static_cast<unsigned>(T + 1)), block(kStreamThreads);
+  const dim3 grid(static_cast<unsigned>((T + 7) / 8 * 8 + 8)), block(kStreamThreads);
   if (dt == FOPD_BF16)
     fopd_k6_grad_kl<FOPD_BF16, kUnroll><<<grid, block, 0, s>>>(logits, second, dlogits, T, static_cast<int>(V), ld,
                                                                ld_second, token_ids, lse_use, dlse_use, kl_use, logp_use,
@@ -1028,7 +1057,7 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
   if (!chunk) {
     float* lse_ws = at<float>(workspace, w.lse);
     float* logp_ws = (logp != nullptr) ? logp : at<float>(workspace, w.logp);
-    if ((st = launch_k1(logits, dt, T, V, ld, token_ids, mask, logp_ws, lse_ws, nullptr, nullptr, flags, s)) != FOPD_OK)
+    if ((st = launch_k1(logits, dt, T, V, ld, token_ids, mask, logp_ws, lse_ws, nullptr, nullptr, flags, true, s)) != FOPD_OK)
       return st;
     lse_use = lse_ws;
     logp_use = logp_ws;
@@ -1545,7 +1574,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     };
     // logits of the chunk, fp32, never rounded to the storage type of stored logits
     if ((st = launch_gemm(false, Wm, ldw, V, V, Hc, ldhc, R, d, Z, ldz, 4, s, live)) != FOPD_OK) return st;
-    if ((st = launch_k1(Z, FOPD_F32, R, V, ldz, tok, msk, lp_o, ls_o, nullptr, nullptr, flags, s)) != FOPD_OK) return st;
+    if ((st = launch_k1(Z, FOPD_F32, R, V, ldz, tok, msk, lp_o, ls_o, nullptr, nullptr, flags, false, s)) != FOPD_OK) return st;
     if (listed != nullptr) {
       // the listed logits of each row are in the chunk's scratch: token loss, G_rest - l_t and the per-slot terms
       if ((st = launch_topk_terms(Z, FOPD_F32, R, V, ldz, tok, msk, lids, llp, list_k, listed->rest_floor, ls_o, tl_o,

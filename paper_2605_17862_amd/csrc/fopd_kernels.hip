@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fopd.h"
 
 namespace fopd {
@@ -533,6 +535,13 @@ struct LossFinal {
   float *loss, *weights, *freshness;       // weights, freshness: may be NULL
 };
 
+// The row at a place of the second pass.  From the end: the last rows that the first pass has read are still in the Infinity
+// Cache.  Eight rows at a time stay in order, so that a row's second reader sits on the XCD of its first (t mod 8) and finds
+// in that L2 what is left of it.  place = 0 .. T rounded up to 8, exclusive; the result may be T or more: no row.
+__device__ __forceinline__ int64_t second_pass_row(int64_t place, int64_t T, bool from_the_end) {
+  return from_the_end ? (((T + 7) >> 3) - 1 - (place >> 3)) * 8 + (place & 7) : place;
+}
+
 template <int NT>
 __device__ __forceinline__ void loss_final(const LossFinal& fin, double* sh) {
   // eight independent partial sums per lane keep eight loads in flight (nparts is T in the
@@ -568,7 +577,7 @@ template <int DT, int U, bool ENT>
 __global__ void __launch_bounds__(kStreamThreads)
 fopd_k1_lse(const void* logits, int64_t T, int V, int64_t ld, const int32_t* token_ids,
             const uint8_t* mask, float* logp, float* lse, int64_t* gather_idx, float* entropy,
-            int32_t* flags) {
+            int32_t* flags, int64_t cached_from) {
   const int64_t t = blockIdx.x;
   const int tid = threadIdx.x;
   const int y = token_ids[t];
@@ -592,7 +601,8 @@ fopd_k1_lse(const void* logits, int64_t T, int V, int64_t ld, const int32_t* tok
   __shared__ float sh_W[kStreamThreads / 64];
   const char* row = static_cast<const char*>(logits) + t * ld * Elem<DT>::kBytes;
   LaneState st;
-  row_lse<DT, kStreamThreads, U, false, ENT>(row, V, y, st, &sh_zy);
+  if (t >= cached_from) row_lse<DT, kStreamThreads, U, true, ENT>(row, V, y, st, &sh_zy);
+  else row_lse<DT, kStreamThreads, U, false, ENT>(row, V, y, st, &sh_zy);
   double lp, ls, ent;
   block_lse_finish<kStreamThreads, ENT>(st, &sh_zy, sh_R, sh_S, sh_W, lp, ls, ent);
   if (tid == 0) {
@@ -611,13 +621,15 @@ fopd_k1_lse(const void* logits, int64_t T, int V, int64_t ld, const int32_t* tok
 template <int DT, int U>
 __global__ void __launch_bounds__(kGradThreads)
 fopd_k4_grad(const void* logits, void* dlogits, int64_t T, int V, int64_t ld,
-             const int32_t* token_ids, const float* lse, const float* logp, const float* coef, LossFinal fin) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) - 1;  // (the first workgroup finishes the loss)
-  if (t < 0) {
+             const int32_t* token_ids, const float* lse, const float* logp, const float* coef, LossFinal fin,
+             bool from_the_end) {
+  if (blockIdx.x < 8) {                                    // ahead of the rows: the first finishes the loss
     __shared__ double sh[kGradThreads / 64];
-    loss_final<kGradThreads>(fin, sh);
+    if (blockIdx.x == 0) loss_final<kGradThreads>(fin, sh);
     return;
   }
+  const int64_t t = second_pass_row(static_cast<int64_t>(blockIdx.x) - 8, T, from_the_end);
+  if (t >= T) return;
   const float c = coef[t];
   const int y = token_ids[t];
   char* orow = static_cast<char*>(dlogits) + t * ld * Elem<DT>::kBytes;
@@ -957,7 +969,9 @@ struct LaneStateKl {
 // =========================================================================================
 // (Requesting a vector of the next row as soon as its register's entry is stored, so that loads and stores of a compute
 // unit overlap, is much slower: 28.1 ms against 18.6 ms on the benchmark's rows.)
-template <int DT, int NV>
+// FROM_THE_END is a template parameter because the choice inside the loop cost 0.5 % where it brings nothing (8192 rows x
+// 262,144: 1947 -> 1956 us).
+template <int DT, int NV, bool FROM_THE_END>
 __global__ void __launch_bounds__(1024)
 fopd_k4_grad_regs(const void* logits, void* dlogits, int64_t T, int V, int64_t ld, const int32_t* token_ids,
                   const float* lse, const float* logp, const float* coef, int segments, int seg_vecs, LossFinal fin) {
@@ -971,10 +985,12 @@ fopd_k4_grad_regs(const void* logits, void* dlogits, int64_t T, int V, int64_t l
   constexpr int NT = 1024;
   const int tid = threadIdx.x;
   const int nvec = V / E;
-  const int64_t items = T * segments;
+  const int64_t items = (FROM_THE_END ? (T + 7) / 8 * 8 : T) * segments;
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-    const int64_t t = item / segments;
-    const int seg = static_cast<int>(item - t * segments);
+    const int64_t place = item / segments;
+    const int seg = static_cast<int>(item - place * segments);
+    const int64_t t = FROM_THE_END ? second_pass_row(place, T, true) : place;
+    if (FROM_THE_END && t >= T) continue;
     const int v0 = seg * seg_vecs;
     const int v1 = min(nvec, v0 + seg_vecs);               // this run: vectors v0 .. v1 - 1
     const bool last = (seg == segments - 1);
@@ -1101,7 +1117,7 @@ template <int DT, int U>
 __global__ void __launch_bounds__(kStreamThreads)
 fopd_k5_kl(const void* logits, const void* logits_stale, int64_t T, int V, int64_t ld, int64_t ld_stale,
            const int32_t* token_ids, const uint8_t* mask, float* roll_kl, float* logp, float* lse, float* dlse,
-           float* logq, int32_t* flags) {
+           float* logq, int32_t* flags, int64_t cached_from) {
   constexpr int E = Elem<DT>::kPerVec;
   constexpr int NT = kStreamThreads;
   const int64_t t = blockIdx.x;
@@ -1135,56 +1151,61 @@ fopd_k5_kl(const void* logits, const void* logits_stale, int64_t T, int V, int64
   LaneStateKl st;
   constexpr int U2 = (U > 1) ? U / 2 : 1;      // two tensors: half the vectors of each per trip
   const int ytrip = jy / (U2 * NT);
-  int trip = 0;
-  int j = tid;
-  for (; j + (U2 - 1) * NT < nvec; j += U2 * NT, ++trip) {
-    u32x4 q[U2], qs[U2];
-#pragma unroll
-    for (int u = 0; u < U2; ++u) {
-      q[u] = __builtin_nontemporal_load(rv + j + u * NT);
-      qs[u] = __builtin_nontemporal_load(rsv + j + u * NT);
-    }
-    float x[U2 * E], xs[U2 * E];
-#pragma unroll
-    for (int u = 0; u < U2; ++u) {
-      unpack<DT>(q[u], x + u * E);
-      unpack<DT>(qs[u], xs + u * E);
-    }
-    if (trip == ytrip) {
-#pragma unroll
+  auto walk = [&](auto cached) {
+    constexpr bool kCached = decltype(cached)::value;
+    int trip = 0;
+    int j = tid;
+    for (; j + (U2 - 1) * NT < nvec; j += U2 * NT, ++trip) {
+      u32x4 q[U2], qs[U2];
+  #pragma unroll
       for (int u = 0; u < U2; ++u) {
-        if (j + u * NT == jy) {
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            if (e == ey) {
-              sh_zy = x[u * E + e];
-              sh_zsy = xs[u * E + e];
-              x[u * E + e] = kNegInf;         // the sampled token is left out of the lane sums
-              xs[u * E + e] = kNegInf;
+        q[u] = load_vec<kCached>(rv + j + u * NT);
+        qs[u] = load_vec<kCached>(rsv + j + u * NT);
+      }
+      float x[U2 * E], xs[U2 * E];
+  #pragma unroll
+      for (int u = 0; u < U2; ++u) {
+        unpack<DT>(q[u], x + u * E);
+        unpack<DT>(qs[u], xs + u * E);
+      }
+      if (trip == ytrip) {
+  #pragma unroll
+        for (int u = 0; u < U2; ++u) {
+          if (j + u * NT == jy) {
+  #pragma unroll
+            for (int e = 0; e < E; ++e) {
+              if (e == ey) {
+                sh_zy = x[u * E + e];
+                sh_zsy = xs[u * E + e];
+                x[u * E + e] = kNegInf;         // the sampled token is left out of the lane sums
+                xs[u * E + e] = kNegInf;
+              }
             }
           }
         }
       }
+      accumulate_kl<U2 * E>(x, xs, st);
     }
-    accumulate_kl<U2 * E>(x, xs, st);
-  }
-  for (; j < nvec; j += NT) {
-    float x[E], xs[E];
-    unpack<DT>(__builtin_nontemporal_load(rv + j), x);
-    unpack<DT>(__builtin_nontemporal_load(rsv + j), xs);
-    if (j == jy) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (e == ey) {
-          sh_zy = x[e];
-          sh_zsy = xs[e];
-          x[e] = kNegInf;
-          xs[e] = kNegInf;
+    for (; j < nvec; j += NT) {
+      float x[E], xs[E];
+      unpack<DT>(load_vec<kCached>(rv + j), x);
+      unpack<DT>(load_vec<kCached>(rsv + j), xs);
+      if (j == jy) {
+  #pragma unroll
+        for (int e = 0; e < E; ++e) {
+          if (e == ey) {
+            sh_zy = x[e];
+            sh_zsy = xs[e];
+            x[e] = kNegInf;
+            xs[e] = kNegInf;
+          }
         }
       }
+      accumulate_kl<E>(x, xs, st);
     }
-    accumulate_kl<E>(x, xs, st);
-  }
+  };
+  if (t >= cached_from) walk(std::true_type());
+  else walk(std::false_type());
   {
     const int idx = nvec * E + tid;
     if (idx < V) {
@@ -1328,13 +1349,14 @@ fopd_k6_grad_kl(const void* logits, const void* logits_stale, void* dlogits, int
                 const float* roll_kl, const float* logp, const float* c1, const float* c2, LossFinal fin) {
   constexpr int E = Elem<DT>::kPerVec;
   constexpr int NT = kStreamThreads;
-  const int64_t t = static_cast<int64_t>(blockIdx.x) - 1;  // (the first workgroup finishes the loss)
-  const int tid = threadIdx.x;
-  if (t < 0) {
+  if (blockIdx.x < 8) {                                    // ahead of the rows: the first finishes the loss
     __shared__ double sh[NT / 64];
-    loss_final<NT>(fin, sh);
+    if (blockIdx.x == 0) loss_final<NT>(fin, sh);
     return;
   }
+  const int64_t t = second_pass_row(static_cast<int64_t>(blockIdx.x) - 8, T, true);
+  if (t >= T) return;
+  const int tid = threadIdx.x;
   const float a = c1[t], b = c2[t];
   char* orow = static_cast<char*>(dlogits) + t * ld * Elem<DT>::kBytes;
   if ((a == 0.f && b == 0.f) || token_ids[t] < 0 || token_ids[t] >= V) {   // out of range: flagged earlier
