@@ -296,6 +296,48 @@ inline fopd_status static_scratch(void** out) {
 
 // ---- launch helpers ---------------------------------------------------------------------
 
+// Rows (or samples) of one launch that has a workgroup for each.  A launch has at most 2^32 - 1 lanes, and a grid beyond
+// that is not refused but cut to its low 32 bits (16,777,224 workgroups of 256 lanes run as 8), so longer calls go
+// through in slabs: launch(first row, rows).
+constexpr int64_t kLaunchRows = 1LL << 21;
+
+template <typename Launch>
+fopd_status in_slabs(int64_t n, Launch launch) {
+  for (int64_t a = 0; a < n; a += kLaunchRows) {
+    const fopd_status st = launch(a, std::min(n - a, kLaunchRows));
+    if (st != FOPD_OK) return st;
+  }
+  return FOPD_OK;
+}
+
+template <typename T>
+T* from(T* p, int64_t n) { return p == nullptr ? nullptr : p + n; }
+
+inline const void* row_of(const void* m, fopd_dtype dt, int64_t ld, int64_t t) {
+  return static_cast<const char*>(m) + t * ld * (dt == FOPD_BF16 ? 2 : 4);
+}
+inline void* row_of(void* m, fopd_dtype dt, int64_t ld, int64_t t) {
+  return static_cast<char*>(m) + t * ld * (dt == FOPD_BF16 ? 2 : 4);
+}
+
+// args: those of fopd_segment_stats from `logp` on.
+template <typename... Args>
+fopd_status launch_segment_stats(int64_t B, const SegmentFold& fold, const SegmentOutputs& out, hipStream_t s,
+                                 Args... args) {
+  return in_slabs(B, [&](int64_t a, int64_t n) {
+    fopd_segment_stats<<<static_cast<unsigned>(n), kStatThreads, 0, s>>>(static_cast<int>(a), fold, out, args...);
+    return launched();
+  });
+}
+
+fopd_status launch_count_train(const uint8_t* mask, const int64_t* cu, int64_t T, int32_t B, int32_t* n_train,
+                               int32_t* n_roll, hipStream_t s) {
+  return in_slabs(B, [&](int64_t a, int64_t n) {
+    fopd_count_train<<<static_cast<unsigned>(n), kSegThreads, 0, s>>>(mask, cu + a, T, n_train + a, n_roll + a);
+    return launched();
+  });
+}
+
 // Calls that read their rows twice.  The rows from first_cached_row on are read by ordinary loads the first time and are then
 // still in the 256 MB Infinity Cache when the second pass, which starts at the end, comes to them; all others are read
 // non-temporally.  One tensor, step of 256 / 1024 / 2048 rows x 151,936: 67.4 / 177.8 / 339.6 -> 60.7 / 167.1 / 328.0 us; the
@@ -317,20 +359,19 @@ fopd_status launch_k1(const void* logits, fopd_dtype dt, int64_t T, int64_t V, i
                       bool timed = true) {
   if (T == 0) return FOPD_OK;
   ScopedTimer timer(0, s, timed);
-  const dim3 grid(static_cast<unsigned>(T)), block(kStreamThreads);
   const int v = static_cast<int>(V);
   const int64_t cached_from = read_again && worth_caching(T, V, dt)
                                   ? first_cached_row(T, V * (dt == FOPD_BF16 ? 2 : 4), kCachedBytes) : T;
-#define FOPD_K1_ARGS logits, T, v, ld, token_ids, mask, logp, lse, gather_idx, entropy, flags, cached_from
-  if (dt == FOPD_BF16) {
-    if (entropy != nullptr) fopd_k1_lse<FOPD_BF16, kUnroll, true><<<grid, block, 0, s>>>(FOPD_K1_ARGS);
-    else fopd_k1_lse<FOPD_BF16, kUnroll, false><<<grid, block, 0, s>>>(FOPD_K1_ARGS);
-  } else {
-    if (entropy != nullptr) fopd_k1_lse<FOPD_F32, kUnroll, true><<<grid, block, 0, s>>>(FOPD_K1_ARGS);
-    else fopd_k1_lse<FOPD_F32, kUnroll, false><<<grid, block, 0, s>>>(FOPD_K1_ARGS);
-  }
-#undef FOPD_K1_ARGS
-  return launched();
+  auto kern = dt == FOPD_BF16 ? (entropy != nullptr ? fopd_k1_lse<FOPD_BF16, kUnroll, true>
+                                                    : fopd_k1_lse<FOPD_BF16, kUnroll, false>)
+                              : (entropy != nullptr ? fopd_k1_lse<FOPD_F32, kUnroll, true>
+                                                    : fopd_k1_lse<FOPD_F32, kUnroll, false>);
+  return in_slabs(T, [&](int64_t a, int64_t n) {
+    kern<<<static_cast<unsigned>(n), kStreamThreads, 0, s>>>(row_of(logits, dt, ld, a), n, v, ld, token_ids + a,
+                                                            from(mask, a), logp + a, lse + a, from(gather_idx, a),
+                                                            from(entropy, a), flags, cached_from - a);
+    return launched();
+  });
 }
 
 fopd_status launch_loss_final(const LossFinal& fin, hipStream_t s) {
@@ -354,11 +395,15 @@ inline SegmentFold fold_offsets(const int32_t* seq_lens, int32_t B, int64_t* cu,
   return fold;
 }
 
-// Gradient rows from coefficients; the loss is finished on the way.
+// Gradient rows from coefficients; the loss is finished on the way (by a launch of its own ahead of several slabs).
 fopd_status launch_k4(const void* logits, void* dlogits, fopd_dtype dt, int64_t T, int64_t V, int64_t ld,
                       const int32_t* token_ids, const float* lse, const float* logp, const float* coef,
-                      const LossFinal& fin, hipStream_t s, bool timed = true) {
-  if (T == 0) return launch_loss_final(fin, s);
+                      LossFinal fin, hipStream_t s, bool timed = true) {
+  if (T == 0 || T > kLaunchRows) {
+    const fopd_status st = launch_loss_final(fin, s);
+    if (st != FOPD_OK || T == 0) return st;
+    fin.loss = nullptr;
+  }
   const bool from_the_end = worth_caching(T, V, dt);
   const Options opt = current_options();
   ScopedTimer timer(1, s, timed);
@@ -382,14 +427,13 @@ fopd_status launch_k4(const void* logits, void* dlogits, fopd_dtype dt, int64_t 
                                 seg_vecs, fin);
     return launched();
   }
-  const dim3 grid(static_cast<unsigned>((T + 7) / 8 * 8 + 8)), block(kGradThreads);
-  if (dt == FOPD_BF16)
-    fopd_k4_grad<FOPD_BF16, kGradUnroll><<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld,
-                                                            token_ids, lse, logp, coef, fin, from_the_end);
-  else
-    fopd_k4_grad<FOPD_F32, kGradUnroll><<<grid, block, 0, s>>>(logits, dlogits, T, static_cast<int>(V), ld,
-                                                           token_ids, lse, logp, coef, fin, from_the_end);
-  return launched();
+  auto kern = dt == FOPD_BF16 ? fopd_k4_grad<FOPD_BF16, kGradUnroll> : fopd_k4_grad<FOPD_F32, kGradUnroll>;
+  return in_slabs(T, [&](int64_t a, int64_t n) {
+    kern<<<static_cast<unsigned>((n + 7) / 8 * 8 + 8), kGradThreads, 0, s>>>(
+        row_of(logits, dt, ld, a), row_of(dlogits, dt, ld, a), n, static_cast<int>(V), ld, token_ids + a, lse + a, logp + a,
+        coef + a, fin, from_the_end);
+    return launched();
+  });
 }
 
 // Everything the two-passes-per-row kernel needs besides the matrices.
@@ -422,11 +466,13 @@ fopd_status launch_k14_t(const void* logits, void* dlogits, int64_t T, int64_t V
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), static_cast<int>(kLdsPerCu - 1024), allowed) != FOPD_OK)
     return FOPD_EHIP;
   const size_t pad = kLdsPerCu / static_cast<size_t>(rows_per_cu) - 1024;
-  kern<<<dim3(static_cast<unsigned>(T)), dim3(NT), pad, s>>>(logits, dlogits, T, static_cast<int>(V), ld, a.token_ids,
-                                                            a.mask, a.lb, a.lq, a.cu, a.n_train, a.n_roll, a.lag,
-                                                            a.fresh32, a.B, a.row_begin, a.hp, a.grad_scale, a.logp,
-                                                            a.row_loss, a.flags);
-  return launched();
+  return in_slabs(T, [&](int64_t r, int64_t n) {
+    kern<<<static_cast<unsigned>(n), NT, pad, s>>>(
+        row_of(logits, static_cast<fopd_dtype>(DT), ld, r), row_of(dlogits, static_cast<fopd_dtype>(DT), ld, r), n,
+        static_cast<int>(V), ld, a.token_ids + r, from(a.mask, r), a.lb + r, a.lq + r, a.cu, a.n_train, a.n_roll, a.lag,
+        a.fresh32, a.B, a.row_begin + r, a.hp, a.grad_scale, a.logp + r, a.row_loss + r, a.flags);
+    return launched();
+  });
 }
 
 fopd_status launch_k14(const void* logits, void* dlogits, fopd_dtype dt, int64_t T, int64_t V, int64_t ld,
@@ -504,8 +550,7 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
     const int32_t* n_use = n_train_in;
     const int32_t* nr_use = n_roll_in;                  // NULL: the two counts coincide
     if (whole) {
-      fopd_count_train<<<B, kSegThreads, 0, s>>>(mask, cu, T, nws, nrws);
-      if ((st = launched()) != FOPD_OK) return st;
+      if ((st = launch_count_train(mask, cu, T, B, nws, nrws, s)) != FOPD_OK) return st;
       n_use = nws;
       nr_use = nrws;
     }
@@ -541,10 +586,9 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
       fold.partials = partials;
       fold.grad_scale = grad_scale;
     }
-    fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_use, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
-                                                 mask, cu, lag, T, hp, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, f64, nws, nrws, fold);
-    if ((st = launched()) != FOPD_OK) return st;
+    st = launch_segment_stats(B, fold, {}, s, logp_use, behav_logp, nullptr, nullptr, teacher_logp,
+                              teacher_logp_stale, mask, cu, lag, T, hp, f64, nws, nrws);
+    if (st != FOPD_OK) return st;
     n_use = nws;
     nr_use = nrws;
   }
@@ -677,10 +721,10 @@ fopd_status fopd_freshness_score(const float* logp, const float* behav_logp, con
     fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, T, 0, cu, flags);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp, behav_logp, roll_kl, token_loss, teacher_logp, teacher_logp_stale,
-                                               mask, cu, lag, T, hp, n_train, n_roll, D_roll, D_sup, ell, cover,
-                                               cover_roll, freshness, f64, nws, nrws, fold);
-  if ((st = launched()) != FOPD_OK) return st;
+  st = launch_segment_stats(B, fold, {n_train, n_roll, D_roll, D_sup, ell, cover, cover_roll, freshness}, s, logp,
+                            behav_logp, roll_kl, token_loss, teacher_logp, teacher_logp_stale, mask, cu, lag, T, hp,
+                            f64, nws, nrws);
+  if (st != FOPD_OK) return st;
   if (agg != nullptr) {
     fopd_aggregate<<<1, kSegThreads, 0, s>>>(f64, nws, nrws, lag, cu, B, agg);
     if ((st = launched()) != FOPD_OK) return st;
@@ -731,17 +775,15 @@ fopd_status fopd_loss_fwd_bwd_unit(const void* logits, fopd_dtype dt, int64_t T,
 
   fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, T, T, cu, flags);
   if ((st = launched()) != FOPD_OK) return st;
-  fopd_count_train<<<B, kSegThreads, 0, s>>>(mask, cu, T, nws, nrws);
-  if ((st = launched()) != FOPD_OK) return st;
+  if ((st = launch_count_train(mask, cu, T, B, nws, nrws, s)) != FOPD_OK) return st;
   // the one pass over the logits: log-probs and the rows at unit weight (no scores: fresh32 == nullptr)
   const RowPassArgs a{token_ids, mask, behav_logp, teacher_logp, cu, nws, nrws, lag, nullptr, B,
                       0, hp, grad_scale, logp_ws, partials, flags};
   if ((st = launch_k14(logits, unit_rows, dt, T, V, ld, a, s, true)) != FOPD_OK) return st;
   // scores, weights and the loss from the log-probs, exactly as the two-pass call forms them
-  fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_ws, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
-                                               mask, cu, lag, T, hp, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                               nullptr, nullptr, nullptr, f64, nws, nrws, SegmentFold());
-  if ((st = launched()) != FOPD_OK) return st;
+  st = launch_segment_stats(B, {}, {}, s, logp_ws, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
+                            mask, cu, lag, T, hp, f64, nws, nrws);
+  if (st != FOPD_OK) return st;
   const int64_t nblk = (T + kStreamThreads - 1) / kStreamThreads;
   if (T > 0) {
     fopd_coef_loss<<<static_cast<unsigned>(nblk), kStreamThreads, 0, s>>>(
@@ -799,16 +841,14 @@ static fopd_status rollout_kl(bool read_again, const void* logits, const void* l
   ScopedTimer timer(0, s);
   const int es = (dt == FOPD_BF16) ? 2 : 4;
   const int64_t cached_from = read_again ? first_cached_row(T, 2 * V * es, kCachedBytesTwo) : T;
-  const dim3 grid(static_cast<unsigned>(T)), block(kStreamThreads);
-  if (dt == FOPD_BF16)
-    fopd_k5_kl<FOPD_BF16, kUnroll><<<grid, block, 0, s>>>(logits, logits_stale, T, static_cast<int>(V), ld, ld_stale,
-                                                          token_ids, mask, roll_kl, logp, lse, dlse, logq,
-                                                          at<int32_t>(workspace, w.flags), cached_from);
-  else
-    fopd_k5_kl<FOPD_F32, kUnroll><<<grid, block, 0, s>>>(logits, logits_stale, T, static_cast<int>(V), ld, ld_stale,
-                                                         token_ids, mask, roll_kl, logp, lse, dlse, logq,
-                                                         at<int32_t>(workspace, w.flags), cached_from);
-  return launched();
+  auto kern = dt == FOPD_BF16 ? fopd_k5_kl<FOPD_BF16, kUnroll> : fopd_k5_kl<FOPD_F32, kUnroll>;
+  return in_slabs(T, [&](int64_t a, int64_t n) {
+    kern<<<static_cast<unsigned>(n), kStreamThreads, 0, s>>>(
+        row_of(logits, dt, ld, a), row_of(logits_stale, dt, ld_stale, a), n, static_cast<int>(V), ld, ld_stale,
+        token_ids + a, from(mask, a), roll_kl + a, logp + a, lse + a, dlse + a, from(logq, a),
+        at<int32_t>(workspace, w.flags), cached_from - a);
+    return launched();
+  });
 }
 
 fopd_status fopd_rollout_kl(const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T, int64_t V,
@@ -888,11 +928,10 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
     if (st != FOPD_OK) return st;
     if (teacher) lq_use = logq_ws;      // the teacher's log-prob of the sampled token, for D^sup
     // stale tensor: drift = the full KL, token loss = sampled form; teacher tensor: the other way round
-    fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_ws, behav_logp, teacher ? nullptr : kl_ws,
-                                                 teacher ? kl_ws : nullptr, lq_use, teacher_logp_stale, mask, cu, lag,
-                                                 T, hp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                 nullptr, f64, nws, nrws, fold);
-    if ((st = launched()) != FOPD_OK) return st;
+    st = launch_segment_stats(B, fold, {}, s, logp_ws, behav_logp, teacher ? nullptr : kl_ws,
+                              teacher ? kl_ws : nullptr, lq_use, teacher_logp_stale, mask, cu, lag, T, hp, f64, nws,
+                              nrws);
+    if (st != FOPD_OK) return st;
     lse_use = lse_ws;
     logp_use = logp_ws;
     dlse_use = dlse_ws;
@@ -917,19 +956,19 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
         grad_scale, !teacher, c1, c2, partials);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  const LossFinal fin{partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights, freshness};
-  if (T == 0) return launch_loss_final(fin, s);
+  LossFinal fin{partials, nblk, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights, freshness};
+  if (T == 0 || T > kLaunchRows) {
+    if ((st = launch_loss_final(fin, s)) != FOPD_OK || T == 0) return st;
+    fin.loss = nullptr;
+  }
   ScopedTimer timer(1, s);
-  const dim3 grid(static_cast<unsigned>((T + 7) / 8 * 8 + 8)), block(kStreamThreads);
-  if (dt == FOPD_BF16)
-    fopd_k6_grad_kl<FOPD_BF16, kUnroll><<<grid, block, 0, s>>>(logits, second, dlogits, T, static_cast<int>(V), ld,
-                                                               ld_second, token_ids, lse_use, dlse_use, kl_use, logp_use,
-                                                               c1, c2, fin);
-  else
-    fopd_k6_grad_kl<FOPD_F32, kUnroll><<<grid, block, 0, s>>>(logits, second, dlogits, T, static_cast<int>(V), ld,
-                                                              ld_second, token_ids, lse_use, dlse_use, kl_use, logp_use,
-                                                              c1, c2, fin);
-  return launched();
+  auto kern = dt == FOPD_BF16 ? fopd_k6_grad_kl<FOPD_BF16, kUnroll> : fopd_k6_grad_kl<FOPD_F32, kUnroll>;
+  return in_slabs(T, [&](int64_t a, int64_t n) {
+    kern<<<static_cast<unsigned>((n + 7) / 8 * 8 + 8), kStreamThreads, 0, s>>>(
+        row_of(logits, dt, ld, a), row_of(second, dt, ld_second, a), row_of(dlogits, dt, ld, a), n, static_cast<int>(V),
+        ld, ld_second, token_ids + a, lse_use + a, dlse_use + a, kl_use + a, logp_use + a, c1 + a, c2 + a, fin);
+    return launched();
+  });
 }
 
 fopd_status fopd_loss_fwd_bwd_full_kl(const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T,
@@ -974,14 +1013,14 @@ static fopd_status launch_topk_terms(const void* logits, fopd_dtype dt, int64_t 
                                      const float* list_logp, int32_t k, float rest_floor, const float* lse,
                                      float* token_loss, float* g_rest, float* p_list, float* h_list, hipStream_t s) {
   if (T == 0) return FOPD_OK;
-  const dim3 grid(static_cast<unsigned>((T + kListRows - 1) / kListRows)), block(kListThreads);
-  if (dt == FOPD_BF16)
-    fopd_topk_terms<FOPD_BF16><<<grid, block, 0, s>>>(logits, T, static_cast<int>(V), ld, token_ids, mask, list_ids,
-                                                     list_logp, k, rest_floor, lse, token_loss, g_rest, p_list, h_list);
-  else
-    fopd_topk_terms<FOPD_F32><<<grid, block, 0, s>>>(logits, T, static_cast<int>(V), ld, token_ids, mask, list_ids,
-                                                    list_logp, k, rest_floor, lse, token_loss, g_rest, p_list, h_list);
-  return launched();
+  auto kern = dt == FOPD_BF16 ? fopd_topk_terms<FOPD_BF16> : fopd_topk_terms<FOPD_F32>;
+  return in_slabs(T, [&](int64_t a, int64_t n) {
+    kern<<<static_cast<unsigned>((n + kListRows - 1) / kListRows), kListThreads, 0, s>>>(
+        row_of(logits, dt, ld, a), n, static_cast<int>(V), ld, token_ids + a, from(mask, a), list_ids + a * k,
+        list_logp + a * k, k, rest_floor, lse + a, token_loss + a, from(g_rest, a), from(p_list, a * k),
+        from(h_list, a * k));
+    return launched();
+  });
 }
 
 fopd_status fopd_topk_token_loss(const void* logits, fopd_dtype dt, int64_t T, int64_t V, int64_t ld,
@@ -1072,10 +1111,9 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
   if (!chunk) {
     // token loss = the distribution-level value per row; rollout drift = the sampled estimator; D^sup from the two
     // sampled-token arrays when both are there
-    fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp_use, behav_logp, nullptr, tl_ws, teacher_logp,
-                                                 teacher_logp_stale, mask, cu, lag, T, hp, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, nullptr, nullptr, f64, nws, nrws, fold);
-    if ((st = launched()) != FOPD_OK) return st;
+    st = launch_segment_stats(B, fold, {}, s, logp_use, behav_logp, nullptr, tl_ws, teacher_logp, teacher_logp_stale,
+                              mask, cu, lag, T, hp, f64, nws, nrws);
+    if (st != FOPD_OK) return st;
     n_use = nws;
     nr_use = nrws;
     f64_use = f64;
@@ -1093,14 +1131,13 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
   if ((st = launched()) != FOPD_OK) return st;
   if ((st = launch_k4(logits, dlogits, dt, T, V, ld, token_ids, lse_use, logp_use, row_coef, fin, s)) != FOPD_OK)
     return st;
-  const dim3 grid(static_cast<unsigned>((T + kListRows - 1) / kListRows)), block(kListThreads);
-  if (dt == FOPD_BF16)
-    fopd_topk_fixup<FOPD_BF16><<<grid, block, 0, s>>>(dlogits, T, static_cast<int>(V), ld, token_ids, list_ids, k,
-                                                     logp_use, c1, c2, g_rest, p_list, h_list, nullptr);
-  else
-    fopd_topk_fixup<FOPD_F32><<<grid, block, 0, s>>>(dlogits, T, static_cast<int>(V), ld, token_ids, list_ids, k,
-                                                    logp_use, c1, c2, g_rest, p_list, h_list, nullptr);
-  return launched();
+  auto kern = dt == FOPD_BF16 ? fopd_topk_fixup<FOPD_BF16> : fopd_topk_fixup<FOPD_F32>;
+  return in_slabs(T, [&](int64_t a, int64_t n) {
+    kern<<<static_cast<unsigned>((n + kListRows - 1) / kListRows), kListThreads, 0, s>>>(
+        row_of(dlogits, dt, ld, a), n, static_cast<int>(V), ld, token_ids + a, list_ids + a * k, k, logp_use + a, c1 + a,
+        c2 + a, g_rest + a, p_list + a * k, h_list + a * k, nullptr);
+    return launched();
+  });
 }
 
 int fopd_refresh_decide(const float* agg_host, const fopd_refresh_config* cfg_host, fopd_refresh_state* state_host,
@@ -1439,17 +1476,15 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   const int32_t* n_use = n_train_in;
   const int32_t* nr_use = n_roll_in;
   if (n_train_in == nullptr) {
-    fopd_count_train<<<B, kSegThreads, 0, s>>>(mask, cu, T, nws, nrws);
-    if ((st = launched()) != FOPD_OK) return st;
+    if ((st = launch_count_train(mask, cu, T, B, nws, nrws, s)) != FOPD_OK) return st;
     n_use = nws;
     nr_use = nrws;
   }
   if (T == 0) {      // an empty batch: loss 0, the weights of the scores, a zero projection gradient
     if (!scored) {
-      fopd_segment_stats<<<B, kStatThreads, 0, s>>>(logp, behav_logp, nullptr, nullptr, teacher_logp, nullptr, mask, cu,
-                                                   lag, T, hp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                   nullptr, nullptr, f64, nws, nrws, SegmentFold());
-      if ((st = launched()) != FOPD_OK) return st;
+      st = launch_segment_stats(B, {}, {}, s, logp, behav_logp, nullptr, nullptr, teacher_logp, nullptr, mask, cu,
+                                lag, T, hp, f64, nws, nrws);
+      if (st != FOPD_OK) return st;
     }
     if ((st = launch_loss_final({partials, 0, n_use, nr_use, lag, f64_use, freshness_in, B, hp.xi, loss, weights,
                                  freshness}, s)) != FOPD_OK) return st;
@@ -1494,9 +1529,12 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if ((st = launched()) != FOPD_OK) return st;
   }
   if (compact && (mask != nullptr || keep != nullptr)) {
-    fopd_masked_rows_zero<<<static_cast<unsigned>(T), 256, 0, s>>>(
-        mask, cu, B, keep, logp, lse, tl, grads ? dhidden : nullptr, lddh, static_cast<int>(d));
-    if ((st = launched()) != FOPD_OK) return st;
+    st = in_slabs(T, [&](int64_t a, int64_t n) {
+      fopd_masked_rows_zero<<<static_cast<unsigned>(n), 256, 0, s>>>(a, mask, cu, B, keep, logp, lse, tl,
+                                                                    grads ? dhidden : nullptr, lddh, static_cast<int>(d));
+      return launched();
+    });
+    if (st != FOPD_OK) return st;
   }
 
   // dL/dhidden in how many runs over the vocabulary: by the rows of the call, not of a chunk, so that a row's sum has the
@@ -1589,15 +1627,13 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if (!fixed) {
       // the chunk holds whole samples: their scores follow from the log-probs just made
       if (compact)
-        fopd_segment_stats<<<static_cast<unsigned>(c.i1 - c.i0), kStatThreads, 0, s>>>(
-            lp_o, bl, nullptr, tl_o, tq, (stale != nullptr) ? at<float>(workspace, lay.stale_c) : nullptr, msk,
-            cu_c + c.i0, lag + c.i0, R, hp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-            f64 + c.i0, nws + c.i0, nrws + c.i0, SegmentFold());
+        st = launch_segment_stats(c.i1 - c.i0, {}, {}, s, lp_o, bl, nullptr, tl_o, tq,
+                                  (stale != nullptr) ? at<float>(workspace, lay.stale_c) : nullptr, msk, cu_c + c.i0,
+                                  lag + c.i0, R, hp, f64 + c.i0, nws + c.i0, nrws + c.i0);
       else
-        fopd_segment_stats<<<static_cast<unsigned>(c.i1 - c.i0), kStatThreads, 0, s>>>(
-            logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu + c.i0, lag + c.i0, T, hp, nullptr, nullptr,
-            nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, f64 + c.i0, nws + c.i0, nrws + c.i0, SegmentFold());
-      if ((st = launched()) != FOPD_OK) return st;
+        st = launch_segment_stats(c.i1 - c.i0, {}, {}, s, logp, behav_logp, nullptr, tl, teacher_logp, stale, mask,
+                                  cu + c.i0, lag + c.i0, T, hp, f64 + c.i0, nws + c.i0, nrws + c.i0);
+      if (st != FOPD_OK) return st;
     }
     const int64_t nblk = (R + kStreamThreads - 1) / kStreamThreads;
     if (listed != nullptr) {
@@ -1686,10 +1722,9 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
   if (sweep == 0) {
     // every sample's log-probs (and token losses) are in the caller's arrays: the scores of all samples at once
-    fopd_segment_stats<<<static_cast<unsigned>(B), kStatThreads, 0, s>>>(
-        logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu, lag, T, hp, nullptr, nullptr, nullptr, nullptr,
-        nullptr, nullptr, nullptr, nullptr, f64, nws, nrws, SegmentFold());
-    if ((st = launched()) != FOPD_OK) return st;
+    st = launch_segment_stats(B, {}, {}, s, logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu, lag, T, hp,
+                              f64, nws, nrws);
+    if (st != FOPD_OK) return st;
     if (global_rows) {
       // the log-probs of every live row are in place: the second sweep leaves the samples of weight 0 out altogether
       keep = at<int32_t>(workspace, lay.keep);
@@ -1700,9 +1735,12 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
                                                     n_live, cu_c, keep);
       if ((st = launched()) != FOPD_OK) return st;
       if (grads) {
-        fopd_masked_rows_zero<<<static_cast<unsigned>(T), 256, 0, s>>>(mask, cu, B, keep, nullptr, nullptr, nullptr,
-                                                                       dhidden, lddh, static_cast<int>(d));
-        if ((st = launched()) != FOPD_OK) return st;
+        st = in_slabs(T, [&](int64_t a, int64_t n) {
+          fopd_masked_rows_zero<<<static_cast<unsigned>(n), 256, 0, s>>>(a, mask, cu, B, keep, nullptr, nullptr, nullptr,
+                                                                        dhidden, lddh, static_cast<int>(d));
+          return launched();
+        });
+        if (st != FOPD_OK) return st;
       }
     }
   }

@@ -591,14 +591,14 @@ fopd_sum_splits(const float* __restrict__ partial, int splits, int64_t split_str
   sum_splits_row(partial + r * d, splits, split_stride, d, dhidden + r * lddh, lddh);
 }
 
-// Zeros in the outputs of the rows 0 .. gridDim.x - 1 that take no part: masked ones (mask != NULL and mask[r] == 0)
+// Zeros in the outputs of the rows first .. first + gridDim.x - 1 that take no part: masked ones (mask != NULL and mask[r] == 0)
 // and, with keep, those of samples with keep[i] == 0 (cu: the samples' offsets).  Log-prob and log-sum-exp (NULL
 // together), token loss (may be NULL), dL/dhidden row (may be NULL).
 __global__ void __launch_bounds__(256)
-fopd_masked_rows_zero(const uint8_t* __restrict__ mask, const int64_t* __restrict__ cu, int B,
+fopd_masked_rows_zero(int64_t first, const uint8_t* __restrict__ mask, const int64_t* __restrict__ cu, int B,
                       const int* __restrict__ keep, float* __restrict__ logp, float* __restrict__ lse,
                       float* __restrict__ token_loss, float* __restrict__ dhidden, int64_t lddh, int d) {
-  const int64_t r = blockIdx.x;
+  const int64_t r = first + blockIdx.x;
   const bool masked = (mask != nullptr && mask[r] == 0);
   if (!masked && (keep == nullptr || keep[sample_of_row(cu, B, r)] != 0)) return;
   if (threadIdx.x == 0) {

@@ -532,7 +532,7 @@ struct LossFinal {
   const float* fresh32;
   int32_t B;
   float xi;
-  float *loss, *weights, *freshness;       // weights, freshness: may be NULL
+  float *loss, *weights, *freshness;       // weights, freshness: may be NULL; loss NULL: all of it is done elsewhere
 };
 
 // The row at a place of the second pass.  From the end: the last rows that the first pass has read are still in the Infinity
@@ -625,7 +625,7 @@ fopd_k4_grad(const void* logits, void* dlogits, int64_t T, int V, int64_t ld,
              bool from_the_end) {
   if (blockIdx.x < 8) {                                    // ahead of the rows: the first finishes the loss
     __shared__ double sh[kGradThreads / 64];
-    if (blockIdx.x == 0) loss_final<kGradThreads>(fin, sh);
+    if (blockIdx.x == 0 && fin.loss != nullptr) loss_final<kGradThreads>(fin, sh);
     return;
   }
   const int64_t t = second_pass_row(static_cast<int64_t>(blockIdx.x) - 8, T, from_the_end);
@@ -975,7 +975,7 @@ template <int DT, int NV, bool FROM_THE_END>
 __global__ void __launch_bounds__(1024)
 fopd_k4_grad_regs(const void* logits, void* dlogits, int64_t T, int V, int64_t ld, const int32_t* token_ids,
                   const float* lse, const float* logp, const float* coef, int segments, int seg_vecs, LossFinal fin) {
-  if (blockIdx.x == 0) {                                   // then its rows as every other workgroup
+  if (blockIdx.x == 0 && fin.loss != nullptr) {            // then its rows as every other workgroup
     __shared__ double sh[1024 / 64];
     loss_final<1024>(fin, sh);
   }
@@ -1351,7 +1351,7 @@ fopd_k6_grad_kl(const void* logits, const void* logits_stale, void* dlogits, int
   constexpr int NT = kStreamThreads;
   if (blockIdx.x < 8) {                                    // ahead of the rows: the first finishes the loss
     __shared__ double sh[NT / 64];
-    if (blockIdx.x == 0) loss_final<NT>(fin, sh);
+    if (blockIdx.x == 0 && fin.loss != nullptr) loss_final<NT>(fin, sh);
     return;
   }
   const int64_t t = second_pass_row(static_cast<int64_t>(blockIdx.x) - 8, T, true);
@@ -1521,23 +1521,27 @@ struct SegmentFold {
   float grad_scale = 0.f;
 };
 
-// One workgroup per sample: D^roll as the token mean over U^roll, D^sup and the token loss as token means
+// Per-sample outputs besides those of the workspace, each may be NULL.
+struct SegmentOutputs {
+  int32_t *n_train = nullptr, *n_roll = nullptr;
+  float *D_roll = nullptr, *D_sup = nullptr, *ell = nullptr, *cover = nullptr, *cover_roll = nullptr, *freshness = nullptr;
+};
+
+// One workgroup per sample, from sample `first` on: D^roll as the token mean over U^roll, D^sup and the token loss as token means
 // over U^sup (Eq. "kl-diagnostics", Eq. "sample-aggregated-loss"), then the freshness score; a sample
 // with either set empty is invalid and gets zeros (Algorithm 1).  Bound by latency: a chain of loads and fp64
 // exponentials per row of a lane, so it has as many lanes as a workgroup can: scoring loop of 16,384 rows in two samples
 // 525 us with 512 lanes and the offsets in a launch of their own, 516 us so.
 __global__ void __launch_bounds__(kStatThreads)
-fopd_segment_stats(const float* logp, const float* behav_logp, const float* roll_kl, const float* ell_term,
-                   const float* teacher_logp, const float* teacher_logp_stale, const uint8_t* mask,
-                   const int64_t* cu,
-                   const int32_t* lag, int64_t T, fopd_hparams hp, int32_t* n_train, int32_t* n_roll, float* D_roll,
-                   float* D_sup, float* ell, float* cover, float* cover_roll, float* freshness, double* fresh64,
-                   int32_t* n_train_ws, int32_t* n_roll_ws, SegmentFold fold) {
+fopd_segment_stats(int first, SegmentFold fold, SegmentOutputs out, const float* logp, const float* behav_logp,
+                   const float* roll_kl, const float* ell_term, const float* teacher_logp,
+                   const float* teacher_logp_stale, const uint8_t* mask, const int64_t* cu, const int32_t* lag, int64_t T,
+                   fopd_hparams hp, double* fresh64, int32_t* n_train_ws, int32_t* n_roll_ws) {
   constexpr int kWaves = kStatThreads / 64;
   __shared__ double sh[5][kWaves];
   __shared__ double sh_w;
   __shared__ int32_t sh_n[2];
-  const int i = blockIdx.x;
+  const int i = first + blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t a, end;
   if (fold.seq_lens != nullptr) {
@@ -1617,16 +1621,16 @@ fopd_segment_stats(const float* logp, const float* behav_logp, const float* roll
                                static_cast<double>(hp.beta) * sqrt(ds > 0.0 ? ds : 0.0);
       f = exp(-surrogate) / (static_cast<double>(lag[i]) + 1.0);
     }
-    if (n_train != nullptr) n_train[i] = ns;
-    if (n_roll != nullptr) n_roll[i] = nr;
+    if (out.n_train != nullptr) out.n_train[i] = ns;
+    if (out.n_roll != nullptr) out.n_roll[i] = nr;
     if (n_train_ws != nullptr) n_train_ws[i] = ns;
     if (n_roll_ws != nullptr) n_roll_ws[i] = nr;
-    if (D_roll != nullptr) D_roll[i] = static_cast<float>(dr);
-    if (D_sup != nullptr) D_sup[i] = static_cast<float>(ds);
-    if (ell != nullptr) ell[i] = static_cast<float>(el);
-    if (cover != nullptr) cover[i] = static_cast<float>(cv);
-    if (cover_roll != nullptr) cover_roll[i] = static_cast<float>(cvr);
-    if (freshness != nullptr) freshness[i] = static_cast<float>(f);
+    if (out.D_roll != nullptr) out.D_roll[i] = static_cast<float>(dr);
+    if (out.D_sup != nullptr) out.D_sup[i] = static_cast<float>(ds);
+    if (out.ell != nullptr) out.ell[i] = static_cast<float>(el);
+    if (out.cover != nullptr) out.cover[i] = static_cast<float>(cv);
+    if (out.cover_roll != nullptr) out.cover_roll[i] = static_cast<float>(cvr);
+    if (out.freshness != nullptr) out.freshness[i] = static_cast<float>(f);
     if (fresh64 != nullptr) fresh64[i] = f;
     sh_w = weight_of(f, ns, nr, lag[i], hp.xi);
     sh_n[0] = ns;
