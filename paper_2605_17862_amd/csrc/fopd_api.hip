@@ -320,12 +320,19 @@ inline void* row_of(void* m, fopd_dtype dt, int64_t ld, int64_t t) {
   return static_cast<char*>(m) + t * ld * (dt == FOPD_BF16 ? 2 : 4);
 }
 
-// args: those of fopd_segment_stats from `logp` on.
+// args: those of fopd_segment_stats from `logp` on; rows: of the B samples together.  512 lanes a sample: three samples share
+// a compute unit.  1024 lanes leave room for one, which pays for few long samples only.  Scores, 512 / 1024 lanes: one
+// sample of 2048 rows 9.9 / 10.6 us, 64 of 2560 11.4 / 11.9, 8 of 4096 13.5 / 12.6, 2 of 8192 19.1 / 15.5, one of 16,384
+// 30.0 / 21.0; 320 of 512 10.7 / 15.0, 1024 of 128 15.0 / 25.0, 4096 of 1024 56.3 / 97.7.
 template <typename... Args>
-fopd_status launch_segment_stats(int64_t B, const SegmentFold& fold, const SegmentOutputs& out, hipStream_t s,
-                                 Args... args) {
+fopd_status launch_segment_stats(int64_t B, int64_t rows, const SegmentFold& fold, const SegmentOutputs& out,
+                                 hipStream_t s, Args... args) {
+  const bool folded = fold.seq_lens != nullptr, wide = B <= 256 && rows >= 4096 * B;
+  auto kern = wide ? (folded ? fopd_segment_stats<1024, true> : fopd_segment_stats<1024, false>)
+                   : (folded ? fopd_segment_stats<512, true> : fopd_segment_stats<512, false>);
+  const unsigned lanes = wide ? 1024 : 512;
   return in_slabs(B, [&](int64_t a, int64_t n) {
-    fopd_segment_stats<<<static_cast<unsigned>(n), kStatThreads, 0, s>>>(static_cast<int>(a), fold, out, args...);
+    kern<<<static_cast<unsigned>(n), lanes, 0, s>>>(static_cast<int>(a), fold, out, args...);
     return launched();
   });
 }
@@ -379,15 +386,17 @@ fopd_status launch_loss_final(const LossFinal& fin, hipStream_t s) {
   return launched();
 }
 
-// The whole-batch calls on stored logits: the offsets are formed by the workgroups of fopd_segment_stats where one length a
-// lane is enough (kStatThreads samples), which saves a launch; the row coefficients as well where a workgroup has few rows a
-// lane.  512 rows x 4096: six launches 30.0 us, three 20.2 us.  Coefficients there / in their own launch, 4096 rows x 4096:
-// one sample 43.6 / 41.8 us, four samples 37.1 / 38.4 us, so the line lies at half of that.
+// The whole-batch calls on stored logits: the offsets are formed by the workgroups of fopd_segment_stats for up to this many
+// samples, which saves a launch (a workgroup reads the lengths before its own: 1024 samples 15.2 / 16.4 us); the row
+// coefficients as well for up to this many rows.  512 rows x 4096, four samples: six launches 20.8 us, three 13.7 us.
+// Coefficients there / in their own launch: 1024 rows in one sample 17.0 / 18.2 us, 2048 rows 23.6 / 23.2, 4096 rows 39.9 /
+// 37.8 (in sixteen samples 28.7 / 31.7).
+constexpr int32_t kFoldSamples = 1024;
 constexpr int64_t kFoldCoefRows = 2048;
 
 inline SegmentFold fold_offsets(const int32_t* seq_lens, int32_t B, int64_t* cu, int32_t* flags) {
   SegmentFold fold;
-  if (B > kStatThreads) return fold;
+  if (B > kFoldSamples) return fold;
   fold.seq_lens = seq_lens;
   fold.cu = cu;
   fold.flags = flags;
@@ -586,7 +595,7 @@ fopd_status loss_fwd_bwd_checked(const void* logits, fopd_dtype dt, int64_t T, i
       fold.partials = partials;
       fold.grad_scale = grad_scale;
     }
-    st = launch_segment_stats(B, fold, {}, s, logp_use, behav_logp, nullptr, nullptr, teacher_logp,
+    st = launch_segment_stats(B, T, fold, {}, s, logp_use, behav_logp, nullptr, nullptr, teacher_logp,
                               teacher_logp_stale, mask, cu, lag, T, hp, f64, nws, nrws);
     if (st != FOPD_OK) return st;
     n_use = nws;
@@ -721,7 +730,7 @@ fopd_status fopd_freshness_score(const float* logp, const float* behav_logp, con
     fopd_scan_seqlens<<<1, kScanThreads, 0, s>>>(seq_lens, lag, B, T, 0, cu, flags);
     if ((st = launched()) != FOPD_OK) return st;
   }
-  st = launch_segment_stats(B, fold, {n_train, n_roll, D_roll, D_sup, ell, cover, cover_roll, freshness}, s, logp,
+  st = launch_segment_stats(B, T, fold, {n_train, n_roll, D_roll, D_sup, ell, cover, cover_roll, freshness}, s, logp,
                             behav_logp, roll_kl, token_loss, teacher_logp, teacher_logp_stale, mask, cu, lag, T, hp,
                             f64, nws, nrws);
   if (st != FOPD_OK) return st;
@@ -781,7 +790,7 @@ fopd_status fopd_loss_fwd_bwd_unit(const void* logits, fopd_dtype dt, int64_t T,
                       0, hp, grad_scale, logp_ws, partials, flags};
   if ((st = launch_k14(logits, unit_rows, dt, T, V, ld, a, s, true)) != FOPD_OK) return st;
   // scores, weights and the loss from the log-probs, exactly as the two-pass call forms them
-  st = launch_segment_stats(B, {}, {}, s, logp_ws, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
+  st = launch_segment_stats(B, T, {}, {}, s, logp_ws, behav_logp, nullptr, nullptr, teacher_logp, teacher_logp_stale,
                             mask, cu, lag, T, hp, f64, nws, nrws);
   if (st != FOPD_OK) return st;
   const int64_t nblk = (T + kStreamThreads - 1) / kStreamThreads;
@@ -928,7 +937,7 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
     if (st != FOPD_OK) return st;
     if (teacher) lq_use = logq_ws;      // the teacher's log-prob of the sampled token, for D^sup
     // stale tensor: drift = the full KL, token loss = sampled form; teacher tensor: the other way round
-    st = launch_segment_stats(B, fold, {}, s, logp_ws, behav_logp, teacher ? nullptr : kl_ws,
+    st = launch_segment_stats(B, T, fold, {}, s, logp_ws, behav_logp, teacher ? nullptr : kl_ws,
                               teacher ? kl_ws : nullptr, lq_use, teacher_logp_stale, mask, cu, lag, T, hp, f64, nws,
                               nrws);
     if (st != FOPD_OK) return st;
@@ -1111,7 +1120,7 @@ fopd_status fopd_loss_fwd_bwd_topk_teacher(const void* logits, fopd_dtype dt, in
   if (!chunk) {
     // token loss = the distribution-level value per row; rollout drift = the sampled estimator; D^sup from the two
     // sampled-token arrays when both are there
-    st = launch_segment_stats(B, fold, {}, s, logp_use, behav_logp, nullptr, tl_ws, teacher_logp, teacher_logp_stale,
+    st = launch_segment_stats(B, T, fold, {}, s, logp_use, behav_logp, nullptr, tl_ws, teacher_logp, teacher_logp_stale,
                               mask, cu, lag, T, hp, f64, nws, nrws);
     if (st != FOPD_OK) return st;
     n_use = nws;
@@ -1482,7 +1491,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
   if (T == 0) {      // an empty batch: loss 0, the weights of the scores, a zero projection gradient
     if (!scored) {
-      st = launch_segment_stats(B, {}, {}, s, logp, behav_logp, nullptr, nullptr, teacher_logp, nullptr, mask, cu,
+      st = launch_segment_stats(B, T, {}, {}, s, logp, behav_logp, nullptr, nullptr, teacher_logp, nullptr, mask, cu,
                                 lag, T, hp, f64, nws, nrws);
       if (st != FOPD_OK) return st;
     }
@@ -1627,11 +1636,11 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if (!fixed) {
       // the chunk holds whole samples: their scores follow from the log-probs just made
       if (compact)
-        st = launch_segment_stats(c.i1 - c.i0, {}, {}, s, lp_o, bl, nullptr, tl_o, tq,
+        st = launch_segment_stats(c.i1 - c.i0, R, {}, {}, s, lp_o, bl, nullptr, tl_o, tq,
                                   (stale != nullptr) ? at<float>(workspace, lay.stale_c) : nullptr, msk, cu_c + c.i0,
                                   lag + c.i0, R, hp, f64 + c.i0, nws + c.i0, nrws + c.i0);
       else
-        st = launch_segment_stats(c.i1 - c.i0, {}, {}, s, logp, behav_logp, nullptr, tl, teacher_logp, stale, mask,
+        st = launch_segment_stats(c.i1 - c.i0, R, {}, {}, s, logp, behav_logp, nullptr, tl, teacher_logp, stale, mask,
                                   cu + c.i0, lag + c.i0, T, hp, f64 + c.i0, nws + c.i0, nrws + c.i0);
       if (st != FOPD_OK) return st;
     }
@@ -1722,7 +1731,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
   if (sweep == 0) {
     // every sample's log-probs (and token losses) are in the caller's arrays: the scores of all samples at once
-    st = launch_segment_stats(B, {}, {}, s, logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu, lag, T, hp,
+    st = launch_segment_stats(B, T, {}, {}, s, logp, behav_logp, nullptr, tl, teacher_logp, stale, mask, cu, lag, T, hp,
                               f64, nws, nrws);
     if (st != FOPD_OK) return st;
     if (global_rows) {

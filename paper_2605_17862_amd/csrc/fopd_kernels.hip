@@ -37,7 +37,6 @@ constexpr int kGradUnroll = 2;        // A/B-tested in one process; all within 1
 constexpr int kUnroll = 4;            // 16-byte loads in flight per lane and loop trip
 constexpr int kScanThreads = 1024;
 constexpr int kSegThreads = 512;
-constexpr int kStatThreads = 1024;
 enum : int32_t { kFlagToken = 1, kFlagSegments = 2, kFlagLag = 4, kFlagSets = 8 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -1508,7 +1507,7 @@ fopd_count_train(const uint8_t* mask, const int64_t* cu, int64_t T, int32_t* n_t
 // What fopd_segment_stats does besides, so that a call of few rows needs fewer launches (each about 3 us of a small call,
 // between 2 and 4 us of work for one workgroup).
 //   seq_lens != NULL   the offsets are formed here, not by fopd_scan_seqlens: a workgroup adds up the lengths before its
-//                      sample, checks its own and writes its entry of cu; at most kStatThreads samples, one length a lane
+//                      sample, checks its own and writes its entry of cu; for few samples (kFoldSamples)
 //   coef != NULL       (needs seq_lens) the row coefficients and the sample's share of the loss, as fopd_coef_loss forms
 //                      them, follow at once; partials has one entry per sample
 struct SegmentFold {
@@ -1530,23 +1529,26 @@ struct SegmentOutputs {
 // One workgroup per sample, from sample `first` on: D^roll as the token mean over U^roll, D^sup and the token loss as token means
 // over U^sup (Eq. "kl-diagnostics", Eq. "sample-aggregated-loss"), then the freshness score; a sample
 // with either set empty is invalid and gets zeros (Algorithm 1).  Bound by latency: a chain of loads and fp64
-// exponentials per row of a lane, so it has as many lanes as a workgroup can: scoring loop of 16,384 rows in two samples
-// 525 us with 512 lanes and the offsets in a launch of their own, 516 us so.
-__global__ void __launch_bounds__(kStatThreads)
+// exponentials per row of a lane.  FOLD (fold.seq_lens is given) is a template parameter because the code for it costs 12
+// registers, which is fewer workgroups on a compute unit: 4096 samples of 1024 rows 64.2 us with a branch, 56.3 us so.
+template <int NT, bool FOLD>
+__global__ void __launch_bounds__(NT)
 fopd_segment_stats(int first, SegmentFold fold, SegmentOutputs out, const float* logp, const float* behav_logp,
                    const float* roll_kl, const float* ell_term, const float* teacher_logp,
                    const float* teacher_logp_stale, const uint8_t* mask, const int64_t* cu, const int32_t* lag, int64_t T,
                    fopd_hparams hp, double* fresh64, int32_t* n_train_ws, int32_t* n_roll_ws) {
-  constexpr int kWaves = kStatThreads / 64;
+  constexpr int kWaves = NT / 64;
   __shared__ double sh[5][kWaves];
   __shared__ double sh_w;
   __shared__ int32_t sh_n[2];
   const int i = first + blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t a, end;
-  if (fold.seq_lens != nullptr) {
+  if constexpr (FOLD) {
     // whole numbers below 2^42: exact in fp64
-    const double before = wave_sum(tid < i ? static_cast<double>(max(fold.seq_lens[tid], 0)) : 0.0);
+    double mine = 0.0;
+    for (int k = tid; k < i; k += NT) mine += static_cast<double>(max(fold.seq_lens[k], 0));
+    const double before = wave_sum(mine);
     if (lane == 0) sh[0][wave] = before;
     __syncthreads();
     double sum = 0.0;
@@ -1571,7 +1573,7 @@ fopd_segment_stats(int first, SegmentFold fold, SegmentOutputs out, const float*
   }
   const int64_t b = min(end, T);         // lengths that overrun T are flagged by the scan
   double sr = 0.0, ss = 0.0, sl = 0.0, cs = 0.0, cr = 0.0;
-  for (int64_t t = a + tid; t < b; t += kStatThreads) {
+  for (int64_t t = a + tid; t < b; t += NT) {
     const bool sup = in_sup_set(mask, t), roll = in_roll_set(mask, t);
     if (!sup && !roll) continue;
     const double lp = logp[t];
@@ -1632,16 +1634,19 @@ fopd_segment_stats(int first, SegmentFold fold, SegmentOutputs out, const float*
     if (out.cover_roll != nullptr) out.cover_roll[i] = static_cast<float>(cvr);
     if (out.freshness != nullptr) out.freshness[i] = static_cast<float>(f);
     if (fresh64 != nullptr) fresh64[i] = f;
-    sh_w = weight_of(f, ns, nr, lag[i], hp.xi);
-    sh_n[0] = ns;
-    sh_n[1] = nr;
+    if constexpr (FOLD) {
+      sh_w = weight_of(f, ns, nr, lag[i], hp.xi);
+      sh_n[0] = ns;
+      sh_n[1] = nr;
+    }
   }
+  if constexpr (!FOLD) return;
   if (fold.coef == nullptr) return;
   __syncthreads();
   const double w = sh_w;
   const int32_t n = sh_n[0], nr = sh_n[1];
   double share = 0.0;
-  for (int64_t t = a + tid; t < b; t += kStatThreads) {
+  for (int64_t t = a + tid; t < b; t += NT) {
     const bool sup = in_sup_set(mask, t), roll = in_roll_set(mask, t);
     float c = 0.f;
     if ((sup || roll) && w > 0.0) {
@@ -1652,8 +1657,8 @@ fopd_segment_stats(int first, SegmentFold fold, SegmentOutputs out, const float*
     fold.coef[t] = c;
   }
   if (i == fold.B - 1)                   // rows that belong to no sample (the lengths fall short, which is flagged)
-    for (int64_t t = b + tid; t < T; t += kStatThreads) fold.coef[t] = 0.f;
-  const double total = block_sum<kStatThreads>(share, sh[0]);
+    for (int64_t t = b + tid; t < T; t += NT) fold.coef[t] = 0.f;
+  const double total = block_sum<NT>(share, sh[0]);
   if (tid == 0) fold.partials[i] = total;
 }
 

@@ -26,6 +26,37 @@ def test_offsets_and_coefficients_at_the_edges(B, length, staged):
     _compare_everything(w, HP, staged=staged)
 
 
+@pytest.mark.parametrize("B,length", [(1, 4095), (1, 4096), (3, 4096), (256, 4096), (257, 4096), (256, 4095), (1025, 5)])
+def test_scores_at_the_line_between_the_lane_counts(B, length):
+    """1024 lanes a sample for up to 256 samples of 4096 rows or more on average, else 512.  1e-6: scores are fp32 results of
+    fp64 sums."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B + length)
+    lens = torch.full((B,), length, dtype=torch.int32, device=DEV)
+    if B > 2:                                    # ragged; the same total
+        lens[0] += length // 2
+        lens[1] -= length // 2
+    T = B * length
+    p = _pass_for(dict(T=T, V=8, B=B, dtype="bf16", ld=8), alloc_dlogits=False)
+    p.logp.copy_(-torch.rand(T, generator=gen, device=DEV))
+    w = dict(behav_logp=p.logp + 0.1 * torch.randn(T, generator=gen, device=DEV), teacher_logp=p.logp - 0.1,
+             teacher_logp_stale=p.logp - 0.15, mask=(torch.rand(T, generator=gen, device=DEV) < 0.7).to(torch.uint8),
+             seq_lens=lens, lag=torch.ones(B, dtype=torch.int32, device=DEV))
+    p.freshness_score(w, HP)
+    assert p.status() == (0, 0)
+    at, live = torch.repeat_interleave(torch.arange(B, device=DEV), lens.long()), (w["mask"] != 0).double()
+    mean = lambda x: torch.zeros(B, dtype=torch.float64, device=DEV).index_add_(0, at, x * live) / n
+    est = lambda d: torch.exp(d) * d - torch.exp(d) + 1.0
+    n = torch.zeros(B, dtype=torch.float64, device=DEV).index_add_(0, at, live)
+    assert torch.equal(p.n_train, n.int()) and torch.equal(p.cu_seqlens[1:], torch.cumsum(lens, 0))
+    roll = mean(est(p.logp.double() - w["behav_logp"].double()))
+    sup = mean(est(w["teacher_logp"].double() - w["teacher_logp_stale"].double()))
+    f = 0.5 * torch.exp(-torch.sqrt(roll) - torch.sqrt(sup))
+    for got, ref in ((p.D_roll, roll), (p.D_sup, sup), (p.freshness, f), (p.cover, n / lens),
+                     (p.ell, mean(p.logp.double() - w["teacher_logp"].double()))):
+        assert float(((got.double() - ref) / ref).abs().max()) <= 1e-6
+
+
 @pytest.mark.parametrize("B", [3, 1024, 1025])
 @pytest.mark.parametrize("what", ["short", "long", "negative length", "negative lag"])
 def test_flags_of_the_offsets(B, what):
