@@ -1206,24 +1206,7 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLmLdsBytes, allowed) != FOPD_OK) return FOPD_EHIP;
   const int n_token_tiles = static_cast<int>(lay.t_pad / kLmTile);
   const int n_vocab_tiles = static_cast<int>((V + kLmTile - 1) / kLmTile);
-  // Strips: the work items (token tile x strip of the vocabulary) go to the 256 compute units round by round, a round
-  // takes as long as its longest strip has tiles (plus a little for the item itself: first loads, last merge), and the
-  // number of strips with the least total is taken.  Few token tiles give many short strips, so that one short rollout
-  // fills the chip too: 300 rows x 151,936 entries, d = 4096: 64 items of 19 tiles 1386 us, 256 items of 5 tiles 522 us.
-  // Whole groups only (tile_place): strips that leave part of a group empty share the weight's L2 copies worse (16,384
-  // rows: 4 strips in half-empty groups 17.0 ms, 8 strips 16.3 ms, although 4 of them end in one even round).
-  const int group_strips = 32 / tile_group_n(n_token_tiles);
-  const int64_t strips_max = kLmStrips + kLmPairsExtra / static_cast<int64_t>(lay.t_pad);
-  int n_strips = group_strips;
-  double best = 0.0;
-  for (int cand = group_strips; cand <= strips_max && (cand == group_strips || cand <= n_vocab_tiles); cand += group_strips) {
-    const int64_t rounds = (static_cast<int64_t>(n_token_tiles) * cand + 255) / 256;
-    const double cost = static_cast<double>(rounds) * (static_cast<double>((n_vocab_tiles + cand - 1) / cand) + 0.15);
-    if (cand == group_strips || cost < best) {
-      best = cost;
-      n_strips = cand;
-    }
-  }
+  const int n_strips = lm_strips(n_token_tiles, n_vocab_tiles);
   const unsigned grid = static_cast<unsigned>((tile_groups(n_strips, n_token_tiles) + 7) / 8) * 256u;
   float2* partial = at<float2>(workspace, lay.partial);
   const __bf16* Wp = static_cast<const __bf16*>(weight);
@@ -1254,28 +1237,6 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
 
 size_t fopd_lm_head_loss_workspace_bytes(int64_t T, int64_t V, int64_t d, int32_t B, int64_t rows_chunk) {
   return LmLossWorkspace(T, V, d, B, rows_chunk).total;
-}
-
-// Into how many runs of the contraction index Out[N, M] = sum over K is cut, at most `most`.  A product with few result
-// tiles leaves most of the 256 compute units idle while the others walk a long contraction index; each run is a result of
-// its own that is summed afterwards.  Estimate in microseconds: the work items (tile x run) go to the compute units round
-// by round, an item takes 1.8 a pair of stages of 64 plus 12 for its first loads and its stores, and the partial results
-// are written and read at 4 TB/s.  512 rows x 4096, K = 151,936 (32 tiles): 1 run 2805 us, 8 runs 520 us.
-static int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
-  const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile), pairs = K / 64;
-  most = std::min<int64_t>(std::min<int64_t>(most, 32), pairs / 8);
-  int best = 1;
-  double least = 0.0;
-  for (int splits = 1; splits == 1 || splits <= most; ++splits) {
-    const double rounds = static_cast<double>((tiles * splits + 255) / 256);
-    double cost = rounds * (1.8 * static_cast<double>((pairs + splits - 1) / splits) + 12.0);
-    if (splits > 1) cost += static_cast<double>(splits) * static_cast<double>(M) * static_cast<double>(N) * 8.0 / 4.0e6;
-    if (splits == 1 || cost < least) {
-      least = cost;
-      best = splits;
-    }
-  }
-  return best;
 }
 
 // Out[n, m] = sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  a_k_major: Am is stored [k, m] and

@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "fopd_kernels.hip"
 #include "fopd_lm_head.hip"
 
@@ -30,6 +32,32 @@ namespace fopd {
 
 constexpr int kGemmTile = kLmTile;          // 256 x 256 result tile
 constexpr int kGemmThreads = kLmThreads;
+
+// Into how many runs of the contraction index Out[N, M] = sum over K is cut, at most `most`.  A product with few result
+// tiles leaves most of the 256 compute units idle while the others walk a long contraction index; each run is a result of
+// its own that is summed afterwards.  Estimate in microseconds: the rounds of the launch (tile_rounds) follow each other, an
+// item takes 1.6 a step of 64 plus 13 for its first loads and its stores, and the partial results are read at 4.5 TB/s
+// when they are summed.  151,936 x 4096, the contraction alone, us by number of runs: 512 rows 1: 2896, 4: 947, 8: 488, 16:
+// 503; 768 rows 1: 3005, 4: 845, 8: 844, 16: 876 (5, which 240 items on 256 compute units seem to ask for: 1286); 2048 rows
+// 1: 3720, 2: 1906, 4: 1902; 3072 rows 1: 3743, 4: 2848, 8: 2928.
+inline int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
+  const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
+  const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
+  const int64_t steps = K / kLmK;
+  most = std::min<int64_t>(std::min<int64_t>(most, 32), steps / 8);
+  int best = 1;
+  double least = 0.0;
+  for (int splits = 1; splits == 1 || splits <= most; ++splits) {
+    const double rounds = static_cast<double>(tile_rounds(tiles_m, tiles_n, splits));
+    double cost = rounds * (1.6 * static_cast<double>((steps + splits - 1) / splits) + 13.0);
+    if (splits > 1) cost += static_cast<double>(splits) * static_cast<double>(M) * static_cast<double>(N) * 4.0 / 4.5e6;
+    if (splits == 1 || cost < least) {
+      least = cost;
+      best = splits;
+    }
+  }
+  return best;
+}
 
 // The wavefront's part of a finished tile, rows n0 .. , columns m0 .. of Out.  The n-side fragment is the matrix
 // instruction's first operand, so register r of acc[a][i][b] is output row n = 128 b + 32 wn + 8 (r / 4) + 4 (lane / 32) +

@@ -80,8 +80,55 @@ __host__ __device__ __forceinline__ int64_t tile_groups(int tiles_m, int tiles_n
   return static_cast<int64_t>((tiles_n + gn - 1) / gn) * ((tiles_m + gm - 1) / gm);
 }
 
+// Rounds of a launch of `runs` times the groups, along n first: the most that one XCD, 32 compute units of one workgroup
+// each, has to go through.  Groups that do not fill it run side by side where whole ones fit (16 tiles: two, 24 tiles: one;
+// measured on 768 rows, whose groups hold 24: a round takes as long for 24 tiles as for 32, whatever follows).
+__host__ inline int64_t tile_rounds(int tiles_m, int tiles_n, int runs) {
+  const int gn = tile_group_n(tiles_n), gm = 32 / gn;
+  const int groups_n = (tiles_n + gn - 1) / gn, groups_m = (tiles_m + gm - 1) / gm;
+  int64_t one[8] = {}, load[8] = {};                       // parts of 32 of a round, by XCD
+  for (int m = 0; m < groups_m; ++m)
+    for (int n = 0; n < groups_n; ++n) {
+      const int m_left = tiles_m - m * gm, n_left = tiles_n - n * gn;
+      const int tiles = (m_left < gm ? m_left : gm) * (n_left < gn ? n_left : gn);
+      one[(static_cast<int64_t>(m) * groups_n + n) % 8] += 32 / (32 / tiles);
+    }
+  const int64_t groups = static_cast<int64_t>(groups_m) * groups_n;
+  int64_t most = 0;
+  for (int r = 0; r < runs; ++r)
+    for (int x = 0; x < 8; ++x) {
+      int64_t& l = load[(x + r * groups) % 8];
+      l += one[x];
+      if (l > most) most = l;
+    }
+  return (most + 31) / 32;
+}
+
+// Strips of the vocabulary for fopd_k7_lm_head_lse: the launch takes its rounds (tile_rounds) one after the other, a round as long as its longest strip has tiles
+// (plus a little for the item itself: first loads, last merge), and the number of strips with the least total is taken.
+// Few token tiles give many short strips, so that one short rollout fills the chip too: 300 rows x 151,936 entries, d =
+// 4096, 32 strips 1850 us, 64 1017, 128 548.  What counts is the fullest XCD, not the number of items: 1280 rows (groups of
+// 32 and of 8 items in turn) 32 strips 1605 us, 48 strips, 240 items, 2081; 768 rows (24 items a group) 64 strips 938 us, 80
+// strips 1354.  Whole groups only (tile_place): strips that leave part of a group empty share the weight's L2 copies worse.
+__host__ inline int lm_strips(int n_token_tiles, int n_vocab_tiles) {
+  const int group_strips = 32 / tile_group_n(n_token_tiles);
+  const int strips_max = kLmStrips + kLmPairsExtra / (n_token_tiles * kLmTile);
+  int n_strips = group_strips;
+  double best = 0.0;
+  for (int cand = group_strips; cand <= strips_max && (cand == group_strips || cand <= n_vocab_tiles);
+       cand += group_strips) {
+    const double rounds = static_cast<double>(tile_rounds(cand, n_token_tiles, 1));
+    const double cost = rounds * (static_cast<double>((n_vocab_tiles + cand - 1) / cand) + 0.15);
+    if (cand == group_strips || cost < best) {
+      best = cost;
+      n_strips = cand;
+    }
+  }
+  return n_strips;
+}
+
 template <bool N_FIRST>
-__device__ __forceinline__ TilePlace tile_place(unsigned group, unsigned slot, int tiles_m, int tiles_n) {
+__host__ __device__ __forceinline__ TilePlace tile_place(unsigned group, unsigned slot, int tiles_m, int tiles_n) {
   const int gn = tile_group_n(tiles_n), gm = 32 / gn;
   const int groups_n = (tiles_n + gn - 1) / gn, groups_m = (tiles_m + gm - 1) / gm;
   const int g = static_cast<int>(group), sl = static_cast<int>(slot);

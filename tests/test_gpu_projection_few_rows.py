@@ -40,10 +40,11 @@ def test_log_probs_at_the_edges_of_tiles_and_groups(T, masked_every):
         assert np.max(np.abs(np64(lse) - ref_lse)) <= 1e-4 and np.max(np.abs(np64(logp) - ref_lp)) <= 1e-4
 
 
-@pytest.mark.parametrize("seq,d,pad_h", [((1,), 64, 0), ((40, 25), 64, 2), ((100, 157), 320, 4), ((300, 214), 512, 3)])
+@pytest.mark.parametrize("seq,d,pad_h", [((1,), 64, 0), ((40, 25), 64, 2), ((100, 157), 320, 4), ((300, 214), 512, 3),
+                                          ((500, 260), 320, 4), ((700, 500), 128, 0)])
 def test_gradients_with_the_vocabulary_cut_into_runs(seq, d, pad_h):
-    """One to sixteen result tiles of dL/dhidden: the contraction over 20,001 entries is cut into runs and the scatter
-    sums them, into rows whose pitch is and is not a multiple of four."""
+    """One to six result tiles of dL/dhidden, one to five along the rows: the contraction over 20,001 entries is cut into
+    runs and the scatter sums them, into rows whose pitch is and is not a multiple of four."""
     T = sum(seq)
     h = wl.generate_lm_head(T, d, 20001, DEV, seed=T, masked_every=4 if T > 1 else 0)
     w = wl.attach_loss_inputs(h, seq, [1, 3][:len(seq)], seed=T)

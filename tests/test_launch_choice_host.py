@@ -1,0 +1,88 @@
+"""Into how many strips or runs the projection kernels cut their work.  The choices are compiled here with a small host
+program that deals the work items out as the card does - workgroups to the eight XCDs in turn, on each to the compute unit
+that is free first - and compares the time of the choice with that of plain alternatives."""
+
+import os
+import subprocess
+
+import pytest
+
+from paper_2605_17862_amd import build as b
+
+SOURCE = r"""
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include "fopd_gemm.hip"
+using namespace fopd;
+
+// Steps until all items are done; an item of strip / run r takes length(r) and `start`, an empty workgroup nothing.
+template <typename Length>
+static double makespan(int tiles_m, int tiles_n, int runs, double start, Length length) {
+  static double busy[8][32];
+  for (auto& x : busy) for (double& c : x) c = 0.0;
+  const int per = static_cast<int>(tile_groups(tiles_m, tiles_n));
+  double last = 0.0;
+  for (int g = 0; g < per * runs; ++g)
+    for (int slot = 0; slot < 32; ++slot) {
+      const TilePlace at = tile_place<true>(static_cast<unsigned>(g % per), static_cast<unsigned>(slot), tiles_m, tiles_n);
+      if (at.m >= tiles_m || at.n >= tiles_n) continue;
+      double* cu = std::min_element(busy[g % 8], busy[g % 8] + 32);
+      *cu += length(at.m, g / per) + start;
+      last = std::max(last, *cu);
+    }
+  return last;
+}
+
+int main() {
+  for (int tokens = 1; tokens <= 72; ++tokens)
+    for (int vocab : {63, 125, 594, 1024}) {
+      const int most = kLmStrips + kLmPairsExtra / (tokens * kLmTile);
+      auto time = [&](int strips) {
+        return makespan(strips, tokens, 1, 0.15, [&](int m, int) {
+          return double((m + 1) * (long)vocab / strips - m * (long)vocab / strips);
+        });
+      };
+      const int own = lm_strips(tokens, vocab);
+      double plain = 1e30;
+      for (int c : {8, 16, 32}) if (c <= most) plain = std::min(plain, time(c));
+      std::printf("strips %d %d %d %d %.3f %.3f\n", tokens, vocab, own, most, time(own), plain);
+    }
+  for (int rows = 1; rows <= 32; ++rows)
+    for (int cols : {4, 8, 10, 16, 20})
+      for (int steps : {500, 2374}) {
+        auto time = [&](int runs) {
+          return makespan(cols, rows, runs, 13.0 / 1.6, [&](int, int r) {
+            return double((r + 1) * (long)steps / runs - r * (long)steps / runs);
+          });
+        };
+        const int most = std::min(steps * 64 / (cols * 256), 32);
+        const int own = gemm_splits(cols * 256, rows * 256, steps * 64L, most);
+        double plain = 1e30;
+        for (int c : {1, 2, 4}) if (c <= most) plain = std::min(plain, time(c));
+        std::printf("runs %d %d %d %d %.3f %.3f\n", rows * 1000 + cols, steps, own, most, time(own), plain);
+      }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def choices(tmp_path_factory):
+    d = tmp_path_factory.mktemp("launch_choice")
+    (d / "choice.hip").write_text(SOURCE)
+    flags = [f for f in b.HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-O3")]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags +
+                   ["-O1", "-I", os.path.join(b.ROOT, "include"), "-I", os.path.join(b.PKG, "csrc"),
+                    str(d / "choice.hip"), "-o", str(d / "choice")], check=True, capture_output=True)
+    out = subprocess.run([str(d / "choice")], check=True, capture_output=True, text=True).stdout
+    return [l.split() for l in out.splitlines()]
+
+
+@pytest.mark.parametrize("what", ["strips", "runs"])
+def test_no_slower_than_plain_choices(choices, what):
+    rows = [r for r in choices if r[0] == what]
+    assert len(rows) > 200
+    for _, where, size, own, most, time, plain in rows:
+        assert 1 <= int(own) <= int(most), (where, size, own)
+        # 8, 16 or 32 strips, 1, 2 or 4 runs; the rule counts whole rounds only, hence the few per cent
+        assert float(time) <= 1.08 * float(plain), (what, where, size, own, time, plain)
