@@ -66,7 +66,10 @@ __device__ __forceinline__ void lm_merge(float& m, float& s, float m2, float s2)
 // workgroup is not free: it asks for the same 128 KB of LDS, so it queues for a compute unit like a working one.
 // Measured on 512 rows x 151,936 entries, d = 4096 (1188 tiles): 4 x 8 groups always, 19,200 workgroups, 928 us;
 // groups without idle workgroups, 1280 in all, 585 us.
-// Consecutive groups, and with them the XCDs, go along n first (N_FIRST) or along m first.
+// Consecutive groups, and with them the XCDs, go along n first (N_FIRST) or along m first.  Along m first there are few groups
+// in a line, and the last of it may be a small one: where the line's length has a factor in common with 8 the same XCDs would
+// get it in every line, so the order in a line moves on by one each time the XCDs have come round to its start (weight
+// gradient of 4096 rows x 151,936, lines of 8 + 2 tiles, d = 2560: 3971 -> 2711 us).
 struct TilePlace {
   int m, n;
 };
@@ -132,8 +135,9 @@ __host__ __device__ __forceinline__ TilePlace tile_place(unsigned group, unsigne
   const int gn = tile_group_n(tiles_n), gm = 32 / gn;
   const int groups_n = (tiles_n + gn - 1) / gn, groups_m = (tiles_m + gm - 1) / gm;
   const int g = static_cast<int>(group), sl = static_cast<int>(slot);
+  const int common = min(groups_m & -groups_m, 8);         // largest common divisor of 8 and the length of a line
   const int at_n = N_FIRST ? g % groups_n : g / groups_m;
-  const int at_m = N_FIRST ? g / groups_n : g % groups_m;
+  const int at_m = N_FIRST ? g / groups_n : (g + g / (8 / common * groups_m)) % groups_m;
   return TilePlace{at_m * gm + sl / gn, at_n * gn + sl % gn};
 }
 

@@ -1,6 +1,7 @@
-"""Into how many strips or runs the projection kernels cut their work.  The choices are compiled here with a small host
-program that deals the work items out as the card does - workgroups to the eight XCDs in turn, on each to the compute unit
-that is free first - and compares the time of the choice with that of plain alternatives."""
+"""Into how many strips or runs the projection kernels cut their work, and the order of the weight gradient's tiles.  They
+are compiled here into a small host program that deals the work items out as the card does - workgroups to the eight XCDs in
+turn, on each to the compute unit that is free first - and compares the time of the choice with that of plain alternatives,
+and the tiles of the fullest XCD with an even share."""
 
 import os
 import subprocess
@@ -62,6 +63,22 @@ int main() {
         for (int c : {1, 2, 4}) if (c <= most) plain = std::min(plain, time(c));
         std::printf("runs %d %d %d %d %.3f %.3f\n", rows * 1000 + cols, steps, own, most, time(own), plain);
       }
+  for (int hidden = 1; hidden <= 40; ++hidden)
+    for (int vocab : {3, 63, 125, 594, 1024}) {
+      int tiles[8] = {}, seen = 0, most = 0;
+      static bool once[64][1024];
+      for (auto& x : once) for (bool& y : x) y = false;
+      for (int g = 0; g < tile_groups(hidden, vocab); ++g)
+        for (int slot = 0; slot < 32; ++slot) {
+          const TilePlace at = tile_place<false>(static_cast<unsigned>(g), static_cast<unsigned>(slot), hidden, vocab);
+          if (at.m >= hidden || at.n >= vocab) continue;
+          if (at.m < 0 || at.n < 0 || once[at.m][at.n]) return 1;
+          once[at.m][at.n] = true;
+          ++seen;
+          most = std::max(most, ++tiles[g % 8]);
+        }
+      std::printf("order %d %d %d %d\n", hidden, vocab, seen, most);
+    }
 }
 """
 
@@ -86,3 +103,13 @@ def test_no_slower_than_plain_choices(choices, what):
         assert 1 <= int(own) <= int(most), (where, size, own)
         # 8, 16 or 32 strips, 1, 2 or 4 runs; the rule counts whole rounds only, hence the few per cent
         assert float(time) <= 1.08 * float(plain), (what, where, size, own, time, plain)
+
+
+def test_tiles_of_the_weight_gradient_are_spread_evenly(choices):
+    rows = [[int(x) for x in r[1:]] for r in choices if r[0] == "order"]
+    assert len(rows) == 200
+    for hidden, vocab, seen, most in rows:
+        assert seen == hidden * vocab                        # each tile once (the program checks that none comes twice)
+        lines, line = -(-vocab // 4), -(-hidden // 8)
+        # an even share, and a group of 32 for each place of a line in which one XCD can be ahead
+        assert most <= hidden * vocab / 8 + 32 * min(line, lines), (hidden, vocab, most)
