@@ -1,5 +1,6 @@
 """Numbers of samples and rows around the lines where a call forms the samples' offsets (1024 samples) and the row
-coefficients (2048 rows) inside the statistics kernel, against float64, and the error flags of the offsets there."""
+coefficients (2048 rows) inside the statistics kernel and where that takes 512 or 1024 lanes a sample, against float64; the
+error flags of the offsets there; rows kept in the caches between the two passes of a call."""
 
 import numpy as np
 import pytest
@@ -79,12 +80,19 @@ def test_flags_of_the_offsets(B, what):
         assert not bool(lp.dlogits[int(cu[B - 2]):int(cu[B - 1])].any()) and float(lp.weights[B - 2]) == 0.0
 
 
-@pytest.mark.parametrize("T,V,two", [(1203, 151936, False), (2207, 151936, False), (9, 4104, False), (1203, 151936, True),
-                                     (5001, 32000, True), (9, 4104, True)])
+CACHED, CACHED_TOTAL = 240 << 20, 640 << 20       # bytes of rows: read by ordinary loads the first time; no more than this in all
+
+
+@pytest.mark.parametrize("T,V,two", [(1203, 151936, False), (2207, 151936, False), (9, 4104, False), (2403, 151936, False),
+                                     (1203, 151936, True), (5001, 32000, True), (9, 4104, True)])
 def test_rows_kept_in_the_caches_between_the_passes(T, V, two):
-    """All rows, the last ones only and none of them read by ordinary loads the first time, the second pass from the last row
-    and from the first; rows not a multiple of eight.  The log-probs are those of the scoring call bit for bit, every gradient
-    row is written, and sampled rows have the properties of c (softmax - onehot)."""
+    """All rows (9), the last ones only (1203 and 2207) and, in a one-tensor call past the line, none of them (2403) read by
+    ordinary loads the first time, the second pass from the last row and there from the first; rows not a multiple of eight.
+    The log-probs are those of the scoring call bit for bit, every gradient row is written, and sampled rows have the
+    properties of c (softmax - onehot)."""
+    if not two:
+        nbytes = T // 3 * 3 * V * 2
+        assert (nbytes <= CACHED) == (T == 9) and (nbytes > CACHED_TOTAL) == (T == 2403)
     B = 3
     w = wl.generate("reasoning", DEV, seed=T, B=B, len_lo=T // B, len_hi=T // B, V=V, **(dict(stale_logit_sigma=0.05) if two else {}))
     lens = w["seq_lens_host"].copy()
@@ -112,3 +120,35 @@ def test_rows_kept_in_the_caches_between_the_passes(T, V, two):
     assert bool((rows.sum(dim=1).abs() <= 2.0 ** -8 * rows.abs().sum(dim=1) + 1e-30).all())
     live = torch.repeat_interleave(lp.weights, w["seq_lens"].long()) > 0
     assert bool((rows.abs().sum(dim=1)[live & (w["mask"] != 0)] > 0).all())
+
+
+@pytest.mark.parametrize("T,V", [(2403, 151936), (1203, 151936), (25011, 16384), (9, 4104)])
+def test_both_gradient_kernels_on_both_sides_of_the_line(T, V):
+    """The kernel of one 256-lane workgroup a row (the only one for rows of at most 2048 vectors: 25,011 x 16,384, which is
+    past the line) and the one that holds a row in registers: the same bits, from the first row and from the last."""
+    assert (T * V * 2 > CACHED_TOTAL) == (T > 2400)
+    w = wl.generate("reasoning", DEV, seed=T, B=3, len_lo=T // 3, len_hi=T // 3, V=V)
+    w["mask"][::5] = 0
+    lp, st = _pass_for(w), _pass_for(w, alloc_dlogits=False)
+    lp.dlogits.fill_(7.0)
+    try:
+        fb.fopd_set_option("k4_regs", 0)
+        lp.loss_fwd_bwd(w, HP)
+        rows, loss = lp.dlogits.clone(), lp.loss.clone()
+        fb.fopd_set_option("k4_regs", 1)
+        lp.dlogits.fill_(7.0)
+        lp.loss_fwd_bwd(w, HP)
+    finally:
+        fb.fopd_set_option("k4_regs", 1)
+    assert lp.status() == (0, 0)
+    assert torch.equal(rows, lp.dlogits) and torch.equal(loss, lp.loss) and not bool((rows == 7.0).any())
+    st.token_logprobs(w)
+    assert torch.equal(lp.logp, st.logp)
+    # sampled rows against c (softmax - onehot) in float64: bf16 entries (2^-9 each) of fp32 values
+    live = torch.nonzero(torch.repeat_interleave(lp.weights, w["seq_lens"].long()) * (w["mask"] != 0))[:, 0]
+    for t in live[[0, 1, len(live) // 2, -2, -1]].tolist() if len(live) > 4 else live.tolist():
+        p = torch.softmax(w["logits"][t, :V].double(), 0)
+        p[w["token_ids"][t].long()] -= 1.0
+        g = rows[t, :V].double()
+        c = (g * p).sum() / (p * p).sum()
+        assert float((g - c * p).abs().max()) <= 2.0 ** -8 * float((c * p).abs().max())
