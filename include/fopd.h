@@ -510,7 +510,10 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
  * path run on them (the gradient rows are written as bf16, as that path stores them), and two more matrix-core
  * contractions fold the rows into dhidden and dweight; then the scratch is reused.  All work is bf16 inputs with
  * fp32 accumulation; the result does not depend on rows_chunk except through the order of the fp32 sums over
- * rows in dweight.  Rows with mask == 0 (observations, prompts: no log-prob, no gradient row) cost no matrix work:
+ * rows in dweight.  With few rows (T, masked ones too) the fp32 sum over the vocabulary of a dhidden row is taken in up to
+ * 32 runs, whose number goes by T, V and d: the same row in a call of another T (micro-batches instead of one batch) may
+ * differ in its last bits.  Many rows in small chunks are expensive, the runs being fewer: take rows_chunk as large as the
+ * scratch allows.  Rows with mask == 0 (observations, prompts: no log-prob, no gradient row) cost no matrix work:
  * each chunk's other rows are gathered to the front, the kernels run on those, and the per-row outputs and dhidden
  * rows are scattered back, zeros at the masked rows; likewise the rows of samples of weight 0 are left out of the
  * two gradient contractions (option "lm_head_compact").

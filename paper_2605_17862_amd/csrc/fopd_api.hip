@@ -98,9 +98,11 @@ struct LmLossWorkspace {
          logp_c = 0, lse_c = 0, tl_c = 0, ids_c = 0, llp_c = 0, h_c = 0, dh_c = 0, grad_ex = 0, h_g = 0, keep = 0;
   int64_t ldz = 0, r_pad = 0, n_chunks = 0;
   // dL/dhidden of more rows than this reads a transposed copy of the projection matrix.  The copy takes 450 us (151,936 x
-  // 4096) whatever the rows; without it the contraction itself is slower by about 0.1 us a row (its A fragments leave the LDS
-  // in two transposing reads instead of one).  Whole call with / without the copy, us: 512 rows 2737 / 2262, 2048 rows
-  // 7619 / 7239, 4096 rows 14159 / 13969, 16,384 rows 54,649 / 55,947.
+  // 4096) whatever the rows; without it the contraction itself is slower by about 0.1 us a row (its A fragments leave the
+  // LDS in two transposing reads instead of one).  Whole call with / without the copy, us: 512 rows 2794 / 2314, 2048 rows
+  // 7789 / 7418, 4096 rows 14,393 / 14,210, 6144 rows 20,963 / 20,963, 8192 rows 27,912 / 28,170, 16,384 rows 55,663 /
+  // 56,794.  The rows are those of the call, masked ones too, whose number the host does not know: 6144 rows with a third
+  // masked 14,378 / 14,182, 8192 rows with half masked 14,409 / 14,260, so such calls take the copy for 1 % too much.
   static constexpr int64_t kTransposeRows = 4096;
   bool with_wt = false;
   LmLossWorkspace(int64_t T, int64_t V, int64_t d, int32_t B, int64_t rows_chunk, int32_t k = 0) {
@@ -834,10 +836,10 @@ fopd_status fopd_loss_fwd_bwd_static(const void* logits, fopd_dtype dt, int64_t 
   return st;
 }
 
-static fopd_status rollout_kl(bool read_again, const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T, int64_t V,
-                            int64_t ld, int64_t ld_stale, const int32_t* token_ids, const uint8_t* mask,
-                            float* roll_kl, float* logp, float* lse, float* dlse, float* logq, void* workspace,
-                            size_t workspace_bytes, void* stream) {
+static fopd_status rollout_kl(bool read_again, const void* logits, const void* logits_stale, fopd_dtype dt, int64_t T,
+                              int64_t V, int64_t ld, int64_t ld_stale, const int32_t* token_ids, const uint8_t* mask,
+                              float* roll_kl, float* logp, float* lse, float* dlse, float* logq, void* workspace,
+                              size_t workspace_bytes, void* stream) {
   fopd_status st = check_matrix(logits, dt, T, V, ld);
   if (st != FOPD_OK) return st;
   if ((st = check_matrix(logits_stale, dt, T, V, ld_stale)) != FOPD_OK) return st;
@@ -933,7 +935,7 @@ static fopd_status two_tensor_call(bool teacher, const void* logits, const void*
     float* logp_ws = (logp != nullptr) ? logp : at<float>(workspace, w.logp);
     float* kl_ws = (token_kl != nullptr) ? token_kl : at<float>(workspace, w.kl);
     st = rollout_kl(true, logits, second, dt, T, V, ld, ld_second, token_ids, mask, kl_ws, logp_ws, lse_ws, dlse_ws,
-                         teacher ? logq_ws : nullptr, workspace, workspace_bytes, stream);
+                    teacher ? logq_ws : nullptr, workspace, workspace_bytes, stream);
     if (st != FOPD_OK) return st;
     if (teacher) lq_use = logq_ws;      // the teacher's log-prob of the sampled token, for D^sup
     // stale tensor: drift = the full KL, token loss = sampled form; teacher tensor: the other way round
@@ -1275,9 +1277,11 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Ak, int64_t lda
                                   const __bf16* Bk, int64_t ldb, int64_t N, int64_t K, float* Out, int64_t ldo, int slot,
                                   hipStream_t s, const int* k_live = nullptr) {
   if (M <= 0 || N <= 0) return FOPD_OK;
-  if (K <= 0 || K % 64 != 0 || rows_a <= K - kLmK || rows_a > K || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL ||
-      M % 8 != 0 || lda % 8 != 0 || ldb % 8 != 0 || lda < M || ldb < (N + 7) / 8 * 8 || kLmK * lda * 2 >= 2147483648LL || kLmK * ldb * 2 >= 2147483648LL)
+  if (K <= 0 || K % kLmK != 0 || rows_a <= K - kLmK || rows_a > K || M > 2147483647LL || N > 2147483647LL ||
+      K > 2147483647LL || M % 8 != 0 || lda % 8 != 0 || ldb % 8 != 0 || lda < M || ldb < (N + 7) / 8 * 8)
     return FOPD_ESHAPE;
+  // byte offsets inside the 64 rows of a step are 32-bit
+  if (kLmK * lda * 2 >= 2147483648LL || kLmK * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
   static bool allowed[2][kMaxDevices] = {};
   const void* kern = accumulate ? reinterpret_cast<const void*>(fopd_gemm_tn<true>)
                                 : reinterpret_cast<const void*>(fopd_gemm_tn<false>);
@@ -1508,8 +1512,9 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
 
   // dL/dhidden in how many runs over the vocabulary: by the rows of the call, not of a chunk, so that a row's sum has the
-  // same order whatever rows_chunk is (and with or without the masked rows).  The partial results of R rows, R d floats
-  // each, fit where the logits of R rows were.
+  // same order whatever rows_chunk is (and with or without the masked rows).  The price: 4096 rows in chunks of 256 take one
+  // run each, 2.7 ms a chunk where 16 runs would take 0.3.  Half of 512 rows masked: 8 runs, 4 % of the call slower than
+  // 16.  The partial results of R rows, R d floats each, fit where the logits of R rows were.
   const int dh_splits = grads ? gemm_splits(d, T, ldz, ldz / d) : 1;
   int64_t ci = 0;
   for (int sweep = two_sweeps ? 0 : 1; sweep < 2; ++sweep) {
@@ -1576,8 +1581,8 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     auto scatter = [&]() -> fopd_status {
       if (!compact) return FOPD_OK;
       fopd_live_scatter<<<static_cast<unsigned>(R), 256, 0, s>>>(
-          row_map, n_live, map_off, row_base, lp_o, ls_o, tl_o, grad_ex, dH, dh_splits, R * d, static_cast<int>(d), logp, lse, tl,
-          (grads && sweep == 1) ? dhidden : nullptr, lddh);
+          row_map, n_live, map_off, row_base, lp_o, ls_o, tl_o, grad_ex, dH, dh_splits, R * d, static_cast<int>(d), logp,
+          lse, tl, (grads && sweep == 1) ? dhidden : nullptr, lddh);
       return launched();
     };
     // logits of the chunk, fp32, never rounded to the storage type of stored logits

@@ -196,7 +196,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
     const int k0 = min(step, n_steps - 1) * kLmK;
     const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
-    const char* src = half >= 2 ? Bb + 2 * static_cast<int64_t>(k0) : Ab + 2 * k0 * (A_K_MAJOR ? lda : 1);
+    const char* src = half >= 2 ? Bb + 2 * static_cast<int64_t>(k0) : Ab + 2 * static_cast<int64_t>(k0) * (A_K_MAJOR ? lda : 1);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       uint32_t off = half >= 2 ? b_at[half & 1][e] : a_at[half & 1][e];

@@ -1156,22 +1156,22 @@ fopd_k5_kl(const void* logits, const void* logits_stale, int64_t T, int V, int64
     int j = tid;
     for (; j + (U2 - 1) * NT < nvec; j += U2 * NT, ++trip) {
       u32x4 q[U2], qs[U2];
-  #pragma unroll
+#pragma unroll
       for (int u = 0; u < U2; ++u) {
         q[u] = load_vec<kCached>(rv + j + u * NT);
         qs[u] = load_vec<kCached>(rsv + j + u * NT);
       }
       float x[U2 * E], xs[U2 * E];
-  #pragma unroll
+#pragma unroll
       for (int u = 0; u < U2; ++u) {
         unpack<DT>(q[u], x + u * E);
         unpack<DT>(qs[u], xs + u * E);
       }
       if (trip == ytrip) {
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < U2; ++u) {
           if (j + u * NT == jy) {
-  #pragma unroll
+#pragma unroll
             for (int e = 0; e < E; ++e) {
               if (e == ey) {
                 sh_zy = x[u * E + e];
@@ -1190,7 +1190,7 @@ fopd_k5_kl(const void* logits, const void* logits_stale, int64_t T, int V, int64
       unpack<DT>(load_vec<kCached>(rv + j), x);
       unpack<DT>(load_vec<kCached>(rsv + j), xs);
       if (j == jy) {
-  #pragma unroll
+#pragma unroll
         for (int e = 0; e < E; ++e) {
           if (e == ey) {
             sh_zy = x[e];

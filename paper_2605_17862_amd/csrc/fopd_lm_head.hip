@@ -64,12 +64,14 @@ __device__ __forceinline__ void lm_merge(float& m, float& s, float m2, float s2)
 // (the side with few tiles when the batch is small) x the 8 (16, 32) along m that fill it: with one or two tiles along n
 // the group takes 16 or 32 tiles along m instead of leaving workgroups without work.  That matters because an idle
 // workgroup is not free: it asks for the same 128 KB of LDS, so it queues for a compute unit like a working one.
-// Measured on 512 rows x 151,936 entries, d = 4096 (1188 tiles): 4 x 8 groups always, 19,200 workgroups, 928 us;
-// groups without idle workgroups, 1280 in all, 585 us.
-// Consecutive groups, and with them the XCDs, go along n first (N_FIRST) or along m first.  Along m first there are few groups
-// in a line, and the last of it may be a small one: where the line's length has a factor in common with 8 the same XCDs would
-// get it in every line, so the order in a line moves on by one each time the XCDs have come round to its start (weight
-// gradient of 4096 rows x 151,936, lines of 8 + 2 tiles, d = 2560: 3971 -> 2711 us).
+// Logits of 512 rows x 151,936 entries, d = 4096 (1188 tiles): 4 x 8 groups always, 2560 workgroups, 836 us; 2 x 16, 1280,
+// 558 us.  Idle workgroups remain where the last group along n has 1 to 3 tiles and another one stands beside it, or the only
+// one has 3, and where the groups are rounded up to eight: 594 tiles take 768 workgroups for 256 rows, 1782 take 2560 for 768
+// rows (0.52 us a tile, 0.46 with the 2376 of 1024 rows), 2970 take 4864 for 1280 rows (0.55).
+// Consecutive groups, and with them the XCDs, go along n first (N_FIRST) or along m first.  Along m first there are few
+// groups in a line, and the last of it may be a small one: where the line's length has a factor in common with 8 the same
+// XCDs would get it in every line, so the order in a line moves on by one each time the XCDs have come round to its start
+// (weight gradient of 4096 rows x 151,936, lines of 8 + 2 tiles, d = 2560: 3971 -> 2711 us).
 struct TilePlace {
   int m, n;
 };
@@ -107,12 +109,13 @@ __host__ inline int64_t tile_rounds(int tiles_m, int tiles_n, int runs) {
   return (most + 31) / 32;
 }
 
-// Strips of the vocabulary for fopd_k7_lm_head_lse: the launch takes its rounds (tile_rounds) one after the other, a round as long as its longest strip has tiles
-// (plus a little for the item itself: first loads, last merge), and the number of strips with the least total is taken.
-// Few token tiles give many short strips, so that one short rollout fills the chip too: 300 rows x 151,936 entries, d =
-// 4096, 32 strips 1850 us, 64 1017, 128 548.  What counts is the fullest XCD, not the number of items: 1280 rows (groups of
-// 32 and of 8 items in turn) 32 strips 1605 us, 48 strips, 240 items, 2081; 768 rows (24 items a group) 64 strips 938 us, 80
-// strips 1354.  Whole groups only (tile_place): strips that leave part of a group empty share the weight's L2 copies worse.
+// Strips of the vocabulary for fopd_k7_lm_head_lse: the launch takes its rounds (tile_rounds) one after the other, a
+// round as long as its longest strip has tiles (plus a little for the item itself: first loads, last merge), and the
+// number of strips with the least total is taken. Few token tiles give many short strips, so that one short rollout fills
+// the chip too: 300 rows x 151,936 entries, d = 4096, 32 strips 1850 us, 64 1017, 128 548.  What counts is the fullest
+// XCD, not the number of items: 1280 rows (groups of 32 and of 8 items in turn) 32 strips 1605 us, 48 strips, 240 items,
+// 2081; 768 rows (24 items a group) 64 strips 938 us, 80 strips 1354.  Whole groups only (tile_place): strips that leave
+// part of a group empty share the weight's L2 copies worse.
 __host__ inline int lm_strips(int n_token_tiles, int n_vocab_tiles) {
   const int group_strips = 32 / tile_group_n(n_token_tiles);
   const int strips_max = kLmStrips + kLmPairsExtra / (n_token_tiles * kLmTile);
