@@ -354,6 +354,11 @@ fopd_status launch_count_train(const uint8_t* mask, const int64_t* cu, int64_t T
 // what the cache gives (4096 rows 665 / 664 us, listed teacher 682 / 691 us, 32,768 rows + 0.9 %), so kCachedTotal is the line.
 // Two tensors: 256 / 1024 / 4096 rows x 151,936 110.5 / 291.9 / 1105 -> 95.0 / 259.7 / 1043 us with the last 320 MB of both
 // (240 MB: 95.2 / 261.9 / 1074), more rows no slower.
+// These loads push out of the cache what was there, so it matters what ran before the call.  512 / 1024 / 2048 rows x 151,936,
+// without and with them: after the GEMM that makes the logits 120 / 199 / 364 -> 104 / 176 / 345 us (two tensors 177 / 317 / 600
+// -> 149 / 272 / 561), which is the case that counts.  After a gigabyte of something else was written, whose lines have to go to
+// memory first, 120 / 196 / 365 -> 129 / 230 / 406 (two tensors 169 / 305 / 596 -> 199 / 338 / 644); zeroing the gradient rows
+// right before the call is such a write from 1024 rows on (192 -> 217), so a buffer with padding columns is best zeroed once.
 constexpr int64_t kCachedBytes = 240LL << 20, kCachedTotal = 640LL << 20;
 constexpr int64_t kCachedBytesTwo = 320LL << 20;
 inline int64_t first_cached_row(int64_t T, int64_t row_bytes, int64_t bytes) {

@@ -17,9 +17,9 @@
 // cross-lane step (the two half-waves).  Both operands are k-contiguous in memory (hidden [T, d],
 // weight [V, d]), so a lane's 8-element fragment is one 16-byte LDS read.
 //
-// The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Measured on MI355X it is
-// bound by the L1 miss path from the L2: about 20 bytes per clock and compute unit where full MFMA rate on a 256 x 256
-// tile needs 32.
+// The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Counters of the contraction
+// on MI355X: matrix cores 0.74 busy at the 1.68 GHz that the part holds under this load, 24 bytes per clock and compute unit
+// through the L1 where full MFMA rate on a 256 x 256 tile needs 32.
 
 #ifndef FOPD_LM_HEAD_HIP_
 #define FOPD_LM_HEAD_HIP_
@@ -167,10 +167,12 @@ __host__ __device__ __forceinline__ TilePlace tile_place(unsigned group, unsigne
 // phase are followed by its wait count one barrier before the earlier kind reads.
 //
 // Measured on the log-probs of 16,384 rows x 151,936 entries, d = 4096, against the loop before (tiles through vector
-// registers, a quarter of 64 elements per 16, one barrier per 64): 16.40 - 16.73 -> 15.91 - 15.95 ms on one box.
-// Without the loads it takes 12.8 ms, with every load a hit in the L2 14.3.  Slower: the loads of a slot before its LDS
-// reads (+ 14 %), inside the run of matrix instructions (+ 10 - 16 %): requests wait at the L1, and hold up what follows
-// them; non-temporal loads (+ 14 %); B0 read a phase earlier to even out the reads (+ 1 %).
+// registers, a quarter of 64 elements per 16, one barrier per 64): 16.40 - 16.73 -> 15.91 - 15.95 ms on one box, 0 - 4 % on
+// others.  Contractions of two steps a tile (d = 128) are up to 25 % slower with it.  Variants of an experiment: with the
+// operands loaded once and not again 14.07 of 16.70 ms (another box 12.8 of 15.9), with every step reading the same 64
+// elements, lines just used, 16.02 (14.3).  Slower: the loads of a slot before its LDS reads (+ 14 %), inside the run of
+// matrix instructions (+ 10 - 16 %): requests wait at the L1, and hold up what follows them; non-temporal loads (+ 14 %); B0
+// read a phase earlier to even out the reads (+ 1 %).
 
 struct MatrixPlace {
   int wm, wn;
