@@ -15,7 +15,7 @@
 //
 // Tiling and loop are those of the projection kernel fused with the log-sum-exp (fopd_lm_head.hip, matrix_step): a
 // workgroup of eight wavefronts owns a 256 x 256 tile of the result.  The n-side fragment is the instruction's first
-// operand: the 32 lanes of a half-wave then hold consecutive m of one output row, the contiguous side of the output.
+// operand: sixteen lanes then hold consecutive m of one output row, the contiguous side of the output.
 
 #ifndef FOPD_GEMM_HIP_
 #define FOPD_GEMM_HIP_
@@ -60,63 +60,73 @@ inline int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
 }
 
 // The wavefront's part of a finished tile, rows n0 .. , columns m0 .. of Out.  The n-side fragment is the matrix
-// instruction's first operand, so register r of acc[a][i][b] is output row n = 128 b + 32 wn + 8 (r / 4) + 4 (lane / 32) +
-// r % 4 of the tile, and the 32 lanes of a half-wave hold consecutive m = 128 a + 64 wm + 32 i + lane % 32: a store
-// instruction writes two whole 128-byte lines.  (With the m side first, a lane holds four consecutive m and an instruction
-// writes 32 bytes to each of 32 rows: 2 - 3 % slower.)  The results are not read by this kernel and are far larger than the
-// L2, whose lines the operand tiles need: non-temporal stores, loss and gradients of 16,384 rows 52.7 -> 51.8 ms, of 4096
-// rows 13.42 -> 13.33 ms, fewer rows unchanged.
+// instruction's first operand, so register r of acc[a][i][b][j] is output row n = 128 b + 32 wn + 16 j + 4 (lane / 16) + r of
+// the tile and column m = 128 a + 64 wm + 16 i + lane % 16: a store of it would write half a 128-byte line to each of four
+// rows.  The second and fourth 16 lanes of one register change places with the first and third of the next block's, and a store
+// writes whole lines of two rows (rows n and n + 8 of one block, n + 4 and n + 12).  Weight gradient of 512 / 2048 rows x
+// 151,936, d = 4096: half lines 1170 / 2647 us, whole lines 967 / 2458; four consecutive m in a lane (the m side first), 16
+// bytes to each of 16 rows four times, 1251 / 2829.  The results are not read by this kernel and are far larger than the L2,
+// whose lines the operand tiles need: non-temporal stores, loss and gradients of 16,384 rows 52.7 -> 51.8 ms, of 4096 rows
+// 13.42 -> 13.33 ms, fewer rows unchanged (with the 32 x 32 x 16 instruction).
 template <bool ACCUMULATE>
-__device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][2][2], const MatrixPlace& place, int m0, int n0, int M,
+__device__ __forceinline__ void store_tile(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M,
                                            int N, float* __restrict__ Out, int64_t ldo) {
   const int lane = threadIdx.x & 63;
   const int m = m0 + place.wm * 64 + (lane & 31);
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int n = n0 + b * 128 + place.wn * 32 + ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
-      if (n >= N) continue;
+    for (int r = 0; r < 4; ++r) {
+      const int n = n0 + (b >> 1) * 128 + place.wn * 32 + (b & 1) * 16 + ((lane >> 5) << 3) + r;
       float* orow = Out + static_cast<int64_t>(n) * ldo;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int mi = m + (i >> 1) * 128 + (i & 1) * 32;
+      for (int i = 0; i < 8; i += 2) {
+        const int mi = m + (i >> 2) * 128 + (i & 3) * 16;
+        const float e0 = acc[i >> 2][i & 3][b >> 1][b & 1][r], e1 = acc[(i + 1) >> 2][(i + 1) & 3][b >> 1][b & 1][r];
+        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(e0), __float_as_uint(e1), false, false);
+        const float v0 = __uint_as_float(sw[0]), v1 = __uint_as_float(sw[1]);
         if (mi < M) {
-          // (every entry of Out belongs to one lane of one workgroup, so the hardware add, which does not wait for the
-          // old value to come back, gives the same sums as load - add - store, in the same order)
-          if (ACCUMULATE) unsafeAtomicAdd(orow + mi, acc[i >> 1][i & 1][b][r]);
-          else __builtin_nontemporal_store(acc[i >> 1][i & 1][b][r], orow + mi);
+          if (n < N) {
+            if (ACCUMULATE) unsafeAtomicAdd(orow + mi, v0);
+            else __builtin_nontemporal_store(v0, orow + mi);
+          }
+          if (n + 4 < N) {
+            if (ACCUMULATE) unsafeAtomicAdd(orow + 4 * ldo + mi, v1);
+            else __builtin_nontemporal_store(v1, orow + 4 * ldo + mi);
+          }
         }
       }
     }
 }
 
 // Operands with the contraction index as their row index (k-major).  A half tile of a step holds 64 k-rows of 128
-// consecutive m or n as they are in memory, 256 bytes per row, the four 64-byte blocks of a row permuted by bits 0 and 1 of
+// consecutive m or n as they are in memory, 256 bytes per row, the eight 32-byte blocks of a row permuted by bits 0, 1 and 3 of
 // the row.  A fragment of the matrix instruction (lane = one m, eight consecutive k) is two LDS transpose reads
 // (ds_read_b64_tr_b16): within a group of 16 lanes, lane 4 e + q supplies the address of four consecutive 16-bit entries and
 // lane i receives entry i % 4 of the lanes 4 e + i / 4, e = 0..3 (measured with an in-bounds probe); with lane 4 e + q
 // pointing at row k + e, entries m + 4 q .. 4 q + 3, lane i gets rows k .. k + 3 of entry m + i.  The 32 lanes of a pass read
-// 4 rows x 64 bytes, by the permutation in four different blocks: all 64 banks once.
+// 32 bytes of rows k .. k + 3 and k + 8 .. + 11, by the permutation in eight different blocks: all 64 banks once.
 //
 // Wavefront w fills k-rows 8 w .. + 7 of a half tile in two loads of four rows: lane i writes 16-byte piece i % 16 of row
-// i / 16 and so fetches piece (i % 16) ^ 4 (row % 4) of the 128 entries.
+// i / 16 and so fetches piece (i % 16) ^ 4 (row % 4) ^ 2 (row / 8 % 2) of the 128 entries.
 typedef short tn_i16x4 __attribute__((ext_vector_type(4)));
 typedef short tn_i16x8 __attribute__((ext_vector_type(8)));
 
 struct KMajorHalf {
   int krow, piece;             // row of the wavefront's first load (the second: + 4), 16-byte piece of the row
-  int a_off[2], b_off;
+  int a_off[4], b_off[2];
   __device__ __forceinline__ explicit KMajorHalf(const MatrixPlace& p) {
     const int lane = threadIdx.x & 63;
-    krow = 8 * (p.wm * 4 + p.wn) + (lane >> 4);
-    piece = (lane & 15) ^ ((lane >> 4) << 2);
-    // LDS -> fragment: lane 16 g + 4 e + q points at row 8 (g / 2) + e (+ 4 for the second read) of the 16 of a slice,
-    // entries 16 (g % 2) + 4 q .. + 3 of a 32-entry block
-    const int in_rows = (((lane >> 5) << 3) + ((lane >> 2) & 3)) * 256 + (((lane >> 4) & 1) << 5) + ((lane & 3) << 3);
-    a_off[0] = in_rows + (((2 * p.wm) ^ ((lane >> 2) & 3)) << 6);
-    a_off[1] = in_rows + (((2 * p.wm + 1) ^ ((lane >> 2) & 3)) << 6);
-    b_off = 2 * kHalfBytes + in_rows + ((p.wn ^ ((lane >> 2) & 3)) << 6);
+    const int wave = p.wm * 4 + p.wn;
+    krow = 8 * wave + (lane >> 4);
+    piece = (lane & 15) ^ ((lane >> 4) << 2) ^ ((wave & 1) << 1);
+    // lane 16 g + 4 e + q: row 8 g + e (+ 4) of the 32 of a slice, entries 4 q .. + 3 of a 16-entry block
+    const int g = lane >> 4, e = (lane >> 2) & 3, q = lane & 3;
+    const int rows = (8 * g + e) * 256 + q * 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a_off[i] = rows + (((4 * p.wm + i) * 32) ^ (e << 6) ^ ((g & 1) << 5));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b_off[j] = 2 * kHalfBytes + rows + (((2 * p.wn + j) * 32) ^ (e << 6) ^ ((g & 1) << 5));
   }
   __device__ __forceinline__ bf16x8 fragment(const unsigned char* p) const {
     typedef __attribute__((address_space(3))) tn_i16x4* lds_ptr;
@@ -126,10 +136,10 @@ struct KMajorHalf {
     return __builtin_bit_cast(bf16x8, both);
   }
   __device__ __forceinline__ bf16x8 a(const unsigned char* step, int half, int i, int ks) const {
-    return fragment(step + half * kHalfBytes + a_off[i] + ks * 4096);
+    return fragment(step + half * kHalfBytes + a_off[i] + ks * 8192);
   }
-  __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int ks) const {
-    return fragment(step + half * kHalfBytes + b_off + ks * 4096);
+  __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int j, int ks) const {
+    return fragment(step + half * kHalfBytes + b_off[j] + ks * 8192);
   }
 };
 
@@ -207,18 +217,18 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
     }
   };
 
-  f32x16 acc[2][2][2];
+  TileAcc acc;
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 32; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+    for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
   matrix_begin(mine, true, [&](int half, int ahead) { request(half, ahead, ahead); });
   for (int step = 0; step < n_steps; ++step) {
     const int cur = step & 1;
     const unsigned char* here = gemm_smem + cur * kStepBytes;
     matrix_step<true>(
         acc, [&](int half, int i, int ks) { return at_a.a(here, half, i, ks); },
-        [&](int half, int ks) { return at.b(here, half, ks); },
+        [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
         [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
   matrix_end(mine);
@@ -279,18 +289,18 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
                                              : static_cast<uint32_t>(k) * ldb2), dst + e * 1024);
     }
   };
-  f32x16 acc[2][2][2];
+  TileAcc acc;
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 32; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+    for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
   matrix_begin(mine, true, [&](int half, int ahead) { request(half, ahead, ahead); });
   for (int step = 0; step < n_steps; ++step) {
     const int cur = step & 1;
     const unsigned char* here = gemm_smem + cur * kStepBytes;
     matrix_step<true>(
         acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
-        [&](int half, int ks) { return at.b(here, half, ks); },
+        [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
         [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
   matrix_end(mine);
@@ -418,8 +428,6 @@ __global__ void __launch_bounds__(256) fopd_fill_zero_f32(float* out, int64_t ld
 // device: the launches cover the whole chunk, the contraction kernels read the count and leave out the rest.
 
 constexpr int kLiveScanThreads = 1024;
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // keep[i] = 1 if sample i has a positive weight under the scores given (float64 ones if fresh64 != NULL, else the
 // float32 ones), else 0.

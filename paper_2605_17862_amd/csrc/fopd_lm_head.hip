@@ -11,15 +11,16 @@
 //
 // Tiling.  A workgroup of eight wavefronts (2 along the vocabulary x 4 along the tokens, two per SIMD)
 // owns 256 tokens and walks a strip of the vocabulary in tiles of 256 rows; each wavefront holds a
-// 128 x 64 block of the tile as 4 x 2 accumulators of v_mfma_f32_32x32x16_bf16.  The vocabulary is the
-// M side of the instruction and the tokens the N side, because a lane of the 32 x 32 result holds 16
-// rows of ONE column: the reduction over the vocabulary then runs inside a lane and needs a single
-// cross-lane step (the two half-waves).  Both operands are k-contiguous in memory (hidden [T, d],
+// 128 x 64 block of the tile as 8 x 4 accumulators of v_mfma_f32_16x16x32_bf16.  The vocabulary is the
+// M side of the instruction and the tokens the N side, because a lane of the 16 x 16 result holds four
+// rows of ONE column: the reduction over the vocabulary then runs inside a lane and needs two
+// cross-lane steps at the very end (the four groups of 16 lanes).  Both operands are k-contiguous in memory (hidden [T, d],
 // weight [V, d]), so a lane's 8-element fragment is one 16-byte LDS read.
 //
-// The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Counters of the contraction
-// on MI355X: matrix cores 0.74 busy at the 1.68 GHz that the part holds under this load, 24 bytes per clock and compute unit
-// through the L1 where full MFMA rate on a 256 x 256 tile needs 32.
+// The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Bound by power: the matrix
+// cores are 0.75 (logits) to 0.80 (dL/dhidden) busy at the 1.5 GHz that the part then holds.  The 16 x 16 x 32 instruction has
+// the rate of the 32 x 32 x 16 one but goes over its accumulators half as often per product; log-probs of 16,384 rows x
+// 151,936, d = 4096: 15.8 - 16.0 -> 15.0 - 15.1 ms, of 2048 rows 1.98 -> 1.86 ms.
 
 #ifndef FOPD_LM_HEAD_HIP_
 #define FOPD_LM_HEAD_HIP_
@@ -45,7 +46,10 @@ constexpr int kLmLdsBytes = kLoopLdsBytes + 2 * kLmTile * 8;                // +
 constexpr float kLmNone = -__builtin_inff();              // "no value yet": the reference of an empty pair
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// A wavefront's block of the result tile: [A half][16-row block of its 64][B half][16-row block of its 32].
+typedef f32x4 TileAcc[2][4][2][2];
 
 namespace {
 
@@ -148,9 +152,9 @@ __host__ __device__ __forceinline__ TilePlace tile_place(unsigned group, unsigne
 // A workgroup of eight wavefronts multiplies a 256-row tile A by a 256-row tile B, 64 elements of the contraction index a
 // step.  Each tile is two halves of 128 rows (A0, A1, B0, B1: 16 KB each); the LDS holds two steps.  Wavefront (wm, wn),
 // wm = wave / 4, wn = wave % 4, owns rows 64 wm .. + 63 of both A halves and 32 wn .. + 31 of both B halves: four
-// products of 64 x 32, acc[A half][32-row block][B half], one a phase.
+// products of 64 x 32, acc[A half][.][B half][.], one a phase.
 //
-// A phase is two slots between barriers: LDS reads and requests of one half tile, then the eight matrix instructions of
+// A phase is two slots between barriers: LDS reads and requests of one half tile, then the sixteen matrix instructions of
 // a product.  The wavefronts of wm = 1 pass one barrier more at the start, so they are always one slot behind: on each
 // SIMD, which holds one wavefront of either kind, one multiplies while the other reads.  A half tile goes from memory
 // straight to the LDS (16 bytes a lane) as soon as both kinds have read what it replaces, five to seven phases before it
@@ -208,49 +212,55 @@ __device__ __forceinline__ void slot_end() {
 
 enum { kHalfA0 = 0, kHalfA1 = 1, kHalfB0 = 2, kHalfB1 = 3 };
 
-// B_FIRST: the B fragment is the matrix instruction's first operand (its 32 rows are then spread over the registers and the
-// A rows over the lanes), else the A fragment is.
+// B_FIRST: the B fragment is the matrix instruction's first operand (a lane then holds four B rows of one A row), else the A
+// fragment is.
 template <bool B_FIRST>
-__device__ __forceinline__ void multiply_phase(f32x16 (&acc)[2][2][2], int a, int b, const bf16x8 (&fa)[2][4],
-                                               const bf16x8 (&fb)[4]) {
+__device__ __forceinline__ void multiply_phase(TileAcc& acc, int a, int b, const bf16x8 (&fa)[4][2],
+                                               const bf16x8 (&fb)[2][2]) {
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
+  for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      acc[a][i][b] = B_FIRST ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks], fa[i][ks], acc[a][i][b], 0, 0, 0)
-                             : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[ks], acc[a][i][b], 0, 0, 0);
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[a][i][b][j] = B_FIRST ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[a][i][b][j], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[a][i][b][j], 0, 0, 0);
   __builtin_amdgcn_s_setprio(0);
 }
 
-// One step.  read_a(half, i, ks) / read_b(half, ks): the fragment of 32-row block i, elements 16 ks .. + 15, from this
+// One step.  read_a(half, i, ks) / read_b(half, j, ks): the fragment of 16-row block i / j, elements 32 ks .. + 31, from this
 // step's buffer.  request(half, ahead): the wavefront's two loads of that half tile of the step `ahead` steps later (any
 // readable step past the last one: never read).
 template <bool B_FIRST, typename ReadA, typename ReadB, typename Request>
-__device__ __forceinline__ void matrix_step(f32x16 (&acc)[2][2][2], ReadA read_a, ReadB read_b, Request request) {
-  bf16x8 fa[2][4], fb0[4], fb1[4];
+__device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB read_b, Request request) {
+  bf16x8 fa[4][2], fb0[2][2], fb1[2][2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) fb0[ks] = read_b(0, ks);
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int ks = 0; ks < 2; ++ks) fb0[j][ks] = read_b(0, j, ks);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) fa[i][ks] = read_a(0, i, ks);
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(0, i, ks);
   request(kHalfA1, 1);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
   multiply_phase<B_FIRST>(acc, 0, 0, fa, fb0);
   slot_end();
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) fb1[ks] = read_b(1, ks);
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) fb1[j][ks] = read_b(1, j, ks);
   request(kHalfB0, 2);
   asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
   slot_end();
   multiply_phase<B_FIRST>(acc, 0, 1, fa, fb1);
   slot_end();
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) fa[i][ks] = read_a(1, i, ks);
+    for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(1, i, ks);
   request(kHalfA0, 2);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
@@ -295,22 +305,22 @@ __device__ __forceinline__ void matrix_end(const MatrixPlace& place) {
 // and so fetches chunk (i % 8) ^ (row / 2 % 8).
 struct RowMajorHalf {
   int row, chunk[2];           // row of the wavefront's first load (the second: + 8), bytes of the chunk in the row
-  uint32_t a_off, b_off, xk[4];
+  uint32_t a_off, b_off, xk[2];
   __device__ __forceinline__ explicit RowMajorHalf(const MatrixPlace& p) {
     const int lane = threadIdx.x & 63;
     row = 16 * (p.wm * 4 + p.wn) + (lane >> 3);
     chunk[0] = ((lane & 7) ^ (lane >> 4)) * 16;
     chunk[1] = chunk[0] ^ 64;
-    a_off = (p.wm * 64 + (lane & 31)) * 128;
-    b_off = 2 * kHalfBytes + (p.wn * 32 + (lane & 31)) * 128;
+    a_off = (p.wm * 64 + (lane & 15)) * 128;
+    b_off = 2 * kHalfBytes + (p.wn * 32 + (lane & 15)) * 128;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) xk[ks] = ((2 * ks + (lane >> 5)) ^ ((lane >> 1) & 7)) << 4;
+    for (int ks = 0; ks < 2; ++ks) xk[ks] = ((4 * ks + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4;
   }
   __device__ __forceinline__ bf16x8 a(const unsigned char* step, int half, int i, int ks) const {
-    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + a_off + i * 4096 + xk[ks]);
+    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + a_off + i * 2048 + xk[ks]);
   }
-  __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int ks) const {
-    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + b_off + xk[ks]);
+  __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int j, int ks) const {
+    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + b_off + j * 2048 + xk[ks]);
   }
 };
 
@@ -385,42 +395,40 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
     }
   };
 
-  f32x16 acc[2][2][2];
-  float run_ref[2], run_sum[2];
+  TileAcc acc;
+  float run_ref[4], run_sum[4];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < 4; ++j) {
     run_ref[j] = kLmNone;
     run_sum[j] = 0.f;
   }
 
-  // One finished tile.  Result register r of block i = 2 (half of the tile) + 32-row block, token half j, is vocabulary
-  // row 128 (i / 2) + 32 (i % 2) + 8 (r / 4) + 4 (lane / 32) + r % 4 from the wavefront's first, token
-  // 128 j + 32 wn + lane % 32.  RAGGED (the last vocabulary tile only): rows at or past V count as "no value".
+  // One finished tile.  Result register r of block i = 4 (half of the tile) + 16-row block, token block j = 2 (half) + block, is
+  // vocabulary row 128 (i / 4) + 16 (i % 4) + 4 (lane / 16) + r from the wavefront's first, token 128 (j / 2) + 32 wn +
+  // 16 (j % 2) + lane % 16.  RAGGED (the last vocabulary tile only): rows at or past V count as "no value".
   auto epilogue = [&](auto ragged_tag, int vlane) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < 4; ++j) {
       auto value = [&](int i, int r) -> float {
-        if (RAGGED && vlane + (i >> 1) * 128 + (i & 1) * 32 + ((r >> 2) << 3) + (r & 3) >= V) return kLmNone;
-        return acc[i >> 1][i & 1][j][r];
+        if (RAGGED && vlane + (i >> 2) * 128 + (i & 3) * 16 + r >= V) return kLmNone;
+        return acc[i >> 2][i & 3][j >> 1][j & 1][r];
       };
       float mx = run_ref[j];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, value(i, r));
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, value(i, r));
       // a lane that has seen no value yet (only in a tile that hangs over the vocabulary's end) keeps
       // a finite reference, so that every term below is exp2(-inf) = 0 rather than a NaN
       const float mref = (mx == kLmNone) ? 0.f : mx * kLog2e;
       const float carried = run_sum[j] * fast_exp2(fmaf(run_ref[j], kLog2e, -mref));
       __builtin_amdgcn_sched_barrier(0);
-      float part[4];                                   // four short chains, added as a tree
+      float part[4] = {0.f, 0.f, 0.f, 0.f};            // four short chains, added as a tree
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        part[i] = 0.f;
+      for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) part[i] += fast_exp2(fmaf(value(i, r), kLog2e, -mref));
-      }
+        for (int r = 0; r < 4; ++r) part[i & 3] += fast_exp2(fmaf(value(i, r), kLog2e, -mref));
       run_ref[j] = mx;
       run_sum[j] = carried + ((part[0] + part[1]) + (part[2] + part[3]));
       __builtin_amdgcn_sched_barrier(0);
@@ -435,33 +443,35 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
   int step = 0;
   for (int vt = vt_begin; vt < vt_end; ++vt) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 32; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
     for (int kt = 0; kt < nkp; ++kt, ++step) {
       const int cur = step & 1;
       const unsigned char* here = lm_smem + cur * kStepBytes;
       matrix_step<false>(
           acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
-          [&](int half, int ks) { return at.b(here, half, ks); },
+          [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
           [&](int half, int ahead) { request(half, vt_at[ahead - 1], k_at[ahead - 1], ahead == 1 ? cur ^ 1 : cur); });
       advance();
     }
-    const int vlane = vt * kLmTile + mine.wm * 64 + ((lane >> 5) << 2);
+    const int vlane = vt * kLmTile + mine.wm * 64 + ((lane >> 4) << 2);
     if (vt * kLmTile + kLmTile > V) epilogue(std::true_type(), vlane);
     else epilogue(std::false_type(), vlane);
   }
   matrix_end(mine);
 
-  // half-waves, then the two wavefronts that share these tokens, then one pair per token and strip
+  // the four groups of 16 lanes, then the two wavefronts that share these tokens, then one pair per token and strip
   float2* ex = reinterpret_cast<float2*>(lm_smem + kLoopLdsBytes);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < 4; ++j) {
     float m = run_ref[j], s = run_sum[j];
     const float m2 = __shfl_xor(m, 32), s2 = __shfl_xor(s, 32);
-    if (lane < 32) {
-      lm_merge(m, s, m2, s2);
-      ex[mine.wm * kLmTile + j * 128 + mine.wn * 32 + lane] = make_float2(m, s);
+    lm_merge(m, s, m2, s2);
+    const float m3 = __shfl_xor(m, 16), s3 = __shfl_xor(s, 16);
+    if (lane < 16) {
+      lm_merge(m, s, m3, s3);
+      ex[mine.wm * kLmTile + (j >> 1) * 128 + mine.wn * 32 + (j & 1) * 16 + lane] = make_float2(m, s);
     }
   }
   __syncthreads();
