@@ -93,9 +93,9 @@ struct LmLossWorkspace {
   size_t token_loss = 0, c2 = 0, g_rest = 0, row_coef = 0, p_list = 0, h_list = 0;
   // the chunk's live rows moved to the front: prefix counts, row map, live count, sample offsets, then the dense
   // copies of the per-row inputs and outputs, of the hidden rows and of their gradient
-  // and, for the gradient side, the same among the live rows for those that have a gradient row
+  // and, for the gradient side, the same among the live rows for those that have a gradient row, their hidden rows transposed
   size_t ex = 0, row_map = 0, n_live = 0, cu_c = 0, tok_c = 0, mask_c = 0, behav_c = 0, teach_c = 0, stale_c = 0,
-         logp_c = 0, lse_c = 0, tl_c = 0, ids_c = 0, llp_c = 0, h_c = 0, dh_c = 0, grad_ex = 0, h_g = 0, keep = 0;
+         logp_c = 0, lse_c = 0, tl_c = 0, ids_c = 0, llp_c = 0, h_c = 0, dh_c = 0, grad_ex = 0, h_t = 0, keep = 0;
   int64_t ldz = 0, r_pad = 0, n_chunks = 0;
   // dL/dhidden of more rows than this reads a transposed copy of the projection matrix.  The copy takes 450 us (151,936 x
   // 4096) whatever the rows; without it the contraction itself is slower by about 0.1 us a row (its A fragments leave the
@@ -154,7 +154,7 @@ struct LmLossWorkspace {
     h_c = Workspace::take(off, r * dd * 2);
     dh_c = Workspace::take(off, r * dd * sizeof(float));
     grad_ex = Workspace::take(off, (r + 1) * sizeof(int32_t));
-    h_g = Workspace::take(off, r * dd * 2);
+    h_t = Workspace::take(off, r * dd * 2);
     keep = Workspace::take(off, b * sizeof(int32_t));
     total = off;
   }
@@ -1276,17 +1276,17 @@ static fopd_status launch_gemm(bool a_k_major, const __bf16* Am, int64_t lda, in
   return launched();
 }
 
-// Out[n, m] (+)= sum_{k < K} Bk[k, n] Ak[k, m] on `s`; Ak has rows_a readable rows, Bk has K and zeros where a row
-// is not to count.  k_live != NULL: a device int, the number of leading rows that count (K is cut to it, rounded up to 64).
-static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Ak, int64_t lda, int64_t M, int64_t rows_a,
-                                  const __bf16* Bk, int64_t ldb, int64_t N, int64_t K, float* Out, int64_t ldo, int slot,
-                                  hipStream_t s, const int* k_live = nullptr) {
+// Out[n, m] (+)= sum_{k < K} Bk[k, n] Am[m, k] on `s`.  k_live != NULL: a device int, the number of leading entries of the
+// contraction index that count (K is cut to it, rounded up to 64).
+static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Am, int64_t lda, int64_t M, const __bf16* Bk, int64_t ldb,
+                                  int64_t N, int64_t K, float* Out, int64_t ldo, int slot, hipStream_t s,
+                                  const int* k_live = nullptr) {
   if (M <= 0 || N <= 0) return FOPD_OK;
-  if (K <= 0 || K % kLmK != 0 || rows_a <= K - kLmK || rows_a > K || M > 2147483647LL || N > 2147483647LL ||
-      K > 2147483647LL || M % 8 != 0 || lda % 8 != 0 || ldb % 8 != 0 || lda < M || ldb < (N + 7) / 8 * 8)
+  if (K <= 0 || K % kLmK != 0 || M > 2147483647LL || N > 2147483647LL || K > 2147483647LL || lda % 8 != 0 ||
+      ldb % 8 != 0 || lda < K || ldb < (N + 7) / 8 * 8)
     return FOPD_ESHAPE;
-  // byte offsets inside the 64 rows of a step are 32-bit
-  if (kLmK * lda * 2 >= 2147483648LL || kLmK * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
+  // byte offsets inside a 256-row tile of Am and inside the 64 rows of a step of Bk are 32-bit
+  if (kGemmTile * lda * 2 >= 2147483648LL || kLmK * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
   static bool allowed[2][kMaxDevices] = {};
   const void* kern = accumulate ? reinterpret_cast<const void*>(fopd_gemm_tn<true>)
                                 : reinterpret_cast<const void*>(fopd_gemm_tn<false>);
@@ -1298,36 +1298,33 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Ak, int64_t lda
   const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
   if (accumulate)
-    fopd_gemm_tn<true><<<grid, block, kLoopLdsBytes, s>>>(Ak, lda, static_cast<int>(M), static_cast<int>(rows_a), Bk, ldb,
+    fopd_gemm_tn<true><<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bk, ldb,
                                                        static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m,
                                                        tiles_n, k_live);
   else
-    fopd_gemm_tn<false><<<grid, block, kLoopLdsBytes, s>>>(Ak, lda, static_cast<int>(M), static_cast<int>(rows_a), Bk, ldb,
+    fopd_gemm_tn<false><<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bk, ldb,
                                                         static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m,
                                                         tiles_n, k_live);
   return launched();
 }
 
+// row_map != NULL: only the rows row_map[0 .. *n_rows - 1] of `in`, densely (fopd_transpose_bf16, GATHER).
 static fopd_status launch_transpose(const void* in, int64_t ld_in, int64_t rows, int64_t cols, void* out, int64_t ld_out,
-                                    int64_t rows_pad, hipStream_t s) {
+                                    int64_t rows_pad, hipStream_t s, const int* row_map = nullptr,
+                                    const int* n_rows = nullptr) {
   if (rows_pad <= 0 || cols <= 0) return FOPD_OK;
-  const dim3 grid(static_cast<unsigned>((rows_pad + kTrTile - 1) / kTrTile),
-                  static_cast<unsigned>((cols + kTrTile - 1) / kTrTile));
-  if (grid.y > 65535u) {      // the second grid dimension is short: walk it in slabs
-    for (int64_t c0 = 0; c0 < cols; c0 += 65535LL * kTrTile) {
-      const int64_t cn = (cols - c0 < 65535LL * kTrTile) ? cols - c0 : 65535LL * kTrTile;
-      const dim3 g2(grid.x, static_cast<unsigned>((cn + kTrTile - 1) / kTrTile));
-      fopd_transpose_bf16<<<g2, 256, 0, s>>>(static_cast<const uint16_t*>(in) + c0, ld_in, static_cast<int>(rows),
-                                             static_cast<int>(cn), static_cast<uint16_t*>(out) + c0 * ld_out, ld_out,
-                                             static_cast<int>(rows_pad));
-      if (launched() != FOPD_OK) return FOPD_EHIP;
-    }
-    return FOPD_OK;
+  auto kern = row_map != nullptr ? fopd_transpose_bf16<true> : fopd_transpose_bf16<false>;
+  // (the second grid dimension is short: walked in slabs)
+  for (int64_t c0 = 0; c0 < cols; c0 += 65535LL * kTrTile) {
+    const int64_t cn = std::min<int64_t>(cols - c0, 65535LL * kTrTile);
+    const dim3 grid(static_cast<unsigned>((rows_pad + kTrTile - 1) / kTrTile),
+                    static_cast<unsigned>((cn + kTrTile - 1) / kTrTile));
+    kern<<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(in) + c0, ld_in, static_cast<int>(rows), static_cast<int>(cn),
+                              static_cast<uint16_t*>(out) + c0 * ld_out, ld_out, static_cast<int>(rows_pad), row_map,
+                              n_rows);
+    if (launched() != FOPD_OK) return FOPD_EHIP;
   }
-  fopd_transpose_bf16<<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(in), ld_in, static_cast<int>(rows),
-                                           static_cast<int>(cols), static_cast<uint16_t*>(out), ld_out,
-                                           static_cast<int>(rows_pad));
-  return launched();
+  return FOPD_OK;
 }
 
 // The loss pass through the projection.  `listed` == nullptr: the sampled-token loss against teacher_logp
@@ -1638,21 +1635,18 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
       continue;
     }
     const int32_t* gex = nullptr;        // the rows that have a gradient row, counted among the chunk's (live) rows
-    const __bf16* Hg = Hc;               // their hidden rows
-    int64_t rows_hg = R;
+    __bf16* Ht = at<__bf16>(workspace, lay.h_t);         // their hidden rows, transposed
+    int32_t* grad_map = at<int32_t>(workspace, lay.behav_c);     // (the coefficients were the last to read those)
     if (compact) {
       fopd_live_scan<<<1, kLiveScanThreads, 0, s>>>(nullptr, coef, (listed != nullptr) ? c2 : nullptr,
-                                                    static_cast<int>(R), nullptr, -1, 0, grad_ex, nullptr, n_grad,
+                                                    static_cast<int>(R), nullptr, -1, 0, grad_ex, grad_map, n_grad,
                                                     nullptr, nullptr);
       if ((st = launched()) != FOPD_OK) return st;
-      fopd_grad_gather<<<static_cast<unsigned>(R), 256, 0, s>>>(grad_ex, reinterpret_cast<const uint16_t*>(Hc), ldhc,
-                                                               static_cast<int>(d), at<uint16_t>(workspace, lay.h_g));
-      if ((st = launched()) != FOPD_OK) return st;
       gex = grad_ex;
-      Hg = at<__bf16>(workspace, lay.h_g);
-      rows_hg = Rp;
       live = n_grad;
     }
+    if (head_grad && (st = launch_transpose(Hc, ldhc, R, d, Ht, Rp, Rp, s, compact ? grad_map : nullptr, n_grad)) != FOPD_OK)
+      return st;
     {
       ScopedTimer timer(1, s);
       fopd_k4_grad_wide<<<static_cast<unsigned>(R), kGradThreads, 0, s>>>(
@@ -1669,8 +1663,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     }
     // the contraction over rows reads whole steps of 64 rows: zeros behind the last gradient row
     if (compact) {
-      fopd_grad_tail_zero<<<64, 256, 0, s>>>(n_grad, reinterpret_cast<uint16_t*>(G), ldz,
-                                             at<uint16_t>(workspace, lay.h_g), static_cast<int>(d));
+      fopd_grad_tail_zero<<<64, 256, 0, s>>>(n_grad, reinterpret_cast<uint16_t*>(G), ldz);
       if ((st = launched()) != FOPD_OK) return st;
     } else if (Rp > R) {
       fopd_fill_zero_f32<<<static_cast<unsigned>(Rp - R), 256, 0, s>>>(reinterpret_cast<float*>(G + R * ldz), ldz / 2,
@@ -1692,11 +1685,9 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
                                                              lddh);
       if ((st = launched()) != FOPD_OK) return st;
     }
-    // dL/dweight: vocabulary x hidden, contraction over the chunk's rows, both operands as they are stored
+    // dL/dweight: vocabulary x hidden, contraction over the chunk's rows, the gradient rows as they are stored
     const bool acc = (ci > 0) || (accumulate_dweight != 0);
-    if (head_grad &&
-        (st = launch_gemm_tn(acc, Hg, compact ? d : ldhc, d, rows_hg, G, ldz, V, Rp, dweight, lddw, 6, s, live)) != FOPD_OK)
-      return st;
+    if (head_grad && (st = launch_gemm_tn(acc, Ht, Rp, d, G, ldz, V, Rp, dweight, lddw, 6, s, live)) != FOPD_OK) return st;
     if ((st = scatter()) != FOPD_OK) return st;
     ++ci;
   }

@@ -3,7 +3,7 @@
 //
 //   fopd_gemm_nt            Out[n, m] = sum_k Bn[n, k] * Am[m, k]         bf16 in, fp32 accumulate, fp32 out; Am as it
 //                                                                        is written or stored [k, m]
-//   fopd_gemm_tn            Out[n, m] (+)= sum_k Bk[k, n] * Ak[k, m]     the same with both operands k-major
+//   fopd_gemm_tn            Out[n, m] (+)= sum_k Bk[k, n] * Am[m, k]     the same with B k-major
 //   fopd_transpose_bf16     out[c, r] = in[r, c], zero-padded along r    (brings an operand into k-contiguous form)
 //   fopd_k4_grad_wide       gradient rows from fp32 logits to bf16        c_t (softmax(z_t) - onehot)
 //
@@ -11,7 +11,8 @@
 //   logits      Z[R, V]   = H[R, d]  . W[V, d]^T          nt: n = row, m = vocabulary entry, k = hidden element
 //   dL/dhidden  dH[R, d]  = dZ[R, V] . W[V, d]            nt: n = row, m = hidden element, k = vocabulary entry; W as it
 //                                                         is (k-major), or for many rows W^T, formed once per call
-//   dL/dweight  dW[V, d] += dZ[R, V]^T . H[R, d]          tn: n = vocabulary entry, m = hidden element, k = row
+//   dL/dweight  dW[V, d] += dZ[R, V]^T . H[R, d]          tn: n = vocabulary entry, m = hidden element, k = row; H^T is
+//                                                         formed once per chunk
 //
 // Tiling and loop are those of the projection kernel fused with the log-sum-exp (fopd_lm_head.hip, matrix_step): a
 // workgroup of eight wavefronts owns a 256 x 256 tile of the result.  The n-side fragment is the instruction's first
@@ -235,27 +236,29 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   store_tile<false>(acc, mine, m0, n0, M, N, Out, ldo);
 }
 
-// The same contraction with both operands k-major (the contraction index is the row index of both matrices):
+// The same contraction with B k-major (the contraction index is its row index):
 //
-//   fopd_gemm_tn            Out[n, m] (+)= sum_{k < K} Bk[k, n] * Ak[k, m]
+//   fopd_gemm_tn            Out[n, m] (+)= sum_{k < K} Bk[k, n] * Am[m, k]
 //
-// which is the weight gradient as its operands are stored, dW[v, j] += sum_t dZ[t, v] H[t, j], without a transposed
-// copy of either.  Loop and result stores are those of fopd_gemm_nt; both operands leave the LDS as KMajorHalf says.
+// which is the weight gradient, dW[v, j] += sum_t dZ[t, v] H[t, j], with the gradient rows as they are stored and the hidden
+// rows transposed (fopd_transpose_bf16: 55 us for 16,384 rows of 4096).  Loop and result stores are those of fopd_gemm_nt;
+// B leaves the LDS as KMajorHalf says.  With the hidden rows k-major too, two thirds of the fragments take two transposing
+// reads each, 48 LDS reads a step instead of 32, and the reading slots are longer than the multiplying ones (matrix cores
+// 0.61 busy at 1.9 GHz): 151,936 x 4096 from 512 / 2048 / 16,384 rows 970 / 2455 / 16,300 us, so 950 / 2285 / 14,720.
 //
-// K must be a positive multiple of 64.  Ak has rows_a (K - 64 < rows_a <= K) readable rows; rows rows_a .. K - 1 are
-// taken from row rows_a - 1, so the caller's Bk must hold zeros in every row that is not to count (Bk has K
-// readable rows).  M and N need not be multiples of the tile: 16-byte pieces past entry M - 1 / N - 1 of a row are
-// clamped (re-read) and their results discarded; M % 8 == 0, lda % 8 == 0, ldb % 8 == 0, and every row of Bk is
-// readable up to N rounded up to 8 (ldb is at least that).  Byte offsets inside 64 rows must fit 32 bits.
+// K must be a positive multiple of 64, and Am and Bk finite up to it; what is not to count is zero in one of them.  M and N need
+// not be multiples of the tile: rows of Am past M - 1 and 16-byte pieces past entry N - 1 of a row of Bk are clamped (re-read)
+// and their results discarded; lda % 8 == 0, ldb % 8 == 0, and every row of Bk is readable up to N rounded up to 8 (ldb is at
+// least that).  Byte offsets inside 256 rows of Am and inside 64 of Bk must fit 32 bits.
 template <bool ACCUMULATE>
 __global__ void __launch_bounds__(kGemmThreads)
-fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, const __bf16* __restrict__ Bk, int64_t ldb,
+fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __restrict__ Bk, int64_t ldb,
              int N, int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
              const int* __restrict__ k_live) {
   extern __shared__ __align__(16) unsigned char gemm_smem[];
   if (k_live != nullptr) {
-    // only the first *k_live rows of the operands count (a device-side count; the rows after them, up to the next
-    // multiple of 64, hold zeros in Bk and finite values in Ak)
+    // only the first *k_live entries of the contraction index count (a device-side count; up to the next multiple of 64
+    // both operands hold zeros behind them)
     const int live = *k_live;
     if (ACCUMULATE && live <= 0) return;
     K = min(K, max(64, (live + 63) & ~63));
@@ -269,25 +272,28 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
   const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
 
   const MatrixPlace mine = matrix_place(gemm_smem);
+  const RowMajorHalf at_a(mine);
   const KMajorHalf at(mine);
-  uint32_t col[4];                                         // byte offset in a row, by half tile
-#pragma unroll
-  for (int h = 0; h < 4; ++h)
-    col[h] = 16u * static_cast<uint32_t>(h < 2 ? min((m0 >> 3) + 16 * h + at.piece, (M >> 3) - 1)
-                                               : min((n0 >> 3) + 16 * (h - 2) + at.piece, ((N + 7) >> 3) - 1));
+  const char* Ab = reinterpret_cast<const char*>(Am) + static_cast<int64_t>(m0) * lda * 2;
   const uint32_t lda2 = static_cast<uint32_t>(lda) * 2u, ldb2 = static_cast<uint32_t>(ldb) * 2u;
+  uint32_t a_at[2][2], col[2];                             // byte offsets: A by half tile and load, B inside a row by half tile
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      a_at[h][e] = static_cast<uint32_t>(min(h * 128 + at_a.row + 8 * e, M - 1 - m0)) * lda2 + at_a.chunk[e];
+    col[h] = 16u * static_cast<uint32_t>(min((n0 >> 3) + 16 * h + at.piece, ((N + 7) >> 3) - 1));
+  }
   const int n_steps = K / kLmK;
   auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
     const int k0 = min(step, n_steps - 1) * kLmK;
-    const char* src = half < 2 ? reinterpret_cast<const char*>(Ak) + static_cast<int64_t>(k0) * lda * 2
+    const char* src = half < 2 ? Ab + 2 * static_cast<int64_t>(k0)
                                : reinterpret_cast<const char*>(Bk) + static_cast<int64_t>(k0) * ldb * 2;
     const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int k = at.krow + 4 * e;
-      load_to_lds(src, col[half] + (half < 2 ? static_cast<uint32_t>(min(k, rows_a - 1 - k0)) * lda2
-                                             : static_cast<uint32_t>(k) * ldb2), dst + e * 1024);
-    }
+    for (int e = 0; e < 2; ++e)
+      load_to_lds(src, half < 2 ? a_at[half & 1][e] : col[half & 1] + static_cast<uint32_t>(at.krow + 4 * e) * ldb2,
+                  dst + e * 1024);
   };
   TileAcc acc;
 #pragma unroll
@@ -299,7 +305,7 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
     const int cur = step & 1;
     const unsigned char* here = gemm_smem + cur * kStepBytes;
     matrix_step<true>(
-        acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
+        acc, [&](int half, int i, int ks) { return at_a.a(here, half, i, ks); },
         [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
         [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
   }
@@ -307,7 +313,9 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
   store_tile<ACCUMULATE>(acc, mine, m0, n0, M, N, Out, ldo);
 }
 
-// out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  128 x 128 tiles through the LDS;
+// out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  GATHER: out[c, r] = in[row_map[r], c] for
+// r < n_rows[0] <= rows instead, zeros from there up to the next multiple of 64 (at least 64), and nothing is written behind
+// that (what fopd_gemm_tn reads of the hidden rows that have a gradient).  128 x 128 tiles through the LDS;
 // grid (ceil(rows_pad / 128), ceil(cols / 128)), 256 lanes.  cols, rows_pad, ld_in and ld_out multiples of 8, both
 // matrices 16-byte aligned.  Bound by HBM (one read, one write): both sides move 16 bytes a lane in whole 128-byte lines.
 // The LDS pitch of 65 words spreads the writes (four rows of sixteen lanes, four words apart) and the reads (rows eight
@@ -315,18 +323,27 @@ fopd_gemm_tn(const __bf16* __restrict__ Ak, int64_t lda, int M, int rows_a, cons
 constexpr int kTrTile = 128;
 constexpr int kTrPitch = 65;              // words
 
+template <bool GATHER>
 __global__ void __launch_bounds__(256)
 fopd_transpose_bf16(const uint16_t* __restrict__ in, int64_t ld_in, int rows, int cols, uint16_t* __restrict__ out,
-                    int64_t ld_out, int rows_pad) {
+                    int64_t ld_out, int rows_pad, const int* __restrict__ row_map, const int* __restrict__ n_rows) {
   __shared__ uint32_t tile[kTrTile * kTrPitch];
+  if constexpr (GATHER) {
+    rows = min(rows, n_rows[0]);
+    rows_pad = min(rows_pad, max(64, (rows + 63) & ~63));
+  }
   const int r0 = blockIdx.x * kTrTile, c0 = blockIdx.y * kTrTile;
   const int tid = threadIdx.x;
+  if (GATHER && r0 >= rows_pad) return;
   u32x4 q[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) {           // sixteen rows of sixteen 16-byte pieces at a time
     const int r = r0 + 16 * u + (tid >> 4), c = c0 + 8 * (tid & 15);
     q[u] = u32x4{0u, 0u, 0u, 0u};
-    if (r < rows && c < cols) q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + static_cast<int64_t>(r) * ld_in + c));
+    if (r < rows && c < cols) {
+      const int64_t from = GATHER ? row_map[r] : r;
+      q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + from * ld_in + c));
+    }
   }
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
@@ -538,33 +555,16 @@ fopd_live_gather(const int* __restrict__ row_map, const int* __restrict__ n_live
   for (int v = tid; v < d / 8; v += 256) dst[v] = live ? src[v] : zero;
 }
 
-// The hidden rows of the compact rows that have a gradient (grad_ex[c + 1] > grad_ex[c]), densely: row c of hidden_c
-// to row grad_ex[c] of hidden_g (d entries per row, d % 8 == 0).  Grid: one workgroup per compact row.
+// Zeros behind the gradient rows, up to the next multiple of 64 (at least 64 rows in all): the contraction over rows reads that
+// far.  Row n_grad[0] + blockIdx.x of G (ldg entries, ldg % 8 == 0); grid: 64 workgroups.
 __global__ void __launch_bounds__(256)
-fopd_grad_gather(const int* __restrict__ grad_ex, const uint16_t* __restrict__ hidden_c, int64_t ldh, int d,
-                 uint16_t* __restrict__ hidden_g) {
-  const int64_t c = blockIdx.x;
-  const int g = grad_ex[c];
-  if (grad_ex[c + 1] == g) return;
-  const u32x4* src = reinterpret_cast<const u32x4*>(hidden_c + c * ldh);
-  u32x4* dst = reinterpret_cast<u32x4*>(hidden_g + static_cast<int64_t>(g) * d);
-  for (int v = threadIdx.x; v < d / 8; v += 256) dst[v] = src[v];
-}
-
-// Zeros behind the rows that have a gradient, up to the next multiple of 64 (at least 64 rows in all): the
-// contraction over rows reads that far.  Row n_grad[0] + blockIdx.x of G (ldg entries, ldg % 8 == 0) and of hidden_g
-// (d entries); grid: 64 workgroups.
-__global__ void __launch_bounds__(256)
-fopd_grad_tail_zero(const int* __restrict__ n_grad, uint16_t* __restrict__ G, int64_t ldg,
-                    uint16_t* __restrict__ hidden_g, int d) {
+fopd_grad_tail_zero(const int* __restrict__ n_grad, uint16_t* __restrict__ G, int64_t ldg) {
   const int n = n_grad[0];
   const int64_t row = static_cast<int64_t>(n) + blockIdx.x;
   if (row >= max(64, (n + 63) & ~63)) return;
   const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
   u32x4* g = reinterpret_cast<u32x4*>(G + row * ldg);
   for (int v = threadIdx.x; v < static_cast<int>(ldg / 8); v += 256) g[v] = zero;
-  u32x4* h = reinterpret_cast<u32x4*>(hidden_g + row * d);
-  for (int v = threadIdx.x; v < d / 8; v += 256) h[v] = zero;
 }
 
 // dst[0 .. d) = sum over k < splits, in that order, of src[k split_stride ..], by 256 lanes.  src 16-byte aligned,

@@ -112,14 +112,14 @@ int main(int argc, char** argv) {
   if (time_groups("fopd_gemm_nt", 4, 1, flops, e0, e1, nt)) return 1;
   if (time_groups("fopd_gemm_nt", groups, 20, flops, e0, e1, nt)) return 1;
   if (N >= 8192 && M == 151936 && K == 4096 && pad == 0) {
-    // the weight gradient's shape with both operands k-major, in the same buffers: Out[151936, 4096] = sum over 4096
-    // rows of Bk[4096, 151936] (all of buffer A) and Ak[4096, 4096] (half of the first 8192 rows of buffer B)
+    // the weight gradient's shape, B k-major, in the same buffers: Out[151936, 4096] = sum over 4096 entries of
+    // Bk[4096, 151936] (all of buffer A) and Am[4096, 4096] (half of the first 8192 rows of buffer B)
     const int tm = 4096 / kGemmTile, tn = (151936 + kGemmTile - 1) / kGemmTile;
     const unsigned grid_tn = static_cast<unsigned>((tile_groups(tm, tn) + 7) / 8 * 256);
     CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fopd_gemm_tn<false>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kLoopLdsBytes));
     if (time_groups("fopd_gemm_tn, Out[151936, 4096], K = 4096", 4, 1, 2.0 * 4096 * 151936.0 * 4096, e0, e1, [&]() {
-          fopd_gemm_tn<false><<<grid_tn, kGemmThreads, kLoopLdsBytes>>>(B, 4096, 4096, 4096, A, 151936, 151936, 4096, out,
+          fopd_gemm_tn<false><<<grid_tn, kGemmThreads, kLoopLdsBytes>>>(B, 4096, 4096, A, 151936, 151936, 4096, out,
                                                                        4096, tm, tn, nullptr);
         }))
       return 1;
