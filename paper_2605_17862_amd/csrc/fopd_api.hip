@@ -1246,6 +1246,11 @@ size_t fopd_lm_head_loss_workspace_bytes(int64_t T, int64_t V, int64_t d, int32_
   return LmLossWorkspace(T, V, d, B, rows_chunk).total;
 }
 
+// Workgroups of a contraction: walking ones (kWalkSteps), else one for every place of every group of tiles, rounds * 256.
+inline unsigned gemm_grid(int64_t rounds, int64_t steps) {
+  return steps <= kWalkSteps ? kGemmGrid : static_cast<unsigned>(rounds * 256);
+}
+
 // Out[n, m] = sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  a_k_major: Am is stored [k, m] and
 // has rows_a readable rows (Bn holds zeros in the columns past them); else it has M rows and rows_a is not used.  n_live !=
 // NULL: a device int, the number of leading rows of Bn that count (the tiles past them are not computed).  splits > 1: that
@@ -1268,7 +1273,7 @@ static fopd_status launch_gemm(bool a_k_major, const __bf16* Am, int64_t lda, in
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (splits * tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
-  const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
+  const dim3 grid(gemm_grid(rounds, K / kLmK / splits)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
   kern<<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), static_cast<int>(rows_a), Bn, ldb,
                                           static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live,
@@ -1295,7 +1300,7 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Am, int64_t lda
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
-  const dim3 grid(static_cast<unsigned>(rounds * 256)), block(kGemmThreads);
+  const dim3 grid(gemm_grid(rounds, K / kLmK)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
   if (accumulate)
     fopd_gemm_tn<true><<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bk, ldb,

@@ -69,9 +69,9 @@ inline int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
 // bytes to each of 16 rows four times, 1251 / 2829.  The results are not read by this kernel and are far larger than the L2,
 // whose lines the operand tiles need: non-temporal stores, loss and gradients of 16,384 rows 52.7 -> 51.8 ms, of 4096 rows
 // 13.42 -> 13.33 ms, fewer rows unchanged (with the 32 x 32 x 16 instruction).
-template <bool ACCUMULATE>
-__device__ __forceinline__ void store_tile(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M,
-                                           int N, float* __restrict__ Out, int64_t ldo) {
+template <bool ACCUMULATE, bool WHOLE>
+__device__ __forceinline__ void store_block(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M,
+                                            int N, float* __restrict__ Out, int64_t ldo) {
   const int lane = threadIdx.x & 63;
   const int m = m0 + place.wm * 64 + (lane & 31);
 #pragma unroll
@@ -85,20 +85,233 @@ __device__ __forceinline__ void store_tile(const TileAcc& acc, const MatrixPlace
         const int mi = m + (i >> 2) * 128 + (i & 3) * 16;
         const float e0 = acc[i >> 2][i & 3][b >> 1][b & 1][r], e1 = acc[(i + 1) >> 2][(i + 1) & 3][b >> 1][b & 1][r];
         const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(e0), __float_as_uint(e1), false, false);
-        const float v0 = __uint_as_float(sw[0]), v1 = __uint_as_float(sw[1]);
-        if (mi < M) {
-          if (n < N) {
-            if (ACCUMULATE) unsafeAtomicAdd(orow + mi, v0);
-            else __builtin_nontemporal_store(v0, orow + mi);
-          }
-          if (n + 4 < N) {
-            if (ACCUMULATE) unsafeAtomicAdd(orow + 4 * ldo + mi, v1);
-            else __builtin_nontemporal_store(v1, orow + 4 * ldo + mi);
+        const float v[2] = {__uint_as_float(sw[0]), __uint_as_float(sw[1])};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          float* to = orow + 4 * h * ldo + mi;
+          if (WHOLE || (mi < M && n + 4 * h < N)) {
+            // (every entry of Out belongs to one lane of one workgroup, so the hardware add, which does not wait for the
+            // old value to come back, gives the same sums as load - add - store, in the same order)
+            if (ACCUMULATE) unsafeAtomicAdd(to, v[h]);
+            else __builtin_nontemporal_store(v[h], to);
           }
         }
       }
     }
 }
+
+// A whole tile: 128 stores a wavefront, none waited for (true); else they are waited for, their number being unknown.
+template <bool ACCUMULATE>
+__device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M, int N,
+                                           float* __restrict__ Out, int64_t ldo) {
+  if (m0 + kGemmTile <= M && n0 + kGemmTile <= N) {
+    store_block<ACCUMULATE, true>(acc, place, m0, n0, M, N, Out, ldo);
+    return true;
+  }
+  store_block<ACCUMULATE, false>(acc, place, m0, n0, M, N, Out, ldo);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  return false;
+}
+
+// A tile of the result and the steps of the contraction index that go into it: all of them, or those of one run (split).
+struct GemmTile {
+  int m0, n0, first, steps, split;
+};
+
+// The tiles of a workgroup.  Launched with a workgroup for every place of every group (tile_place), each has one tile or none.
+// Launched with kGemmGrid, one a compute unit, workgroup 8 s + x is the s-th of XCD x and takes every 32nd tile of that XCD's
+// groups x, x + 8, .. in their order, only tiles that exist being counted.  The next tile's first steps are then requested
+// before this one's results are stored, and no workgroup waits for its place: workgroups are started in the order of their
+// ids, which keeps the compute units at the same point of their tiles.  Weight gradient of 151,936 x 4096, a workgroup a
+// tile / walking, us: 256 rows 725 / 615, 512 rows 934 / 830, 2048 rows 2185 / 2120, 8192 rows 7395 / 7330, 16,384 rows
+// 14,720 / 14,835; logits (64 steps a tile) 512 rows 514 / 511, 16,384 rows 14,670 / 14,460; dL/dhidden, 150 and more
+// steps a tile, 16,384 rows 14,155 / 14,230.  So tiles of up to kWalkSteps steps are walked.  (Workgroups started a fraction
+// of a tile apart: no difference; results stored 16 bytes a lane: 1 % on the logits.)
+constexpr unsigned kGemmGrid = 256;
+constexpr int64_t kWalkSteps = 128;
+
+// A value that is the same in every lane, for a scalar register.
+__host__ __device__ __forceinline__ int uniform(int x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_readfirstlane(x);
+#else
+  return x;
+#endif
+}
+
+// (Places are moved on by additions: a division is some thirty vector instructions in every wavefront.)
+template <bool N_FIRST>
+struct TileWalk {
+  int tiles_m, tiles_n, all_steps, splits;
+  int gn, gm, groups_n, groups_m;                // tiles and groups either way
+  int split, line, pos;                          // the group: pos-th of a line of groups along n (N_FIRST) or m
+  int slot;                                      // place from the group's first tile on
+  bool walk;
+
+  __host__ __device__ __forceinline__ bool first(GemmTile& t, unsigned block, unsigned grid) {
+    gn = tile_group_n(tiles_n);
+    gm = 32 / gn;
+    groups_n = (tiles_n + gn - 1) / gn;
+    groups_m = (tiles_m + gm - 1) / gm;
+    walk = grid == kGemmGrid;
+    const int per_split = groups_n * groups_m, group = static_cast<int>((block >> 8) << 3) + static_cast<int>(block & 7);
+    slot = static_cast<int>(block >> 3) & 31;
+    split = uniform(group / per_split);
+    const int in_split = group - split * per_split;
+    line = uniform(in_split / (N_FIRST ? groups_n : groups_m));
+    pos = in_split - line * (N_FIRST ? groups_n : groups_m);
+    if (walk) return find(t);
+    if (split >= splits) return false;
+    const TilePlace place = tile_place<N_FIRST>(static_cast<unsigned>(in_split), static_cast<unsigned>(slot), tiles_m, tiles_n);
+    if (place.m >= tiles_m || place.n >= tiles_n) return false;
+    set(t, place.m, place.n);
+    return true;
+  }
+  // (asked again after the last tile, the answer stays)
+  __host__ __device__ __forceinline__ bool next(GemmTile& t) {
+    if (!walk || split >= splits) return false;
+    slot += 32;
+    return find(t);
+  }
+
+ private:
+  __host__ __device__ __forceinline__ bool find(GemmTile& t) {
+    const int length = N_FIRST ? groups_n : groups_m, lines = N_FIRST ? groups_m : groups_n;
+    while (split < splits) {
+      int at_m = line, at_n = pos;
+      if (!N_FIRST) {                            // as tile_place: the order in a line moves on
+        const int common = min(groups_m & -groups_m, 8);
+        at_n = line;
+        at_m = uniform((pos + (line >> (common == 1 ? 3 : common == 2 ? 2 : common == 4 ? 1 : 0))) % groups_m);
+      }
+      const int m = at_m * gm, n = at_n * gn;
+      const int here_m = min(gm, tiles_m - m), here_n = min(gn, tiles_n - n);
+      if (slot < here_m * here_n) {
+        const int row = here_n == 3 ? slot / 3 : slot >> (here_n >> 1);          // here_n is 1 to 4
+        set(t, m + row, n + slot - row * here_n);
+        return true;
+      }
+      slot -= here_m * here_n;
+      pos += 8;                                  // the XCD's next group
+      while (pos >= length) {
+        pos -= length;
+        if (++line == lines) {
+          line = 0;
+          ++split;
+        }
+      }
+    }
+    return false;
+  }
+  __host__ __device__ __forceinline__ void set(GemmTile& t, int m, int n) {
+    int from = 0, to = all_steps;
+    if (splits > 1) {
+      from = static_cast<int>(static_cast<int64_t>(all_steps) * split / splits);
+      to = static_cast<int>(static_cast<int64_t>(all_steps) * (split + 1) / splits);
+    }
+    t = GemmTile{uniform(m * kGemmTile), uniform(n * kGemmTile), uniform(from), uniform(to - from), uniform(split)};
+  }
+};
+
+// The loop over a workgroup's tiles: their steps are one stream.  The requests run ahead of the products into the next tile
+// (past the last step of all: that one again, never read), so a tile has no first loads to wait for.  A step in which the
+// requests pass from one tile to the next, or which follows a tile's stores, is code of its own: branches in the others cost
+// 10 % (16,384 rows 14.1 -> 15.7 ms).
+//   load.locate(tile)        the requests go on at the tile's first step
+//   load.step()              ... at the next step
+//   load.request(half, buf)  the wavefront's two loads of a half tile into a step buffer
+//   store(tile, acc)         returns whether it left at least 63 stores behind the requests and waited for none
+template <typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
+__device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
+                                             Loader& load, ReadA read_a, ReadB read_b, Store store) {
+  GemmTile ahead_tile = tile;
+  Walk ahead = walk;
+  int left = tile.steps;
+  load.locate(tile);
+  auto advance = [&]() {
+    if (--left > 0) {
+      load.step();
+    } else if (ahead.next(ahead_tile)) {
+      left = ahead_tile.steps;
+      load.locate(ahead_tile);
+    } else {
+      left = 1;                                            // the last step again, never read
+    }
+  };
+  matrix_begin(mine, true, [&](int half, int buf) {
+    load.request(half, buf);
+    if (half == kHalfA1) advance();
+  });
+  int step = 0;
+  bool stored = false;
+  TileAcc acc;
+  while (true) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
+    auto run = [&](auto stored_tag, auto switch_tag) {
+      const int cur = step & 1;
+      const unsigned char* here = smem + cur * kStepBytes;
+      matrix_step<true, decltype(stored_tag)::value>(
+          acc, [&](int half, int i, int ks) { return read_a(here, half, i, ks); },
+          [&](int half, int j, int ks) { return read_b(here, half, j, ks); },
+          [&](int half, int steps_ahead) {
+            load.request(half, steps_ahead == 1 ? cur ^ 1 : cur);
+            if (half == kHalfA1) {
+              if constexpr (decltype(switch_tag)::value) {
+                advance();
+              } else {
+                --left;
+                load.step();
+              }
+            }
+          });
+      ++step;
+    };
+    int kt = tile.steps;
+    if (stored) {
+      if (left > 1) run(std::true_type(), std::false_type());
+      else run(std::true_type(), std::true_type());
+      --kt;
+    }
+    while (kt > 0) {
+      const int plain = min(kt, left - 1);
+      for (int i = 0; i < plain; ++i) run(std::false_type(), std::false_type());
+      kt -= plain;
+      if (kt > 0) {
+        run(std::false_type(), std::true_type());
+        --kt;
+      }
+    }
+    stored = store(tile, acc);
+    if (!walk.next(tile)) break;
+  }
+  matrix_end(mine);
+}
+
+// Where the loads of a tile come from.  Operands with the contraction index contiguous: rows past the last are clamped, so the
+// loop has no branch.
+struct RowMajorSource {
+  const char* base;
+  int64_t ld;
+  int rows;
+  const char* src;
+  uint32_t off[2][2];
+  __device__ __forceinline__ void locate(const RowMajorHalf& at, int r0, int64_t k0) {
+    src = base + (static_cast<int64_t>(r0) * ld + k0) * 2;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        off[h][e] = static_cast<uint32_t>(min(h * 128 + at.row + 8 * e, rows - 1 - r0)) * (static_cast<uint32_t>(ld) * 2u) + at.chunk[e];
+  }
+  __device__ __forceinline__ void step() { src += 2 * kLmK; }
+  __device__ __forceinline__ void request(int half, uint32_t dst) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
+  }
+};
 
 // Operands with the contraction index as their row index (k-major).  A half tile of a step holds 64 k-rows of 128
 // consecutive m or n as they are in memory, 256 bytes per row, the eight 32-byte blocks of a row permuted by bits 0, 1 and 3 of
@@ -144,6 +357,66 @@ struct KMajorHalf {
   }
 };
 
+// k-major operands: pieces past the last of a row are clamped, rows past the last are taken from it.
+struct KMajorSource {
+  const char* base;
+  int64_t ld;
+  int cols, rows;              // 16-byte pieces of a row, readable rows
+  const char* src;
+  int left;                    // rows from this step's first on
+  uint32_t off[2][2];
+  int krow;
+  __device__ __forceinline__ void locate(const KMajorHalf& at, int c0, int64_t k0) {
+    src = base + k0 * ld * 2;
+    left = rows - static_cast<int>(k0);
+    krow = at.krow;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        off[h][e] = 16u * static_cast<uint32_t>(min((c0 >> 3) + 16 * h + at.piece, cols - 1)) +
+                    static_cast<uint32_t>(krow + 4 * e) * (static_cast<uint32_t>(ld) * 2u);
+  }
+  __device__ __forceinline__ void step() {
+    src += 2 * kLmK * ld;
+    left -= kLmK;
+  }
+  __device__ __forceinline__ void request(int half, uint32_t dst) {
+    if (left >= kLmK) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        load_to_lds(src, off[half][e] - static_cast<uint32_t>(max(krow + 4 * e - (left - 1), 0)) * (static_cast<uint32_t>(ld) * 2u),
+                    dst + e * 1024);
+    }
+  }
+};
+
+template <typename A, typename B, typename AtA, typename AtB>
+struct TileLoader {
+  A a;
+  B b;
+  const AtA& at_a;
+  const AtB& at_b;
+  uint32_t lds;
+  __device__ __forceinline__ void locate(const GemmTile& t) {
+    const int64_t k0 = static_cast<int64_t>(t.first) * kLmK;
+    a.locate(at_a, t.m0, k0);
+    b.locate(at_b, t.n0, k0);
+  }
+  __device__ __forceinline__ void step() {
+    a.step();
+    b.step();
+  }
+  __device__ __forceinline__ void request(int half, int buf) {
+    const uint32_t dst = lds + buf * kStepBytes + half * kHalfBytes;
+    if (half < 2) a.request(half, dst);
+    else b.request(half - 2, dst);
+  }
+};
+
 // K must be a positive multiple of 64 (at least 64 for every split); rows of Bn, and with A_K_MAJOR = false of Am, past the
 // end of an operand are clamped (re-read) and their results discarded.  Byte offsets inside one 256-row operand tile must
 // fit 32 bits (checked on the host).
@@ -167,73 +440,30 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   }
   // With splits > 1 the contraction index is cut into that many runs of whole steps, each with a result of its
   // own, split_stride floats apart, which the caller sums; the groups of a run follow each other.
-  unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7);
-  const unsigned slot = (blockIdx.x >> 3) & 31;
-  if (splits > 1) {
-    const unsigned per_split = static_cast<unsigned>(tile_groups(tiles_m, tiles_n));
-    const int split = static_cast<int>(group / per_split);
-    if (split >= splits) return;
-    group -= static_cast<unsigned>(split) * per_split;
-    const int steps = K / kLmK, first = static_cast<int>(static_cast<int64_t>(steps) * split / splits);
-    K = kLmK * (static_cast<int>(static_cast<int64_t>(steps) * (split + 1) / splits) - first);
-    Am += static_cast<int64_t>(first) * kLmK * (A_K_MAJOR ? lda : 1);
-    rows_a -= first * kLmK;
-    Bn += static_cast<int64_t>(first) * kLmK;
-    Out += split * split_stride;
-  }
-  const TilePlace place = tile_place<true>(group, slot, tiles_m, tiles_n);
-  const int tile_m = place.m, tile_n = place.n;
-  if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
-  const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
+  TileWalk<true> walk = {tiles_m, tiles_n, K / kLmK, splits};
+  GemmTile tile;
+  if (!walk.first(tile, blockIdx.x, gridDim.x)) return;                           // whole workgroup, before any barrier
 
   const MatrixPlace mine = matrix_place(gemm_smem);
   typedef typename std::conditional<A_K_MAJOR, KMajorHalf, RowMajorHalf>::type HalfA;
   const HalfA at_a(mine);
   const RowMajorHalf at(mine);
-  const char* Ab = reinterpret_cast<const char*>(Am) + (A_K_MAJOR ? 0 : static_cast<int64_t>(m0) * lda * 2);
-  const char* Bb = reinterpret_cast<const char*>(Bn) + static_cast<int64_t>(n0) * ldb * 2;
-  const uint32_t lda2 = static_cast<uint32_t>(lda) * 2u, ldb2 = static_cast<uint32_t>(ldb) * 2u;
-  uint32_t a_at[2][2], b_at[2][2];                         // byte offsets by half tile, load (k-major: inside a row)
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int row = h * 128 + at.row + 8 * e;
-      if constexpr (A_K_MAJOR) a_at[h][e] = 16u * static_cast<uint32_t>(min((m0 >> 3) + 16 * h + at_a.piece, (M >> 3) - 1));
-      else a_at[h][e] = static_cast<uint32_t>(min(row, M - 1 - m0)) * lda2 + at.chunk[e];
-      b_at[h][e] = static_cast<uint32_t>(min(row, N - 1 - n0)) * ldb2 + at.chunk[e];
-    }
-  const int n_steps = K / kLmK;
-  auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
-    const int k0 = min(step, n_steps - 1) * kLmK;
-    const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
-    const char* src = half >= 2 ? Bb + 2 * static_cast<int64_t>(k0) : Ab + 2 * static_cast<int64_t>(k0) * (A_K_MAJOR ? lda : 1);
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      uint32_t off = half >= 2 ? b_at[half & 1][e] : a_at[half & 1][e];
-      if constexpr (A_K_MAJOR) {
-        if (half < 2) off += static_cast<uint32_t>(min(at_a.krow + 4 * e, rows_a - 1 - k0)) * lda2;
-      }
-      load_to_lds(src, off, dst + e * 1024);
-    }
-  };
-
-  TileAcc acc;
-#pragma unroll
-  for (int i = 0; i < 32; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
-  matrix_begin(mine, true, [&](int half, int ahead) { request(half, ahead, ahead); });
-  for (int step = 0; step < n_steps; ++step) {
-    const int cur = step & 1;
-    const unsigned char* here = gemm_smem + cur * kStepBytes;
-    matrix_step<true>(
-        acc, [&](int half, int i, int ks) { return at_a.a(here, half, i, ks); },
-        [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
-        [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
-  }
-  matrix_end(mine);
-  store_tile<false>(acc, mine, m0, n0, M, N, Out, ldo);
+  typedef typename std::conditional<A_K_MAJOR, KMajorSource, RowMajorSource>::type SourceA;
+  TileLoader<SourceA, RowMajorSource, HalfA, RowMajorHalf> load = {{}, {}, at_a, at, mine.lds};
+  load.a.base = reinterpret_cast<const char*>(Am);
+  load.a.ld = lda;
+  load.a.rows = A_K_MAJOR ? rows_a : M;
+  if constexpr (A_K_MAJOR) load.a.cols = M >> 3;
+  load.b.base = reinterpret_cast<const char*>(Bn);
+  load.b.ld = ldb;
+  load.b.rows = N;
+  matrix_tiles(
+      mine, gemm_smem, tile, walk, load,
+      [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
+      [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
+      [&](const GemmTile& t, const TileAcc& acc) {
+        return store_tile<false>(acc, mine, t.m0, t.n0, M, N, Out + t.split * split_stride, ldo);
+      });
 }
 
 // The same contraction with B k-major (the contraction index is its row index):
@@ -265,52 +495,26 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   }
   // the groups of one set of tiles along n follow each other on neighbouring XCDs: they read the same columns of Bk, by
   // far the larger operand
-  const TilePlace place = tile_place<false>(((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), (blockIdx.x >> 3) & 31, tiles_m,
-                                            tiles_n);
-  const int tile_m = place.m, tile_n = place.n;
-  if (tile_m >= tiles_m || tile_n >= tiles_n) return;      // whole workgroup, before any barrier
-  const int m0 = tile_m * kGemmTile, n0 = tile_n * kGemmTile;
+  TileWalk<false> walk = {tiles_m, tiles_n, K / kLmK, 1};
+  GemmTile tile;
+  if (!walk.first(tile, blockIdx.x, gridDim.x)) return;                           // whole workgroup, before any barrier
 
   const MatrixPlace mine = matrix_place(gemm_smem);
   const RowMajorHalf at_a(mine);
   const KMajorHalf at(mine);
-  const char* Ab = reinterpret_cast<const char*>(Am) + static_cast<int64_t>(m0) * lda * 2;
-  const uint32_t lda2 = static_cast<uint32_t>(lda) * 2u, ldb2 = static_cast<uint32_t>(ldb) * 2u;
-  uint32_t a_at[2][2], col[2];                             // byte offsets: A by half tile and load, B inside a row by half tile
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-      a_at[h][e] = static_cast<uint32_t>(min(h * 128 + at_a.row + 8 * e, M - 1 - m0)) * lda2 + at_a.chunk[e];
-    col[h] = 16u * static_cast<uint32_t>(min((n0 >> 3) + 16 * h + at.piece, ((N + 7) >> 3) - 1));
-  }
-  const int n_steps = K / kLmK;
-  auto request = [&](int half, int step, int buf) {        // past the last step: that one again, never read
-    const int k0 = min(step, n_steps - 1) * kLmK;
-    const char* src = half < 2 ? Ab + 2 * static_cast<int64_t>(k0)
-                               : reinterpret_cast<const char*>(Bk) + static_cast<int64_t>(k0) * ldb * 2;
-    const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-      load_to_lds(src, half < 2 ? a_at[half & 1][e] : col[half & 1] + static_cast<uint32_t>(at.krow + 4 * e) * ldb2,
-                  dst + e * 1024);
-  };
-  TileAcc acc;
-#pragma unroll
-  for (int i = 0; i < 32; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
-  matrix_begin(mine, true, [&](int half, int ahead) { request(half, ahead, ahead); });
-  for (int step = 0; step < n_steps; ++step) {
-    const int cur = step & 1;
-    const unsigned char* here = gemm_smem + cur * kStepBytes;
-    matrix_step<true>(
-        acc, [&](int half, int i, int ks) { return at_a.a(here, half, i, ks); },
-        [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
-        [&](int half, int ahead) { request(half, step + ahead, ahead == 1 ? cur ^ 1 : cur); });
-  }
-  matrix_end(mine);
-  store_tile<ACCUMULATE>(acc, mine, m0, n0, M, N, Out, ldo);
+  TileLoader<RowMajorSource, KMajorSource, RowMajorHalf, KMajorHalf> load = {{}, {}, at_a, at, mine.lds};
+  load.a.base = reinterpret_cast<const char*>(Am);
+  load.a.ld = lda;
+  load.a.rows = M;
+  load.b.base = reinterpret_cast<const char*>(Bk);
+  load.b.ld = ldb;
+  load.b.rows = K;
+  load.b.cols = (N + 7) >> 3;
+  matrix_tiles(
+      mine, gemm_smem, tile, walk, load,
+      [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
+      [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
+      [&](const GemmTile& t, const TileAcc& acc) { return store_tile<ACCUMULATE>(acc, mine, t.m0, t.n0, M, N, Out, ldo); });
 }
 
 // out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  GATHER: out[c, r] = in[row_map[r], c] for

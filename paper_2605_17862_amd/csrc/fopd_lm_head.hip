@@ -231,8 +231,9 @@ __device__ __forceinline__ void multiply_phase(TileAcc& acc, int a, int b, const
 
 // One step.  read_a(half, i, ks) / read_b(half, j, ks): the fragment of 16-row block i / j, elements 32 ks .. + 31, from this
 // step's buffer.  request(half, ahead): the wavefront's two loads of that half tile of the step `ahead` steps later (any
-// readable step past the last one: never read).
-template <bool B_FIRST, typename ReadA, typename ReadB, typename Request>
+// readable step past the last one: never read).  STORED: at least 63 stores have been issued since the requests that this
+// step waits for, which are done when 63 later ones are all that is left (loads and stores count and end in order).
+template <bool B_FIRST, bool STORED, typename ReadA, typename ReadB, typename Request>
 __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB read_b, Request request) {
   bf16x8 fa[4][2], fb0[2][2], fb1[2][2];
 #pragma unroll
@@ -253,7 +254,8 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) fb1[j][ks] = read_b(1, j, ks);
   request(kHalfB0, 2);
-  asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
+  if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63) lgkmcnt(0)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
   slot_end();
   multiply_phase<B_FIRST>(acc, 0, 1, fa, fb1);
   slot_end();
@@ -267,7 +269,8 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   multiply_phase<B_FIRST>(acc, 1, 1, fa, fb1);
   slot_end();
   request(kHalfB1, 2);
-  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
   slot_end();
   multiply_phase<B_FIRST>(acc, 1, 0, fa, fb0);
   slot_end();
@@ -449,7 +452,7 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
     for (int kt = 0; kt < nkp; ++kt, ++step) {
       const int cur = step & 1;
       const unsigned char* here = lm_smem + cur * kStepBytes;
-      matrix_step<false>(
+      matrix_step<false, false>(
           acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
           [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
           [&](int half, int ahead) { request(half, vt_at[ahead - 1], k_at[ahead - 1], ahead == 1 ? cur ^ 1 : cur); });

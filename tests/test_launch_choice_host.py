@@ -14,6 +14,7 @@ SOURCE = r"""
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 #include "fopd_gemm.hip"
 using namespace fopd;
 
@@ -33,6 +34,30 @@ static double makespan(int tiles_m, int tiles_n, int runs, double start, Length 
       last = std::max(last, *cu);
     }
   return last;
+}
+
+// Every tile of every run comes once, whether a launch has a workgroup for each place or 256 that walk, and the same ones.
+template <bool N_FIRST>
+static bool walked(int tiles_m, int tiles_n, int steps, int splits) {
+  for (unsigned grid : {256u, static_cast<unsigned>((splits * tile_groups(tiles_m, tiles_n) + 7) / 8 * 256)}) {
+    std::vector<int> seen(static_cast<size_t>(tiles_m) * tiles_n * splits, 0);
+    for (unsigned block = 0; block < grid; ++block) {
+      TileWalk<N_FIRST> walk = {tiles_m, tiles_n, steps, splits};
+      GemmTile t;
+      if (!walk.first(t, block, grid)) continue;
+      do {
+        if (t.m0 < 0 || t.m0 % 256 || t.m0 / 256 >= tiles_m || t.n0 < 0 || t.n0 % 256 || t.n0 / 256 >= tiles_n) return false;
+        if (t.split < 0 || t.split >= splits || t.steps < 1 || t.first != steps * t.split / splits ||
+            t.first + t.steps != steps * (t.split + 1) / splits)
+          return false;
+        ++seen[(static_cast<size_t>(t.split) * tiles_n + t.n0 / 256) * tiles_m + t.m0 / 256];
+      } while (walk.next(t));
+      const GemmTile last = t;
+      if (walk.next(t) || t.m0 != last.m0 || t.n0 != last.n0) return false;
+    }
+    for (int c : seen) if (c != 1) return false;
+  }
+  return true;
 }
 
 int main() {
@@ -79,6 +104,13 @@ int main() {
         }
       std::printf("order %d %d %d %d\n", hidden, vocab, seen, most);
     }
+  for (int m : {1, 2, 4, 7, 8, 9, 16, 33, 594})
+    for (int n : {1, 2, 3, 4, 5, 8, 64, 594})
+      for (int splits : {1, 3, 8})
+        for (int first : {0, 1}) {
+          if (first ? !walked<true>(m, n, 19, splits) : !walked<false>(m, n, 19, splits)) return 2;
+          std::printf("walk %d %d %d %d\n", m, n, splits, first);
+        }
 }
 """
 
@@ -113,3 +145,7 @@ def test_tiles_of_the_weight_gradient_are_spread_evenly(choices):
         lines, line = -(-vocab // 4), -(-hidden // 8)
         # an even share, and a group of 32 for each place of a line in which one XCD can be ahead
         assert most <= hidden * vocab / 8 + 32 * min(line, lines), (hidden, vocab, most)
+
+
+def test_walking_workgroups_take_every_tile_once(choices):
+    assert sum(r[0] == "walk" for r in choices) == 9 * 8 * 3 * 2           # the program stops at one that does not
