@@ -1211,10 +1211,10 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   auto kern = fopd_k7_lm_head_lse;
   static bool allowed[kMaxDevices] = {};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLmLdsBytes, allowed) != FOPD_OK) return FOPD_EHIP;
-  const int n_token_tiles = static_cast<int>(lay.t_pad / kLmTile);
   const int n_vocab_tiles = static_cast<int>((V + kLmTile - 1) / kLmTile);
-  const int n_strips = lm_strips(n_token_tiles, n_vocab_tiles);
-  const unsigned grid = static_cast<unsigned>((tile_groups(n_strips, n_token_tiles) + 7) / 8) * 256u;
+  const LmSplit split = lm_split(T, n_vocab_tiles);
+  const int64_t groups = tile_groups(split.strips, split.whole) + (split.tail_strips + 31) / 32;
+  const unsigned grid = static_cast<unsigned>((groups + 7) / 8) * 256u;
   float2* partial = at<float2>(workspace, lay.partial);
   const __bf16* Wp = static_cast<const __bf16*>(weight);
   const __bf16* Hp = static_cast<const __bf16*>(hidden);
@@ -1232,13 +1232,12 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   {
     ScopedTimer timer(3, s);
     kern<<<dim3(grid), dim3(kLmThreads), kLmLdsBytes, s>>>(Wp, ldw, Hp, ldh, static_cast<int>(T), static_cast<int>(V),
-                                                    static_cast<int>(d), partial, n_token_tiles, n_vocab_tiles,
-                                                    n_strips, static_cast<int64_t>(lay.t_pad), row_map, n_live);
+                                                    static_cast<int>(d), partial, split, n_vocab_tiles, row_map, n_live);
   }
   if (launched() != FOPD_OK) return FOPD_EHIP;
   fopd_k7_finish<<<dim3(static_cast<unsigned>((T + 3) / 4)), dim3(256), 0, s>>>(
-      Wp, ldw, Hp, ldh, partial, n_strips, static_cast<int>(T), static_cast<int>(V), static_cast<int>(d),
-      static_cast<int64_t>(lay.t_pad), token_ids, mask, logp, lse, at<int32_t>(workspace, lay.flags), ex);
+      Wp, ldw, Hp, ldh, partial, split, static_cast<int>(T), static_cast<int>(V), static_cast<int>(d), token_ids, mask, logp,
+      lse, at<int32_t>(workspace, lay.flags), ex);
   return launched();
 }
 

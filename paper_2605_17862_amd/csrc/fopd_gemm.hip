@@ -113,11 +113,6 @@ __device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace
   return false;
 }
 
-// A tile of the result and the steps of the contraction index that go into it: all of them, or those of one run (split).
-struct GemmTile {
-  int m0, n0, first, steps, split;
-};
-
 // The tiles of a workgroup.  Launched with a workgroup for every place of every group (tile_place), each has one tile or none.
 // Launched with kGemmGrid, one a compute unit, workgroup 8 s + x is the s-th of XCD x and takes every 32nd tile of that XCD's
 // groups x, x + 8, .. in their order, only tiles that exist being counted.  The next tile's first steps are then requested
@@ -213,106 +208,6 @@ struct TileWalk {
   }
 };
 
-// The loop over a workgroup's tiles: their steps are one stream.  The requests run ahead of the products into the next tile
-// (past the last step of all: that one again, never read), so a tile has no first loads to wait for.  A step in which the
-// requests pass from one tile to the next, or which follows a tile's stores, is code of its own: branches in the others cost
-// 10 % (16,384 rows 14.1 -> 15.7 ms).
-//   load.locate(tile)        the requests go on at the tile's first step
-//   load.step()              ... at the next step
-//   load.request(half, buf)  the wavefront's two loads of a half tile into a step buffer
-//   store(tile, acc)         returns whether it left at least 63 stores behind the requests and waited for none
-template <typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
-__device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
-                                             Loader& load, ReadA read_a, ReadB read_b, Store store) {
-  GemmTile ahead_tile = tile;
-  Walk ahead = walk;
-  int left = tile.steps;
-  load.locate(tile);
-  auto advance = [&]() {
-    if (--left > 0) {
-      load.step();
-    } else if (ahead.next(ahead_tile)) {
-      left = ahead_tile.steps;
-      load.locate(ahead_tile);
-    } else {
-      left = 1;                                            // the last step again, never read
-    }
-  };
-  matrix_begin(mine, true, [&](int half, int buf) {
-    load.request(half, buf);
-    if (half == kHalfA1) advance();
-  });
-  int step = 0;
-  bool stored = false;
-  TileAcc acc;
-  while (true) {
-#pragma unroll
-    for (int i = 0; i < 32; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
-    auto run = [&](auto stored_tag, auto switch_tag) {
-      const int cur = step & 1;
-      const unsigned char* here = smem + cur * kStepBytes;
-      matrix_step<true, decltype(stored_tag)::value>(
-          acc, [&](int half, int i, int ks) { return read_a(here, half, i, ks); },
-          [&](int half, int j, int ks) { return read_b(here, half, j, ks); },
-          [&](int half, int steps_ahead) {
-            load.request(half, steps_ahead == 1 ? cur ^ 1 : cur);
-            if (half == kHalfA1) {
-              if constexpr (decltype(switch_tag)::value) {
-                advance();
-              } else {
-                --left;
-                load.step();
-              }
-            }
-          });
-      ++step;
-    };
-    int kt = tile.steps;
-    if (stored) {
-      if (left > 1) run(std::true_type(), std::false_type());
-      else run(std::true_type(), std::true_type());
-      --kt;
-    }
-    while (kt > 0) {
-      const int plain = min(kt, left - 1);
-      for (int i = 0; i < plain; ++i) run(std::false_type(), std::false_type());
-      kt -= plain;
-      if (kt > 0) {
-        run(std::false_type(), std::true_type());
-        --kt;
-      }
-    }
-    stored = store(tile, acc);
-    if (!walk.next(tile)) break;
-  }
-  matrix_end(mine);
-}
-
-// Where the loads of a tile come from.  Operands with the contraction index contiguous: rows past the last are clamped, so the
-// loop has no branch.
-struct RowMajorSource {
-  const char* base;
-  int64_t ld;
-  int rows;
-  const char* src;
-  uint32_t off[2][2];
-  __device__ __forceinline__ void locate(const RowMajorHalf& at, int r0, int64_t k0) {
-    src = base + (static_cast<int64_t>(r0) * ld + k0) * 2;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-        off[h][e] = static_cast<uint32_t>(min(h * 128 + at.row + 8 * e, rows - 1 - r0)) * (static_cast<uint32_t>(ld) * 2u) + at.chunk[e];
-  }
-  __device__ __forceinline__ void step() { src += 2 * kLmK; }
-  __device__ __forceinline__ void request(int half, uint32_t dst) {
-#pragma unroll
-    for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
-  }
-};
-
 // Operands with the contraction index as their row index (k-major).  A half tile of a step holds 64 k-rows of 128
 // consecutive m or n as they are in memory, 256 bytes per row, the eight 32-byte blocks of a row permuted by bits 0, 1 and 3 of
 // the row.  A fragment of the matrix instruction (lane = one m, eight consecutive k) is two LDS transpose reads
@@ -394,29 +289,6 @@ struct KMajorSource {
   }
 };
 
-template <typename A, typename B, typename AtA, typename AtB>
-struct TileLoader {
-  A a;
-  B b;
-  const AtA& at_a;
-  const AtB& at_b;
-  uint32_t lds;
-  __device__ __forceinline__ void locate(const GemmTile& t) {
-    const int64_t k0 = static_cast<int64_t>(t.first) * kLmK;
-    a.locate(at_a, t.m0, k0);
-    b.locate(at_b, t.n0, k0);
-  }
-  __device__ __forceinline__ void step() {
-    a.step();
-    b.step();
-  }
-  __device__ __forceinline__ void request(int half, int buf) {
-    const uint32_t dst = lds + buf * kStepBytes + half * kHalfBytes;
-    if (half < 2) a.request(half, dst);
-    else b.request(half - 2, dst);
-  }
-};
-
 // K must be a positive multiple of 64 (at least 64 for every split); rows of Bn, and with A_K_MAJOR = false of Am, past the
 // end of an operand are clamped (re-read) and their results discarded.  Byte offsets inside one 256-row operand tile must
 // fit 32 bits (checked on the host).
@@ -457,7 +329,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   load.b.base = reinterpret_cast<const char*>(Bn);
   load.b.ld = ldb;
   load.b.rows = N;
-  matrix_tiles(
+  matrix_tiles<true, false>(
       mine, gemm_smem, tile, walk, load,
       [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
@@ -510,7 +382,7 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   load.b.ld = ldb;
   load.b.rows = K;
   load.b.cols = (N + 7) >> 3;
-  matrix_tiles(
+  matrix_tiles<true, false>(
       mine, gemm_smem, tile, walk, load,
       [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },

@@ -20,7 +20,8 @@
 // The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Bound by power: the matrix
 // cores are 0.75 (logits) to 0.80 (dL/dhidden) busy at the 1.5 GHz that the part then holds.  The 16 x 16 x 32 instruction has
 // the rate of the 32 x 32 x 16 one but goes over its accumulators half as often per product; log-probs of 16,384 rows x
-// 151,936, d = 4096: 15.8 - 16.0 -> 15.0 - 15.1 ms, of 2048 rows 1.98 -> 1.86 ms.
+// 151,936, d = 4096: 15.4 - 16.0 -> 14.7 - 15.1 ms, of 2048 rows 1.92 - 1.98 -> 1.86 ms.  With the vocabulary tiles of a strip as
+// one stream (matrix_tiles), whose loads have offsets that stay from step to step, 14.15 - 14.4 and 1.73 ms.
 
 #ifndef FOPD_LM_HEAD_HIP_
 #define FOPD_LM_HEAD_HIP_
@@ -28,6 +29,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "fopd_kernels.hip"
@@ -42,7 +44,8 @@ constexpr int kLmThreads = 512;                           // 8 wavefronts: 2 (vo
 constexpr int kHalfBytes = 128 * kLmK * 2;                // half an operand tile of a step: 16 KB
 constexpr int kStepBytes = 4 * kHalfBytes;                // both operand tiles of a step
 constexpr int kLoopLdsBytes = 2 * kStepBytes;             // two steps: 128 KB of the compute unit's 160
-constexpr int kLmLdsBytes = kLoopLdsBytes + 2 * kLmTile * 8;                // + the cross-wave exchange
+constexpr int kNarrowBytes = 3 * kHalfBytes;              // a step with half a B tile, of which the LDS holds three
+constexpr int kLmLdsBytes = 3 * kNarrowBytes;             // (the loop with whole tiles, then the exchange between wavefronts: 132 KB)
 constexpr float kLmNone = -__builtin_inff();              // "no value yet": the reference of an empty pair
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -135,6 +138,39 @@ __host__ inline int lm_strips(int n_token_tiles, int n_vocab_tiles) {
     }
   }
   return n_strips;
+}
+
+// Token tiles of fopd_k7_lm_head_lse: `whole` of them in `strips` strips each, and a last one of at most 128 tokens in
+// `tail_strips` (0: none).
+struct LmSplit {
+  int whole, strips, tail_strips;
+};
+
+// A last tile of up to 128 tokens goes through a step in kNarrowCost of the time of a whole one, so few whole tiles and that one
+// share the chip best with strips of their own: all of them in one round, a group for each XCD, as long as the longer of the
+// two strips.  With more tiles the tail is one tile of many and has the strips of the others.  151,936 x 4096, us, all tiles whole /
+// so: 64 rows 318 / 260, 300 rows 510 / 465, 600 rows 847 / 680, 1100 rows 1480 / 1075, 1600 rows (a tail among seven) 1770 /
+// 1620.
+constexpr double kNarrowCost = 0.6;
+__host__ inline LmSplit lm_split(int64_t T, int n_vocab_tiles) {
+  const int tiles = static_cast<int>((T + kLmTile - 1) / kLmTile);
+  const int tail = static_cast<int>(T - static_cast<int64_t>(tiles - 1) * kLmTile);
+  LmSplit best = {tiles, lm_strips(tiles, n_vocab_tiles), 0};
+  if (tail > kLmTile / 2) return best;
+  auto steps = [&](int strips) { return (n_vocab_tiles + strips - 1) / strips; };
+  if (tiles == 1) return {0, 0, std::min(256, (n_vocab_tiles + 31) / 32 * 32)};
+  const int whole = tiles - 1, group_strips = 32 / tile_group_n(whole), groups_n = (whole + 3) / 4;
+  double least = static_cast<double>(tile_rounds(best.strips, tiles, 1)) * steps(best.strips);
+  for (int tail_groups = 1; tail_groups < 8; ++tail_groups) {
+    const int strips = (8 - tail_groups) / groups_n * group_strips, tail_strips = 32 * tail_groups;
+    if (strips <= 0 || strips > n_vocab_tiles || tail_strips > n_vocab_tiles) continue;
+    const double cost = std::max<double>(steps(strips), kNarrowCost * steps(tail_strips));
+    if (cost < least) {
+      least = cost;
+      best = {whole, strips, tail_strips};
+    }
+  }
+  return best;
 }
 
 template <bool N_FIRST>
@@ -230,8 +266,8 @@ __device__ __forceinline__ void multiply_phase(TileAcc& acc, int a, int b, const
 }
 
 // One step.  read_a(half, i, ks) / read_b(half, j, ks): the fragment of 16-row block i / j, elements 32 ks .. + 31, from this
-// step's buffer.  request(half, ahead): the wavefront's two loads of that half tile of the step `ahead` steps later (any
-// readable step past the last one: never read).  STORED: at least 63 stores have been issued since the requests that this
+// step's buffer.  request(half): the wavefront's two loads of that half tile of a later step (any readable one past the last:
+// never read).  STORED: at least 63 stores have been issued since the requests that this
 // step waits for, which are done when 63 later ones are all that is left (loads and stores count and end in order).
 template <bool B_FIRST, bool STORED, typename ReadA, typename ReadB, typename Request>
 __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB read_b, Request request) {
@@ -244,7 +280,7 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(0, i, ks);
-  request(kHalfA1, 1);
+  request(kHalfA1);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
   multiply_phase<B_FIRST>(acc, 0, 0, fa, fb0);
@@ -253,7 +289,7 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) fb1[j][ks] = read_b(1, j, ks);
-  request(kHalfB0, 2);
+  request(kHalfB0);
   if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63) lgkmcnt(0)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
   slot_end();
@@ -263,12 +299,12 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(1, i, ks);
-  request(kHalfA0, 2);
+  request(kHalfA0);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
   multiply_phase<B_FIRST>(acc, 1, 1, fa, fb1);
   slot_end();
-  request(kHalfB1, 2);
+  request(kHalfB1);
   if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
   slot_end();
@@ -277,19 +313,62 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
 }
 
 // Before the first step: the seven half tiles that precede its own requests, in the order of the steps, and the extra
-// barrier of wm = 1.  request(half, ahead) counts from step 0 here.
+// barrier of wm = 1.
 template <typename Request>
-__device__ __forceinline__ void matrix_begin(const MatrixPlace& place, bool any_step, Request request) {
-  if (any_step) {
-    request(kHalfB0, 0);
-    request(kHalfA0, 0);
-    request(kHalfB1, 0);
-    request(kHalfA1, 0);
-    request(kHalfB0, 1);
-    request(kHalfA0, 1);
-    request(kHalfB1, 1);
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+__device__ __forceinline__ void matrix_begin(const MatrixPlace& place, Request request) {
+  request(kHalfB0, 0);
+  request(kHalfA0, 0);
+  request(kHalfB1, 0);
+  request(kHalfA1, 0);
+  request(kHalfB0, 1);
+  request(kHalfA0, 1);
+  request(kHalfB1, 1);
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  slot_end();
+  if (place.wm == 1) slot_end();
+}
+
+// The same for a tile with at most 128 rows of B: without B1 a step is two phases, and the LDS holds three steps of 48 KB.
+//
+//   phase   reads      multiplies   requests                        waits for (besides its own LDS reads)
+//     1     B0, A0     A0 x B0      A1 of the next step but one     A1 of this step          (6 half tiles stay in flight)
+//     2     A1         A1 x B0      B0, A0 of the next but two      B0, A0 of the next step  (6 stay in flight)
+//
+template <bool B_FIRST, typename ReadA, typename ReadB, typename Request>
+__device__ __forceinline__ void matrix_step_narrow(TileAcc& acc, ReadA read_a, ReadB read_b, Request request) {
+  bf16x8 fa[4][2], fb[2][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) fb[j][ks] = read_b(0, j, ks);
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(a, i, ks);
+    if (a == 0) {
+      request(kHalfA1);
+    } else {
+      request(kHalfB0);
+      request(kHalfA0);
+    }
+    asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
+    slot_end();
+    multiply_phase<B_FIRST>(acc, a, 0, fa, fb);
+    slot_end();
   }
+}
+
+template <typename Request>
+__device__ __forceinline__ void matrix_begin_narrow(const MatrixPlace& place, Request request) {
+#pragma unroll
+  for (int buf = 0; buf < 3; ++buf) {
+    request(kHalfB0, buf);
+    request(kHalfA0, buf);
+    if (buf < 2) request(kHalfA1, buf);
+  }
+  asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
   slot_end();
   if (place.wm == 1) slot_end();
 }
@@ -327,92 +406,206 @@ struct RowMajorHalf {
   }
 };
 
-}  // namespace
+// A tile of the result and the steps of the contraction index that go into it: all of them, or those of one run (split).
+struct GemmTile {
+  int m0, n0, first, steps, split;
+};
 
-__global__ void __launch_bounds__(kLmThreads)
-fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restrict__ H, int64_t ldh,
-                    int T, int V, int d, float2* __restrict__ partial, int n_token_tiles, int n_vocab_tiles,
-                    int n_strips, int64_t t_pad, const int* __restrict__ row_map, const int* __restrict__ n_live) {
-  extern __shared__ __align__(16) unsigned char lm_smem[];
-  const int tid = threadIdx.x, lane = tid & 63;
-
-  // Only the rows row_map[0 .. *n_live - 1] of H take part when a count is given (masked rows left out; the count stays
-  // on the device and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the
-  // loads.
-  if (n_live != nullptr) {
-    T = *n_live;
-    if (T <= 0) return;
-    n_token_tiles = min(n_token_tiles, (T + kLmTile - 1) / kLmTile);
-  }
-  // m: vocabulary strips, n: token tiles; each L2 serves up to 4 hidden tiles and 8 strips of the weight to 32 users
-  const TilePlace place = tile_place<true>(((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), (blockIdx.x >> 3) & 31, n_strips,
-                                           n_token_tiles);
-  const int strip = place.m, token_tile = place.n;
-  if (strip >= n_strips || token_tile >= n_token_tiles) return;      // whole workgroup, before any barrier
-  const int vt_begin = static_cast<int>(static_cast<int64_t>(strip) * n_vocab_tiles / n_strips);
-  const int vt_end = static_cast<int>(static_cast<int64_t>(strip + 1) * n_vocab_tiles / n_strips);
-  const int t0 = token_tile * kLmTile;
-  const int nkp = d / kLmK, n_steps = (vt_end - vt_begin) * nkp;
-  const MatrixPlace mine = matrix_place(lm_smem);
-  const RowMajorHalf at(mine);
-
-  // Rows past the end of a matrix re-read its last row (they are discarded later): the row is clamped, which changes
-  // nothing inside the matrix, so the loop has no branch.  All offsets fit 32 bits (checked on the host).
-  const char* Wb = reinterpret_cast<const char*>(W);
-  const char* Hb = reinterpret_cast<const char*>(H) + (row_map != nullptr ? 0 : static_cast<int64_t>(t0) * ldh * 2);
-  const uint32_t ldw2 = static_cast<uint32_t>(ldw) * 2u;
-  uint32_t h_off[2][2];
+// Where the loads of a tile come from.  Operands with the contraction index contiguous: rows past the last are clamped, so the
+// loop has no branch.
+struct RowMajorSource {
+  const char* base;
+  int64_t ld;
+  int rows;
+  const char* src;
+  uint32_t off[2][2];
+  __device__ __forceinline__ void locate(const RowMajorHalf& at, int r0, int64_t k0) {
+    src = base + (static_cast<int64_t>(r0) * ld + k0) * 2;
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int r = min(h * 128 + at.row + 8 * e, T - 1 - t0);
-      const uint32_t row = (row_map != nullptr) ? static_cast<uint32_t>(row_map[t0 + r]) : static_cast<uint32_t>(r);
-      h_off[h][e] = row * static_cast<uint32_t>(ldh) * 2u + at.chunk[e];
-    }
-  // vocabulary tile and 64 hidden elements of the next step [0] and the one after it [1]; they stop at the last
-  int vt_at[2] = {vt_begin, vt_begin}, k_at[2] = {0, 0}, left = n_steps - 1;
-  auto advance = [&]() {
-    vt_at[0] = vt_at[1];
-    k_at[0] = k_at[1];
-    if (left > 0) {
-      --left;
-      if (++k_at[1] == nkp) {
-        k_at[1] = 0;
-        ++vt_at[1];
-      }
-    }
-  };
-  auto request = [&](int half, int vtile, int k, int buf) {
-    const uint32_t dst = mine.lds + buf * kStepBytes + half * kHalfBytes;
-    const int64_t kb = static_cast<int64_t>(k) * (2 * kLmK);
-    if (half < 2) {
-      const int last = V - 1 - vtile * kLmTile;
-      const char* src = Wb + static_cast<int64_t>(vtile) * kLmTile * ldw * 2 + kb;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int e = 0; e < 2; ++e)
-        load_to_lds(src, static_cast<uint32_t>(min(half * 128 + at.row + 8 * e, last)) * ldw2 + at.chunk[e], dst + e * 1024);
-    } else {
+        off[h][e] = static_cast<uint32_t>(min(h * 128 + at.row + 8 * e, rows - 1 - r0)) * (static_cast<uint32_t>(ld) * 2u) + at.chunk[e];
+  }
+  __device__ __forceinline__ void step() { src += 2 * kLmK; }
+  __device__ __forceinline__ void request(int half, uint32_t dst) {
 #pragma unroll
-      for (int e = 0; e < 2; ++e) load_to_lds(Hb + kb, h_off[half - 2][e], dst + e * 1024);
+    for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
+  }
+};
+
+template <typename A, typename B, typename AtA, typename AtB, int STEP_BYTES = kStepBytes>
+struct TileLoader {
+  A a;
+  B b;
+  const AtA& at_a;
+  const AtB& at_b;
+  uint32_t lds;
+  __device__ __forceinline__ void locate(const GemmTile& t) {
+    const int64_t k0 = static_cast<int64_t>(t.first) * kLmK;
+    a.locate(at_a, t.m0, k0);
+    b.locate(at_b, t.n0, k0);
+  }
+  __device__ __forceinline__ void step() {
+    a.step();
+    b.step();
+  }
+  __device__ __forceinline__ void request(int half, int buf) {
+    const uint32_t dst = lds + buf * STEP_BYTES + half * kHalfBytes;
+    if (half < 2) a.request(half, dst);
+    else b.request(half - 2, dst);
+  }
+};
+
+// The loop over a workgroup's tiles: their steps are one stream.  The requests run ahead of the products into the next tile
+// (past the last step of all: that one again, never read), so a tile has no first loads to wait for.  A step in which the
+// requests pass from one tile to the next, or which follows a tile's stores, is code of its own: branches in the others cost
+// 10 % (16,384 rows 14.1 -> 15.7 ms).
+//   load.locate(tile)        the requests go on at the tile's first step
+//   load.step()              ... at the next step
+//   load.request(half, buf)  the wavefront's two loads of a half tile into a step buffer
+//   store(tile, acc)         what to do with a finished tile; returns whether it left at least 63 stores behind the requests and
+//                            waited for none
+// NARROW: tiles of up to 128 rows of B (matrix_step_narrow).
+template <bool B_FIRST, bool NARROW, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
+__device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
+                                             Loader& load, ReadA read_a, ReadB read_b, Store store) {
+  GemmTile ahead_tile = tile;
+  Walk ahead = walk;
+  int left = tile.steps;
+  load.locate(tile);
+  auto advance = [&]() {
+    if (--left > 0) {
+      load.step();
+    } else if (ahead.next(ahead_tile)) {
+      left = ahead_tile.steps;
+      load.locate(ahead_tile);
+    } else {
+      left = 1;                                            // the last step again, never read
     }
   };
-
+  auto request_from = [&](int half, int buf) {
+    load.request(half, buf);
+    if (half == kHalfA1) advance();
+  };
+  if constexpr (NARROW) matrix_begin_narrow(mine, request_from);
+  else matrix_begin(mine, request_from);
+  int cur = 0;                                             // the step's buffer
+  bool stored = false;
   TileAcc acc;
-  float run_ref[4], run_sum[4];
+  while (true) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+    for (int i = 0; i < 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
+    auto run = [&](auto stored_tag, auto switch_tag) {
+      constexpr int kBufs = NARROW ? 3 : 2;
+      const unsigned char* here = smem + cur * (NARROW ? kNarrowBytes : kStepBytes);
+      const int before = cur == 0 ? kBufs - 1 : cur - 1;
+      auto a = [&](int half, int i, int ks) { return read_a(here, half, i, ks); };
+      auto b = [&](int half, int j, int ks) { return read_b(here, half, j, ks); };
+      auto request = [&](int half) {                       // A1 is a buffer behind the other half tiles
+        load.request(half, half == kHalfA1 ? before : cur);
+        if (half == kHalfA1) {
+          if constexpr (decltype(switch_tag)::value) {
+            advance();
+          } else {
+            --left;
+            load.step();
+          }
+        }
+      };
+      if constexpr (NARROW) matrix_step_narrow<B_FIRST>(acc, a, b, request);
+      else matrix_step<B_FIRST, decltype(stored_tag)::value>(acc, a, b, request);
+      cur = cur == kBufs - 1 ? 0 : cur + 1;
+    };
+    int kt = tile.steps;
+    if (stored) {
+      if (left > 1) run(std::true_type(), std::false_type());
+      else run(std::true_type(), std::true_type());
+      --kt;
+    }
+    while (kt > 0) {
+      const int plain = min(kt, left - 1);
+      for (int i = 0; i < plain; ++i) run(std::false_type(), std::false_type());
+      kt -= plain;
+      if (kt > 0) {
+        run(std::false_type(), std::true_type());
+        --kt;
+      }
+    }
+    stored = store(tile, acc);
+    if (!walk.next(tile)) break;
+  }
+  matrix_end(mine);
+}
+
+}  // namespace
+
+namespace {
+
+// The vocabulary tiles of a strip, one after the other.
+struct StripWalk {
+  int end;                     // first vocabulary row past the strip
+  __device__ __forceinline__ bool next(GemmTile& t) const {
+    if (t.m0 + kLmTile >= end) return false;
+    t.m0 += kLmTile;
+    return true;
+  }
+};
+
+// The tokens of a workgroup, the same for every vocabulary tile: rows of the hidden states, perhaps through a row map.
+struct HiddenSource {
+  const char* base;
+  const char* src;
+  uint32_t off[2][2];
+  __device__ __forceinline__ void locate(const RowMajorHalf&, int, int64_t) { src = base; }
+  __device__ __forceinline__ void step() { src += 2 * kLmK; }
+  __device__ __forceinline__ void request(int half, uint32_t dst) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
+  }
+};
+
+// One strip of the vocabulary for the up to 256 (NARROW: 128) tokens of a tile: pair (reference, sum) of token i to pairs[i].
+template <bool NARROW>
+__device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __restrict__ W, int64_t ldw,
+                                         const __bf16* __restrict__ H, int64_t ldh, int tokens, int V, int d, int t0,
+                                         int vt_begin, int vt_end, const int* __restrict__ row_map,
+                                         float2* __restrict__ pairs) {
+  constexpr int J = NARROW ? 2 : 4;                        // 16-token blocks of a wavefront
+  const int tid = threadIdx.x, lane = tid & 63;
+  const MatrixPlace mine = matrix_place(smem);
+  const RowMajorHalf at(mine);
+  // Rows past the end of a matrix re-read its last row (they are discarded later).  All offsets fit 32 bits (checked on the host).
+  TileLoader<RowMajorSource, HiddenSource, RowMajorHalf, RowMajorHalf, NARROW ? kNarrowBytes : kStepBytes> load = {
+      {}, {}, at, at, mine.lds};
+  load.a.base = reinterpret_cast<const char*>(W);
+  load.a.ld = ldw;
+  load.a.rows = V;
+  load.b.base = reinterpret_cast<const char*>(H) + (row_map != nullptr ? 0 : static_cast<int64_t>(t0) * ldh * 2);
+#pragma unroll
+  for (int h = 0; h < J / 2; ++h)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int r = min(h * 128 + at.row + 8 * e, tokens - 1);
+      const uint32_t row = (row_map != nullptr) ? static_cast<uint32_t>(row_map[t0 + r]) : static_cast<uint32_t>(r);
+      load.b.off[h][e] = row * static_cast<uint32_t>(ldh) * 2u + at.chunk[e];
+    }
+
+  float run_ref[J], run_sum[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
     run_ref[j] = kLmNone;
     run_sum[j] = 0.f;
   }
-
   // One finished tile.  Result register r of block i = 4 (half of the tile) + 16-row block, token block j = 2 (half) + block, is
   // vocabulary row 128 (i / 4) + 16 (i % 4) + 4 (lane / 16) + r from the wavefront's first, token 128 (j / 2) + 32 wn +
   // 16 (j % 2) + lane % 16.  RAGGED (the last vocabulary tile only): rows at or past V count as "no value".
-  auto epilogue = [&](auto ragged_tag, int vlane) {
+  auto epilogue = [&](auto ragged_tag, const TileAcc& acc, int vlane) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < J; ++j) {
       auto value = [&](int i, int r) -> float {
         if (RAGGED && vlane + (i >> 2) * 128 + (i & 3) * 16 + r >= V) return kLmNone;
         return acc[i >> 2][i & 3][j >> 1][j & 1][r];
@@ -437,37 +630,22 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-
-  matrix_begin(mine, n_steps > 0, [&](int half, int ahead) {
-    if (half == kHalfB0 && ahead == 1) advance();
-    request(half, vt_at[1], k_at[1], ahead);
-  });
-  if (n_steps > 0) advance();
-  int step = 0;
-  for (int vt = vt_begin; vt < vt_end; ++vt) {
-#pragma unroll
-    for (int i = 0; i < 32; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
-    for (int kt = 0; kt < nkp; ++kt, ++step) {
-      const int cur = step & 1;
-      const unsigned char* here = lm_smem + cur * kStepBytes;
-      matrix_step<false, false>(
-          acc, [&](int half, int i, int ks) { return at.a(here, half, i, ks); },
-          [&](int half, int j, int ks) { return at.b(here, half, j, ks); },
-          [&](int half, int ahead) { request(half, vt_at[ahead - 1], k_at[ahead - 1], ahead == 1 ? cur ^ 1 : cur); });
-      advance();
-    }
-    const int vlane = vt * kLmTile + mine.wm * 64 + ((lane >> 4) << 2);
-    if (vt * kLmTile + kLmTile > V) epilogue(std::true_type(), vlane);
-    else epilogue(std::false_type(), vlane);
-  }
-  matrix_end(mine);
+  const GemmTile first = {vt_begin * kLmTile, t0, 0, d / kLmK, 0};
+  matrix_tiles<false, NARROW>(
+      mine, smem, first, StripWalk{min(vt_end * kLmTile, V)}, load,
+      [&](const unsigned char* here, int half, int i, int ks) { return at.a(here, half, i, ks); },
+      [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
+      [&](const GemmTile& t, const TileAcc& acc) {
+        const int vlane = t.m0 + mine.wm * 64 + ((lane >> 4) << 2);
+        if (t.m0 + kLmTile > V) epilogue(std::true_type(), acc, vlane);
+        else epilogue(std::false_type(), acc, vlane);
+        return false;
+      });
 
   // the four groups of 16 lanes, then the two wavefronts that share these tokens, then one pair per token and strip
-  float2* ex = reinterpret_cast<float2*>(lm_smem + kLoopLdsBytes);
+  float2* ex = reinterpret_cast<float2*>(smem);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < J; ++j) {
     float m = run_ref[j], s = run_sum[j];
     const float m2 = __shfl_xor(m, 32), s2 = __shfl_xor(s, 32);
     lm_merge(m, s, m2, s2);
@@ -478,12 +656,61 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
     }
   }
   __syncthreads();
-  if (tid < kLmTile && t0 + tid < T) {
+  if (tid < min(tokens, J * 64)) {
     const float2 e0 = ex[tid], e1 = ex[kLmTile + tid];
     float m = e0.x, s = e0.y;
     lm_merge(m, s, e1.x, e1.y);
-    partial[static_cast<int64_t>(strip) * t_pad + t0 + tid] = make_float2(m, s);
+    pairs[tid] = make_float2(m, s);
   }
+}
+
+}  // namespace
+
+// The launch: `whole` token tiles of 256 in n_strips strips each, then, if tail_strips > 0, one more tile of at most 128 tokens
+// in strips of its own.  partial[strip * pitch + token] with pitch = 256 whole, behind them [strip * 128 + token] of the tail.
+__global__ void __launch_bounds__(kLmThreads)
+fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restrict__ H, int64_t ldh,
+                    int T, int V, int d, float2* __restrict__ partial, LmSplit split, int n_vocab_tiles,
+                    const int* __restrict__ row_map, const int* __restrict__ n_live) {
+  extern __shared__ __align__(16) unsigned char lm_smem[];
+  // Only the rows row_map[0 .. *n_live - 1] of H take part when a count is given (masked rows left out; the count stays
+  // on the device and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the
+  // loads.
+  if (n_live != nullptr) {
+    T = *n_live;
+    if (T <= 0) return;
+  }
+  // m: vocabulary strips, n: token tiles; each L2 serves up to 4 hidden tiles and 8 strips of the weight to 32 users
+  const unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), slot = (blockIdx.x >> 3) & 31;
+  const unsigned whole_groups = static_cast<unsigned>(tile_groups(split.strips, split.whole));
+  int strip, token_tile, strips = split.strips;
+  float2* pairs = partial;
+  if (group < whole_groups) {
+    // (tiles past the count are left out, and the others packed as if there were no more)
+    const int tiles = min(split.whole, (T + kLmTile - 1) / kLmTile);
+    const TilePlace place = tile_place<true>(group, slot, strips, tiles);
+    strip = place.m;
+    token_tile = place.n;
+    if (token_tile >= tiles) return;                       // whole workgroup, before any barrier
+    pairs += static_cast<int64_t>(strip) * (split.whole * kLmTile) + token_tile * kLmTile;
+  } else {
+    strip = static_cast<int>((group - whole_groups) * 32 + slot);
+    strips = split.tail_strips;
+    token_tile = split.whole;
+    pairs += static_cast<int64_t>(split.strips) * (split.whole * kLmTile) + strip * 128;
+  }
+  const int t0 = token_tile * kLmTile, tokens = T - t0;
+  if (strip >= strips || tokens <= 0) return;
+  const int vt_begin = static_cast<int>(static_cast<int64_t>(strip) * n_vocab_tiles / strips);
+  const int vt_end = static_cast<int>(static_cast<int64_t>(strip + 1) * n_vocab_tiles / strips);
+  if (vt_begin == vt_end) {                                // more strips than vocabulary tiles: pairs of nothing
+    if (static_cast<int>(threadIdx.x) < min(tokens, kLmTile)) pairs[threadIdx.x] = make_float2(kLmNone, 0.f);
+    return;
+  }
+  if (tokens > 128)
+    lm_strip<false>(lm_smem, W, ldw, H, ldh, tokens, V, d, t0, vt_begin, vt_end, row_map, pairs);
+  else
+    lm_strip<true>(lm_smem, W, ldw, H, ldh, tokens, V, d, t0, vt_begin, vt_end, row_map, pairs);
 }
 
 // One wavefront per token: the sampled token's logit as a dot product of two rows (fp32 products of
@@ -492,7 +719,7 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
 // rows were projected, row t as compact row ex[t] (ex[t] = unmasked rows before row t).
 __global__ void __launch_bounds__(256)
 fopd_k7_finish(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restrict__ H, int64_t ldh,
-               const float2* __restrict__ partial, int n_strips, int T, int V, int d, int64_t t_pad,
+               const float2* __restrict__ partial, LmSplit split, int T, int V, int d,
                const int32_t* __restrict__ token_ids, const uint8_t* __restrict__ mask,
                float* __restrict__ logp, float* __restrict__ lse, int32_t* flags, const int* __restrict__ ex) {
   const int lane = threadIdx.x & 63;
@@ -524,11 +751,14 @@ fopd_k7_finish(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restri
     for (int e = 0; e < 8; ++e) dot = fmaf(hx[e], wx[e], dot);
   }
   dot = wave_sum(dot);
-  // the strips' pairs: one per lane (up to 256 of them, at a distance of t_pad pairs), then across the wavefront
+  // the strips' pairs: one per lane (up to 256 of them, a token's at a distance of the tokens), then across the wavefront
   const int c = (ex != nullptr) ? ex[t] : t;             // the token's place among the rows that were projected
+  const bool in_tail = split.tail_strips > 0 && c >= split.whole * kLmTile;
+  const int n_strips = in_tail ? split.tail_strips : split.strips, pitch = in_tail ? 128 : split.whole * kLmTile;
+  const float2* pairs = partial + (in_tail ? static_cast<int64_t>(split.strips - 1) * (split.whole * kLmTile) : 0) + c;
   float m = kLmNone, s = 0.f;
   for (int k = lane; k < n_strips; k += 64) {
-    const float2 e = partial[static_cast<int64_t>(k) * t_pad + c];
+    const float2 e = pairs[static_cast<int64_t>(k) * pitch];
     lm_merge(m, s, e.x, e.y);
   }
 #pragma unroll

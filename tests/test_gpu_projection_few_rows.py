@@ -40,6 +40,26 @@ def test_log_probs_at_the_edges_of_tiles_and_groups(T, masked_every):
         assert np.max(np.abs(np64(lse) - ref_lse)) <= 1e-4 and np.max(np.abs(np64(logp) - ref_lp)) <= 1e-4
 
 
+@pytest.mark.parametrize("T", [64, 128, 129, 300, 384, 385, 600, 1100])
+@pytest.mark.parametrize("d", [64, 192])
+def test_log_probs_with_a_last_tile_of_few_tokens(T, d):
+    """A last tile of up to 128 tokens beside 0, 1, 2 or 4 whole ones, with strips of its own, and one token more; one and three
+    steps a vocabulary tile.  Half of the rows masked moves the last tile to another place than the launch was made for."""
+    w = wl.generate_lm_head(T, d, 20001, DEV, seed=T + d)
+    ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
+    half = torch.ones(T, dtype=torch.uint8, device=DEV)
+    half[::2] = 0
+    for mask in (None, half):
+        ref_lse, ref_lp = orc.lm_head_token_logprobs(np64(w["hidden"].float()), np64(w["weight"].float()),
+                                                     w["token_ids"].cpu().numpy(), None if mask is None else mask.cpu().numpy())
+        logp = torch.full((T,), 7.0, device=DEV)
+        lse = torch.full((T,), 7.0, device=DEV)
+        fb.fopd_lm_head_token_logprobs(w["hidden"], w["ldh"], w["weight"], w["ldw"], T, w["V"], w["d"],
+                                       w["token_ids"], mask, logp, lse, ws)
+        assert fb.fopd_workspace_status(ws) == (0, 0)
+        assert np.max(np.abs(np64(lse) - ref_lse)) <= 1e-4 and np.max(np.abs(np64(logp) - ref_lp)) <= 1e-4
+
+
 @pytest.mark.parametrize("seq,d,pad_h", [((1,), 64, 0), ((40, 25), 64, 2), ((100, 157), 320, 4), ((300, 214), 512, 3),
                                           ((500, 260), 320, 4), ((700, 500), 128, 0)])
 def test_gradients_with_the_vocabulary_cut_into_runs(seq, d, pad_h):
