@@ -157,11 +157,22 @@ def _ptr(x, dtype=None, name="argument"):
     return x.data_ptr()
 
 
+_raw_stream = None
+
+
+def _current_stream():
+    """Handle of torch's current stream on its current device.  torch.cuda.current_stream() builds an object for it, 2.8 us of a
+    call of 17.5 on a tiny batch; the number alone is 0.3 us."""
+    global _raw_stream
+    import torch
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
+
+
 def _stream(stream):
-    if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    return ctypes.c_void_p(int(stream))
+    return ctypes.c_void_p(_current_stream() if stream is None else int(stream))
 
 
 def _check(status, where):
