@@ -1208,12 +1208,15 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   if (workspace == nullptr || misaligned(workspace, 256) || workspace_bytes < lay.total) return FOPD_EWORKSPACE;
   if (T == 0) return FOPD_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  auto kern = fopd_k7_lm_head_lse;
-  static bool allowed[kMaxDevices] = {};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLmLdsBytes, allowed) != FOPD_OK) return FOPD_EHIP;
-  const int n_vocab_tiles = static_cast<int>((V + kLmTile - 1) / kLmTile);
-  const LmSplit split = lm_split(T, n_vocab_tiles);
-  const int64_t groups = tile_groups(split.strips, split.whole) + (split.tail_strips + 31) / 32;
+  const LmSplit split = lm_split(T, V);
+  auto kern = split.wide() ? fopd_k7_lm_head_lse<true> : fopd_k7_lm_head_lse<false>;
+  static bool allowed[2][kMaxDevices] = {};
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLmLdsBytes, allowed[split.wide() ? 1 : 0]) != FOPD_OK)
+    return FOPD_EHIP;
+  const int vocab_tile = split.wide() ? kLmTile / 2 : kLmTile;
+  const int n_vocab_tiles = static_cast<int>((V + vocab_tile - 1) / vocab_tile);
+  const int64_t groups = split.wide() ? (split.strips + 31) / 32
+                                      : tile_groups(split.strips, split.whole) + (split.tail_strips + 31) / 32;
   const unsigned grid = static_cast<unsigned>((groups + 7) / 8) * 256u;
   float2* partial = at<float2>(workspace, lay.partial);
   const __bf16* Wp = static_cast<const __bf16*>(weight);

@@ -329,7 +329,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   load.b.base = reinterpret_cast<const char*>(Bn);
   load.b.ld = ldb;
   load.b.rows = N;
-  matrix_tiles<true, false>(
+  matrix_tiles<true, 2, 2>(
       mine, gemm_smem, tile, walk, load,
       [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
@@ -382,7 +382,7 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   load.b.ld = ldb;
   load.b.rows = K;
   load.b.cols = (N + 7) >> 3;
-  matrix_tiles<true, false>(
+  matrix_tiles<true, 2, 2>(
       mine, gemm_smem, tile, walk, load,
       [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },

@@ -52,7 +52,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A wavefront's block of the result tile: [A half][16-row block of its 64][B half][16-row block of its 32].
-typedef f32x4 TileAcc[2][4][2][2];
+template <int A_HALVES, int B_HALVES>
+using BlockAcc = f32x4[A_HALVES][4][B_HALVES][2];
+typedef BlockAcc<2, 2> TileAcc;
 
 namespace {
 
@@ -141,18 +143,20 @@ __host__ inline int lm_strips(int n_token_tiles, int n_vocab_tiles) {
 }
 
 // Token tiles of fopd_k7_lm_head_lse: `whole` of them in `strips` strips each, and a last one of at most 128 tokens in
-// `tail_strips` (0: none).
+// `tail_strips` (0: none).  whole = tail_strips = 0: all tokens in one tile of at most 384 (wide).
 struct LmSplit {
   int whole, strips, tail_strips;
+  __host__ __device__ bool wide() const { return whole == 0 && tail_strips == 0; }
 };
 
 // A last tile of up to 128 tokens goes through a step in kNarrowCost of the time of a whole one, so few whole tiles and that one
 // share the chip best with strips of their own: all of them in one round, a group for each XCD, as long as the longer of the
 // two strips.  With more tiles the tail is one tile of many and has the strips of the others.  151,936 x 4096, us, all tiles whole /
-// so: 64 rows 318 / 260, 300 rows 510 / 465, 600 rows 847 / 680, 1100 rows 1480 / 1075, 1600 rows (a tail among seven) 1770 /
+// so: 64 rows 318 / 260, 600 rows 847 / 680, 1100 rows 1480 / 1075, 1600 rows (a tail among seven) 1770 /
 // 1620.
 constexpr double kNarrowCost = 0.6;
-__host__ inline LmSplit lm_split(int64_t T, int n_vocab_tiles) {
+__host__ inline LmSplit lm_split(int64_t T, int64_t V) {
+  const int n_vocab_tiles = static_cast<int>((V + kLmTile - 1) / kLmTile);
   const int tiles = static_cast<int>((T + kLmTile - 1) / kLmTile);
   const int tail = static_cast<int>(T - static_cast<int64_t>(tiles - 1) * kLmTile);
   LmSplit best = {tiles, lm_strips(tiles, n_vocab_tiles), 0};
@@ -161,6 +165,16 @@ __host__ inline LmSplit lm_split(int64_t T, int n_vocab_tiles) {
   if (tiles == 1) return {0, 0, std::min(256, (n_vocab_tiles + 31) / 32 * 32)};
   const int whole = tiles - 1, group_strips = 32 / tile_group_n(whole), groups_n = (whole + 3) / 4;
   double least = static_cast<double>(tile_rounds(best.strips, tiles, 1)) * steps(best.strips);
+  if (tiles == 2) {
+    // 257 to 384 tokens: as two tiles with strips of their own the projection matrix is read twice, at different times (2.5 GB at
+    // 5.4 TB/s).  In one tile of 128 x 384 a step has three products of four, for half the vocabulary rows.  As many strips as
+    // the pairs have room for, at most one a compute unit, in whole rounds.  151,936 x 4096, two tiles / one, us: 257 - 300 rows
+    // 462 / 412 (five rounds), 310 - 372 rows 470 - 485 / 450 (six), 384 rows 493 / 506 (seven, so two tiles).
+    const int vocab_tiles = static_cast<int>((V + kLmTile / 2 - 1) / (kLmTile / 2));
+    const int64_t most = std::min<int64_t>(256, (static_cast<int64_t>(kLmStrips) * tiles * kLmTile + kLmPairsExtra) / T);
+    const int rounds = static_cast<int>((vocab_tiles + most - 1) / most);
+    if (3.0 * rounds < 4.0 * least) return {0, (vocab_tiles + rounds - 1) / rounds, 0};
+  }
   for (int tail_groups = 1; tail_groups < 8; ++tail_groups) {
     const int strips = (8 - tail_groups) / groups_n * group_strips, tail_strips = 32 * tail_groups;
     if (strips <= 0 || strips > n_vocab_tiles || tail_strips > n_vocab_tiles) continue;
@@ -246,12 +260,12 @@ __device__ __forceinline__ void slot_end() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-enum { kHalfA0 = 0, kHalfA1 = 1, kHalfB0 = 2, kHalfB1 = 3 };
+enum { kHalfA0 = 0, kHalfA1 = 1, kHalfB0 = 2, kHalfB1 = 3, kHalfB2 = 1 };          // (places in a step's buffer)
 
 // B_FIRST: the B fragment is the matrix instruction's first operand (a lane then holds four B rows of one A row), else the A
 // fragment is.
-template <bool B_FIRST>
-__device__ __forceinline__ void multiply_phase(TileAcc& acc, int a, int b, const bf16x8 (&fa)[4][2],
+template <bool B_FIRST, int A_HALVES, int B_HALVES>
+__device__ __forceinline__ void multiply_phase(BlockAcc<A_HALVES, B_HALVES>& acc, int a, int b, const bf16x8 (&fa)[4][2],
                                                const bf16x8 (&fb)[2][2]) {
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -283,7 +297,7 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   request(kHalfA1);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST>(acc, 0, 0, fa, fb0);
+  multiply_phase<B_FIRST, 2, 2>(acc, 0, 0, fa, fb0);
   slot_end();
 #pragma unroll
   for (int j = 0; j < 2; ++j)
@@ -293,7 +307,7 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63) lgkmcnt(0)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST>(acc, 0, 1, fa, fb1);
+  multiply_phase<B_FIRST, 2, 2>(acc, 0, 1, fa, fb1);
   slot_end();
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -302,13 +316,13 @@ __device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB re
   request(kHalfA0);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST>(acc, 1, 1, fa, fb1);
+  multiply_phase<B_FIRST, 2, 2>(acc, 1, 1, fa, fb1);
   slot_end();
   request(kHalfB1);
   if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST>(acc, 1, 0, fa, fb0);
+  multiply_phase<B_FIRST, 2, 2>(acc, 1, 0, fa, fb0);
   slot_end();
 }
 
@@ -335,7 +349,7 @@ __device__ __forceinline__ void matrix_begin(const MatrixPlace& place, Request r
 //     2     A1         A1 x B0      B0, A0 of the next but two      B0, A0 of the next step  (6 stay in flight)
 //
 template <bool B_FIRST, typename ReadA, typename ReadB, typename Request>
-__device__ __forceinline__ void matrix_step_narrow(TileAcc& acc, ReadA read_a, ReadB read_b, Request request) {
+__device__ __forceinline__ void matrix_step_narrow(BlockAcc<2, 1>& acc, ReadA read_a, ReadB read_b, Request request) {
   bf16x8 fa[4][2], fb[2][2];
 #pragma unroll
   for (int j = 0; j < 2; ++j)
@@ -355,7 +369,7 @@ __device__ __forceinline__ void matrix_step_narrow(TileAcc& acc, ReadA read_a, R
     }
     asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
     slot_end();
-    multiply_phase<B_FIRST>(acc, a, 0, fa, fb);
+    multiply_phase<B_FIRST, 2, 1>(acc, a, 0, fa, fb);
     slot_end();
   }
 }
@@ -369,6 +383,57 @@ __device__ __forceinline__ void matrix_begin_narrow(const MatrixPlace& place, Re
     if (buf < 2) request(kHalfA1, buf);
   }
   asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+  slot_end();
+  if (place.wm == 1) slot_end();
+}
+
+// The same for a tile of 128 rows of A and up to 384 of B (B2 in the place of A1), three phases a step:
+//
+//   phase   reads      multiplies   requests                     waits for (besides its own LDS reads)
+//     1     A0, B0     A0 x B0      B2 of the next step          B1 of this step           (5 half tiles stay in flight)
+//     2     B1         A0 x B1      A0, B0 of the next but one   B2 of this step           (6 stay in flight)
+//     3     B2         A0 x B2      B1 of the next but one       A0, B0 of the next step   (5 stay in flight)
+//
+template <bool B_FIRST, typename ReadA, typename ReadB, typename Request>
+__device__ __forceinline__ void matrix_step_wide(BlockAcc<1, 3>& acc, ReadA read_a, ReadB read_b, Request request) {
+  bf16x8 fa[4][2], fb[2][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(0, i, ks);
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) fb[j][ks] = read_b(b < 2 ? b : -1, j, ks);
+    if (b == 0) {
+      request(kHalfB2);
+      asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
+    } else if (b == 1) {
+      request(kHalfA0);
+      request(kHalfB0);
+      asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
+    } else {
+      request(kHalfB1);
+      asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
+    }
+    slot_end();
+    multiply_phase<B_FIRST, 1, 3>(acc, 0, b, fa, fb);
+    slot_end();
+  }
+}
+
+template <typename Request>
+__device__ __forceinline__ void matrix_begin_wide(const MatrixPlace& place, Request request) {
+#pragma unroll
+  for (int buf = 0; buf < 2; ++buf) {
+    request(kHalfA0, buf);
+    request(kHalfB0, buf);
+    request(kHalfB1, buf);
+    if (buf == 0) request(kHalfB2, buf);
+  }
+  asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
   slot_end();
   if (place.wm == 1) slot_end();
 }
@@ -434,7 +499,7 @@ struct RowMajorSource {
   }
 };
 
-template <typename A, typename B, typename AtA, typename AtB, int STEP_BYTES = kStepBytes>
+template <typename A, typename B, typename AtA, typename AtB, int STEP_BYTES = kStepBytes, bool WIDE = false>
 struct TileLoader {
   A a;
   B b;
@@ -452,8 +517,8 @@ struct TileLoader {
   }
   __device__ __forceinline__ void request(int half, int buf) {
     const uint32_t dst = lds + buf * STEP_BYTES + half * kHalfBytes;
-    if (half < 2) a.request(half, dst);
-    else b.request(half - 2, dst);
+    if (half < (WIDE ? 1 : 2)) a.request(half, dst);
+    else b.request(half == kHalfB2 ? 2 : half - 2, dst);
   }
 };
 
@@ -466,8 +531,8 @@ struct TileLoader {
 //   load.request(half, buf)  the wavefront's two loads of a half tile into a step buffer
 //   store(tile, acc)         what to do with a finished tile; returns whether it left at least 63 stores behind the requests and
 //                            waited for none
-// NARROW: tiles of up to 128 rows of B (matrix_step_narrow).
-template <bool B_FIRST, bool NARROW, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
+// A_HALVES x B_HALVES: 2 x 2, 2 x 1 (matrix_step_narrow) or 1 x 3 (matrix_step_wide).
+template <bool B_FIRST, int A_HALVES, int B_HALVES, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
 __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
                                              Loader& load, ReadA read_a, ReadB read_b, Store store) {
   GemmTile ahead_tile = tile;
@@ -484,29 +549,36 @@ __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsi
       left = 1;                                            // the last step again, never read
     }
   };
+  constexpr bool kNarrow = B_HALVES == 1, kWide = B_HALVES == 3;
+  constexpr int kLast = 1;                                 // A1, or with three B halves B2: the last half tile of a step
   auto request_from = [&](int half, int buf) {
     load.request(half, buf);
-    if (half == kHalfA1) advance();
+    if (half == kLast) advance();
   };
-  if constexpr (NARROW) matrix_begin_narrow(mine, request_from);
+  if constexpr (kNarrow) matrix_begin_narrow(mine, request_from);
+  else if constexpr (kWide) matrix_begin_wide(mine, request_from);
   else matrix_begin(mine, request_from);
   int cur = 0;                                             // the step's buffer
   bool stored = false;
-  TileAcc acc;
+  BlockAcc<A_HALVES, B_HALVES> acc;
   while (true) {
 #pragma unroll
-    for (int i = 0; i < 32; ++i)
+    for (int h = 0; h < A_HALVES; ++h)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 2) & 3][(i >> 1) & 1][i & 1][r] = 0.f;
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int b = 0; b < B_HALVES; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[h][i][b][0][r] = acc[h][i][b][1][r] = 0.f;
     auto run = [&](auto stored_tag, auto switch_tag) {
-      constexpr int kBufs = NARROW ? 3 : 2;
-      const unsigned char* here = smem + cur * (NARROW ? kNarrowBytes : kStepBytes);
+      constexpr int kBufs = kNarrow ? 3 : 2;
+      const unsigned char* here = smem + cur * (kNarrow ? kNarrowBytes : kStepBytes);
       const int before = cur == 0 ? kBufs - 1 : cur - 1;
       auto a = [&](int half, int i, int ks) { return read_a(here, half, i, ks); };
       auto b = [&](int half, int j, int ks) { return read_b(here, half, j, ks); };
-      auto request = [&](int half) {                       // A1 is a buffer behind the other half tiles
-        load.request(half, half == kHalfA1 ? before : cur);
-        if (half == kHalfA1) {
+      auto request = [&](int half) {                       // a step's last half tile is a buffer behind the others
+        load.request(half, half == kLast ? before : cur);
+        if (half == kLast) {
           if constexpr (decltype(switch_tag)::value) {
             advance();
           } else {
@@ -515,7 +587,8 @@ __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsi
           }
         }
       };
-      if constexpr (NARROW) matrix_step_narrow<B_FIRST>(acc, a, b, request);
+      if constexpr (kNarrow) matrix_step_narrow<B_FIRST>(acc, a, b, request);
+      else if constexpr (kWide) matrix_step_wide<B_FIRST>(acc, a, b, request);
       else matrix_step<B_FIRST, decltype(stored_tag)::value>(acc, a, b, request);
       cur = cur == kBufs - 1 ? 0 : cur + 1;
     };
@@ -546,10 +619,10 @@ namespace {
 
 // The vocabulary tiles of a strip, one after the other.
 struct StripWalk {
-  int end;                     // first vocabulary row past the strip
+  int end, tile;               // first vocabulary row past the strip; rows of a tile
   __device__ __forceinline__ bool next(GemmTile& t) const {
-    if (t.m0 + kLmTile >= end) return false;
-    t.m0 += kLmTile;
+    if (t.m0 + tile >= end) return false;
+    t.m0 += tile;
     return true;
   }
 };
@@ -558,7 +631,7 @@ struct StripWalk {
 struct HiddenSource {
   const char* base;
   const char* src;
-  uint32_t off[2][2];
+  uint32_t off[3][2];
   __device__ __forceinline__ void locate(const RowMajorHalf&, int, int64_t) { src = base; }
   __device__ __forceinline__ void step() { src += 2 * kLmK; }
   __device__ __forceinline__ void request(int half, uint32_t dst) {
@@ -567,18 +640,21 @@ struct HiddenSource {
   }
 };
 
-// One strip of the vocabulary for the up to 256 (NARROW: 128) tokens of a tile: pair (reference, sum) of token i to pairs[i].
-template <bool NARROW>
+// One strip of the vocabulary for the up to 128 B_HALVES tokens of a tile: pair (reference, sum) of token i to pairs[i].  The
+// strip's vocabulary tiles have 128 A_HALVES rows.
+template <int A_HALVES, int B_HALVES>
 __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __restrict__ W, int64_t ldw,
                                          const __bf16* __restrict__ H, int64_t ldh, int tokens, int V, int d, int t0,
                                          int vt_begin, int vt_end, const int* __restrict__ row_map,
                                          float2* __restrict__ pairs) {
-  constexpr int J = NARROW ? 2 : 4;                        // 16-token blocks of a wavefront
+  constexpr int J = 2 * B_HALVES;                          // 16-token blocks of a wavefront
+  constexpr int kTile = 128 * A_HALVES;
   const int tid = threadIdx.x, lane = tid & 63;
   const MatrixPlace mine = matrix_place(smem);
   const RowMajorHalf at(mine);
   // Rows past the end of a matrix re-read its last row (they are discarded later).  All offsets fit 32 bits (checked on the host).
-  TileLoader<RowMajorSource, HiddenSource, RowMajorHalf, RowMajorHalf, NARROW ? kNarrowBytes : kStepBytes> load = {
+  TileLoader<RowMajorSource, HiddenSource, RowMajorHalf, RowMajorHalf, B_HALVES == 1 ? kNarrowBytes : kStepBytes, B_HALVES == 3>
+      load = {
       {}, {}, at, at, mine.lds};
   load.a.base = reinterpret_cast<const char*>(W);
   load.a.ld = ldw;
@@ -602,7 +678,7 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
   // One finished tile.  Result register r of block i = 4 (half of the tile) + 16-row block, token block j = 2 (half) + block, is
   // vocabulary row 128 (i / 4) + 16 (i % 4) + 4 (lane / 16) + r from the wavefront's first, token 128 (j / 2) + 32 wn +
   // 16 (j % 2) + lane % 16.  RAGGED (the last vocabulary tile only): rows at or past V count as "no value".
-  auto epilogue = [&](auto ragged_tag, const TileAcc& acc, int vlane) {
+  auto epilogue = [&](auto ragged_tag, const BlockAcc<A_HALVES, B_HALVES>& acc, int vlane) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -612,7 +688,7 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
       };
       float mx = run_ref[j];
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 4 * A_HALVES; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) mx = fmaxf(mx, value(i, r));
       // a lane that has seen no value yet (only in a tile that hangs over the vocabulary's end) keeps
@@ -622,7 +698,7 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
       __builtin_amdgcn_sched_barrier(0);
       float part[4] = {0.f, 0.f, 0.f, 0.f};            // four short chains, added as a tree
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 4 * A_HALVES; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) part[i & 3] += fast_exp2(fmaf(value(i, r), kLog2e, -mref));
       run_ref[j] = mx;
@@ -630,14 +706,14 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  const GemmTile first = {vt_begin * kLmTile, t0, 0, d / kLmK, 0};
-  matrix_tiles<false, NARROW>(
-      mine, smem, first, StripWalk{min(vt_end * kLmTile, V)}, load,
+  const GemmTile first = {vt_begin * kTile, t0, 0, d / kLmK, 0};
+  matrix_tiles<false, A_HALVES, B_HALVES>(
+      mine, smem, first, StripWalk{min(vt_end * kTile, V), kTile}, load,
       [&](const unsigned char* here, int half, int i, int ks) { return at.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
-      [&](const GemmTile& t, const TileAcc& acc) {
+      [&](const GemmTile& t, const BlockAcc<A_HALVES, B_HALVES>& acc) {
         const int vlane = t.m0 + mine.wm * 64 + ((lane >> 4) << 2);
-        if (t.m0 + kLmTile > V) epilogue(std::true_type(), acc, vlane);
+        if (t.m0 + kTile > V) epilogue(std::true_type(), acc, vlane);
         else epilogue(std::false_type(), acc, vlane);
         return false;
       });
@@ -652,12 +728,12 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
     const float m3 = __shfl_xor(m, 16), s3 = __shfl_xor(s, 16);
     if (lane < 16) {
       lm_merge(m, s, m3, s3);
-      ex[mine.wm * kLmTile + (j >> 1) * 128 + mine.wn * 32 + (j & 1) * 16 + lane] = make_float2(m, s);
+      ex[mine.wm * 64 * J + (j >> 1) * 128 + mine.wn * 32 + (j & 1) * 16 + lane] = make_float2(m, s);
     }
   }
   __syncthreads();
   if (tid < min(tokens, J * 64)) {
-    const float2 e0 = ex[tid], e1 = ex[kLmTile + tid];
+    const float2 e0 = ex[tid], e1 = ex[64 * J + tid];
     float m = e0.x, s = e0.y;
     lm_merge(m, s, e1.x, e1.y);
     pairs[tid] = make_float2(m, s);
@@ -666,13 +742,17 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
 
 }  // namespace
 
-// The launch: `whole` token tiles of 256 in n_strips strips each, then, if tail_strips > 0, one more tile of at most 128 tokens
+// The launch: `whole` token tiles of 256 in `strips` strips each, then, if tail_strips > 0, one more tile of at most 128 tokens
 // in strips of its own.  partial[strip * pitch + token] with pitch = 256 whole, behind them [strip * 128 + token] of the tail.
+// WIDE (no whole tiles, no tail; a kernel of its own, the code of the others is 2 % slower with it): all tokens in one tile of at
+// most 384, strips of 128-row vocabulary tiles, pitch T of the call.
+template <bool WIDE>
 __global__ void __launch_bounds__(kLmThreads)
 fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restrict__ H, int64_t ldh,
                     int T, int V, int d, float2* __restrict__ partial, LmSplit split, int n_vocab_tiles,
                     const int* __restrict__ row_map, const int* __restrict__ n_live) {
   extern __shared__ __align__(16) unsigned char lm_smem[];
+  const int pitch = WIDE ? T : split.whole * kLmTile;
   // Only the rows row_map[0 .. *n_live - 1] of H take part when a count is given (masked rows left out; the count stays
   // on the device and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the
   // loads.
@@ -682,6 +762,14 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
   }
   // m: vocabulary strips, n: token tiles; each L2 serves up to 4 hidden tiles and 8 strips of the weight to 32 users
   const unsigned group = ((blockIdx.x >> 8) << 3) + (blockIdx.x & 7), slot = (blockIdx.x >> 3) & 31;
+  if constexpr (WIDE) {
+    const int strip = static_cast<int>(group * 32 + slot);
+    if (strip >= split.strips) return;                     // whole workgroup, before any barrier
+    const int vt_begin = static_cast<int>(static_cast<int64_t>(strip) * n_vocab_tiles / split.strips);
+    const int vt_end = static_cast<int>(static_cast<int64_t>(strip + 1) * n_vocab_tiles / split.strips);
+    lm_strip<1, 3>(lm_smem, W, ldw, H, ldh, T, V, d, 0, vt_begin, vt_end, row_map, partial + static_cast<int64_t>(strip) * pitch);
+    return;
+  }
   const unsigned whole_groups = static_cast<unsigned>(tile_groups(split.strips, split.whole));
   int strip, token_tile, strips = split.strips;
   float2* pairs = partial;
@@ -692,7 +780,7 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
     strip = place.m;
     token_tile = place.n;
     if (token_tile >= tiles) return;                       // whole workgroup, before any barrier
-    pairs += static_cast<int64_t>(strip) * (split.whole * kLmTile) + token_tile * kLmTile;
+    pairs += static_cast<int64_t>(strip) * pitch + token_tile * kLmTile;
   } else {
     strip = static_cast<int>((group - whole_groups) * 32 + slot);
     strips = split.tail_strips;
@@ -708,9 +796,9 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
     return;
   }
   if (tokens > 128)
-    lm_strip<false>(lm_smem, W, ldw, H, ldh, tokens, V, d, t0, vt_begin, vt_end, row_map, pairs);
+    lm_strip<2, 2>(lm_smem, W, ldw, H, ldh, tokens, V, d, t0, vt_begin, vt_end, row_map, pairs);
   else
-    lm_strip<true>(lm_smem, W, ldw, H, ldh, tokens, V, d, t0, vt_begin, vt_end, row_map, pairs);
+    lm_strip<2, 1>(lm_smem, W, ldw, H, ldh, tokens, V, d, t0, vt_begin, vt_end, row_map, pairs);
 }
 
 // One wavefront per token: the sampled token's logit as a dot product of two rows (fp32 products of
@@ -754,7 +842,7 @@ fopd_k7_finish(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restri
   // the strips' pairs: one per lane (up to 256 of them, a token's at a distance of the tokens), then across the wavefront
   const int c = (ex != nullptr) ? ex[t] : t;             // the token's place among the rows that were projected
   const bool in_tail = split.tail_strips > 0 && c >= split.whole * kLmTile;
-  const int n_strips = in_tail ? split.tail_strips : split.strips, pitch = in_tail ? 128 : split.whole * kLmTile;
+  const int n_strips = in_tail ? split.tail_strips : split.strips, pitch = in_tail ? 128 : (split.whole > 0 ? split.whole * kLmTile : T);
   const float2* pairs = partial + (in_tail ? static_cast<int64_t>(split.strips - 1) * (split.whole * kLmTile) : 0) + c;
   float m = kLmNone, s = 0.f;
   for (int k = lane; k < n_strips; k += 64) {

@@ -41,11 +41,12 @@ def test_log_probs_at_the_edges_of_tiles_and_groups(T, masked_every):
 
 
 @pytest.mark.parametrize("T", [64, 128, 129, 300, 384, 385, 600, 1100])
-@pytest.mark.parametrize("d", [64, 192])
-def test_log_probs_with_a_last_tile_of_few_tokens(T, d):
-    """A last tile of up to 128 tokens beside 0, 1, 2 or 4 whole ones, with strips of its own, and one token more; one and three
-    steps a vocabulary tile.  Half of the rows masked moves the last tile to another place than the launch was made for."""
-    w = wl.generate_lm_head(T, d, 20001, DEV, seed=T + d)
+@pytest.mark.parametrize("d,V", [(64, 20001), (192, 20001), (128, 100), (64, 385)])
+def test_log_probs_with_a_last_tile_of_few_tokens(T, d, V):
+    """A last tile of up to 128 tokens beside 0, 2 or 4 whole ones, with strips of its own, and one token more; beside one, all
+    tokens in one tile; one to three steps a vocabulary tile, vocabularies of less than a tile and of an entry more than whole
+    ones.  Half of the rows masked moves the last tile to another place than the launch was made for."""
+    w = wl.generate_lm_head(T, d, V, DEV, seed=T + d)
     ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
     half = torch.ones(T, dtype=torch.uint8, device=DEV)
     half[::2] = 0
