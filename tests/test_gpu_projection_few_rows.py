@@ -84,3 +84,19 @@ def test_gradients_at_the_line_between_the_two_layouts_of_the_projection_matrix(
     scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
     out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, 4160, scores)
     _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)
+
+
+@pytest.mark.parametrize("seq,d", [((40, 23), 64), ((40, 24), 128), ((70, 58, 1), 64), ((90, 110), 192), ((330, 200), 64)])
+def test_gradients_with_more_result_tiles_than_workgroups(seq, d):
+    """274 vocabulary tiles, the last with 113 entries: workgroups walk from one tile to the next, which changes after every step
+    (64 hidden elements, 64 rows), every second or third, or later.  A third of the rows masked, the first sample gated out: the
+    hidden rows of the others are gathered and transposed, 64 to 128 of them or a few more than 128."""
+    T = sum(seq)
+    h = wl.generate_lm_head(T, d, 70001, DEV, seed=T + d, masked_every=3)
+    w = wl.attach_loss_inputs(h, seq, [45] + [1] * (len(seq) - 1), seed=T)
+    scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
+    out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, (T + 63) // 64 * 64, scores, pad_w=4)
+    _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)
+    first = torch.zeros(70001, d, device=DEV)
+    again = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, (T + 63) // 64 * 64, scores, accumulate=True, dweight=first)
+    assert torch.equal(again["dweight"], out["dweight"])

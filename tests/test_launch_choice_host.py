@@ -104,6 +104,15 @@ int main() {
         }
       std::printf("order %d %d %d %d\n", hidden, vocab, seen, most);
     }
+  for (int T = 1; T <= 4200; T += T < 1400 ? 1 : 7)
+    for (int V : {100, 385, 20001, 32000, 151936}) {
+      const LmSplit s = lm_split(T, V);
+      const long tiles = (T + 255) / 256, room = 32 * tiles * 256 + kLmPairsExtra;
+      const long pairs = s.wide() ? (long)s.strips * T : (long)s.strips * s.whole * 256 + (long)s.tail_strips * 128;
+      const long covered = s.wide() ? 384 : s.whole * 256L + (s.tail_strips > 0 ? 128 : 0);
+      std::printf("split %d %d %d %ld %ld %ld %d\n", T, V, s.wide() || s.whole > 0 ? s.strips : s.tail_strips, room, pairs, covered,
+                  (int)(s.wide() ? s.strips <= (V + 127) / 128 : 1));
+    }
   for (int m : {1, 2, 4, 7, 8, 9, 16, 33, 594})
     for (int n : {1, 2, 3, 4, 5, 8, 64, 594})
       for (int splits : {1, 3, 8})
@@ -149,3 +158,11 @@ def test_tiles_of_the_weight_gradient_are_spread_evenly(choices):
 
 def test_walking_workgroups_take_every_tile_once(choices):
     assert sum(r[0] == "walk" for r in choices) == 9 * 8 * 3 * 2           # the program stops at one that does not
+
+
+def test_strips_of_whole_narrow_and_wide_token_tiles(choices):
+    rows = [[int(x) for x in r[1:]] for r in choices if r[0] == "split"]
+    assert len(rows) > 5000
+    for T, V, strips, room, pairs, covered, filled in rows:
+        assert strips >= 1 and covered >= T and filled, (T, V)
+        assert pairs <= room, (T, V)                         # the workspace has so many (reference, sum) pairs
