@@ -1210,8 +1210,10 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   hipStream_t s = static_cast<hipStream_t>(stream);
   const LmSplit split = lm_split(T, V);
   auto kern = split.wide() ? fopd_k7_lm_head_lse<true> : fopd_k7_lm_head_lse<false>;
+  // both kernels at the first call, whichever it takes: one call of any size before a capture is enough
   static bool allowed[2][kMaxDevices] = {};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLmLdsBytes, allowed[split.wide() ? 1 : 0]) != FOPD_OK)
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(fopd_k7_lm_head_lse<false>), kLmLdsBytes, allowed[0]) != FOPD_OK ||
+      allow_dynamic_lds(reinterpret_cast<const void*>(fopd_k7_lm_head_lse<true>), kLmLdsBytes, allowed[1]) != FOPD_OK)
     return FOPD_EHIP;
   const int vocab_tile = split.wide() ? kLmTile / 2 : kLmTile;
   const int n_vocab_tiles = static_cast<int>((V + vocab_tile - 1) / vocab_tile);
@@ -1222,20 +1224,23 @@ fopd_status fopd_lm_head_token_logprobs(const void* hidden, int64_t ldh, const v
   const __bf16* Wp = static_cast<const __bf16*>(weight);
   const __bf16* Hp = static_cast<const __bf16*>(hidden);
   // Masked rows have no log-prob: with a mask only the other rows are projected.  Their count stays on the device;
-  // the kernel gathers them through a row map as it loads and leaves out the token tiles past the count.
+  // the kernel gathers them through a row map as it loads and leaves out the token tiles past the count.  Without that option
+  // every row is projected; where the last tile has strips of its own, in the same order (the masked rows behind the others), so
+  // that an unmasked row is in the same tile, summed over the same strips, either way.
   int32_t *ex = nullptr, *row_map = nullptr, *n_live = nullptr;
-  if (mask != nullptr && current_options().lm_head_compact != 0) {
+  const bool compact = current_options().lm_head_compact != 0;
+  if (mask != nullptr && (compact || (split.whole > 0 && split.tail_strips > 0))) {
     ex = at<int32_t>(workspace, lay.ex);
     row_map = at<int32_t>(workspace, lay.row_map);
     n_live = at<int32_t>(workspace, lay.n_live);
     fopd_live_scan<<<1, kLiveScanThreads, 0, s>>>(mask, nullptr, nullptr, static_cast<int>(T), nullptr, -1, 0, ex, row_map,
-                                                  n_live, nullptr, nullptr);
+                                                  n_live, nullptr, nullptr, !compact);
     if (launched() != FOPD_OK) return FOPD_EHIP;
   }
   {
     ScopedTimer timer(3, s);
     kern<<<dim3(grid), dim3(kLmThreads), kLmLdsBytes, s>>>(Wp, ldw, Hp, ldh, static_cast<int>(T), static_cast<int>(V),
-                                                    static_cast<int>(d), partial, split, n_vocab_tiles, row_map, n_live);
+                                                    static_cast<int>(d), partial, split, n_vocab_tiles, row_map, compact ? n_live : nullptr);
   }
   if (launched() != FOPD_OK) return FOPD_EHIP;
   fopd_k7_finish<<<dim3(static_cast<unsigned>((T + 3) / 4)), dim3(256), 0, s>>>(
@@ -1508,7 +1513,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
   if (global_rows) {
     fopd_live_scan<<<1, kLiveScanThreads, 0, s>>>(mask, nullptr, nullptr, static_cast<int>(T), cu, B, 0, ex, row_map,
-                                                  n_live, cu_c, keep);
+                                                  n_live, cu_c, keep, false);
     if ((st = launched()) != FOPD_OK) return st;
   }
   if (compact && (mask != nullptr || keep != nullptr)) {
@@ -1555,7 +1560,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if (compact) {
       if (!global_rows) {
         fopd_live_scan<<<1, kLiveScanThreads, 0, s>>>(msk, nullptr, nullptr, static_cast<int>(R), cu, B, a, ex, row_map,
-                                                      n_live, cu_c, nullptr);
+                                                      n_live, cu_c, nullptr, false);
         if ((st = launched()) != FOPD_OK) return st;
       }
       fopd_live_gather<<<static_cast<unsigned>(R), 256, 0, s>>>(
@@ -1647,7 +1652,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
     if (compact) {
       fopd_live_scan<<<1, kLiveScanThreads, 0, s>>>(nullptr, coef, (listed != nullptr) ? c2 : nullptr,
                                                     static_cast<int>(R), nullptr, -1, 0, grad_ex, grad_map, n_grad,
-                                                    nullptr, nullptr);
+                                                    nullptr, nullptr, false);
       if ((st = launched()) != FOPD_OK) return st;
       gex = grad_ex;
       live = n_grad;
@@ -1710,7 +1715,7 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
                                                                             keep);
       if ((st = launched()) != FOPD_OK) return st;
       fopd_live_scan<<<1, kLiveScanThreads, 0, s>>>(mask, nullptr, nullptr, static_cast<int>(T), cu, B, 0, ex, row_map,
-                                                    n_live, cu_c, keep);
+                                                    n_live, cu_c, keep, false);
       if ((st = launched()) != FOPD_OK) return st;
       if (grads) {
         st = in_slabs(T, [&](int64_t a, int64_t n) {

@@ -538,13 +538,13 @@ fopd_sample_keep(const double* __restrict__ fresh64, const float* __restrict__ f
 // One workgroup.  A row is live if coef != NULL ? (coef[j] != 0 or, with coef2, coef2[j] != 0) : (mask == NULL ||
 // mask[j] != 0) and, with keep, keep[sample of row row_begin + j] != 0; mask / coef / coef2 point at the chunk's
 // first row.  ex[j] = live rows before chunk row j, j = 0 .. R; row_map[c] = chunk row of compact row c
-// (row_map may be NULL); n_live[0] = ex[R]; cu_c[i] = ex[clamp(cu[i] - row_begin, 0, R)], i = 0 .. B: the samples'
-// offsets among the chunk's live rows (B < 0: none wanted).
+// (row_map may be NULL; with rest_too the other rows follow in it, the last first); n_live[0] = ex[R]; cu_c[i] =
+// ex[clamp(cu[i] - row_begin, 0, R)], i = 0 .. B: the samples' offsets among the chunk's live rows (B < 0: none wanted).
 __global__ void __launch_bounds__(kLiveScanThreads)
 fopd_live_scan(const uint8_t* __restrict__ mask, const float* __restrict__ coef, const float* __restrict__ coef2, int R,
                const int64_t* __restrict__ cu,
                int B, int64_t row_begin, int* __restrict__ ex, int* __restrict__ row_map, int* __restrict__ n_live,
-               int64_t* __restrict__ cu_c, const int* __restrict__ keep) {
+               int64_t* __restrict__ cu_c, const int* __restrict__ keep, bool rest_too) {
   __shared__ int wave_total[kLiveScanThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   auto is_live = [&](int j) {
@@ -573,6 +573,7 @@ fopd_live_scan(const uint8_t* __restrict__ mask, const float* __restrict__ coef,
       const int at = run + before_wave + before_lane;
       ex[j] = at;
       if (live && row_map != nullptr) row_map[at] = static_cast<int>(j);
+      if (!live && rest_too) row_map[R - 1 - (j - at)] = static_cast<int>(j);
     }
     run += all;
     __syncthreads();                                         // before the totals are overwritten

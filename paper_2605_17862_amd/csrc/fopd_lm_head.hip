@@ -755,7 +755,7 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
   const int pitch = WIDE ? T : split.whole * kLmTile;
   // Only the rows row_map[0 .. *n_live - 1] of H take part when a count is given (masked rows left out; the count stays
   // on the device and the launch covers all T): token tile c holds compact rows 256 c .. 256 c + 255, gathered by the
-  // loads.
+  // loads.  (A row map without a count holds all T rows.)
   if (n_live != nullptr) {
     T = *n_live;
     if (T <= 0) return;
@@ -803,8 +803,8 @@ fopd_k7_lm_head_lse(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __r
 
 // One wavefront per token: the sampled token's logit as a dot product of two rows (fp32 products of
 // bf16 are exact, the sum is fp32), then the merge of the strip pairs.  lp is clamped at 0 because
-// this dot product and the matrix cores sum the same products in different orders.  ex != NULL: only the unmasked
-// rows were projected, row t as compact row ex[t] (ex[t] = unmasked rows before row t).
+// this dot product and the matrix cores sum the same products in different orders.  ex != NULL: the unmasked rows were
+// projected first or alone, row t as compact row ex[t] (ex[t] = unmasked rows before row t).
 __global__ void __launch_bounds__(256)
 fopd_k7_finish(const __bf16* __restrict__ W, int64_t ldw, const __bf16* __restrict__ H, int64_t ldh,
                const float2* __restrict__ partial, LmSplit split, int T, int V, int d,

@@ -61,6 +61,26 @@ def test_log_probs_with_a_last_tile_of_few_tokens(T, d, V):
         assert np.max(np.abs(np64(lse) - ref_lse)) <= 1e-4 and np.max(np.abs(np64(logp) - ref_lp)) <= 1e-4
 
 
+@pytest.mark.parametrize("T,masked_every", [(300, 2), (600, 2), (600, 3), (1100, 9)])
+def test_masked_rows_left_out_or_projected_give_the_same_bits(T, masked_every):
+    """Few whole tiles and a last one with strips of its own (600, 1100 rows), or all tokens in one tile: an unmasked row is
+    summed over the same strips whether the masked rows are projected or not."""
+    w = wl.generate_lm_head(T, 64, 20001, DEV, seed=T, masked_every=masked_every)
+    ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
+    out = {}
+    try:
+        for compact in (0, 1):
+            fb.fopd_set_option("lm_head_compact", compact)
+            logp, lse = torch.full((T,), 7.0, device=DEV), torch.full((T,), 7.0, device=DEV)
+            fb.fopd_lm_head_token_logprobs(w["hidden"], w["ldh"], w["weight"], w["ldw"], T, w["V"], w["d"],
+                                           w["token_ids"], w["mask"], logp, lse, ws)
+            out[compact] = (logp, lse)
+    finally:
+        fb.fopd_set_option("lm_head_compact", 1)
+    assert not bool(out[0][0][w["mask"] == 0].any())
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("seq,d,pad_h", [((1,), 64, 0), ((40, 25), 64, 2), ((100, 157), 320, 4), ((300, 214), 512, 3),
                                           ((500, 260), 320, 4), ((700, 500), 128, 0)])
 def test_gradients_with_the_vocabulary_cut_into_runs(seq, d, pad_h):
