@@ -60,6 +60,15 @@ inline int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
   return best;
 }
 
+// A value that is the same in every lane, for a scalar register.
+__host__ __device__ __forceinline__ int uniform(int x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_readfirstlane(x);
+#else
+  return x;
+#endif
+}
+
 // The wavefront's part of a finished tile, rows n0 .. , columns m0 .. of Out.  The n-side fragment is the matrix
 // instruction's first operand, so register r of acc[a][i][b][j] is output row n = 128 b + 32 wn + 16 j + 4 (lane / 16) + r of
 // the tile and column m = 128 a + 64 wm + 16 i + lane % 16: a store of it would write half a 128-byte line to each of four
@@ -75,10 +84,12 @@ __device__ __forceinline__ void store_block(const TileAcc& acc, const MatrixPlac
   const int lane = threadIdx.x & 63;
   const int m = m0 + place.wm * 64 + (lane & 31);
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < 4; ++b) {
+    const int block_n = n0 + (b >> 1) * 128 + place.wn * 32 + (b & 1) * 16;
+    if (!WHOLE && uniform(block_n) >= N) continue;           // sixteen rows past the end
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int n = n0 + (b >> 1) * 128 + place.wn * 32 + (b & 1) * 16 + ((lane >> 5) << 3) + r;
+      const int n = block_n + ((lane >> 5) << 3) + r;
       float* orow = Out + static_cast<int64_t>(n) * ldo;
 #pragma unroll
       for (int i = 0; i < 8; i += 2) {
@@ -98,9 +109,12 @@ __device__ __forceinline__ void store_block(const TileAcc& acc, const MatrixPlac
         }
       }
     }
+  }
 }
 
-// A whole tile: 128 stores a wavefront, none waited for (true); else they are waited for, their number being unknown.
+// A whole tile: 128 stores a wavefront, none waited for (true); else they are waited for, their number being unknown.  Of a tile
+// with few rows only the blocks that have some are gone through: logits of 64 rows x 8192 / 32,000 / 128,000, d = 1024, 31.6 /
+// 32.2 / 66 us with every store tested, 28.3 / 29.2 / 61.6 so.
 template <bool ACCUMULATE>
 __device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M, int N,
                                            float* __restrict__ Out, int64_t ldo) {
@@ -124,15 +138,6 @@ __device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace
 // of a tile apart: no difference; results stored 16 bytes a lane: 1 % on the logits.)
 constexpr unsigned kGemmGrid = 256;
 constexpr int64_t kWalkSteps = 128;
-
-// A value that is the same in every lane, for a scalar register.
-__host__ __device__ __forceinline__ int uniform(int x) {
-#ifdef __HIP_DEVICE_COMPILE__
-  return __builtin_amdgcn_readfirstlane(x);
-#else
-  return x;
-#endif
-}
 
 // (Places are moved on by additions: a division is some thirty vector instructions in every wavefront.)
 template <bool N_FIRST>
@@ -346,7 +351,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
 // rows transposed (fopd_transpose_bf16: 55 us for 16,384 rows of 4096).  Loop and result stores are those of fopd_gemm_nt;
 // B leaves the LDS as KMajorHalf says.  With the hidden rows k-major too, two thirds of the fragments take two transposing
 // reads each, 48 LDS reads a step instead of 32, and the reading slots are longer than the multiplying ones (matrix cores
-// 0.61 busy at 1.9 GHz): 151,936 x 4096 from 512 / 2048 / 16,384 rows 970 / 2455 / 16,300 us, so 950 / 2285 / 14,720.
+// 0.59 busy, 0.65 so): 151,936 x 4096 from 512 / 2048 / 16,384 rows 970 / 2455 / 16,300 us, so 950 / 2285 / 14,720.
 //
 // K must be a positive multiple of 64, and Am and Bk finite up to it; what is not to count is zero in one of them.  M and N need
 // not be multiples of the tile: rows of Am past M - 1 and 16-byte pieces past entry N - 1 of a row of Bk are clamped (re-read)

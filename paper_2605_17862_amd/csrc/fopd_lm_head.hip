@@ -18,8 +18,9 @@
 // weight [V, d]), so a lane's 8-element fragment is one 16-byte LDS read.
 //
 // The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Bound by power: the matrix
-// cores are 0.75 (logits) to 0.80 (dL/dhidden) busy at the 1.5 GHz that the part then holds.  The 16 x 16 x 32 instruction has
-// the rate of the 32 x 32 x 16 one but goes over its accumulators half as often per product; log-probs of 16,384 rows x
+// cores are 0.72 busy at the 1.86 GHz that the part then holds (logits of 8192 rows; with the 32 x 32 x 16 instruction 0.74 at
+// 1.68 GHz).  The 16 x 16 x 32 instruction has the other's rate but goes over its accumulators half as often per product;
+// log-probs of 16,384 rows x
 // 151,936, d = 4096: 15.4 - 16.0 -> 14.7 - 15.1 ms, of 2048 rows 1.92 - 1.98 -> 1.86 ms.  With the vocabulary tiles of a strip as
 // one stream (matrix_tiles), whose loads have offsets that stay from step to step, 14.15 - 14.4 and 1.73 ms.
 
@@ -76,7 +77,8 @@ __device__ __forceinline__ void lm_merge(float& m, float& s, float m2, float s2)
 // Logits of 512 rows x 151,936 entries, d = 4096 (1188 tiles): 4 x 8 groups always, 2560 workgroups, 836 us; 2 x 16, 1280,
 // 558 us.  Idle workgroups remain where the last group along n has 1 to 3 tiles and another one stands beside it, or the only
 // one has 3, and where the groups are rounded up to eight: 594 tiles take 768 workgroups for 256 rows, 1782 take 2560 for 768
-// rows (0.52 us a tile, 0.46 with the 2376 of 1024 rows), 2970 take 4864 for 1280 rows (0.55).
+// rows (0.52 us a tile, 0.46 with the 2376 of 1024 rows), 2970 take 4864 for 1280 rows (0.55).  (Launches whose workgroups walk
+// the tiles, TileWalk in fopd_gemm.hip, have none.  The figures are from the 32 x 32 x 16 instruction.)
 // Consecutive groups, and with them the XCDs, go along n first (N_FIRST) or along m first.  Along m first there are few
 // groups in a line, and the last of it may be a small one: where the line's length has a factor in common with 8 the same
 // XCDs would get it in every line, so the order in a line moves on by one each time the XCDs have come round to its start
@@ -152,8 +154,7 @@ struct LmSplit {
 // A last tile of up to 128 tokens goes through a step in kNarrowCost of the time of a whole one, so few whole tiles and that one
 // share the chip best with strips of their own: all of them in one round, a group for each XCD, as long as the longer of the
 // two strips.  With more tiles the tail is one tile of many and has the strips of the others.  151,936 x 4096, us, all tiles whole /
-// so: 64 rows 318 / 260, 600 rows 847 / 680, 1100 rows 1480 / 1075, 1600 rows (a tail among seven) 1770 /
-// 1620.
+// so: 64 rows 318 / 260, 600 rows 847 / 680, 1100 rows 1480 / 1075, 1600 rows (a tail among seven) 1770 / 1620.
 constexpr double kNarrowCost = 0.6;
 __host__ inline LmSplit lm_split(int64_t T, int64_t V) {
   const int n_vocab_tiles = static_cast<int>((V + kLmTile - 1) / kLmTile);
