@@ -1253,11 +1253,18 @@ size_t fopd_lm_head_loss_workspace_bytes(int64_t T, int64_t V, int64_t d, int32_
   return LmLossWorkspace(T, V, d, B, rows_chunk).total;
 }
 
-// Workgroups of a contraction: walking ones (kWalkSteps), else one for every place of every group of tiles, rounds * 256.  Also
-// where a result is added to after a single step: the memory's adds are all there is (weight gradient of 64 more rows,
-// 32,000 x 1024 / 128,000 x 1024: 102 / 410 us, walking 105 / 418).
-inline unsigned gemm_grid(int64_t rounds, int64_t steps, bool accumulate) {
-  return steps <= kWalkSteps && !(accumulate && steps == 1) ? kGemmGrid : static_cast<unsigned>(rounds * 256);
+// All contraction kernels at the first call, whichever it takes: one call of any size before a capture is enough.  Before
+// launch_gemm and launch_gemm_tn.
+static fopd_status allow_contractions() {
+  static bool allowed[8][kMaxDevices] = {};
+  const void* const kernels[8] = {
+      reinterpret_cast<const void*>(fopd_gemm_nt<false, false>), reinterpret_cast<const void*>(fopd_gemm_nt<false, true>),
+      reinterpret_cast<const void*>(fopd_gemm_nt<true, false>),  reinterpret_cast<const void*>(fopd_gemm_nt<true, true>),
+      reinterpret_cast<const void*>(fopd_gemm_tn<false, false>), reinterpret_cast<const void*>(fopd_gemm_tn<false, true>),
+      reinterpret_cast<const void*>(fopd_gemm_tn<true, false>),  reinterpret_cast<const void*>(fopd_gemm_tn<true, true>)};
+  for (int i = 0; i < 8; ++i)
+    if (allow_dynamic_lds(kernels[i], kLoopLdsBytes, allowed[i]) != FOPD_OK) return FOPD_EHIP;
+  return FOPD_OK;
 }
 
 // Out[n, m] = sum_k Bn[n, k] Am[m, k] on `s`; `slot` = timing slot of this contraction.  a_k_major: Am is stored [k, m] and
@@ -1274,15 +1281,14 @@ static fopd_status launch_gemm(bool a_k_major, const __bf16* Am, int64_t lda, in
   if (a_k_major && (rows_a <= K - kLmK || rows_a > K || M % 8 != 0 || lda % 8 != 0 || lda < M)) return FOPD_ESHAPE;
   // byte offsets inside one 256-row operand tile are 32-bit
   if (256 * lda * 2 >= 2147483648LL || 256 * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
-  static bool allowed[2][kMaxDevices] = {};
-  auto kern = a_k_major ? fopd_gemm_nt<true> : fopd_gemm_nt<false>;
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kLoopLdsBytes, allowed[a_k_major ? 1 : 0]) != FOPD_OK)
-    return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (splits * tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
-  const dim3 grid(gemm_grid(rounds, K / kLmK / splits, false)), block(kGemmThreads);
+  const bool walk = gemm_walks(static_cast<int64_t>(splits) * tiles_m * tiles_n, K / kLmK / splits, false);
+  auto kern = a_k_major ? (walk ? fopd_gemm_nt<true, true> : fopd_gemm_nt<true, false>)
+                        : (walk ? fopd_gemm_nt<false, true> : fopd_gemm_nt<false, false>);
+  const dim3 grid(gemm_grid(rounds, walk)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
   kern<<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), static_cast<int>(rows_a), Bn, ldb,
                                           static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m, tiles_n, n_live,
@@ -1301,24 +1307,17 @@ static fopd_status launch_gemm_tn(bool accumulate, const __bf16* Am, int64_t lda
     return FOPD_ESHAPE;
   // byte offsets inside a 256-row tile of Am and inside the 64 rows of a step of Bk are 32-bit
   if (kGemmTile * lda * 2 >= 2147483648LL || kLmK * ldb * 2 >= 2147483648LL) return FOPD_ESHAPE;
-  static bool allowed[2][kMaxDevices] = {};
-  const void* kern = accumulate ? reinterpret_cast<const void*>(fopd_gemm_tn<true>)
-                                : reinterpret_cast<const void*>(fopd_gemm_tn<false>);
-  if (allow_dynamic_lds(kern, kLoopLdsBytes, allowed[accumulate ? 1 : 0]) != FOPD_OK) return FOPD_EHIP;
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
-  const dim3 grid(gemm_grid(rounds, K / kLmK, accumulate)), block(kGemmThreads);
+  const bool walk = gemm_walks(static_cast<int64_t>(tiles_m) * tiles_n, K / kLmK, accumulate);
+  auto kern = accumulate ? (walk ? fopd_gemm_tn<true, true> : fopd_gemm_tn<true, false>)
+                         : (walk ? fopd_gemm_tn<false, true> : fopd_gemm_tn<false, false>);
+  const dim3 grid(gemm_grid(rounds, walk)), block(kGemmThreads);
   ScopedTimer timer(slot, s);
-  if (accumulate)
-    fopd_gemm_tn<true><<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bk, ldb,
-                                                       static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m,
-                                                       tiles_n, k_live);
-  else
-    fopd_gemm_tn<false><<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bk, ldb,
-                                                        static_cast<int>(N), static_cast<int>(K), Out, ldo, tiles_m,
-                                                        tiles_n, k_live);
+  kern<<<grid, block, kLoopLdsBytes, s>>>(Am, lda, static_cast<int>(M), Bk, ldb, static_cast<int>(N), static_cast<int>(K), Out,
+                                          ldo, tiles_m, tiles_n, k_live);
   return launched();
 }
 
@@ -1434,7 +1433,8 @@ static fopd_status lm_head_loss_impl(const void* hidden, int64_t ldh, const void
   }
 
   hipStream_t s = static_cast<hipStream_t>(stream);
-  fopd_status st;
+  fopd_status st = allow_contractions();
+  if (st != FOPD_OK) return st;
   int32_t* flags = at<int32_t>(workspace, lay.flags);
   int64_t* cu = at<int64_t>(workspace, lay.cu);
   int32_t* nws = at<int32_t>(workspace, lay.n_train);

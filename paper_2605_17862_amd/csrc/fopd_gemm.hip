@@ -112,10 +112,11 @@ __device__ __forceinline__ void store_block(const TileAcc& acc, const MatrixPlac
   }
 }
 
-// A whole tile: 128 stores a wavefront, none waited for (true); else they are waited for, their number being unknown.  Of a tile
+// A whole tile: 128 stores a wavefront, none waited for (true); else, where a tile follows, they are waited for, their number
+// being unknown.  Of a tile
 // with few rows only the blocks that have some are gone through: logits of 64 rows x 8192 / 32,000 / 128,000, d = 1024, 31.6 /
 // 32.2 / 66 us with every store tested, 28.3 / 29.2 / 61.6 so.
-template <bool ACCUMULATE>
+template <bool ACCUMULATE, bool WALK>
 __device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M, int N,
                                            float* __restrict__ Out, int64_t ldo) {
   if (m0 + kGemmTile <= M && n0 + kGemmTile <= N) {
@@ -123,45 +124,57 @@ __device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace
     return true;
   }
   store_block<ACCUMULATE, false>(acc, place, m0, n0, M, N, Out, ldo);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (WALK) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   return false;
 }
 
 // The tiles of a workgroup.  Launched with a workgroup for every place of every group (tile_place), each has one tile or none.
-// Launched with kGemmGrid, one a compute unit, workgroup 8 s + x is the s-th of XCD x and takes every 32nd tile of that XCD's
-// groups x, x + 8, .. in their order, only tiles that exist being counted.  The next tile's first steps are then requested
+// Launched with kGemmGrid, one a compute unit (WALK), workgroup 8 s + x is the s-th of XCD x and takes every 32nd tile of that
+// XCD's groups x, x + 8, .. in their order, only tiles that exist being counted.  The next tile's first steps are then requested
 // before this one's results are stored, and no workgroup waits for its place: workgroups are started in the order of their
 // ids, which keeps the compute units at the same point of their tiles.  Weight gradient of 151,936 x 4096, a workgroup a
 // tile / walking, us: 256 rows 725 / 615, 512 rows 934 / 830, 2048 rows 2185 / 2120, 8192 rows 7395 / 7330, 16,384 rows
 // 14,720 / 14,835; logits (64 steps a tile) 512 rows 514 / 511, 16,384 rows 14,670 / 14,460; dL/dhidden, 150 and more
 // steps a tile, 16,384 rows 14,155 / 14,230.  So tiles of up to kWalkSteps steps are walked.  (Workgroups started a fraction
-// of a tile apart: no difference; results stored 16 bytes a lane: 1 % on the logits.)
+// of a tile apart: no difference; results stored 16 bytes a lane: 1 % on the logits.)  With no more tiles than workgroups there
+// is nothing to walk, and the walk's code (four forms of a step, twice the instructions to fetch before the first one) is 4 - 6
+// us a launch: walking / not, us: weight gradient of 3000 rows x 8192, d = 64, 65.6 / 60.3, x 1000, d = 1024, 65.4 / 60.1; loss
+// and gradients of 64 rows x 8192, d = 1024, 110 / 102.  Nor where a result is added to after a single step: the memory's
+// adds are all there is (weight gradient of 64 more rows, 32,000 x 1024 / 128,000 x 1024, not walking 102 / 410, walking 105 / 418).
 constexpr unsigned kGemmGrid = 256;
 constexpr int64_t kWalkSteps = 128;
 
+inline bool gemm_walks(int64_t tiles, int64_t steps, bool accumulate) {
+  return tiles > kGemmGrid && steps <= kWalkSteps && !(accumulate && steps == 1);
+}
+
+// Workgroups: walking ones, else one for every place of every group of tiles (rounds of eight groups).
+inline unsigned gemm_grid(int64_t rounds, bool walk) { return walk ? kGemmGrid : static_cast<unsigned>(rounds * 256); }
+
 // (Places are moved on by additions: a division is some thirty vector instructions in every wavefront.)
-template <bool N_FIRST>
+template <bool N_FIRST, bool WALK>
 struct TileWalk {
+  static constexpr bool kWalks = WALK;
   int tiles_m, tiles_n, all_steps, splits;
   int gn, gm, groups_n, groups_m;                // tiles and groups either way
   int split, line, pos;                          // the group: pos-th of a line of groups along n (N_FIRST) or m
   int slot;                                      // place from the group's first tile on
-  bool walk;
 
-  __host__ __device__ __forceinline__ bool first(GemmTile& t, unsigned block, unsigned grid) {
+  __host__ __device__ __forceinline__ bool first(GemmTile& t, unsigned block) {
     gn = tile_group_n(tiles_n);
     gm = 32 / gn;
     groups_n = (tiles_n + gn - 1) / gn;
     groups_m = (tiles_m + gm - 1) / gm;
-    walk = grid == kGemmGrid;
     const int per_split = groups_n * groups_m, group = static_cast<int>((block >> 8) << 3) + static_cast<int>(block & 7);
     slot = static_cast<int>(block >> 3) & 31;
-    split = uniform(group / per_split);
-    const int in_split = group - split * per_split;
-    line = uniform(in_split / (N_FIRST ? groups_n : groups_m));
-    pos = in_split - line * (N_FIRST ? groups_n : groups_m);
-    if (walk) return find(t);
+    split = WALK || splits > 1 ? uniform(group / per_split) : 0;
     if (split >= splits) return false;
+    const int in_split = group - split * per_split;
+    if constexpr (WALK) {
+      line = uniform(in_split / (N_FIRST ? groups_n : groups_m));
+      pos = in_split - line * (N_FIRST ? groups_n : groups_m);
+      return find(t);
+    }
     const TilePlace place = tile_place<N_FIRST>(static_cast<unsigned>(in_split), static_cast<unsigned>(slot), tiles_m, tiles_n);
     if (place.m >= tiles_m || place.n >= tiles_n) return false;
     set(t, place.m, place.n);
@@ -169,7 +182,7 @@ struct TileWalk {
   }
   // (asked again after the last tile, the answer stays)
   __host__ __device__ __forceinline__ bool next(GemmTile& t) {
-    if (!walk || split >= splits) return false;
+    if (!WALK || split >= splits) return false;
     slot += 32;
     return find(t);
   }
@@ -279,9 +292,9 @@ struct KMajorSource {
       for (int e = 0; e < 2; ++e) off[h][e] = piece[h] + static_cast<uint32_t>(at.krow + 4 * e) * (static_cast<uint32_t>(ld) * 2u);
     }
   }
-  __device__ __forceinline__ void step() {
-    src += 2 * kLmK * ld;
-    left -= kLmK;
+  __device__ __forceinline__ void step(bool on = true) {
+    src += on ? 2 * kLmK * ld : 0;
+    left -= on ? kLmK : 0;
   }
   __device__ __forceinline__ void request(int half, uint32_t dst) {
     const uint32_t last = piece[half] + static_cast<uint32_t>(min(left, kLmK) - 1) * (static_cast<uint32_t>(ld) * 2u);
@@ -297,7 +310,7 @@ struct KMajorSource {
 // A_K_MAJOR: Am is stored [k, m] and has rows_a (K - 64 < rows_a <= K) readable rows; rows rows_a .. K - 1 are taken from
 // row rows_a - 1, so Bn must hold zeros in those columns; pieces past entry M - 1 of a row are clamped.  M % 8 == 0, lda % 8
 // == 0.  This is dL/dhidden with the projection matrix as it is stored, for few rows.
-template <bool A_K_MAJOR>
+template <bool A_K_MAJOR, bool WALK>
 __global__ void __launch_bounds__(kGemmThreads)
 fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, const __bf16* __restrict__ Bn, int64_t ldb,
              int N, int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
@@ -313,9 +326,9 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   }
   // With splits > 1 the contraction index is cut into that many runs of whole steps, each with a result of its
   // own, split_stride floats apart, which the caller sums; the groups of a run follow each other.
-  TileWalk<true> walk = {tiles_m, tiles_n, K / kLmK, splits};
+  TileWalk<true, WALK> walk = {tiles_m, tiles_n, K / kLmK, splits};
   GemmTile tile;
-  if (!walk.first(tile, blockIdx.x, gridDim.x)) return;                           // whole workgroup, before any barrier
+  if (!walk.first(tile, blockIdx.x)) return;               // whole workgroup, before any barrier
 
   const MatrixPlace mine = matrix_place(gemm_smem);
   typedef typename std::conditional<A_K_MAJOR, KMajorHalf, RowMajorHalf>::type HalfA;
@@ -335,7 +348,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
       [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
       [&](const GemmTile& t, const TileAcc& acc) {
-        return store_tile<false>(acc, mine, t.m0, t.n0, M, N, Out + t.split * split_stride, ldo);
+        return store_tile<false, WALK>(acc, mine, t.m0, t.n0, M, N, Out + t.split * split_stride, ldo);
       });
 }
 
@@ -353,7 +366,7 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
 // not be multiples of the tile: rows of Am past M - 1 and 16-byte pieces past entry N - 1 of a row of Bk are clamped (re-read)
 // and their results discarded; lda % 8 == 0, ldb % 8 == 0, and every row of Bk is readable up to N rounded up to 8 (ldb is at
 // least that).  Byte offsets inside 256 rows of Am and inside 64 of Bk must fit 32 bits.
-template <bool ACCUMULATE>
+template <bool ACCUMULATE, bool WALK>
 __global__ void __launch_bounds__(kGemmThreads)
 fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __restrict__ Bk, int64_t ldb,
              int N, int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
@@ -368,9 +381,9 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   }
   // the groups of one set of tiles along n follow each other on neighbouring XCDs: they read the same columns of Bk, by
   // far the larger operand
-  TileWalk<false> walk = {tiles_m, tiles_n, K / kLmK, 1};
+  TileWalk<false, WALK> walk = {tiles_m, tiles_n, K / kLmK, 1};
   GemmTile tile;
-  if (!walk.first(tile, blockIdx.x, gridDim.x)) return;                           // whole workgroup, before any barrier
+  if (!walk.first(tile, blockIdx.x)) return;               // whole workgroup, before any barrier
 
   const MatrixPlace mine = matrix_place(gemm_smem);
   const RowMajorHalf at_a(mine);
@@ -387,7 +400,7 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
       mine, gemm_smem, tile, walk, load,
       [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
-      [&](const GemmTile& t, const TileAcc& acc) { return store_tile<ACCUMULATE>(acc, mine, t.m0, t.n0, M, N, Out, ldo); });
+      [&](const GemmTile& t, const TileAcc& acc) { return store_tile<ACCUMULATE, WALK>(acc, mine, t.m0, t.n0, M, N, Out, ldo); });
 }
 
 // out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  GATHER: out[c, r] = in[row_map[r], c] for

@@ -493,7 +493,7 @@ struct RowMajorSource {
       for (int e = 0; e < 2; ++e)
         off[h][e] = static_cast<uint32_t>(min(h * 128 + at.row + 8 * e, rows - 1 - r0)) * (static_cast<uint32_t>(ld) * 2u) + at.chunk[e];
   }
-  __device__ __forceinline__ void step() { src += 2 * kLmK; }
+  __device__ __forceinline__ void step(bool on = true) { src += on ? 2 * kLmK : 0; }
   __device__ __forceinline__ void request(int half, uint32_t dst) {
 #pragma unroll
     for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);
@@ -512,9 +512,9 @@ struct TileLoader {
     a.locate(at_a, t.m0, k0);
     b.locate(at_b, t.n0, k0);
   }
-  __device__ __forceinline__ void step() {
-    a.step();
-    b.step();
+  __device__ __forceinline__ void step(bool on = true) {                          // (not on: stays where it is)
+    a.step(on);
+    b.step(on);
   }
   __device__ __forceinline__ void request(int half, int buf) {
     const uint32_t dst = lds + buf * STEP_BYTES + half * kHalfBytes;
@@ -532,7 +532,8 @@ struct TileLoader {
 //   load.request(half, buf)  the wavefront's two loads of a half tile into a step buffer
 //   store(tile, acc)         what to do with a finished tile; returns whether it left at least 63 stores behind the requests and
 //                            waited for none
-// A_HALVES x B_HALVES: 2 x 2, 2 x 1 (matrix_step_narrow) or 1 x 3 (matrix_step_wide).
+// A Walk without kWalks has one tile: its steps have one form, in which the requests stop at the last one without a branch, and
+// the tile is stored after the end of the loop.  A_HALVES x B_HALVES: 2 x 2, 2 x 1 (matrix_step_narrow) or 1 x 3 (matrix_step_wide).
 template <bool B_FIRST, int A_HALVES, int B_HALVES, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
 __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
                                              Loader& load, ReadA read_a, ReadB read_b, Store store) {
@@ -541,7 +542,11 @@ __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsi
   int left = tile.steps;
   load.locate(tile);
   auto advance = [&]() {
-    if (--left > 0) {
+    if constexpr (!Walk::kWalks) {
+      const bool more = left > 1;
+      left -= more ? 1 : 0;
+      load.step(more);
+    } else if (--left > 0) {
       load.step();
     } else if (ahead.next(ahead_tile)) {
       left = ahead_tile.steps;
@@ -594,6 +599,12 @@ __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsi
       cur = cur == kBufs - 1 ? 0 : cur + 1;
     };
     int kt = tile.steps;
+    if constexpr (!Walk::kWalks) {
+      for (; kt > 0; --kt) run(std::false_type(), std::true_type());
+      matrix_end(mine);
+      store(tile, acc);
+      return;
+    }
     if (stored) {
       if (left > 1) run(std::true_type(), std::false_type());
       else run(std::true_type(), std::true_type());
@@ -620,6 +631,7 @@ namespace {
 
 // The vocabulary tiles of a strip, one after the other.
 struct StripWalk {
+  static constexpr bool kWalks = true;
   int end, tile;               // first vocabulary row past the strip; rows of a tile
   __device__ __forceinline__ bool next(GemmTile& t) const {
     if (t.m0 + tile >= end) return false;
@@ -634,7 +646,7 @@ struct HiddenSource {
   const char* src;
   uint32_t off[3][2];
   __device__ __forceinline__ void locate(const RowMajorHalf&, int, int64_t) { src = base; }
-  __device__ __forceinline__ void step() { src += 2 * kLmK; }
+  __device__ __forceinline__ void step(bool on = true) { src += on ? 2 * kLmK : 0; }
   __device__ __forceinline__ void request(int half, uint32_t dst) {
 #pragma unroll
     for (int e = 0; e < 2; ++e) load_to_lds(src, off[half][e], dst + e * 1024);

@@ -101,13 +101,14 @@ int main(int argc, char** argv) {
          normal ? "operands close to N(0, 1) and N(0, (3/64)^2)" : "operand magnitudes in [0.5, 1)");
   using namespace fopd;
   const int tiles_m = (M + kGemmTile - 1) / kGemmTile, tiles_n = (N + kGemmTile - 1) / kGemmTile;
-  const unsigned grid = static_cast<unsigned>((tile_groups(tiles_m, tiles_n) + 7) / 8 * 256);
+  const int64_t rounds = (tile_groups(tiles_m, tiles_n) + 7) / 8;
+  const bool walk = gemm_walks(static_cast<int64_t>(tiles_m) * tiles_n, K / kLmK, false);
+  const unsigned grid = gemm_grid(rounds, walk);
   const double flops = 2.0 * M * static_cast<double>(N) * K;
-  CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fopd_gemm_nt<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kLoopLdsBytes));
+  auto kern = walk ? fopd_gemm_nt<false, true> : fopd_gemm_nt<false, false>;
+  CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLoopLdsBytes));
   auto nt = [&]() {
-    fopd_gemm_nt<false><<<grid, kGemmThreads, kLoopLdsBytes>>>(A, ld, M, M, B, ld, N, K, out, M, tiles_m, tiles_n, nullptr,
-                                                               1, 0);
+    kern<<<grid, kGemmThreads, kLoopLdsBytes>>>(A, ld, M, M, B, ld, N, K, out, M, tiles_m, tiles_n, nullptr, 1, 0);
   };
   if (time_groups("fopd_gemm_nt", 4, 1, flops, e0, e1, nt)) return 1;
   if (time_groups("fopd_gemm_nt", groups, 20, flops, e0, e1, nt)) return 1;
@@ -115,12 +116,14 @@ int main(int argc, char** argv) {
     // the weight gradient's shape, B k-major, in the same buffers: Out[151936, 4096] = sum over 4096 entries of
     // Bk[4096, 151936] (all of buffer A) and Am[4096, 4096] (half of the first 8192 rows of buffer B)
     const int tm = 4096 / kGemmTile, tn = (151936 + kGemmTile - 1) / kGemmTile;
-    const unsigned grid_tn = static_cast<unsigned>((tile_groups(tm, tn) + 7) / 8 * 256);
-    CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fopd_gemm_tn<false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kLoopLdsBytes));
+    const int64_t rounds_tn = (tile_groups(tm, tn) + 7) / 8;
+    const bool walk_tn = gemm_walks(static_cast<int64_t>(tm) * tn, 4096 / kLmK, false);
+    auto kern_tn = walk_tn ? fopd_gemm_tn<false, true> : fopd_gemm_tn<false, false>;
+    CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern_tn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              kLoopLdsBytes));
     if (time_groups("fopd_gemm_tn, Out[151936, 4096], K = 4096", 4, 1, 2.0 * 4096 * 151936.0 * 4096, e0, e1, [&]() {
-          fopd_gemm_tn<false><<<grid_tn, kGemmThreads, kLoopLdsBytes>>>(B, 4096, 4096, A, 151936, 151936, 4096, out,
-                                                                       4096, tm, tn, nullptr);
+          kern_tn<<<gemm_grid(rounds_tn, walk_tn), kGemmThreads, kLoopLdsBytes>>>(B, 4096, 4096, A, 151936, 151936, 4096, out,
+                                                                                 4096, tm, tn, nullptr);
         }))
       return 1;
   }

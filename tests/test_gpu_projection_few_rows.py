@@ -120,3 +120,14 @@ def test_gradients_with_more_result_tiles_than_workgroups(seq, d):
     first = torch.zeros(70001, d, device=DEV)
     again = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, (T + 63) // 64 * 64, scores, accumulate=True, dweight=first)
     assert torch.equal(again["dweight"], out["dweight"])
+
+
+@pytest.mark.parametrize("T", [4096, 4097])
+def test_gradients_with_more_tiles_of_dhidden_than_workgroups(T):
+    """Four steps over 200 vocabulary entries, the last one of 8, and 16 or 17 times 18 tiles of dL/dhidden, the last one of 64
+    hidden elements: workgroups walk from tile to tile in both layouts of the projection matrix (4096 and 4097 rows)."""
+    h = wl.generate_lm_head(T, 4416, 200, DEV, seed=T, masked_every=7)
+    w = wl.attach_loss_inputs(h, (T - 700, 700), [1, 2], seed=T)
+    scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
+    out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, 4160, scores)
+    _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)

@@ -37,14 +37,15 @@ static double makespan(int tiles_m, int tiles_n, int runs, double start, Length 
 }
 
 // Every tile of every run comes once, whether a launch has a workgroup for each place or 256 that walk, and the same ones.
-template <bool N_FIRST>
+template <bool N_FIRST, bool WALK>
 static bool walked(int tiles_m, int tiles_n, int steps, int splits) {
-  for (unsigned grid : {256u, static_cast<unsigned>((splits * tile_groups(tiles_m, tiles_n) + 7) / 8 * 256)}) {
+  {
+    const unsigned grid = gemm_grid((splits * tile_groups(tiles_m, tiles_n) + 7) / 8, WALK);
     std::vector<int> seen(static_cast<size_t>(tiles_m) * tiles_n * splits, 0);
     for (unsigned block = 0; block < grid; ++block) {
-      TileWalk<N_FIRST> walk = {tiles_m, tiles_n, steps, splits};
+      TileWalk<N_FIRST, WALK> walk = {tiles_m, tiles_n, steps, splits};
       GemmTile t;
-      if (!walk.first(t, block, grid)) continue;
+      if (!walk.first(t, block)) continue;
       do {
         if (t.m0 < 0 || t.m0 % 256 || t.m0 / 256 >= tiles_m || t.n0 < 0 || t.n0 % 256 || t.n0 / 256 >= tiles_n) return false;
         if (t.split < 0 || t.split >= splits || t.steps < 1 || t.first != steps * t.split / splits ||
@@ -117,9 +118,15 @@ int main() {
     for (int n : {1, 2, 3, 4, 5, 8, 64, 594})
       for (int splits : {1, 3, 8})
         for (int first : {0, 1}) {
-          if (first ? !walked<true>(m, n, 19, splits) : !walked<false>(m, n, 19, splits)) return 2;
+          if (first ? !walked<true, true>(m, n, 19, splits) || !walked<true, false>(m, n, 19, splits)
+                    : !walked<false, true>(m, n, 19, splits) || !walked<false, false>(m, n, 19, splits))
+            return 2;
           std::printf("walk %d %d %d %d\n", m, n, splits, first);
         }
+  for (int tiles : {1, 16, 125, 256, 257, 594, 9504})
+    for (int steps : {1, 2, 64, 128, 129, 2374})
+      for (int accumulate : {0, 1})
+        std::printf("walks %d %d %d %d\n", tiles, steps, accumulate, static_cast<int>(gemm_walks(tiles, steps, accumulate != 0)));
 }
 """
 
@@ -166,3 +173,11 @@ def test_strips_of_whole_narrow_and_wide_token_tiles(choices):
     for T, V, strips, room, pairs, covered, filled in rows:
         assert strips >= 1 and covered >= T and filled, (T, V)
         assert pairs <= room, (T, V)                         # the workspace has so many (reference, sum) pairs
+
+
+def test_only_launches_with_more_tiles_than_workgroups_walk(choices):
+    rows = [[int(x) for x in r[1:]] for r in choices if r[0] == "walks"]
+    assert len(rows) == 7 * 6 * 2
+    for tiles, steps, accumulate, walks in rows:
+        # the walk's code costs a launch 4 - 6 us, for nothing where no workgroup has a second tile
+        assert walks == (tiles > 256 and steps <= 128 and not (accumulate and steps == 1)), (tiles, steps, accumulate)
