@@ -227,7 +227,10 @@ __host__ __device__ __forceinline__ TilePlace tile_place(unsigned group, unsigne
 // operands loaded once and not again 14.07 of 16.70 ms (another box 12.8 of 15.9), with every step reading the same 64
 // elements, lines just used, 16.02 (14.3).  Slower: the loads of a slot before its LDS reads (+ 14 %), inside the run of
 // matrix instructions (+ 10 - 16 %): requests wait at the L1, and hold up what follows them; non-temporal loads (+ 14 %); B0
-// read a phase earlier to even out the reads (+ 1 %).
+// read a phase earlier to even out the reads (+ 1 %).  A higher wave priority for the multiplying slots held up the other kind's
+// LDS reads once the instructions came twice as often: with / without, dL/dhidden of 256 rows x 4096 over 151,936 entries 2895 /
+// 2850 us, of 512 rows of 1024 over 32,000 155.4 / 153.5; loss and gradients of 4096 rows 12.60 / 12.49 ms, of 16,384 rows 49.5 /
+// 49.0; log-probs of 16,384 rows 14.63 / 14.42 ms.
 
 struct MatrixPlace {
   int wm, wn;
@@ -268,7 +271,6 @@ enum { kHalfA0 = 0, kHalfA1 = 1, kHalfB0 = 2, kHalfB1 = 3, kHalfB2 = 1 };       
 template <bool B_FIRST, int A_HALVES, int B_HALVES>
 __device__ __forceinline__ void multiply_phase(BlockAcc<A_HALVES, B_HALVES>& acc, int a, int b, const bf16x8 (&fa)[4][2],
                                                const bf16x8 (&fb)[2][2]) {
-  __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -277,7 +279,6 @@ __device__ __forceinline__ void multiply_phase(BlockAcc<A_HALVES, B_HALVES>& acc
       for (int j = 0; j < 2; ++j)
         acc[a][i][b][j] = B_FIRST ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[a][i][b][j], 0, 0, 0)
                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[a][i][b][j], 0, 0, 0);
-  __builtin_amdgcn_s_setprio(0);
 }
 
 // One step.  read_a(half, i, ks) / read_b(half, j, ks): the fragment of 16-row block i / j, elements 32 ks .. + 31, from this
