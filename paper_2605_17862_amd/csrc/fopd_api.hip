@@ -1256,13 +1256,14 @@ size_t fopd_lm_head_loss_workspace_bytes(int64_t T, int64_t V, int64_t d, int32_
 // All contraction kernels at the first call, whichever it takes: one call of any size before a capture is enough.  Before
 // launch_gemm and launch_gemm_tn.
 static fopd_status allow_contractions() {
-  static bool allowed[8][kMaxDevices] = {};
-  const void* const kernels[8] = {
+  static bool allowed[9][kMaxDevices] = {};
+  const void* const kernels[9] = {
       reinterpret_cast<const void*>(fopd_gemm_nt<false, false>), reinterpret_cast<const void*>(fopd_gemm_nt<false, true>),
       reinterpret_cast<const void*>(fopd_gemm_nt<true, false>),  reinterpret_cast<const void*>(fopd_gemm_nt<true, true>),
+      reinterpret_cast<const void*>(fopd_gemm_nt<true, false, 32>),
       reinterpret_cast<const void*>(fopd_gemm_tn<false, false>), reinterpret_cast<const void*>(fopd_gemm_tn<false, true>),
       reinterpret_cast<const void*>(fopd_gemm_tn<true, false>),  reinterpret_cast<const void*>(fopd_gemm_tn<true, true>)};
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 9; ++i)
     if (allow_dynamic_lds(kernels[i], kLoopLdsBytes, allowed[i]) != FOPD_OK) return FOPD_EHIP;
   return FOPD_OK;
 }
@@ -1285,8 +1286,9 @@ static fopd_status launch_gemm(bool a_k_major, const __bf16* Am, int64_t lda, in
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
   const int64_t rounds = (splits * tile_groups(tiles_m, tiles_n) + 7) / 8;
   if (rounds * 256 > 2147483647LL) return FOPD_ESHAPE;
-  const bool walk = gemm_walks(static_cast<int64_t>(splits) * tiles_m * tiles_n, K / kLmK / splits, false);
-  auto kern = a_k_major ? (walk ? fopd_gemm_nt<true, true> : fopd_gemm_nt<true, false>)
+  const int64_t tiles = static_cast<int64_t>(splits) * tiles_m * tiles_n;
+  const bool walk = gemm_walks(tiles, K / kLmK / splits, false);
+  auto kern = a_k_major ? (walk ? fopd_gemm_nt<true, true> : gemm_tall(tiles) ? fopd_gemm_nt<true, false, 32> : fopd_gemm_nt<true, false>)
                         : (walk ? fopd_gemm_nt<false, true> : fopd_gemm_nt<false, false>);
   const dim3 grid(gemm_grid(rounds, walk)), block(kGemmThreads);
   ScopedTimer timer(slot, s);

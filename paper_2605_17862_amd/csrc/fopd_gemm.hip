@@ -79,7 +79,17 @@ __host__ __device__ __forceinline__ int uniform(int x) {
 // whose lines the operand tiles need: non-temporal stores, loss and gradients of 16,384 rows 52.7 -> 51.8 ms, of 4096 rows
 // 13.42 -> 13.33 ms, fewer rows unchanged (with the 32 x 32 x 16 instruction).
 template <bool ACCUMULATE, bool WHOLE>
-__device__ __forceinline__ void store_block(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M,
+__device__ __forceinline__ void store_entry(float* to, float v, bool exists) {
+  if (WHOLE || exists) {
+    // (every entry of Out belongs to one lane of one workgroup, so the hardware add, which does not wait for the
+    // old value to come back, gives the same sums as load - add - store, in the same order)
+    if (ACCUMULATE) unsafeAtomicAdd(to, v);
+    else __builtin_nontemporal_store(v, to);
+  }
+}
+
+template <bool ACCUMULATE, bool WHOLE>
+__device__ __forceinline__ void store_block(const BlockAcc<2, 2, 16>& acc, const MatrixPlace& place, int m0, int n0, int M,
                                             int N, float* __restrict__ Out, int64_t ldo) {
   const int lane = threadIdx.x & 63;
   const int m = m0 + place.wm * 64 + (lane & 31);
@@ -98,26 +108,42 @@ __device__ __forceinline__ void store_block(const TileAcc& acc, const MatrixPlac
         const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(e0), __float_as_uint(e1), false, false);
         const float v[2] = {__uint_as_float(sw[0]), __uint_as_float(sw[1])};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          float* to = orow + 4 * h * ldo + mi;
-          if (WHOLE || (mi < M && n + 4 * h < N)) {
-            // (every entry of Out belongs to one lane of one workgroup, so the hardware add, which does not wait for the
-            // old value to come back, gives the same sums as load - add - store, in the same order)
-            if (ACCUMULATE) unsafeAtomicAdd(to, v[h]);
-            else __builtin_nontemporal_store(v[h], to);
-          }
-        }
+        for (int h = 0; h < 2; ++h)
+          store_entry<ACCUMULATE, WHOLE>(orow + 4 * h * ldo + mi, v[h], mi < M && n + 4 * h < N);
       }
     }
   }
+}
+
+// With the 32 x 32 result register r is row n = 128 b + 32 wn + 8 (r / 4) + 4 (lane / 32) + r % 4, column m = 128 a + 64 wm + 32 i +
+// lane % 32: whole lines of two rows.
+template <bool ACCUMULATE, bool WHOLE>
+__device__ __forceinline__ void store_block(const BlockAcc<2, 2, 32>& acc, const MatrixPlace& place, int m0, int n0, int M,
+                                            int N, float* __restrict__ Out, int64_t ldo) {
+  const int lane = threadIdx.x & 63;
+  const int m = m0 + place.wm * 64 + (lane & 31);
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int rows_n = n0 + b * 128 + place.wn * 32 + ((r >> 2) << 3);
+      if (!WHOLE && uniform(rows_n) >= N) continue;          // eight rows past the end
+      const int n = rows_n + ((lane >> 5) << 2) + (r & 3);
+      float* orow = Out + static_cast<int64_t>(n) * ldo;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int mi = m + (i >> 1) * 128 + (i & 1) * 32;
+        store_entry<ACCUMULATE, WHOLE>(orow + mi, acc[i >> 1][i & 1][b][0][r], mi < M && n < N);
+      }
+    }
 }
 
 // A whole tile: 128 stores a wavefront, none waited for (true); else, where a tile follows, they are waited for, their number
 // being unknown.  Of a tile
 // with few rows only the blocks that have some are gone through: logits of 64 rows x 8192 / 32,000 / 128,000, d = 1024, 31.6 /
 // 32.2 / 66 us with every store tested, 28.3 / 29.2 / 61.6 so.
-template <bool ACCUMULATE, bool WALK>
-__device__ __forceinline__ bool store_tile(const TileAcc& acc, const MatrixPlace& place, int m0, int n0, int M, int N,
+template <bool ACCUMULATE, bool WALK, int SIDE>
+__device__ __forceinline__ bool store_tile(const BlockAcc<2, 2, SIDE>& acc, const MatrixPlace& place, int m0, int n0, int M, int N,
                                            float* __restrict__ Out, int64_t ldo) {
   if (m0 + kGemmTile <= M && n0 + kGemmTile <= N) {
     store_block<ACCUMULATE, true>(acc, place, m0, n0, M, N, Out, ldo);
@@ -147,6 +173,14 @@ constexpr int64_t kWalkSteps = 128;
 inline bool gemm_walks(int64_t tiles, int64_t steps, bool accumulate) {
   return tiles > kGemmGrid && steps <= kWalkSteps && !(accumulate && steps == 1);
 }
+
+// dL/dhidden from the matrix as it is stored, where it has few tiles (a chunk of few rows of a call of many, whose sums take the
+// order of the whole call): with the 32 x 32 x 16 instruction.  The multiplying slots issue half as many instructions, which
+// leaves the transposing reads of the other kind their way to the LDS, and with this many compute units at work there is no
+// power to be saved.  16 x 16 x 32 / 32 x 32 x 16, us by number of tiles: over 151,936 entries x 4096 16: 2850 / 2707, 32: 2986 /
+// 2784, 48: 2910 / 2940, 64: 3374 / 3655, 256: 3570 / 3750; over 32,000 x 1024 8: 83.6 / 77.7, 16: 158.5 / 150.4, 32: 170 /
+// 161, 64: 206 / 222.  (Both operands k-contiguous: no difference up to 32 tiles.)
+inline bool gemm_tall(int64_t tiles) { return tiles <= 32; }
 
 // Workgroups: walking ones, else one for every place of every group of tiles (rounds of eight groups).
 inline unsigned gemm_grid(int64_t rounds, bool walk) { return walk ? kGemmGrid : static_cast<unsigned>(rounds * 256); }
@@ -241,19 +275,28 @@ typedef short tn_i16x8 __attribute__((ext_vector_type(8)));
 
 struct KMajorHalf {
   int krow, piece;             // row of the wavefront's first load (the second: + 4), 16-byte piece of the row
-  int a_off[4], b_off[2];
   __device__ __forceinline__ explicit KMajorHalf(const MatrixPlace& p) {
     const int lane = threadIdx.x & 63;
     const int wave = p.wm * 4 + p.wn;
     krow = 8 * wave + (lane >> 4);
     piece = (lane & 15) ^ ((lane >> 4) << 2) ^ ((wave & 1) << 1);
-    // lane 16 g + 4 e + q: row 8 g + e (+ 4) of the 32 of a slice, entries 4 q .. + 3 of a 16-entry block
-    const int g = lane >> 4, e = (lane >> 2) & 3, q = lane & 3;
+  }
+};
+
+template <int SIDE = 16>
+struct KMajorFragments {
+  static constexpr int kBlocks = SIDE / 16;      // 16-entry blocks of a fragment; the other groups of 16 lanes: rows 8 on
+  int a_off[64 / SIDE], b_off[32 / SIDE];
+  __device__ __forceinline__ explicit KMajorFragments(const MatrixPlace& p) {
+    // lane 16 g + 4 e + q: row 8 (g / kBlocks) + e (+ 4) of those of a slice, entries 4 q .. + 3 of 16-entry block g % kBlocks
+    const int lane = threadIdx.x & 63;
+    const int g = (lane >> 4) / kBlocks, block = (lane >> 4) % kBlocks, e = (lane >> 2) & 3, q = lane & 3;
     const int rows = (8 * g + e) * 256 + q * 8;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a_off[i] = rows + (((4 * p.wm + i) * 32) ^ (e << 6) ^ ((g & 1) << 5));
+    for (int i = 0; i < 64 / SIDE; ++i) a_off[i] = rows + (((4 * p.wm + i * kBlocks + block) * 32) ^ (e << 6) ^ ((g & 1) << 5));
 #pragma unroll
-    for (int j = 0; j < 2; ++j) b_off[j] = 2 * kHalfBytes + rows + (((2 * p.wn + j) * 32) ^ (e << 6) ^ ((g & 1) << 5));
+    for (int j = 0; j < 32 / SIDE; ++j)
+      b_off[j] = 2 * kHalfBytes + rows + (((2 * p.wn + j * kBlocks + block) * 32) ^ (e << 6) ^ ((g & 1) << 5));
   }
   __device__ __forceinline__ bf16x8 fragment(const unsigned char* p) const {
     typedef __attribute__((address_space(3))) tn_i16x4* lds_ptr;
@@ -263,10 +306,10 @@ struct KMajorHalf {
     return __builtin_bit_cast(bf16x8, both);
   }
   __device__ __forceinline__ bf16x8 a(const unsigned char* step, int half, int i, int ks) const {
-    return fragment(step + half * kHalfBytes + a_off[i] + ks * 8192);
+    return fragment(step + half * kHalfBytes + a_off[i] + ks * (512 / SIDE * 256));
   }
   __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int j, int ks) const {
-    return fragment(step + half * kHalfBytes + b_off[j] + ks * 8192);
+    return fragment(step + half * kHalfBytes + b_off[j] + ks * (512 / SIDE * 256));
   }
 };
 
@@ -310,7 +353,7 @@ struct KMajorSource {
 // A_K_MAJOR: Am is stored [k, m] and has rows_a (K - 64 < rows_a <= K) readable rows; rows rows_a .. K - 1 are taken from
 // row rows_a - 1, so Bn must hold zeros in those columns; pieces past entry M - 1 of a row are clamped.  M % 8 == 0, lda % 8
 // == 0.  This is dL/dhidden with the projection matrix as it is stored, for few rows.
-template <bool A_K_MAJOR, bool WALK>
+template <bool A_K_MAJOR, bool WALK, int SIDE = 16>
 __global__ void __launch_bounds__(kGemmThreads)
 fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, const __bf16* __restrict__ Bn, int64_t ldb,
              int N, int K, float* __restrict__ Out, int64_t ldo, int tiles_m, int tiles_n,
@@ -333,9 +376,11 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   const MatrixPlace mine = matrix_place(gemm_smem);
   typedef typename std::conditional<A_K_MAJOR, KMajorHalf, RowMajorHalf>::type HalfA;
   const HalfA at_a(mine);
-  const RowMajorHalf at(mine);
+  const RowMajorHalf at_b(mine);
+  const typename std::conditional<A_K_MAJOR, KMajorFragments<SIDE>, RowMajorFragments<SIDE>>::type frags_a(mine);
+  const RowMajorFragments<SIDE> frags_b(mine);
   typedef typename std::conditional<A_K_MAJOR, KMajorSource<true>, RowMajorSource>::type SourceA;
-  TileLoader<SourceA, RowMajorSource, HalfA, RowMajorHalf> load = {{}, {}, at_a, at, mine.lds};
+  TileLoader<SourceA, RowMajorSource, HalfA, RowMajorHalf> load = {{}, {}, at_a, at_b, mine.lds};
   load.a.base = reinterpret_cast<const char*>(Am);
   load.a.ld = lda;
   load.a.rows = A_K_MAJOR ? rows_a : M;
@@ -343,12 +388,12 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
   load.b.base = reinterpret_cast<const char*>(Bn);
   load.b.ld = ldb;
   load.b.rows = N;
-  matrix_tiles<true, 2, 2>(
+  matrix_tiles<true, 2, 2, SIDE>(
       mine, gemm_smem, tile, walk, load,
-      [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
-      [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
-      [&](const GemmTile& t, const TileAcc& acc) {
-        return store_tile<false, WALK>(acc, mine, t.m0, t.n0, M, N, Out + t.split * split_stride, ldo);
+      [&](const unsigned char* here, int half, int i, int ks) { return frags_a.a(here, half, i, ks); },
+      [&](const unsigned char* here, int half, int j, int ks) { return frags_b.b(here, half, j, ks); },
+      [&](const GemmTile& t, const BlockAcc<2, 2, SIDE>& acc) {
+        return store_tile<false, WALK, SIDE>(acc, mine, t.m0, t.n0, M, N, Out + t.split * split_stride, ldo);
       });
 }
 
@@ -387,8 +432,10 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
 
   const MatrixPlace mine = matrix_place(gemm_smem);
   const RowMajorHalf at_a(mine);
-  const KMajorHalf at(mine);
-  TileLoader<RowMajorSource, KMajorSource<false>, RowMajorHalf, KMajorHalf> load = {{}, {}, at_a, at, mine.lds};
+  const KMajorHalf at_b(mine);
+  const RowMajorFragments<> frags_a(mine);
+  const KMajorFragments<> frags_b(mine);
+  TileLoader<RowMajorSource, KMajorSource<false>, RowMajorHalf, KMajorHalf> load = {{}, {}, at_a, at_b, mine.lds};
   load.a.base = reinterpret_cast<const char*>(Am);
   load.a.ld = lda;
   load.a.rows = M;
@@ -398,9 +445,9 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
   load.b.cols = (N + 7) >> 3;
   matrix_tiles<true, 2, 2>(
       mine, gemm_smem, tile, walk, load,
-      [&](const unsigned char* here, int half, int i, int ks) { return at_a.a(here, half, i, ks); },
-      [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
-      [&](const GemmTile& t, const TileAcc& acc) { return store_tile<ACCUMULATE, WALK>(acc, mine, t.m0, t.n0, M, N, Out, ldo); });
+      [&](const unsigned char* here, int half, int i, int ks) { return frags_a.a(here, half, i, ks); },
+      [&](const unsigned char* here, int half, int j, int ks) { return frags_b.b(here, half, j, ks); },
+      [&](const GemmTile& t, const BlockAcc<2, 2>& acc) { return store_tile<ACCUMULATE, WALK, 16>(acc, mine, t.m0, t.n0, M, N, Out, ldo); });
 }
 
 // out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  GATHER: out[c, r] = in[row_map[r], c] for

@@ -51,11 +51,12 @@ constexpr float kLmNone = -__builtin_inff();              // "no value yet": the
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// A wavefront's block of the result tile: [A half][16-row block of its 64][B half][16-row block of its 32].
-template <int A_HALVES, int B_HALVES>
-using BlockAcc = f32x4[A_HALVES][4][B_HALVES][2];
-typedef BlockAcc<2, 2> TileAcc;
+// A wavefront's block of the result tile: [A half][SIDE-row block of its 64][B half][SIDE-row block of its 32].  SIDE is that of
+// the matrix instruction's result, 16 (v_mfma_f32_16x16x32_bf16) or 32 (v_mfma_f32_32x32x16_bf16).
+template <int A_HALVES, int B_HALVES, int SIDE = 16>
+using BlockAcc = typename std::conditional<SIDE == 16, f32x4, f32x16>::type[A_HALVES][64 / SIDE][B_HALVES][32 / SIDE];
 
 namespace {
 
@@ -268,63 +269,67 @@ enum { kHalfA0 = 0, kHalfA1 = 1, kHalfB0 = 2, kHalfB1 = 3, kHalfB2 = 1 };       
 
 // B_FIRST: the B fragment is the matrix instruction's first operand (a lane then holds four B rows of one A row), else the A
 // fragment is.
-template <bool B_FIRST, int A_HALVES, int B_HALVES>
-__device__ __forceinline__ void multiply_phase(BlockAcc<A_HALVES, B_HALVES>& acc, int a, int b, const bf16x8 (&fa)[4][2],
-                                               const bf16x8 (&fb)[2][2]) {
+template <bool B_FIRST, int SIDE, typename Acc, typename FragsA, typename FragsB>
+__device__ __forceinline__ void multiply_phase(Acc& acc, int a, int b, const FragsA& fa, const FragsB& fb) {
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
+  for (int ks = 0; ks < SIDE / 8; ++ks)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 64 / SIDE; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[a][i][b][j] = B_FIRST ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][ks], fa[i][ks], acc[a][i][b][j], 0, 0, 0)
-                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[j][ks], acc[a][i][b][j], 0, 0, 0);
+      for (int j = 0; j < 32 / SIDE; ++j) {
+        const bf16x8 first = B_FIRST ? fb[j][ks] : fa[i][ks], second = B_FIRST ? fa[i][ks] : fb[j][ks];
+        if constexpr (SIDE == 16)
+          acc[a][i][b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(first, second, acc[a][i][b][j], 0, 0, 0);
+        else
+          acc[a][i][b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(first, second, acc[a][i][b][j], 0, 0, 0);
+      }
 }
 
-// One step.  read_a(half, i, ks) / read_b(half, j, ks): the fragment of 16-row block i / j, elements 32 ks .. + 31, from this
-// step's buffer.  request(half): the wavefront's two loads of that half tile of a later step (any readable one past the last:
+// One step.  read_a(half, i, ks) / read_b(half, j, ks): the fragment of SIDE-row block i / j, elements (512 / SIDE) ks on, from
+// this step's buffer.  request(half): the wavefront's two loads of that half tile of a later step (any readable one past the last:
 // never read).  STORED: at least 63 stores have been issued since the requests that this
 // step waits for, which are done when 63 later ones are all that is left (loads and stores count and end in order).
-template <bool B_FIRST, bool STORED, typename ReadA, typename ReadB, typename Request>
-__device__ __forceinline__ void matrix_step(TileAcc& acc, ReadA read_a, ReadB read_b, Request request) {
-  bf16x8 fa[4][2], fb0[2][2], fb1[2][2];
+template <bool B_FIRST, bool STORED, int SIDE, typename ReadA, typename ReadB, typename Request>
+__device__ __forceinline__ void matrix_step(BlockAcc<2, 2, SIDE>& acc, ReadA read_a, ReadB read_b, Request request) {
+  constexpr int I = 64 / SIDE, J = 32 / SIDE, KS = SIDE / 8;
+  bf16x8 fa[I][KS], fb0[J][KS], fb1[J][KS];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < J; ++j)
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) fb0[j][ks] = read_b(0, j, ks);
+    for (int ks = 0; ks < KS; ++ks) fb0[j][ks] = read_b(0, j, ks);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < I; ++i)
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(0, i, ks);
+    for (int ks = 0; ks < KS; ++ks) fa[i][ks] = read_a(0, i, ks);
   request(kHalfA1);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST, 2, 2>(acc, 0, 0, fa, fb0);
+  multiply_phase<B_FIRST, SIDE>(acc, 0, 0, fa, fb0);
   slot_end();
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < J; ++j)
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) fb1[j][ks] = read_b(1, j, ks);
+    for (int ks = 0; ks < KS; ++ks) fb1[j][ks] = read_b(1, j, ks);
   request(kHalfB0);
   if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63) lgkmcnt(0)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST, 2, 2>(acc, 0, 1, fa, fb1);
+  multiply_phase<B_FIRST, SIDE>(acc, 0, 1, fa, fb1);
   slot_end();
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < I; ++i)
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) fa[i][ks] = read_a(1, i, ks);
+    for (int ks = 0; ks < KS; ++ks) fa[i][ks] = read_a(1, i, ks);
   request(kHalfA0);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST, 2, 2>(acc, 1, 1, fa, fb1);
+  multiply_phase<B_FIRST, SIDE>(acc, 1, 1, fa, fb1);
   slot_end();
   request(kHalfB1);
   if constexpr (STORED) asm volatile("s_waitcnt vmcnt(63)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
   slot_end();
-  multiply_phase<B_FIRST, 2, 2>(acc, 1, 0, fa, fb0);
+  multiply_phase<B_FIRST, SIDE>(acc, 1, 0, fa, fb0);
   slot_end();
 }
 
@@ -371,7 +376,7 @@ __device__ __forceinline__ void matrix_step_narrow(BlockAcc<2, 1>& acc, ReadA re
     }
     asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
     slot_end();
-    multiply_phase<B_FIRST, 2, 1>(acc, a, 0, fa, fb);
+    multiply_phase<B_FIRST, 16>(acc, a, 0, fa, fb);
     slot_end();
   }
 }
@@ -421,7 +426,7 @@ __device__ __forceinline__ void matrix_step_wide(BlockAcc<1, 3>& acc, ReadA read
       asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
     }
     slot_end();
-    multiply_phase<B_FIRST, 1, 3>(acc, 0, b, fa, fb);
+    multiply_phase<B_FIRST, 16>(acc, 0, b, fa, fb);
     slot_end();
   }
 }
@@ -454,22 +459,30 @@ __device__ __forceinline__ void matrix_end(const MatrixPlace& place) {
 // and so fetches chunk (i % 8) ^ (row / 2 % 8).
 struct RowMajorHalf {
   int row, chunk[2];           // row of the wavefront's first load (the second: + 8), bytes of the chunk in the row
-  uint32_t a_off, b_off, xk[2];
   __device__ __forceinline__ explicit RowMajorHalf(const MatrixPlace& p) {
     const int lane = threadIdx.x & 63;
     row = 16 * (p.wm * 4 + p.wn) + (lane >> 3);
     chunk[0] = ((lane & 7) ^ (lane >> 4)) * 16;
     chunk[1] = chunk[0] ^ 64;
-    a_off = (p.wm * 64 + (lane & 15)) * 128;
-    b_off = 2 * kHalfBytes + (p.wn * 32 + (lane & 15)) * 128;
+  }
+};
+
+template <int SIDE = 16>
+struct RowMajorFragments {
+  static constexpr int KS = SIDE / 8;
+  uint32_t a_off, b_off, xk[KS];
+  __device__ __forceinline__ explicit RowMajorFragments(const MatrixPlace& p) {
+    const int lane = threadIdx.x & 63;
+    a_off = (p.wm * 64 + (lane & (SIDE - 1))) * 128;
+    b_off = 2 * kHalfBytes + (p.wn * 32 + (lane & (SIDE - 1))) * 128;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) xk[ks] = ((4 * ks + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4;
+    for (int ks = 0; ks < KS; ++ks) xk[ks] = (((64 / SIDE) * ks + lane / SIDE) ^ ((lane >> 1) & 7)) << 4;
   }
   __device__ __forceinline__ bf16x8 a(const unsigned char* step, int half, int i, int ks) const {
-    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + a_off + i * 2048 + xk[ks]);
+    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + a_off + i * (SIDE * 128) + xk[ks]);
   }
   __device__ __forceinline__ bf16x8 b(const unsigned char* step, int half, int j, int ks) const {
-    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + b_off + j * 2048 + xk[ks]);
+    return *reinterpret_cast<const bf16x8*>(step + half * kHalfBytes + b_off + j * (SIDE * 128) + xk[ks]);
   }
 };
 
@@ -535,7 +548,7 @@ struct TileLoader {
 //                            waited for none
 // A Walk without kWalks has one tile: its steps have one form, in which the requests stop at the last one without a branch, and
 // the tile is stored after the end of the loop.  A_HALVES x B_HALVES: 2 x 2, 2 x 1 (matrix_step_narrow) or 1 x 3 (matrix_step_wide).
-template <bool B_FIRST, int A_HALVES, int B_HALVES, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
+template <bool B_FIRST, int A_HALVES, int B_HALVES, int SIDE = 16, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
 __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
                                              Loader& load, ReadA read_a, ReadB read_b, Store store) {
   GemmTile ahead_tile = tile;
@@ -567,16 +580,18 @@ __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsi
   else matrix_begin(mine, request_from);
   int cur = 0;                                             // the step's buffer
   bool stored = false;
-  BlockAcc<A_HALVES, B_HALVES> acc;
+  BlockAcc<A_HALVES, B_HALVES, SIDE> acc;
   while (true) {
 #pragma unroll
     for (int h = 0; h < A_HALVES; ++h)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 64 / SIDE; ++i)
 #pragma unroll
         for (int b = 0; b < B_HALVES; ++b)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[h][i][b][0][r] = acc[h][i][b][1][r] = 0.f;
+          for (int j = 0; j < 32 / SIDE; ++j)
+#pragma unroll
+            for (int r = 0; r < SIDE * SIDE / 64; ++r) acc[h][i][b][j][r] = 0.f;
     auto run = [&](auto stored_tag, auto switch_tag) {
       constexpr int kBufs = kNarrow ? 3 : 2;
       const unsigned char* here = smem + cur * (kNarrow ? kNarrowBytes : kStepBytes);
@@ -596,7 +611,7 @@ __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsi
       };
       if constexpr (kNarrow) matrix_step_narrow<B_FIRST>(acc, a, b, request);
       else if constexpr (kWide) matrix_step_wide<B_FIRST>(acc, a, b, request);
-      else matrix_step<B_FIRST, decltype(stored_tag)::value>(acc, a, b, request);
+      else matrix_step<B_FIRST, decltype(stored_tag)::value, SIDE>(acc, a, b, request);
       cur = cur == kBufs - 1 ? 0 : cur + 1;
     };
     int kt = tile.steps;
@@ -666,6 +681,7 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
   const int tid = threadIdx.x, lane = tid & 63;
   const MatrixPlace mine = matrix_place(smem);
   const RowMajorHalf at(mine);
+  const RowMajorFragments<> frags(mine);
   // Rows past the end of a matrix re-read its last row (they are discarded later).  All offsets fit 32 bits (checked on the host).
   TileLoader<RowMajorSource, HiddenSource, RowMajorHalf, RowMajorHalf, B_HALVES == 1 ? kNarrowBytes : kStepBytes, B_HALVES == 3>
       load = {
@@ -723,8 +739,8 @@ __device__ __forceinline__ void lm_strip(unsigned char* smem, const __bf16* __re
   const GemmTile first = {vt_begin * kTile, t0, 0, d / kLmK, 0};
   matrix_tiles<false, A_HALVES, B_HALVES>(
       mine, smem, first, StripWalk{min(vt_end * kTile, V), kTile}, load,
-      [&](const unsigned char* here, int half, int i, int ks) { return at.a(here, half, i, ks); },
-      [&](const unsigned char* here, int half, int j, int ks) { return at.b(here, half, j, ks); },
+      [&](const unsigned char* here, int half, int i, int ks) { return frags.a(here, half, i, ks); },
+      [&](const unsigned char* here, int half, int j, int ks) { return frags.b(here, half, j, ks); },
       [&](const GemmTile& t, const BlockAcc<A_HALVES, B_HALVES>& acc) {
         const int vlane = t.m0 + mine.wm * 64 + ((lane >> 4) << 2);
         if (t.m0 + kTile > V) epilogue(std::true_type(), acc, vlane);

@@ -131,3 +131,19 @@ def test_gradients_with_more_tiles_of_dhidden_than_workgroups(T):
     scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
     out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, 4160, scores)
     _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores)
+
+
+@pytest.mark.parametrize("T,d,V", [(2304, 1024, 3000), (4096, 576, 200), (1100, 1856, 3001)])
+def test_dhidden_of_few_and_of_many_tiles_has_the_same_bits(T, d, V):
+    """36 to 48 tiles of dL/dhidden in one chunk, 3 to 8 a chunk of 256 rows, which go through the other matrix instruction: a
+    row's sum is the same.  The last tile of 64 hidden elements or of few rows, the last step of 8, 56 or 57 vocabulary entries.
+    (Entries are bounded one by one, two units in the last place of each bf16 gradient entry; one alone, 2^-8 of it, is more than
+    2e-3 of the largest result where a single entry makes that.)"""
+    h = wl.generate_lm_head(T, d, V, DEV, seed=T, masked_every=5)
+    w = wl.attach_loss_inputs(h, (T - 300, 300), [1, 3], seed=T)
+    scores = _scores_from_the_oracle(w, (1.0, 1.0, 0.05, 0.1))
+    out = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, (T + 63) // 64 * 64, scores)
+    _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, out, scores, check_scale=False)
+    chunks = _run(w, (1.0, 1.0, 0.05, 0.1), 1.0, 256, scores)
+    _compare(w, (1.0, 1.0, 0.05, 0.1), 1.0, chunks, scores, check_scale=False)
+    assert torch.equal(out["dhidden"], chunks["dhidden"])
