@@ -465,22 +465,25 @@ __global__ void __launch_bounds__(256)
 fopd_transpose_bf16(const uint16_t* __restrict__ in, int64_t ld_in, int rows, int cols, uint16_t* __restrict__ out,
                     int64_t ld_out, int rows_pad, const int* __restrict__ row_map, const int* __restrict__ n_rows) {
   __shared__ uint32_t tile[kTrTile * kTrPitch];
+  const int r0 = blockIdx.x * kTrTile, c0 = blockIdx.y * kTrTile;
+  const int tid = threadIdx.x;
+  int from[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {           // (map and count asked for together; entries behind the count are not used)
+    from[u] = r0 + 16 * u + (tid >> 4);
+    if (GATHER) from[u] = row_map[min(from[u], rows - 1)];
+  }
   if constexpr (GATHER) {
     rows = min(rows, n_rows[0]);
     rows_pad = min(rows_pad, max(64, (rows + 63) & ~63));
+    if (r0 >= rows_pad) return;
   }
-  const int r0 = blockIdx.x * kTrTile, c0 = blockIdx.y * kTrTile;
-  const int tid = threadIdx.x;
-  if (GATHER && r0 >= rows_pad) return;
   u32x4 q[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) {           // sixteen rows of sixteen 16-byte pieces at a time
     const int r = r0 + 16 * u + (tid >> 4), c = c0 + 8 * (tid & 15);
     q[u] = u32x4{0u, 0u, 0u, 0u};
-    if (r < rows && c < cols) {
-      const int64_t from = GATHER ? row_map[r] : r;
-      q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + from * ld_in + c));
-    }
+    if (r < rows && c < cols) q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + from[u] * ld_in + c));
   }
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
