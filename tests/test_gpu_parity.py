@@ -1498,8 +1498,9 @@ def test_projection_fused_replay_from_a_hip_graph():
 
 @pytest.mark.gpu
 def test_projection_fused_wide_logits():
-    """Logits with a spread of 40 (row maxima around 150): the running reference rises by tens between
-    vocabulary tiles, so every rescale path of the on-the-fly log-sum-exp is taken."""
+    """Logits with a spread of 40 (row maxima around 150): the references of a vocabulary tile's lanes, wavefronts and
+    strips are tens apart, so every rescale of the merges is taken.  (A strip has one vocabulary tile here; that a
+    reference rises between a strip's tiles is in the tests of few rows.)"""
     T, d, V = 300, 128, 3000
     w = wl.generate_lm_head(T, d, V, DEV, seed=8, logit_sigma=40.0)
     logp, lse, ws = _lm_head_call(w)

@@ -9,6 +9,7 @@ from harness import workloads as wl
 from oracle import fopd_oracle as orc
 from paper_2605_17862_amd import binding as fb
 from parity_util import np64
+from projection_cases import STRIPS_OF_SEVERAL_TILES
 from test_gpu_projection_loss import _compare, _run, _scores_from_the_oracle
 
 pytestmark = pytest.mark.gpu
@@ -43,9 +44,10 @@ def test_log_probs_at_the_edges_of_tiles_and_groups(T, masked_every):
 @pytest.mark.parametrize("T", [64, 128, 129, 300, 384, 385, 600, 1100])
 @pytest.mark.parametrize("d,V", [(64, 20001), (192, 20001), (128, 100), (64, 385)])
 def test_log_probs_with_a_last_tile_of_few_tokens(T, d, V):
-    """A last tile of up to 128 tokens beside 0, 2 or 4 whole ones, with strips of its own, and one token more; beside one, all
-    tokens in one tile; one to three steps a vocabulary tile, vocabularies of less than a tile and of an entry more than whole
-    ones.  Half of the rows masked moves the last tile to another place than the launch was made for."""
+    """A last tile of up to 128 tokens alone, beside 2 whole ones with the same strips and, with 20,001 entries, beside 4 with strips
+    of its own, and one token more; beside one, all tokens in one tile, one vocabulary tile a strip; one to three steps a
+    vocabulary tile, vocabularies of less than a tile and of an entry more than whole ones.  Half of the rows masked moves the
+    last tile to another place than the launch was made for."""
     w = wl.generate_lm_head(T, d, V, DEV, seed=T + d)
     ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
     half = torch.ones(T, dtype=torch.uint8, device=DEV)
@@ -63,8 +65,9 @@ def test_log_probs_with_a_last_tile_of_few_tokens(T, d, V):
 
 @pytest.mark.parametrize("T,masked_every", [(300, 2), (600, 2), (600, 3), (1100, 9)])
 def test_masked_rows_left_out_or_projected_give_the_same_bits(T, masked_every):
-    """Few whole tiles and a last one with strips of its own (600, 1100 rows), or all tokens in one tile: an unmasked row is
-    summed over the same strips whether the masked rows are projected or not."""
+    """All tokens in one tile (300 rows), three tiles with the same strips (600) and four with a last one with strips of its own,
+    which has no unmasked row (1100): an unmasked row is summed over the same strips whether the masked rows are projected or
+    not.  Unmasked rows in the last one's own strips: the next test."""
     w = wl.generate_lm_head(T, 64, 20001, DEV, seed=T, masked_every=masked_every)
     ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
     out = {}
@@ -79,6 +82,43 @@ def test_masked_rows_left_out_or_projected_give_the_same_bits(T, masked_every):
         fb.fopd_set_option("lm_head_compact", 1)
     assert not bool(out[0][0][w["mask"] == 0].any())
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("T,V,form,whole", STRIPS_OF_SEVERAL_TILES)
+@pytest.mark.parametrize("d,sigma", [(64, 3.0), (192, 40.0)])
+def test_log_probs_of_strips_with_several_vocabulary_tiles(T, V, form, whole, d, sigma):
+    """In every form of the token tiles the requests run on from one vocabulary tile into the next, after one or after three steps,
+    and the running pair of a token is carried over; with a spread of 40 its reference rises by tens on the way.  No mask, and
+    every 20th row masked, which leaves unmasked rows in a last tile with strips of its own; the same bits where the masked rows
+    are projected too."""
+    w = wl.generate_lm_head(T, d, V, DEV, seed=T + d, logit_sigma=sigma, masked_every=20)
+    ws = _aligned(fb.fopd_lm_head_workspace_bytes(T))
+    some = w["mask"]
+    assert form != "own" or int(some.sum()) > whole
+    ref_lse, ref_lp = orc.lm_head_token_logprobs(np64(w["hidden"].float()), np64(w["weight"].float()),
+                                                 w["token_ids"].cpu().numpy(), None)
+
+    def call(mask):
+        logp, lse = torch.full((T,), 7.0, device=DEV), torch.full((T,), 7.0, device=DEV)
+        fb.fopd_lm_head_token_logprobs(w["hidden"], w["ldh"], w["weight"], w["ldw"], T, V, d, w["token_ids"], mask, logp, lse, ws)
+        assert fb.fopd_workspace_status(ws) == (0, 0)
+        return logp, lse
+
+    # fp32 sums of d products: a few 1e-6 on a logit of the ordinary spread, a few 1e-5 on one of magnitude 150
+    atol = 1e-4 if sigma <= 3.0 else 2e-4
+    try:
+        for mask in (None, some):
+            fb.fopd_set_option("lm_head_compact", 1)
+            logp, lse = call(mask)
+            live = np.ones(T, dtype=bool) if mask is None else mask.cpu().numpy() != 0
+            assert np.all(np.abs(np64(lse) - ref_lse)[live] <= atol + 2e-6 * np.abs(ref_lse)[live])
+            assert np.all(np.abs(np64(logp) - ref_lp)[live] <= atol + 2e-6 * np.abs(ref_lp)[live])
+            assert not np64(lse)[~live].any() and not np64(logp)[~live].any()
+            fb.fopd_set_option("lm_head_compact", 0)
+            again = call(mask)
+            assert torch.equal(logp, again[0]) and torch.equal(lse, again[1])
+    finally:
+        fb.fopd_set_option("lm_head_compact", 1)
 
 
 @pytest.mark.parametrize("seq,d,pad_h", [((1,), 64, 0), ((40, 25), 64, 2), ((100, 157), 320, 4), ((300, 214), 512, 3),

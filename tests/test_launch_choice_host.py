@@ -9,6 +9,7 @@ import subprocess
 import pytest
 
 from paper_2605_17862_amd import build as b
+from projection_cases import STRIPS_OF_SEVERAL_TILES
 
 SOURCE = r"""
 #include <algorithm>
@@ -17,6 +18,8 @@ SOURCE = r"""
 #include <vector>
 #include "fopd_gemm.hip"
 using namespace fopd;
+
+CASES
 
 // Steps until all items are done; an item of strip / run r takes length(r) and `start`, an empty workgroup nothing.
 template <typename Length>
@@ -114,6 +117,11 @@ int main() {
       std::printf("split %d %d %d %ld %ld %ld %d\n", T, V, s.wide() || s.whole > 0 ? s.strips : s.tail_strips, room, pairs, covered,
                   (int)(s.wide() ? s.strips <= (V + 127) / 128 : 1));
     }
+  for (const auto& c : kCases) {
+    const LmSplit s = lm_split(c[0], c[1]);
+    std::printf("case %d %d %d %d %d %d %d\n", c[0], c[1], (int)s.wide(), s.whole, s.strips, s.tail_strips,
+                (c[1] + (s.wide() ? 127 : 255)) / (s.wide() ? 128 : 256));
+  }
   for (int m : {1, 2, 4, 7, 8, 9, 16, 33, 594})
     for (int n : {1, 2, 3, 4, 5, 8, 64, 594})
       for (int splits : {1, 3, 8})
@@ -134,7 +142,8 @@ int main() {
 @pytest.fixture(scope="module")
 def choices(tmp_path_factory):
     d = tmp_path_factory.mktemp("launch_choice")
-    (d / "choice.hip").write_text(SOURCE)
+    cases = ", ".join("{%d, %d}" % c[:2] for c in STRIPS_OF_SEVERAL_TILES)
+    (d / "choice.hip").write_text(SOURCE.replace("CASES", "static const int kCases[][2] = {%s};" % cases))
     flags = [f for f in b.HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-O3")]
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags +
                    ["-O1", "-I", os.path.join(b.ROOT, "include"), "-I", os.path.join(b.PKG, "csrc"),
@@ -181,3 +190,15 @@ def test_only_launches_with_more_tiles_than_workgroups_walk(choices):
     for tiles, steps, accumulate, walks in rows:
         # the walk's code costs a launch 4 - 6 us, for nothing where no workgroup has a second tile
         assert walks == (tiles > 256 and steps <= 128 and not (accumulate and steps == 1)), (tiles, steps, accumulate)
+
+
+def test_cases_of_strips_with_several_vocabulary_tiles(choices):
+    rows = {(int(r[1]), int(r[2])): [int(x) for x in r[3:]] for r in choices if r[0] == "case"}
+    assert len(rows) == len(STRIPS_OF_SEVERAL_TILES)
+    for T, V, form, whole_rows in STRIPS_OF_SEVERAL_TILES:
+        wide, whole, strips, tail_strips, vocab_tiles = rows[T, V]
+        assert form == ("one" if wide else "shared" if tail_strips == 0 else "own" if whole > 0 else "narrow"), (T, V)
+        assert whole * 256 == whole_rows, (T, V)
+        assert form != "shared" or 0 < T - 256 * (whole - 1) <= 128, (T, V)
+        # some strip has two tiles or more, in the own strips of a last tile too
+        assert all(vocab_tiles > n for n in (strips, tail_strips) if n > 0), (T, V)
