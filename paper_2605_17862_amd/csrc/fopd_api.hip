@@ -99,10 +99,10 @@ struct LmLossWorkspace {
   int64_t ldz = 0, r_pad = 0, n_chunks = 0;
   // dL/dhidden of more rows than this reads a transposed copy of the projection matrix.  The copy takes 450 us (151,936 x
   // 4096) whatever the rows; without it the contraction itself is slower by about 0.1 us a row (its A fragments leave the
-  // LDS in two transposing reads instead of one).  Whole call with / without the copy, us: 512 rows 2794 / 2314, 2048 rows
-  // 7789 / 7418, 4096 rows 14,393 / 14,210, 6144 rows 20,963 / 20,963, 8192 rows 27,912 / 28,170, 16,384 rows 55,663 /
-  // 56,794.  The rows are those of the call, masked ones too, whose number the host does not know: 6144 rows with a third
-  // masked 14,378 / 14,182, 8192 rows with half masked 14,409 / 14,260, so such calls take the copy for 1 % too much.
+  // LDS in two transposing reads instead of one).  Whole call with / without the copy, us: 512 rows 2526 / 2074, 2048 rows
+  // 6851 / 6553, 4096 rows 12,672 / 12,568, 6144 rows 18,741 / 18,733, 8192 rows 24,322 / 24,389, 16,384 rows 48,157 /
+  // 49,043.  The rows are those of the call, masked ones too, whose number the host does not know: 6144 rows with a third
+  // masked 12,706 / 12,552, 8192 rows with half masked 12,792 / 12,630, so such calls take the copy for 1 % too much.
   static constexpr int64_t kTransposeRows = 4096;
   bool with_wt = false;
   LmLossWorkspace(int64_t T, int64_t V, int64_t d, int32_t B, int64_t rows_chunk, int32_t k = 0) {

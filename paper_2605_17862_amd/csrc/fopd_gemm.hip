@@ -37,10 +37,11 @@ constexpr int kGemmThreads = kLmThreads;
 // Into how many runs of the contraction index Out[N, M] = sum over K is cut, at most `most`.  A product with few result
 // tiles leaves most of the 256 compute units idle while the others walk a long contraction index; each run is a result of
 // its own that is summed afterwards.  Estimate in microseconds: the rounds of the launch (tile_rounds) follow each other, an
-// item takes 1.6 a step of 64 plus 13 for its first loads and its stores, and the partial results are read at 4.5 TB/s
-// when they are summed.  151,936 x 4096, the contraction alone, us by number of runs: 512 rows 1: 2896, 4: 947, 8: 488, 16:
-// 503; 768 rows 1: 3005, 4: 845, 8: 844, 16: 876 (5, which 240 items on 256 compute units seem to ask for: 1286); 2048 rows
-// 1: 3720, 2: 1906, 4: 1902; 3072 rows 1: 3743, 4: 2848, 8: 2928.
+// item takes 1.6 a step of 64 (with all compute units at work; 1.2 with sixteen) plus 13 for its first loads and its stores,
+// and the partial results are read at 4.5 TB/s when they are summed.  151,936 x 4096, the contraction alone, us by number of
+// runs: 256 rows 1: 2728, 8: 420, 16: 265; 512 rows 1: 2882, 4: 905, 8: 474, 16: 477; 768 rows 1: 3022, 4: 902, 8: 834, 16: 846
+// (5, which 240 items on 256 compute units seem to ask for: 1289); 2048 rows 1: 3637, 2: 1863, 4: 1871; 3072 rows 1: 3602, 4:
+// 2838, 8: 2887.
 inline int gemm_splits(int64_t M, int64_t N, int64_t K, int64_t most) {
   const int tiles_m = static_cast<int>((M + kGemmTile - 1) / kGemmTile);
   const int tiles_n = static_cast<int>((N + kGemmTile - 1) / kGemmTile);
@@ -115,8 +116,8 @@ __device__ __forceinline__ void store_block(const BlockAcc<2, 2, 16>& acc, const
   }
 }
 
-// With the 32 x 32 result register r is row n = 128 b + 32 wn + 8 (r / 4) + 4 (lane / 32) + r % 4, column m = 128 a + 64 wm + 32 i +
-// lane % 32: whole lines of two rows.
+// With the 32 x 32 result register r is row n = 128 b + 32 wn + 8 (r / 4) + 4 (lane / 32) + r % 4, column m = 128 a + 64 wm +
+// 32 i + lane % 32: whole lines of two rows.
 template <bool ACCUMULATE, bool WHOLE>
 __device__ __forceinline__ void store_block(const BlockAcc<2, 2, 32>& acc, const MatrixPlace& place, int m0, int n0, int M,
                                             int N, float* __restrict__ Out, int64_t ldo) {
@@ -159,14 +160,14 @@ __device__ __forceinline__ bool store_tile(const BlockAcc<2, 2, SIDE>& acc, cons
 // XCD's groups x, x + 8, .. in their order, only tiles that exist being counted.  The next tile's first steps are then requested
 // before this one's results are stored, and no workgroup waits for its place: workgroups are started in the order of their
 // ids, which keeps the compute units at the same point of their tiles.  Weight gradient of 151,936 x 4096, a workgroup a
-// tile / walking, us: 256 rows 725 / 615, 512 rows 934 / 830, 2048 rows 2185 / 2120, 8192 rows 7395 / 7330, 16,384 rows
-// 14,720 / 14,835; logits (64 steps a tile) 512 rows 514 / 511, 16,384 rows 14,670 / 14,460; dL/dhidden, 150 and more
-// steps a tile, 16,384 rows 14,155 / 14,230.  So tiles of up to kWalkSteps steps are walked.  (Workgroups started a fraction
-// of a tile apart: no difference; results stored 16 bytes a lane: 1 % on the logits.)  With no more tiles than workgroups there
+// tile / walking, us: 256 rows 738 / 640 - 700, 512 rows 947 / 861, 1024 rows 1357 / 1286, 2048 rows 2257 / 2226, 8192 rows
+// 7408 / 7334, 16,384 rows 14,804 / 14,852; logits (64 steps a tile) 512 rows 516 / 513 - 519, 16,384 rows 14,550 / 14,380;
+// dL/dhidden (2374 steps) 16,384 rows 13,885 / 13,894.  So tiles of up to kWalkSteps steps are walked.  (Workgroups started a
+// fraction of a tile apart: no difference; results stored 16 bytes a lane: 1 % on the logits.)  With no more tiles than workgroups there
 // is nothing to walk, and the walk's code (four forms of a step, twice the instructions to fetch before the first one) is 4 - 6
 // us a launch: walking / not, us: weight gradient of 3000 rows x 8192, d = 64, 65.6 / 60.3, x 1000, d = 1024, 65.4 / 60.1; loss
 // and gradients of 64 rows x 8192, d = 1024, 110 / 102.  Nor where a result is added to after a single step: the memory's
-// adds are all there is (weight gradient of 64 more rows, 32,000 x 1024 / 128,000 x 1024, not walking 102 / 410, walking 105 / 418).
+// adds are all there is (weight gradient of 64 more rows, 32,000 x 1024 / 128,000 x 1024, walking 105 / 408, not 102 / 404).
 constexpr unsigned kGemmGrid = 256;
 constexpr int64_t kWalkSteps = 128;
 
@@ -177,9 +178,10 @@ inline bool gemm_walks(int64_t tiles, int64_t steps, bool accumulate) {
 // dL/dhidden from the matrix as it is stored, where it has few tiles (a chunk of few rows of a call of many, whose sums take the
 // order of the whole call): with the 32 x 32 x 16 instruction.  The multiplying slots issue half as many instructions, which
 // leaves the transposing reads of the other kind their way to the LDS, and with this many compute units at work there is no
-// power to be saved.  16 x 16 x 32 / 32 x 32 x 16, us by number of tiles: over 151,936 entries x 4096 16: 2850 / 2707, 32: 2986 /
-// 2784, 48: 2910 / 2940, 64: 3374 / 3655, 256: 3570 / 3750; over 32,000 x 1024 8: 83.6 / 77.7, 16: 158.5 / 150.4, 32: 170 /
-// 161, 64: 206 / 222.  (Both operands k-contiguous: no difference up to 32 tiles.)
+// power to be saved.  16 x 16 x 32 / 32 x 32 x 16, us by number of tiles of all runs: 151,936 entries x 4096, one run, 16: 2850
+// / 2707, 32: 2986 / 2784, 48: 2910 / 2940, 64: 3374 / 3655, 128: 3570 / 3750; 32,000 x 1024, four runs, 16: 153 / 141, 32: 154
+// / 143, 64: 159 / 150, 128: 170 / 161, 256: 206 / 222.  (Past 32 the larger one loses where the tiles fill their XCDs and gains
+// where they fill half.  Both operands k-contiguous, 4 tiles: 1 %.)
 inline bool gemm_tall(int64_t tiles) { return tiles <= 32; }
 
 // Workgroups: walking ones, else one for every place of every group of tiles (rounds of eight groups).
@@ -402,10 +404,11 @@ fopd_gemm_nt(const __bf16* __restrict__ Am, int64_t lda, int M, int rows_a, cons
 //   fopd_gemm_tn            Out[n, m] (+)= sum_{k < K} Bk[k, n] * Am[m, k]
 //
 // which is the weight gradient, dW[v, j] += sum_t dZ[t, v] H[t, j], with the gradient rows as they are stored and the hidden
-// rows transposed (fopd_transpose_bf16: 55 us for 16,384 rows of 4096).  Loop and result stores are those of fopd_gemm_nt;
+// rows transposed (fopd_transpose_bf16: 41 - 49 us for 16,384 rows of 4096).  Loop and result stores are those of fopd_gemm_nt;
 // B leaves the LDS as KMajorHalf says.  With the hidden rows k-major too, two thirds of the fragments take two transposing
 // reads each, 48 LDS reads a step instead of 32, and the reading slots are longer than the multiplying ones (matrix cores
-// 0.59 busy, 0.65 so): 151,936 x 4096 from 512 / 2048 / 16,384 rows 970 / 2455 / 16,300 us, so 950 / 2285 / 14,720.
+// 0.59 busy, 0.65 so): 151,936 x 4096 from 512 / 2048 / 16,384 rows 970 / 2455 / 16,300 us, so 950 / 2285 / 14,720 (a workgroup
+// a tile; as it is now, 0.69 busy, 860 / 2200 / 14,800).
 //
 // K must be a positive multiple of 64, and Am and Bk finite up to it; what is not to count is zero in one of them.  M and N need
 // not be multiples of the tile: rows of Am past M - 1 and 16-byte pieces past entry N - 1 of a row of Bk are clamped (re-read)
@@ -447,7 +450,9 @@ fopd_gemm_tn(const __bf16* __restrict__ Am, int64_t lda, int M, const __bf16* __
       mine, gemm_smem, tile, walk, load,
       [&](const unsigned char* here, int half, int i, int ks) { return frags_a.a(here, half, i, ks); },
       [&](const unsigned char* here, int half, int j, int ks) { return frags_b.b(here, half, j, ks); },
-      [&](const GemmTile& t, const BlockAcc<2, 2>& acc) { return store_tile<ACCUMULATE, WALK, 16>(acc, mine, t.m0, t.n0, M, N, Out, ldo); });
+      [&](const GemmTile& t, const BlockAcc<2, 2>& acc) {
+        return store_tile<ACCUMULATE, WALK, 16>(acc, mine, t.m0, t.n0, M, N, Out, ldo);
+      });
 }
 
 // out[c, r] = in[r, c] for r < rows, c < cols; out[c, r] = 0 for rows <= r < rows_pad.  GATHER: out[c, r] = in[row_map[r], c] for

@@ -18,11 +18,12 @@
 // weight [V, d]), so a lane's 8-element fragment is one 16-byte LDS read.
 //
 // The loop over the hidden elements (matrix_step below) is shared with the contraction kernels.  Bound by power: the matrix
-// cores are 0.72 busy at the 1.86 GHz that the part then holds (logits of 8192 rows; with the 32 x 32 x 16 instruction 0.74 at
+// cores are 0.75 busy at the 1.83 GHz that the part then holds (logits of 8192 rows; with the 32 x 32 x 16 instruction 0.74 at
 // 1.68 GHz).  The 16 x 16 x 32 instruction has the other's rate but goes over its accumulators half as often per product;
 // log-probs of 16,384 rows x
 // 151,936, d = 4096: 15.4 - 16.0 -> 14.7 - 15.1 ms, of 2048 rows 1.92 - 1.98 -> 1.86 ms.  With the vocabulary tiles of a strip as
-// one stream (matrix_tiles), whose loads have offsets that stay from step to step, 14.15 - 14.4 and 1.73 ms.
+// one stream (matrix_tiles), whose loads have offsets that stay from step to step, 14.15 - 14.4 and 1.73 ms, and without a wave
+// priority 13.9 - 14.4 and 1.70 - 1.75 ms.
 
 #ifndef FOPD_LM_HEAD_HIP_
 #define FOPD_LM_HEAD_HIP_
@@ -46,7 +47,8 @@ constexpr int kHalfBytes = 128 * kLmK * 2;                // half an operand til
 constexpr int kStepBytes = 4 * kHalfBytes;                // both operand tiles of a step
 constexpr int kLoopLdsBytes = 2 * kStepBytes;             // two steps: 128 KB of the compute unit's 160
 constexpr int kNarrowBytes = 3 * kHalfBytes;              // a step with half a B tile, of which the LDS holds three
-constexpr int kLmLdsBytes = 3 * kNarrowBytes;             // (the loop with whole tiles, then the exchange between wavefronts: 132 KB)
+constexpr int kLmLdsBytes = 3 * kNarrowBytes;             // 144 KB; the other forms of the loop take 128 of it, and the exchange
+                                                          // between wavefronts at the end the first few again
 constexpr float kLmNone = -__builtin_inff();              // "no value yet": the reference of an empty pair
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -74,7 +76,7 @@ __device__ __forceinline__ void lm_merge(float& m, float& s, float m2, float s2)
 // (id mod 8), so group g runs on XCD g mod 8 and its 32 tiles share that XCD's L2.  A group is up to 4 tiles along n
 // (the side with few tiles when the batch is small) x the 8 (16, 32) along m that fill it: with one or two tiles along n
 // the group takes 16 or 32 tiles along m instead of leaving workgroups without work.  That matters because an idle
-// workgroup is not free: it asks for the same 128 KB of LDS, so it queues for a compute unit like a working one.
+// workgroup is not free: it asks for the same 128 or 144 KB of LDS, so it queues for a compute unit like a working one.
 // Logits of 512 rows x 151,936 entries, d = 4096 (1188 tiles): 4 x 8 groups always, 2560 workgroups, 836 us; 2 x 16, 1280,
 // 558 us.  Idle workgroups remain where the last group along n has 1 to 3 tiles and another one stands beside it, or the only
 // one has 3, and where the groups are rounded up to eight: 594 tiles take 768 workgroups for 256 rows, 1782 take 2560 for 768
@@ -124,10 +126,10 @@ __host__ inline int64_t tile_rounds(int tiles_m, int tiles_n, int runs) {
 // Strips of the vocabulary for fopd_k7_lm_head_lse: the launch takes its rounds (tile_rounds) one after the other, a
 // round as long as its longest strip has tiles (plus a little for the item itself: first loads, last merge), and the
 // number of strips with the least total is taken. Few token tiles give many short strips, so that one short rollout fills
-// the chip too: 300 rows x 151,936 entries, d = 4096, 32 strips 1850 us, 64 1017, 128 548.  What counts is the fullest
-// XCD, not the number of items: 1280 rows (groups of 32 and of 8 items in turn) 32 strips 1605 us, 48 strips, 240 items,
-// 2081; 768 rows (24 items a group) 64 strips 938 us, 80 strips 1354.  Whole groups only (tile_place): strips that leave
-// part of a group empty share the weight's L2 copies worse.
+// the chip too: 200 rows x 151,936 entries, d = 4096, 32 strips 1408 us, 64 848, 128 448, 224 297; 512 rows 32 strips 1613, 64
+// 865, 128 525.  What counts is the fullest XCD, not the number of items: 1280 rows (groups of 32 and of 8 items in turn) 32
+// strips 1389 us, 48 strips, 240 items, 1835; 768 rows (24 items a group) 64 strips 882 us, 80 strips 1181.  Whole groups
+// only (tile_place): strips that leave part of a group empty share the weight's L2 copies worse.
 __host__ inline int lm_strips(int n_token_tiles, int n_vocab_tiles) {
   const int group_strips = 32 / tile_group_n(n_token_tiles);
   const int strips_max = kLmStrips + kLmPairsExtra / (n_token_tiles * kLmTile);
@@ -171,7 +173,8 @@ __host__ inline LmSplit lm_split(int64_t T, int64_t V) {
     // 257 to 384 tokens: as two tiles with strips of their own the projection matrix is read twice, at different times (2.5 GB at
     // 5.4 TB/s).  In one tile of 128 x 384 a step has three products of four, for half the vocabulary rows.  As many strips as
     // the pairs have room for, at most one a compute unit, in whole rounds.  151,936 x 4096, two tiles / one, us: 257 - 300 rows
-    // 462 / 412 (five rounds), 310 - 372 rows 470 - 485 / 450 (six), 384 rows 493 / 506 (seven, so two tiles).
+    // 462 / 412 (five rounds), 310 - 372 rows 470 - 485 / 450 (six), 384 rows 493 / 506 (seven, so two tiles).  How far one
+    // tile goes follows from the rounds: 376 rows at 50,000 entries, all 384 at 32,000 and 70,000.
     const int vocab_tiles = static_cast<int>((V + kLmTile / 2 - 1) / (kLmTile / 2));
     const int64_t most = std::min<int64_t>(256, (static_cast<int64_t>(kLmStrips) * tiles * kLmTile + kLmPairsExtra) / T);
     const int rounds = static_cast<int>((vocab_tiles + most - 1) / most);
@@ -547,8 +550,10 @@ struct TileLoader {
 //   store(tile, acc)         what to do with a finished tile; returns whether it left at least 63 stores behind the requests and
 //                            waited for none
 // A Walk without kWalks has one tile: its steps have one form, in which the requests stop at the last one without a branch, and
-// the tile is stored after the end of the loop.  A_HALVES x B_HALVES: 2 x 2, 2 x 1 (matrix_step_narrow) or 1 x 3 (matrix_step_wide).
-template <bool B_FIRST, int A_HALVES, int B_HALVES, int SIDE = 16, typename Walk, typename Loader, typename ReadA, typename ReadB, typename Store>
+// the tile is stored after the end of the loop.  A_HALVES x B_HALVES: 2 x 2, 2 x 1 (matrix_step_narrow) or 1 x 3
+// (matrix_step_wide); SIDE other than 16 with 2 x 2 only.
+template <bool B_FIRST, int A_HALVES, int B_HALVES, int SIDE = 16, typename Walk, typename Loader, typename ReadA, typename ReadB,
+          typename Store>
 __device__ __forceinline__ void matrix_tiles(const MatrixPlace& mine, const unsigned char* smem, GemmTile tile, Walk walk,
                                              Loader& load, ReadA read_a, ReadB read_b, Store store) {
   GemmTile ahead_tile = tile;

@@ -175,7 +175,7 @@ def test_gradients_with_more_tiles_of_dhidden_than_workgroups(T):
 
 @pytest.mark.parametrize("T,d,V", [(2304, 1024, 3000), (4096, 576, 200), (1100, 1856, 3001)])
 def test_dhidden_of_few_and_of_many_tiles_has_the_same_bits(T, d, V):
-    """36 to 48 tiles of dL/dhidden in one chunk, 3 to 8 a chunk of 256 rows, which go through the other matrix instruction: a
+    """40 to 72 tiles of dL/dhidden in one chunk, 3 to 8 a chunk of 256 rows, which go through the other matrix instruction: a
     row's sum is the same.  The last tile of 64 hidden elements or of few rows, the last step of 8, 56 or 57 vocabulary entries.
     (Entries are bounded one by one, two units in the last place of each bf16 gradient entry; one alone, 2^-8 of it, is more than
     2e-3 of the largest result where a single entry makes that.)"""
