@@ -98,7 +98,7 @@ struct LmLossWorkspace {
          logp_c = 0, lse_c = 0, tl_c = 0, ids_c = 0, llp_c = 0, h_c = 0, dh_c = 0, grad_ex = 0, h_t = 0, keep = 0;
   int64_t ldz = 0, r_pad = 0, n_chunks = 0;
   // dL/dhidden of more rows than this reads a transposed copy of the projection matrix.  The copy takes 450 us (151,936 x
-  // 4096) whatever the rows; without it the contraction itself is slower by about 0.1 us a row (its A fragments leave the
+  // 4096) whatever the rows; without it the contraction itself is slower by about 0.07 us a row (its A fragments leave the
   // LDS in two transposing reads instead of one).  Whole call with / without the copy, us: 512 rows 2526 / 2074, 2048 rows
   // 6851 / 6553, 4096 rows 12,672 / 12,568, 6144 rows 18,741 / 18,733, 8192 rows 24,322 / 24,389, 16,384 rows 48,157 /
   // 49,043.  The rows are those of the call, masked ones too, whose number the host does not know: 6144 rows with a third
